@@ -4,7 +4,8 @@
 //   u <- u + c (u[y+1,x] + u[y-1,x] + u[y,x+1] + u[y,x-1] - 4u) + rho sin(u)
 // where every read is of the previous field (`get` yields a value, Sec. 5.3.2),
 // so each step is a Jacobi sweep into a second buffer. Every `every`-th state
-// (t = 0, every, 2 every, ...) is copied out as a checkpoint.
+// (t = 0, every, 2 every, ...) is a checkpoint. By default up to eight steps run
+// per launch, the levels in between held in registers (stencil_tb).
 // Loss L = 1/2 ||u_T - target||^2.
 //
 // Reverse (ForTranspose runs the loop backwards; GetTranspose/PutTranspose carry
@@ -20,6 +21,193 @@
 #include "internal.h"
 
 namespace dexk {
+
+// Sine and cosine of the non-linear term, for a row of VW cells per lane.
+// x = k pi/2 + r, |r| <= pi/4; sin r and cos r are polynomials in t = r^2
+// (minimax fits of the Remez exchange, coefficients rounded to FP32 one after the
+// other; 4.0e-9 relative for the sine, 1.2e-10 for the cosine), and k's low bits
+// pick one and its sign. Three ways to (k, r), taken by the whole wave:
+//   every |x| <= 0.785   k = 0, r = x: six operations a sine instead of about 22
+//                        (with the reduction); where the field has been
+//                        smoothed, most rows take it
+//   |x| <= 2^14          k = rint(2x/pi), r = x - k pi/2 by three fused
+//                        multiply-adds (pi/2 in three FP32 parts, Cody and Waite)
+//   larger               by lane, Payne and Hanek's way: x = m 2^e with a 24-bit m,
+//                        and kTurn[e + 9] holds 2^e (2/pi) modulo 4 in two doubles
+// Lanes with the same x get the same bits whichever way their wave goes.
+struct Turn {
+  double hi, lo;
+};
+__device__ const Turn kTurn[114] = {
+    {0x1.45f306dc9c883p-10, -0x1.6b01ec5417056p-64},
+    {0x1.45f306dc9c883p-9, -0x1.6b01ec5417056p-63},
+    {0x1.45f306dc9c883p-8, -0x1.6b01ec5417056p-62},
+    {0x1.45f306dc9c883p-7, -0x1.6b01ec5417056p-61},
+    {0x1.45f306dc9c883p-6, -0x1.6b01ec5417056p-60},
+    {0x1.45f306dc9c883p-5, -0x1.6b01ec5417056p-59},
+    {0x1.45f306dc9c883p-4, -0x1.6b01ec5417056p-58},
+    {0x1.45f306dc9c883p-3, -0x1.6b01ec5417056p-57},
+    {0x1.45f306dc9c883p-2, -0x1.6b01ec5417056p-56},
+    {0x1.45f306dc9c883p-1, -0x1.6b01ec5417056p-55},
+    {0x1.45f306dc9c883p+0, -0x1.6b01ec5417056p-54},
+    {-0x1.7419f246c6efbp+0, 0x1.29fc2757d1f53p-54},
+    {0x1.17cc1b727220bp+0, -0x1.ac07b1505c159p-54},
+    {-0x1.d067c91b1bbebp+0, 0x1.4fe13abe8fa9ap-55}, {0x1.7cc1b727220a9p-2, 0x1.3f84eafa3ea6ap-56},
+    {0x1.7cc1b727220a9p-1, 0x1.3f84eafa3ea6ap-55}, {0x1.7cc1b727220a9p+0, 0x1.3f84eafa3ea6ap-54},
+    {-0x1.067c91b1bbeadp+0, -0x1.80f62a0b82b2dp-54},
+    {0x1.f306dc9c882a5p+0, 0x1.fc2757d1f534ep-55},
+    {-0x1.9f246c6efab58p-4, -0x1.ec54170565912p-61},
+    {-0x1.9f246c6efab58p-3, -0x1.ec54170565912p-60},
+    {-0x1.9f246c6efab58p-2, -0x1.ec54170565912p-59},
+    {-0x1.9f246c6efab58p-1, -0x1.ec54170565912p-58},
+    {-0x1.9f246c6efab58p+0, -0x1.ec54170565912p-57},
+    {0x1.836e4e44152a0p-1, -0x1.ec54170565912p-56},
+    {0x1.836e4e44152a0p+0, -0x1.ec54170565912p-55},
+    {-0x1.f246c6efab581p-1, 0x1.3abe8fa9a6ee0p-58},
+    {-0x1.f246c6efab581p+0, 0x1.3abe8fa9a6ee0p-57}, {0x1.b727220a94fe1p-4, 0x1.d5f47d4d37703p-59},
+    {0x1.b727220a94fe1p-3, 0x1.d5f47d4d37703p-58}, {0x1.b727220a94fe1p-2, 0x1.d5f47d4d37703p-57},
+    {0x1.b727220a94fe1p-1, 0x1.d5f47d4d37703p-56}, {0x1.b727220a94fe1p+0, 0x1.d5f47d4d37703p-55},
+    {-0x1.236377d5ac07bp-1, -0x1.505c1596447e5p-57},
+    {-0x1.236377d5ac07bp+0, -0x1.505c1596447e5p-56},
+    {0x1.b9391054a7f0ap+0, -0x1.505c1596447e5p-55},
+    {-0x1.1b1bbead603d9p-1, 0x1.5f47d4d377037p-55},
+    {-0x1.1b1bbead603d9p+0, 0x1.5f47d4d377037p-54},
+    {0x1.c9c882a53f84fp+0, -0x1.4170565911f92p-54},
+    {-0x1.b1bbead603d8bp-2, 0x1.f47d4d377036ep-56},
+    {-0x1.b1bbead603d8bp-1, 0x1.f47d4d377036ep-55},
+    {-0x1.b1bbead603d8bp+0, 0x1.f47d4d377036ep-54},
+    {0x1.391054a7f09d6p-1, -0x1.70565911f924fp-58},
+    {0x1.391054a7f09d6p+0, -0x1.70565911f924fp-57},
+    {-0x1.8ddf56b01ec54p+0, -0x1.70565911f924fp-56},
+    {0x1.c882a53f84eb0p-1, -0x1.70565911f924fp-55},
+    {0x1.c882a53f84eb0p+0, -0x1.70565911f924fp-54},
+    {-0x1.bbead603d8a83p-2, 0x1.f534ddc0db629p-58},
+    {-0x1.bbead603d8a83p-1, 0x1.f534ddc0db629p-57},
+    {-0x1.bbead603d8a83p+0, 0x1.f534ddc0db629p-56}, {0x1.1054a7f09d5f4p-1, 0x1.f534ddc0db629p-55},
+    {0x1.1054a7f09d5f4p+0, 0x1.f534ddc0db629p-54},
+    {-0x1.df56b01ec5417p+0, -0x1.596447e493ad5p-58},
+    {0x1.054a7f09d5f48p-2, -0x1.596447e493ad5p-57},
+    {0x1.054a7f09d5f48p-1, -0x1.596447e493ad5p-56},
+    {0x1.054a7f09d5f48p+0, -0x1.596447e493ad5p-55},
+    {-0x1.f56b01ec54170p+0, -0x1.596447e493ad5p-54},
+    {0x1.529fc2757d1f5p-4, 0x1.a6ee06db14acdp-59}, {0x1.529fc2757d1f5p-3, 0x1.a6ee06db14acdp-58},
+    {0x1.529fc2757d1f5p-2, 0x1.a6ee06db14acdp-57}, {0x1.529fc2757d1f5p-1, 0x1.a6ee06db14acdp-56},
+    {0x1.529fc2757d1f5p+0, 0x1.a6ee06db14acdp-55}, {-0x1.5ac07b1505c16p+0, 0x1.a6ee06db14acdp-54},
+    {0x1.4a7f09d5f47d5p+0, -0x1.6447e493ad4cep-55},
+    {-0x1.6b01ec5417056p+0, -0x1.6447e493ad4cep-54},
+    {0x1.29fc2757d1f53p+0, 0x1.377036d8a5665p-54},
+    {-0x1.ac07b1505c159p+0, -0x1.911f924eb5336p-54},
+    {0x1.4fe13abe8fa9ap-1, 0x1.bb81b6c52b328p-55}, {0x1.4fe13abe8fa9ap+0, 0x1.bb81b6c52b328p-54},
+    {-0x1.603d8a82e0acbp+0, -0x1.11f924eb53362p-55},
+    {0x1.3f84eafa3ea6ap+0, -0x1.11f924eb53362p-54},
+    {-0x1.80f62a0b82b2dp+0, 0x1.dc0db6295993cp-54},
+    {0x1.fc2757d1f534ep-1, -0x1.1f924eb53361ep-56},
+    {0x1.fc2757d1f534ep+0, -0x1.1f924eb53361ep-55},
+    {-0x1.ec54170565912p-6, 0x1.b6c52b3278872p-64},
+    {-0x1.ec54170565912p-5, 0x1.b6c52b3278872p-63},
+    {-0x1.ec54170565912p-4, 0x1.b6c52b3278872p-62},
+    {-0x1.ec54170565912p-3, 0x1.b6c52b3278872p-61},
+    {-0x1.ec54170565912p-2, 0x1.b6c52b3278872p-60},
+    {-0x1.ec54170565912p-1, 0x1.b6c52b3278872p-59},
+    {-0x1.ec54170565912p+0, 0x1.b6c52b3278872p-58}, {0x1.3abe8fa9a6ee0p-3, 0x1.b6c52b3278872p-57},
+    {0x1.3abe8fa9a6ee0p-2, 0x1.b6c52b3278872p-56}, {0x1.3abe8fa9a6ee0p-1, 0x1.b6c52b3278872p-55},
+    {0x1.3abe8fa9a6ee0p+0, 0x1.b6c52b3278872p-54},
+    {-0x1.8a82e0acb223fp+0, -0x1.24eb53361de38p-55},
+    {0x1.d5f47d4d37703p-1, 0x1.b6295993c4390p-55}, {0x1.d5f47d4d37703p+0, 0x1.b6295993c4390p-54},
+    {-0x1.505c1596447e5p-2, 0x1.b14acc9e21c82p-56},
+    {-0x1.505c1596447e5p-1, 0x1.b14acc9e21c82p-55},
+    {-0x1.505c1596447e5p+0, 0x1.b14acc9e21c82p-54},
+    {0x1.5f47d4d377037p+0, -0x1.3ad4cd8778df8p-55},
+    {-0x1.4170565911f92p+0, -0x1.3ad4cd8778df8p-54},
+    {0x1.7d1f534ddc0dbp+0, 0x1.8a5664f10e410p-54},
+    {-0x1.05c1596447e49p+0, -0x1.d6a66c3bc6fbep-55},
+    {0x1.f47d4d377036ep+0, -0x1.d6a66c3bc6fbep-54},
+    {-0x1.70565911f924fp-4, 0x1.2b32788720840p-58},
+    {-0x1.70565911f924fp-3, 0x1.2b32788720840p-57},
+    {-0x1.70565911f924fp-2, 0x1.2b32788720840p-56},
+    {-0x1.70565911f924fp-1, 0x1.2b32788720840p-55},
+    {-0x1.70565911f924fp+0, 0x1.2b32788720840p-54},
+    {0x1.1f534ddc0db63p+0, -0x1.a99b0ef1bef80p-54},
+    {-0x1.c1596447e493bp+0, 0x1.5993c439041fep-55}, {0x1.f534ddc0db629p-2, 0x1.664f10e4107f9p-56},
+    {0x1.f534ddc0db629p-1, 0x1.664f10e4107f9p-55}, {0x1.f534ddc0db629p+0, 0x1.664f10e4107f9p-54},
+    {-0x1.596447e493ad5p-4, 0x1.93c439041fe51p-59},
+    {-0x1.596447e493ad5p-3, 0x1.93c439041fe51p-58},
+    {-0x1.596447e493ad5p-2, 0x1.93c439041fe51p-57},
+    {-0x1.596447e493ad5p-1, 0x1.93c439041fe51p-56},
+    {-0x1.596447e493ad5p+0, 0x1.93c439041fe51p-55}, {0x1.4d377036d8a56p+0, 0x1.93c439041fe51p-54},
+    {-0x1.65911f924eb53p+0, -0x1.b0ef1bef806bap-55},
+    {0x1.34ddc0db6295ap+0, -0x1.b0ef1bef806bap-54},
+};
+
+template <int VW>
+struct Cells {
+  float v[VW];
+};
+
+template <bool SIN, bool COS, int VW>
+DEX_DEV void trig(const Cells<VW>& x, Cells<VW>& s, Cells<VW>& c) {
+  auto poly = [](float r, float& sn, float& cs) {
+    const float t = r * r;
+    sn = fmaf(r * t, fmaf(t, fmaf(t, -0x1.9952fap-13f, 0x1.110776p-7f), -0x1.555546p-3f), r);
+    cs = fmaf(t, fmaf(t, fmaf(t, fmaf(t, 0x1.99e80cp-16f, -0x1.6c0c28p-10f), 0x1.55554ap-5f), -0.5f), 1.f);
+  };
+  float m = 0.f;
+#pragma unroll
+  for (int e = 0; e < VW; ++e) m = fmaxf(m, fabsf(x.v[e]));
+  if (__all(m <= 0.785f)) {
+#pragma unroll
+    for (int e = 0; e < VW; ++e) poly(x.v[e], s.v[e], c.v[e]);
+    return;
+  }
+  const bool huge = !__all(m <= 16384.f);
+#pragma unroll
+  for (int e = 0; e < VW; ++e) {
+    const float xe = x.v[e], kf = rintf(xe * 0x1.45f306p-1f);
+    int k = (int)kf;
+    float r = fmaf(-kf, 0x1.921fb6p0f, xe);
+    r = fmaf(-kf, -0x1.777a5cp-25f, r);
+    r = fmaf(-kf, -0x1.ee59dap-50f, r);
+    if (huge) {
+      if (!(fabsf(xe) <= 16384.f)) {
+        const uint32_t b = __float_as_uint(xe);
+        const int ex = (int)((b >> 23) & 255u);
+        const Turn tn = kTurn[min(ex - 141, 113)];
+        const double md = (double)(int)((b & 0x7FFFFFu) | 0x800000u);
+        double p = md * tn.hi;
+        const double err = fma(md, tn.hi, -p) + md * tn.lo;
+        p -= 4.0 * rint(0.25 * p);
+        const double kd = rint(p);
+        float rr = (float)(((p - kd) + err) * 1.57079632679489661923);
+        int kk = (int)kd;
+        if (b >> 31) {
+          rr = -rr;
+          kk = -kk;
+        }
+        r = rr + (xe - xe);  // an infinity or NaN gives NaN
+        k = kk;
+      }
+    }
+    float sn, cs;
+    poly(r, sn, cs);
+    const bool odd = k & 1;
+    if constexpr (SIN)
+      s.v[e] = __uint_as_float(__float_as_uint(odd ? cs : sn) ^ ((uint32_t)(k & 2) << 30));
+    if constexpr (COS)
+      c.v[e] = __uint_as_float(__float_as_uint(odd ? sn : cs) ^ ((uint32_t)((k + 1) & 2) << 30));
+  }
+}
+
+// rho * sin / cos of one value (the one-step kernels; rows of one cell)
+DEX_DEV float sin1(float x) {
+  Cells<1> s, c;
+  trig<true, false, 1>(Cells<1>{{x}}, s, c);
+  return s.v[0];
+}
+DEX_DEV float cos1(float x) {
+  Cells<1> s, c;
+  trig<false, true, 1>(Cells<1>{{x}}, s, c);
+  return c.v[0];
+}
 
 // One forward step, 4 cells per thread (W % 4 == 0, W >= 8).
 __global__ void __launch_bounds__(256) stencil_step_vec(const float* __restrict__ u,
@@ -43,81 +231,292 @@ __global__ void __launch_bounds__(256) stencil_step_vec(const float* __restrict_
   o.z = cc.z + c * (((ss.z + nn.z) + cc.w) + cc.y - 4.f * cc.z);
   o.w = cc.w + c * (((ss.w + nn.w) + rt) + cc.z - 4.f * cc.w);
   if (rho != 0.f) {
-    o.x += rho * sinf(cc.x);
-    o.y += rho * sinf(cc.y);
-    o.z += rho * sinf(cc.z);
-    o.w += rho * sinf(cc.w);
+    o.x += rho * sin1(cc.x);
+    o.y += rho * sin1(cc.y);
+    o.z += rho * sin1(cc.z);
+    o.w += rho * sin1(cc.w);
   }
   *reinterpret_cast<float4*>(un + (int64_t)y * W + x0) = o;
   if (snap) *reinterpret_cast<float4*>(snap + (int64_t)y * W + x0) = cc;
 }
 
-// Strip form (W % 256 == 0, H % (4 RB) == 0): each wave owns 256 columns
-// (4 per lane) of RB consecutive rows. The RB + 2 input rows it needs are
-// loaded once into registers; left and right neighbours come from the
-// adjacent lanes, and only the two strip-edge cells are read separately. In
-// the adjoint (ADJ) the same body computes S^T g + rho cos(u) g.
-template <int RB, bool ADJ>
-__global__ void __launch_bounds__(256) stencil_strip(const float* __restrict__ u,
-                                                     float* __restrict__ out,
-                                                     float* __restrict__ snap,
-                                                     const float* __restrict__ ustate, int H, int W,
-                                                     float c, float rho, int accumulate) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int x0 = blockIdx.x * 256;
-  const int y0 = (blockIdx.y * 4 + wv) * RB;
-  const int xl = x0 == 0 ? W - 1 : x0 - 1;
-  const int xr = x0 + 256 == W ? 0 : x0 + 256;
-  f32x4 r[RB + 2];
-  float el[RB + 2], er[RB + 2];
+// ---------------------------------------------------------------------------
+// Time-blocked steps: one launch advances the field TB steps.
+//
+// A step alone is bound by memory (the field read and written, 8 bytes per
+// cell, against 5 vector instructions), so TB steps per pass divide the traffic
+// by TB. Each wave owns a strip of 64 VW columns (VW per lane) and streams down
+// a chunk of rows, keeping the last two rows of every intermediate time level
+// in registers: when row i of level 0 arrives, level 1 forms its row i - 1, level
+// 2 its row i - 2, ..., level TB its row i - TB, which is stored. Horizontal
+// neighbours are the adjacent lanes' registers (wave shifts folded into the
+// additions), so there is no LDS, no barrier and no exchange between waves; the
+// price is a halo of TB columns on either side of a strip (whole lanes: HL) and
+// 2 TB rows read ahead of a chunk's first output row. All indices are periodic,
+// so any H, W >= 1 is accepted. Measured per step, 4096^2, against one step per
+// launch: forward 6.5 us (24.0), adjoint 6.2 us (23.3); with the non-linear term
+// forward 10.5 us (25.8), adjoint with its recomputation 49 us (62); 601 x 333:
+// 0.77 us (3.0). Bound by issuing the vector instructions (5 a cell, halo and
+// row overlap on top: 1.75 times the cells are computed at 4096^2).
+//
+// MODE   FWD   u -> u after TB steps; `snap` (if given) receives the input rows
+//        REC   FWD, and rho cos(u) of every level, which is all the adjoint
+//              steps read of the states they linearize about
+//        ADJ   cotangent back through TB steps (reads what REC wrote)
+//        ADJI  ADJ, the first cotangent dL (u_T - target) formed on the fly
+//        TAN   a state and its tangent together (forward mode)
+// NL: rho != 0. Products and sums are written as explicit fused
+// multiply-adds in the order of the one-step kernels, so every TB, VW and MODE
+// rounds alike and results do not depend on how the steps are grouped.
+enum { TB_FWD = 0, TB_REC = 1, TB_ADJ = 2, TB_ADJI = 3, TB_TAN = 4 };
+
+struct TbArgs {
+  const float* in;    // level 0 (ADJI: u_T; TAN: the state)
+  const float* in2;   // ADJI: target; TAN: the tangent
+  float* out;         // level TB; may be null for REC (only the rho cos(u) are wanted)
+  float* out2;        // TAN: the tangent's
+  float* snap;        // FWD: copy of level 0, or null
+  float* rc;          // REC: rho cos(u) of level 0 (level t at rc + t rcs); ADJ*: of the first
+                      // step taken back (step t at rc - t rcs)
+  const float* dL;    // ADJI
+  int64_t rcs;        // elements between the levels of rc
+  int H, W, RB, strips, accumulate;
+  float c, rho;
+};
+
+// Value of the lane below (left neighbour) / above; lanes 0 / 63 get zero.
+DEX_DEV float from_left(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xF, 0xF, true));
+}
+DEX_DEV float from_right(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xF, 0xF, true));
+}
+
+// Sum of the four neighbours in the order ((south + north) + east) + west.
+template <int VW>
+DEX_DEV Cells<VW> neighbours(const Cells<VW>& n, const Cells<VW>& c, const Cells<VW>& s) {
+  Cells<VW> o;
+  const float lf = from_left(c.v[VW - 1]), rt = from_right(c.v[0]);
 #pragma unroll
-  for (int q = 0; q < RB + 2; ++q) {
-    int y = y0 - 1 + q;
-    y = y < 0 ? y + H : (y >= H ? y - H : y);
-    const float* row = u + (int64_t)y * W;
-    r[q] = *reinterpret_cast<const f32x4*>(row + x0 + 4 * lane);
-    el[q] = row[xl];
-    er[q] = row[xr];
+  for (int e = 0; e < VW; ++e)
+    o.v[e] = ((s.v[e] + n.v[e]) + (e + 1 < VW ? c.v[(e + 1) % VW] : rt)) +
+             (e > 0 ? c.v[(e + VW - 1) % VW] : lf);
+  return o;
+}
+
+// 4-byte aligned vectors: a strip may start at any column
+template <int VW>
+struct UVec {
+  typedef float T __attribute__((ext_vector_type(VW), aligned(4)));
+};
+template <>
+struct UVec<1> {
+  typedef float T;
+};
+
+template <int TB, int VW, int MODE, bool NL>
+__global__ void __launch_bounds__(256) stencil_tb(TbArgs a) {
+  constexpr bool kAdj = MODE == TB_ADJ || MODE == TB_ADJI;
+  constexpr bool kTwo = MODE == TB_TAN || MODE == TB_ADJI;  // a second input field
+  constexpr bool kTan = MODE == TB_TAN;
+  constexpr bool kRc = kAdj && NL;
+  constexpr int HL = (TB + VW - 1) / VW, WV = VW * (64 - 2 * HL);
+  using C = Cells<VW>;
+  using U = typename UVec<VW>::T;
+  const int lane = threadIdx.x & 63;
+  const int wave = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int chunk = wave / a.strips, strip = wave - chunk * a.strips;
+  const int y0 = chunk * a.RB;
+  if (y0 >= a.H) return;  // (no barrier follows)
+  const int H = a.H, W = a.W;
+  const int total = min(a.RB, H - y0) + 2 * TB;  // level-0 rows this wave needs
+  // the lane's columns: xc .. xc + VW - 1, taken modulo W for the loads
+  const int xc = strip * WV + VW * (lane - HL);
+  int col[VW];
+#pragma unroll
+  for (int e = 0; e < VW; ++e) {
+    int m = (xc + e) % W;
+    col[e] = m < 0 ? m + W : m;
   }
-  const float a = 1.f - 4.f * c;
-  // a compile-time row index (static_for): r, el and er stay in registers
-  static_for<RB>([&](auto qc) {
-    constexpr int q = decltype(qc)::value + 1;
-    const f32x4 cc = r[q], nn = r[q - 1], ss = r[q + 1];
-    float lf = __shfl_up(cc[3], 1, 64);
-    float rt = __shfl_down(cc[0], 1, 64);
-    if (lane == 0) lf = el[q];
-    if (lane == 63) rt = er[q];
-    const int64_t off = (int64_t)(y0 + q - 1) * W + x0 + 4 * lane;
-    f32x4 o;
-    if constexpr (!ADJ) {
-      o[0] = cc[0] + c * (((ss[0] + nn[0]) + cc[1]) + lf - 4.f * cc[0]);
-      o[1] = cc[1] + c * (((ss[1] + nn[1]) + cc[2]) + cc[0] - 4.f * cc[1]);
-      o[2] = cc[2] + c * (((ss[2] + nn[2]) + cc[3]) + cc[1] - 4.f * cc[2]);
-      o[3] = cc[3] + c * (((ss[3] + nn[3]) + rt) + cc[2] - 4.f * cc[3]);
-      if (rho != 0.f) {
+  const bool whole = __all(col[VW - 1] - col[0] == VW - 1);  // no lane straddles the wrap
+  const bool mine = lane >= HL && lane < 64 - HL && xc < W;
+  const int nmine = mine ? min(VW, W - xc) : 0;  // columns this lane stores
+  const bool even = __all(nmine == 0 || nmine == VW);
+  auto load = [&](const float* f, int y) {
+    C r;
+    const float* row = f + (int64_t)y * W;
+    if (VW == 1 || whole) {
+      const U v = *reinterpret_cast<const U*>(row + col[0]);
+      if constexpr (VW == 1) {
+        r.v[0] = v;
+      } else {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] += rho * sinf(cc[e]);
+        for (int e = 0; e < VW; ++e) r.v[e] = v[e];
       }
-      if (snap) *reinterpret_cast<f32x4*>(snap + off) = cc;
     } else {
-      o[0] = a * cc[0] + c * (((ss[0] + nn[0]) + cc[1]) + lf);
-      o[1] = a * cc[1] + c * (((ss[1] + nn[1]) + cc[2]) + cc[0]);
-      o[2] = a * cc[2] + c * (((ss[2] + nn[2]) + cc[3]) + cc[1]);
-      o[3] = a * cc[3] + c * (((ss[3] + nn[3]) + rt) + cc[2]);
-      if (rho != 0.f) {
-        const f32x4 us = *reinterpret_cast<const f32x4*>(ustate + off);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] += rho * cosf(us[e]) * cc[e];
+      for (int e = 0; e < VW; ++e) r.v[e] = row[col[e]];
+    }
+    return r;
+  };
+  auto store = [&](float* f, int y, const C& r) {
+    float* row = f + (int64_t)y * W + xc;
+    if (VW == 1 || even) {
+      if (nmine) {
+        U v;
+        if constexpr (VW == 1) {
+          v = r.v[0];
+        } else {
+#pragma unroll
+          for (int e = 0; e < VW; ++e) v[e] = r.v[e];
+        }
+        *reinterpret_cast<U*>(row) = v;
       }
-      if (accumulate) {
-        const f32x4 p = *reinterpret_cast<const f32x4*>(out + off);
+    } else {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] += p[e];
+      for (int e = 0; e < VW; ++e)
+        if (e < nmine) row[e] = r.v[e];
+    }
+  };
+  const float cw = a.c, rho = a.rho, ac = 1.f - 4.f * a.c;
+  const float dL = MODE == TB_ADJI ? a.dL[0] : 0.f;
+
+  // rows y of the next loads, and of the first level's centre row, modulo H
+  int yl = (y0 - TB) % H;
+  if (yl < 0) yl += H;
+  auto next = [&](int y) { return y + 1 == H ? 0 : y + 1; };
+  // level t's row i - 1 - t has y = (yc - t) mod H at row i
+  int yc = yl == 0 ? H - 1 : yl - 1;
+  auto back = [&](int y, int t) {
+    int r = y - t;
+    while (r < 0) r += H;
+    return r;
+  };
+
+  C sl[2][TB], sl2[2][TB];     // the last two rows of every level (sl2: the tangent's)
+  C pf[2], pf2[2];             // rows loaded two ahead
+  C rp[2][kRc ? TB : 1];       // rho cos(u) rows, loaded two ahead
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int t = 0; t < TB; ++t)
+#pragma unroll
+      for (int e = 0; e < VW; ++e) sl[q][t].v[e] = sl2[q][t].v[e] = 0.f;
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    pf[q] = load(a.in, yl);
+    if constexpr (kTwo) pf2[q] = load(a.in2, yl);
+    if constexpr (kRc) {
+      int y = yc;
+      if (q) y = next(y);
+#pragma unroll
+      for (int t = 0; t < TB; ++t) rp[q][t] = load(a.rc - t * a.rcs, back(y, t));
+    }
+    yl = next(yl);
+  }
+  int yc2 = next(next(yc));
+
+  // row i of level 0: P = i % 2; FULL: every level has its rows
+  auto advance = [&](auto pc, auto fullc, int i) {
+    constexpr int P = decltype(pc)::value;
+    constexpr bool FULL = decltype(fullc)::value;
+    C s = pf[P], s2;
+    C rc[kRc ? TB : 1];
+    pf[P] = load(a.in, yl);
+    if constexpr (kTwo) {
+      s2 = pf2[P];
+      pf2[P] = load(a.in2, yl);
+    }
+    if constexpr (kRc) {
+#pragma unroll
+      for (int t = 0; t < TB; ++t) {
+        rc[t] = rp[P][t];
+        rp[P][t] = load(a.rc - t * a.rcs, back(yc2, t));
       }
     }
-    *reinterpret_cast<f32x4*>(out + off) = o;
-  });
+    yl = next(yl);
+    if constexpr (kRc) yc2 = next(yc2);
+    if constexpr (MODE == TB_ADJI) {
+#pragma unroll
+      for (int e = 0; e < VW; ++e) s.v[e] = dL * (s.v[e] - s2.v[e]);
+    }
+    if constexpr (MODE == TB_FWD) {
+      if (a.snap && i >= TB && i < total - TB) store(a.snap, y0 + i - TB, s);
+    }
+    static_for<TB>([&](auto tc) {
+      constexpr int t = decltype(tc)::value;
+      if (!FULL && i < 2 * (t + 1)) {  // (uniform) level t + 1 has no complete row yet
+        if (i >= 2 * t) {
+          sl[P][t] = s;
+          if constexpr (kTan) sl2[P][t] = s2;
+        }
+        return;
+      }
+      const C c = sl[P ^ 1][t];
+      C o = neighbours<VW>(sl[P][t], c, s), o2;
+      if constexpr (kAdj) {
+#pragma unroll
+        for (int e = 0; e < VW; ++e) {
+          o.v[e] = fmaf(ac, c.v[e], cw * o.v[e]);
+          if constexpr (NL) o.v[e] = fmaf(rc[t].v[e], c.v[e], o.v[e]);
+        }
+      } else {
+        C sn, cs;
+        if constexpr (NL) trig<true, MODE == TB_REC || kTan, VW>(c, sn, cs);
+        if constexpr (kTan) {
+          const C c2 = sl2[P ^ 1][t];
+          o2 = neighbours<VW>(sl2[P][t], c2, s2);
+#pragma unroll
+          for (int e = 0; e < VW; ++e) o2.v[e] = fmaf(cw, fmaf(-4.f, c2.v[e], o2.v[e]), c2.v[e]);
+        }
+#pragma unroll
+        for (int e = 0; e < VW; ++e) {
+          o.v[e] = fmaf(cw, fmaf(-4.f, c.v[e], o.v[e]), c.v[e]);
+          if constexpr (NL) {
+            o.v[e] = fmaf(rho, sn.v[e], o.v[e]);
+            if constexpr (MODE == TB_REC || kTan) cs.v[e] = rho * cs.v[e];
+            if constexpr (kTan) o2.v[e] = fmaf(cs.v[e], sl2[P ^ 1][t].v[e], o2.v[e]);
+          }
+        }
+        if constexpr (MODE == TB_REC) {
+          // the centre row of level t: row i - 1 - t of the loaded ones
+          const int q = i - 1 - t;
+          if (q >= TB && q < total - TB) store(a.rc + t * a.rcs, y0 + q - TB, cs);
+        }
+      }
+      sl[P][t] = s;
+      s = o;
+      if constexpr (kTan) {
+        sl2[P][t] = s2;
+        s2 = o2;
+      }
+    });
+    if constexpr (FULL) {
+      const int y = y0 + i - 2 * TB;
+      if (MODE != TB_REC || a.out) {
+        if (kAdj && a.accumulate && nmine) {
+          const float* row = a.out + (int64_t)y * W + xc;
+#pragma unroll
+          for (int e = 0; e < VW; ++e)
+            if (e < nmine) s.v[e] += row[e];
+        }
+        store(a.out, y, s);
+        if constexpr (kTan) store(a.out2, y, s2);
+      }
+    }
+  };
+  using F = std::integral_constant<bool, false>;
+  using T = std::integral_constant<bool, true>;
+  using P0 = std::integral_constant<int, 0>;
+  using P1 = std::integral_constant<int, 1>;
+  for (int i = 0; i < 2 * TB; i += 2) {
+    advance(P0{}, F{}, i);
+    advance(P1{}, F{}, i + 1);
+  }
+  for (int i = 2 * TB; i < total; i += 2) {
+    advance(P0{}, T{}, i);
+    if (i + 1 < total) advance(P1{}, T{}, i + 1);
+  }
 }
 
 __global__ void __launch_bounds__(256) stencil_step_scalar(const float* __restrict__ u,
@@ -132,7 +531,7 @@ __global__ void __launch_bounds__(256) stencil_step_scalar(const float* __restri
   const float cc = u[t];
   float o = cc + c * (((u[(int64_t)ys * W + x] + u[(int64_t)yn * W + x]) + u[(int64_t)y * W + xr]) +
                       u[(int64_t)y * W + xl] - 4.f * cc);
-  if (rho != 0.f) o += rho * sinf(cc);
+  if (rho != 0.f) o += rho * sin1(cc);
   un[t] = o;
   if (snap) snap[t] = cc;
 }
@@ -152,7 +551,7 @@ __global__ void __launch_bounds__(256) stencil_adj_gather(const float* __restric
   float v = (1.f - 4.f * c) * gc +
             c * (((g[(int64_t)ys * W + x] + g[(int64_t)yn * W + x]) + g[(int64_t)y * W + xr]) +
                  g[(int64_t)y * W + xl]);
-  if (rho != 0.f) v += rho * cosf(u[t]) * gc;
+  if (rho != 0.f) v += rho * cos1(u[t]) * gc;
   out[t] = accumulate ? out[t] + v : v;
 }
 
@@ -181,10 +580,10 @@ __global__ void __launch_bounds__(256) stencil_adj_gather_vec(const float* __res
   v.w = a * cc.w + c * (((ss.w + nn.w) + rt) + cc.z);
   if (rho != 0.f) {
     const float4 uu = *reinterpret_cast<const float4*>(u + (int64_t)y * W + x0);
-    v.x += rho * cosf(uu.x) * cc.x;
-    v.y += rho * cosf(uu.y) * cc.y;
-    v.z += rho * cosf(uu.z) * cc.z;
-    v.w += rho * cosf(uu.w) * cc.w;
+    v.x += rho * cos1(uu.x) * cc.x;
+    v.y += rho * cos1(uu.y) * cc.y;
+    v.z += rho * cos1(uu.z) * cc.z;
+    v.w += rho * cos1(uu.w) * cc.w;
   }
   float4* o = reinterpret_cast<float4*>(out + (int64_t)y * W + x0);
   if (accumulate) {
@@ -211,41 +610,12 @@ __global__ void __launch_bounds__(256) stencil_adj_scatter(const float* __restri
   const int xl = x == 0 ? W - 1 : x - 1, xr = x == W - 1 ? 0 : x + 1;
   const float gc = g[t];
   float self = (1.f - 4.f * c) * gc;
-  if (rho != 0.f) self += rho * cosf(u[t]) * gc;
+  if (rho != 0.f) self += rho * cos1(u[t]) * gc;
   atomicAdd(&out[t], self);
   atomicAdd(&out[(int64_t)ys * W + x], c * gc);
   atomicAdd(&out[(int64_t)yn * W + x], c * gc);
   atomicAdd(&out[(int64_t)y * W + xr], c * gc);
   atomicAdd(&out[(int64_t)y * W + xl], c * gc);
-}
-
-// Forward mode, one step of the primal and its tangent together (the
-// linearized step, Sec. 5.1: the diffusion part is linear, the non-linear term
-// linearizes to rho cos(u) du, which reads the primal state of the same step):
-//   un  = u  + c (sum of the 4 neighbours of u  - 4 u ) + rho sin(u)
-//   dun = du + c (sum of the 4 neighbours of du - 4 du) + rho cos(u) du
-// One cell per thread, periodic indices.
-__global__ void __launch_bounds__(256) stencil_tan_step(const float* __restrict__ u,
-                                                        const float* __restrict__ du,
-                                                        float* __restrict__ un,
-                                                        float* __restrict__ dun, int H, int W,
-                                                        float c, float rho) {
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (t >= (int64_t)H * W) return;
-  const int y = (int)(t / W), x = (int)(t % W);
-  const int yn = y == 0 ? H - 1 : y - 1, ys = y == H - 1 ? 0 : y + 1;
-  const int xl = x == 0 ? W - 1 : x - 1, xr = x == W - 1 ? 0 : x + 1;
-  const int64_t is = (int64_t)ys * W + x, in = (int64_t)yn * W + x;
-  const int64_t ir = (int64_t)y * W + xr, il = (int64_t)y * W + xl;
-  const float cc = u[t], dc = du[t];
-  float o = cc + c * (((u[is] + u[in]) + u[ir]) + u[il] - 4.f * cc);
-  float d = dc + c * (((du[is] + du[in]) + du[ir]) + du[il] - 4.f * dc);
-  if (rho != 0.f) {
-    o += rho * sinf(cc);
-    d += rho * cosf(cc) * dc;
-  }
-  un[t] = o;
-  dun[t] = d;
 }
 
 // Per-block partial sums of (u - target)(du - dtarget) in FP64: the tangent of
@@ -339,26 +709,112 @@ St st_of(const dex_desc& d) {
   return s;
 }
 
-// Rows per wave of the strip kernels (0: the grid does not allow the strip
-// form). Taller strips re-read fewer halo rows (RB + 2 rows read per RB
-// written) but 16 rows measured no faster than 8 at 4096^2 (fewer waves per
-// SIMD, 170 registers).
-constexpr int kRB = 8;
-int strip_rb(const St& s) { return s.W % 256 == 0 && s.H % (4 * kRB) == 0 ? kRB : 0; }
+// Steps per launch are powers of two up to kTB: a stretch of n steps runs as
+// n / kTB launches of kTB steps and the binary digits of the rest.
+constexpr int kTB = 8;
+int tb_of(int left) {
+  int tb = kTB;
+  while (tb > left) tb >>= 1;
+  return tb;
+}
+int tb_pieces(int n) { return n / kTB + __builtin_popcount(n % kTB); }
 
-template <bool ADJ>
-void launch_strip(const St& s, const float* in, float* out, float* snap, const float* ustate,
-                  int accumulate, hipStream_t st) {
-  hipLaunchKernelGGL((stencil_strip<kRB, ADJ>), dim3(s.W / 256, s.H / (4 * kRB)), dim3(256), 0, st,
-                     in, out, snap, ustate, s.H, s.W, s.c, s.rho, accumulate);
+template <int MODE, int TB, int VW>
+void tb_launch(const TbArgs& a, bool nl, int blocks, hipStream_t st) {
+  if constexpr (MODE == TB_REC) {
+    hipLaunchKernelGGL((stencil_tb<TB, VW, MODE, true>), dim3(blocks), dim3(256), 0, st, a);
+  } else {
+    if (nl)
+      hipLaunchKernelGGL((stencil_tb<TB, VW, MODE, true>), dim3(blocks), dim3(256), 0, st, a);
+    else
+      hipLaunchKernelGGL((stencil_tb<TB, VW, MODE, false>), dim3(blocks), dim3(256), 0, st, a);
+  }
 }
 
-// strip: use the strip kernels where the grid allows them (a tuning config).
-void step(const St& s, const float* u, float* un, float* snap, bool strip, hipStream_t st) {
-  const int rb = strip ? strip_rb(s) : 0;
-  if (rb) {
-    launch_strip<false>(s, u, un, snap, nullptr, 0, st);
-  } else if (s.vec) {
+// Launch shape of a tb-step launch on a grid: columns per lane, rows per wave,
+// strips.
+struct TbShape {
+  int vw, rb, strips;
+};
+TbShape tb_shape(const St& s, int tb) {
+  const bool nl = s.rho != 0.f;
+  // Columns per lane (1 or 2) and rows per wave: the least modelled time. A wave
+  // takes rb + 3/2 tb row-times (the 2 tb rows ahead of its first output cost half),
+  // tb levels each; a level is about ins vector instructions, which one wave of a
+  // SIMD issues every 9 cycles or so (a dependent chain) and several waves every
+  // 4.4. Wide lanes waste fewer halo columns (112 of 128 kept against 48 of 64 at
+  // tb = 8), narrow ones give small grids more waves. Measured per step at tb = 8,
+  // rho = 0: 4096^2 two columns x 32 rows 6.2 us (one x 72: 6.2, one x 32: 6.4, two x
+  // 64: 6.5; four columns per lane, 32 rows: 6.9); 1024^2 one x 12 1.30 us (two x 8:
+  // 1.47); 601 x 333 one x 4 0.77 us (two x 4: 0.90, one x 16: 1.1).
+  const int simds = 4 * num_cus();
+  TbShape g{2, 32, 0};
+  double best = 1e300;
+  for (int v = 1; v <= 2; ++v) {
+    const int wv = v * (64 - 2 * ((tb + v - 1) / v));
+    const int64_t strips = (s.W + wv - 1) / wv;
+    const double ins = nl ? 14.0 * v + 6.0 : 5.5 * v + 2.5;
+    for (int r = 4; r <= 128; r += r < 32 ? 4 : 16) {
+      const int64_t per_simd = (strips * ((s.H + r - 1) / r) + simds - 1) / simds;
+      const double t = (r + 1.5 * tb) * tb * ins * std::max(9.0, 4.4 * (double)per_simd);
+      if (t < best) {
+        best = t;
+        g = {v, r, (int)strips};
+      }
+    }
+  }
+  return g;
+}
+
+// The shapes of one call's launches, found once per number of steps.
+struct TbPlan {
+  const St& s;
+  TbShape shape[4];
+  explicit TbPlan(const St& s_) : s(s_), shape{} {}
+  const TbShape& at(int tb) {
+    TbShape& g = shape[__builtin_ctz(tb)];
+    if (!g.vw) g = tb_shape(s, tb);
+    return g;
+  }
+};
+
+// One launch of tb steps (a power of two up to kTB).
+template <int MODE>
+void tb_steps(TbPlan& plan, int tb, TbArgs a, hipStream_t st) {
+  const St& s = plan.s;
+  const TbShape& g = plan.at(tb);
+  const bool nl = s.rho != 0.f;
+  const int vw = g.vw;
+  a.H = s.H;
+  a.W = s.W;
+  a.c = s.c;
+  a.rho = s.rho;
+  a.RB = g.rb;
+  a.strips = g.strips;
+  const int64_t waves = (int64_t)g.strips * ((s.H + g.rb - 1) / g.rb);
+  const int blocks = (int)((waves + 3) / 4);
+#define DEX_TB(T_)                                     \
+  (vw == 2 ? tb_launch<MODE, T_, 2>(a, nl, blocks, st) \
+           : tb_launch<MODE, T_, 1>(a, nl, blocks, st))
+  switch (tb) {
+    case 8:
+      DEX_TB(8);
+      break;
+    case 4:
+      DEX_TB(4);
+      break;
+    case 2:
+      DEX_TB(2);
+      break;
+    default:
+      DEX_TB(1);
+  }
+#undef DEX_TB
+}
+
+// One step of the vector kernels (a tuning configuration).
+void step(const St& s, const float* u, float* un, float* snap, hipStream_t st) {
+  if (s.vec) {
     const int64_t nt = s.n / 4;
     hipLaunchKernelGGL(stencil_step_vec, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, st, u,
                        un, snap, s.H, s.W, s.c, s.rho);
@@ -368,7 +824,7 @@ void step(const St& s, const float* u, float* un, float* snap, bool strip, hipSt
   }
 }
 
-// form: 0 gather (strip kernel where the grid allows), 1 scatter, 2 gather (vector kernel).
+// One adjoint step; form: 1 scatter, 2 gather (vector kernel).
 void adj(const St& s, int form, const float* g, const float* u, float* out, bool accumulate,
          hipStream_t st) {
   const unsigned nb = (unsigned)((s.n + 255) / 256);
@@ -376,8 +832,6 @@ void adj(const St& s, int form, const float* g, const float* u, float* out, bool
     if (!accumulate) fill_zero(out, (size_t)s.n * 4, st);
     hipLaunchKernelGGL(stencil_adj_scatter, dim3(nb), dim3(256), 0, st, g, u, out, s.H, s.W, s.c,
                        s.rho);
-  } else if (form == 0 && strip_rb(s)) {
-    launch_strip<true>(s, g, out, nullptr, u, accumulate ? 1 : 0, st);
   } else if (s.vec) {
     hipLaunchKernelGGL(stencil_adj_gather_vec, dim3((unsigned)((s.n / 4 + 255) / 256)), dim3(256),
                        0, st, g, u, out, s.H, s.W, s.c, s.rho, accumulate ? 1 : 0);
@@ -403,9 +857,8 @@ size_t stencil_ws_bytes(const dex_desc& d, int role) {
 
 int stencil_num_configs(const dex_desc& d, int role) {
   (void)d;
-  // fwd: 0 strip kernel (where the grid allows), 1 vector kernel; vjp: 0 gather
-  // form (strip kernels where allowed), 1 scatter form, 2 gather form with
-  // vector kernels
+  // fwd: 0 time-blocked kernel, 1 vector kernel; vjp: 0 gather form,
+  // time-blocked, 1 scatter form, 2 gather form with vector kernels
   return role == DEX_WS_VJP ? 3 : 2;
 }
 
@@ -414,14 +867,38 @@ dex_status stencil_fwd(const dex_desc& d, int cfg, const float* u0, const float*
   St s = st_of(d);
   float* other = (float*)ws;
   double* part = (double*)((char*)ws + align256((size_t)s.n * 4));
-  // step t writes into uT when (T-1-t) is even, so the last step lands in uT
   const float* cur = u0;
   ProfRange pr(DEX_PROF_STENCIL_FWD, st);
-  for (int t = 0; t < s.T; ++t) {
-    float* dst = ((s.T - 1 - t) % 2 == 0) ? uT : other;
-    float* snap = (t % s.every == 0) ? ckpt + (int64_t)(t / s.every) * s.n : nullptr;
-    step(s, cur, dst, snap, cfg == 0, st);
-    cur = dst;
+  if (cfg == 0) {
+    TbPlan plan(s);
+    // each stretch between checkpoints ends in the next one's storage (the last
+    // in uT); its inner launches alternate between uT and the workspace field,
+    // the one before uT's writing the workspace. The first launch also copies
+    // u0 to its checkpoint.
+    for (int sg = 0; sg < s.nck; ++sg) {
+      const int len = std::min(s.every, s.T - sg * s.every);
+      const bool last = sg == s.nck - 1;
+      int pieces = tb_pieces(len);
+      for (int left = len; left > 0; --pieces) {
+        const int tb = tb_of(left);
+        left -= tb;
+        TbArgs a{};
+        a.in = cur;
+        a.out = left == 0 ? (last ? uT : ckpt + (int64_t)(sg + 1) * s.n)
+                          : (pieces % 2 == 0 ? other : uT);
+        if (sg == 0 && left + tb == len) a.snap = ckpt;
+        tb_steps<TB_FWD>(plan, tb, a, st);
+        cur = a.out;
+      }
+    }
+  } else {
+    // step t writes into uT when (T-1-t) is even, so the last step lands in uT
+    for (int t = 0; t < s.T; ++t) {
+      float* dst = ((s.T - 1 - t) % 2 == 0) ? uT : other;
+      float* snap = (t % s.every == 0) ? ckpt + (int64_t)(t / s.every) * s.n : nullptr;
+      step(s, cur, dst, snap, st);
+      cur = dst;
+    }
   }
   pr.end(s.T);
   if (s.T == 0) {
@@ -442,14 +919,18 @@ dex_status stencil_jvp(const dex_desc& d, const float* u0, const float* target, 
                       {(float*)((char*)ws + 2 * fb), (float*)((char*)ws + 3 * fb)}};
   double* part = (double*)((char*)ws + 4 * fb);
   const float *u = u0, *du = du0;
-  const unsigned nb = (unsigned)((s.n + 255) / 256);
-  for (int t = 0; t < s.T; ++t) {
-    float* un = buf[t & 1][0];
-    float* dun = buf[t & 1][1];
-    hipLaunchKernelGGL(stencil_tan_step, dim3(nb), dim3(256), 0, st, u, du, un, dun, s.H, s.W, s.c,
-                       s.rho);
-    u = un;
-    du = dun;
+  TbPlan plan(s);
+  for (int left = s.T, q = 0; left > 0; q ^= 1) {
+    const int tb = tb_of(left);
+    left -= tb;
+    TbArgs a{};
+    a.in = u;
+    a.in2 = du;
+    a.out = buf[q][0];
+    a.out2 = buf[q][1];
+    tb_steps<TB_TAN>(plan, tb, a, st);
+    u = a.out;
+    du = a.out2;
   }
   hipLaunchKernelGGL(stencil_tan_loss_partial, dim3(kLossBlocks), dim3(256), 0, st, u, target, du,
                      dtarget, s.n, part);
@@ -467,7 +948,9 @@ dex_status stencil_vjp(const dex_desc& d, int cfg, const float* u0, const float*
   const size_t fb = align256((size_t)s.n * 4);
   float* lamA = (float*)ws;
   float* lamB = (float*)((char*)ws + fb);
-  float* seg = (float*)((char*)ws + 2 * fb);  // states u_{s0+1} .. u_{s0+len-1}
+  // recompute: a segment's states u_{s0+1} .. u_{s0+len-1} (vector and scatter
+  // forms), or rho cos(u) of its states u_{s0} .. u_{s0+len-1} (time-blocked form)
+  float* seg = (float*)((char*)ws + 2 * fb);
   const unsigned nb = (unsigned)((s.n + 255) / 256);
   if (s.T == 0) {
     if (accumulate) {
@@ -480,14 +963,70 @@ dex_status stencil_vjp(const dex_desc& d, int cfg, const float* u0, const float*
     }
     return check_hip(hipGetLastError(), "stencil_vjp");
   }
-  hipLaunchKernelGGL(stencil_lam_init, dim3(nb), dim3(256), 0, st, uT_in, target, dL, s.n, lamA);
-  float* g = lamA;
-  float* o = lamB;
   const bool recompute = d.variant == DEX_STENCIL_RECOMPUTE;
   if (!recompute && s.rho != 0.f)
     return fail(DEX_ERR_INVALID_ARG, "the no-recompute reverse pass needs rho == 0");
-  ProfRange pr(DEX_PROF_STENCIL_VJP, st);
+  float* g = lamA;
+  float* o = lamB;
   int64_t launches = 0;
+  if (form == 0) {
+    ProfRange pr(DEX_PROF_STENCIL_VJP, st);
+    TbPlan plan(s);
+    const bool nl = s.rho != 0.f;
+    const int64_t rcs = (int64_t)(fb / 4);
+    bool first = true;
+    for (int sg = s.nck - 1; sg >= 0; --sg) {
+      const int s0 = sg * s.every;
+      const int len = std::min(s.every, s.T - s0);
+      if (nl) {
+        // the segment's states again, from its checkpoint, keeping only what the
+        // adjoint steps read: rho cos(u_t). With rho = 0 they read no state, and
+        // none is rebuilt. The states between launches alternate between the
+        // cotangent field that is free here and the last rc field, which only
+        // the last launch fills: the state that launch reads is in the former.
+        const float* cur = ckpt + (int64_t)sg * s.n;
+        int pieces = tb_pieces(len);
+        for (int done = 0; done < len; --pieces) {
+          const int tb = tb_of(len - done);
+          TbArgs a{};
+          a.in = cur;
+          a.rc = seg + done * rcs;
+          a.rcs = rcs;
+          done += tb;
+          a.out = done == len ? nullptr : pieces % 2 == 0 ? o : seg + (len - 1) * rcs;
+          tb_steps<TB_REC>(plan, tb, a, st);
+          cur = a.out;
+          launches += tb;
+        }
+      }
+      for (int left = len; left > 0;) {
+        const int tb = tb_of(left);
+        TbArgs a{};
+        a.rc = nl ? seg + (left - 1) * rcs : nullptr;
+        a.rcs = rcs;
+        left -= tb;
+        const bool last = sg == 0 && left == 0;
+        a.out = last ? du0 : o;
+        a.accumulate = last && accumulate;
+        if (first) {
+          a.in = uT_in;
+          a.in2 = target;
+          a.dL = dL;
+          tb_steps<TB_ADJI>(plan, tb, a, st);
+        } else {
+          a.in = g;
+          tb_steps<TB_ADJ>(plan, tb, a, st);
+        }
+        first = false;
+        launches += tb;
+        std::swap(g, o);
+      }
+    }
+    pr.end(launches);
+    return check_hip(hipGetLastError(), "stencil_vjp");
+  }
+  hipLaunchKernelGGL(stencil_lam_init, dim3(nb), dim3(256), 0, st, uT_in, target, dL, s.n, lamA);
+  ProfRange pr(DEX_PROF_STENCIL_VJP, st);
   for (int sg = s.nck - 1; sg >= 0; --sg) {
     const int s0 = sg * s.every;
     const int len = std::min(s.every, s.T - s0);
@@ -497,7 +1036,7 @@ dex_status stencil_vjp(const dex_desc& d, int cfg, const float* u0, const float*
       const float* cur = ck;
       for (int q = 1; q < len; ++q) {
         float* dst = seg + (int64_t)(q - 1) * (fb / 4);
-        step(s, cur, dst, nullptr, form == 0, st);
+        step(s, cur, dst, nullptr, st);
         cur = dst;
         ++launches;
       }

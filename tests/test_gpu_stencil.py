@@ -171,3 +171,51 @@ def test_full_size_forward_mode_against_closed_form(dev):
     want = float(np.sum((uTo - tg) * (fft_power(du0.astype(np.float64), c["steps"]) - dtg)))
     print(f"  full size forward mode: rel {abs(got - want) / abs(want):.2e}", flush=True)
     assert abs(got - want) <= 1e-5 * abs(want)
+
+
+# Time-blocked kernels: grids smaller than a launch's halo, widths on either side
+# of a strip's kept columns (48 or 112 at eight steps), chunks with a partial last
+# row group, step counts of every mix of launch lengths (8, 4, 2, 1), segments of
+# one step. FP32 results against the FP64 oracle: the documented 1e-5.
+@pytest.mark.parametrize("H,W,steps,every,rho", [(1, 1, 9, 4, 0.0), (3, 5, 17, 32, -0.2), (2, 113, 15, 15, 0.05),
+                                                 (13, 47, 8, 8, 0.0), (13, 48, 12, 5, -0.2), (70, 49, 31, 16, 0.0),
+                                                 (37, 112, 26, 13, -0.2), (131, 225, 23, 11, 0.05),
+                                                 (600, 333, 16, 1, -0.2), (257, 2051, 10, 32, 0.0)])
+def test_time_blocked_edges(dev, H, W, steps, every, rho):
+    u0, tg = workloads.stencil_inputs(H, W, 17)
+    L, uT, du, ck = run(u0, tg, steps, every, rho=rho)
+    Lo, uTo, duo = ost.loss_and_grad(u0, tg, steps, rho=rho)
+    assert abs(L - Lo) <= 1e-5 * abs(Lo)
+    assert rel(uT, uTo) <= 1e-5 and rel(du, duo) <= 1e-5
+    for s in range(ck.shape[0]):
+        assert rel(ck[s], ost.forward(u0, s * every, rho=rho)) <= 1e-5
+    # the grouping of the steps changes no bit
+    d1 = run(u0, tg, steps, 3, rho=rho)
+    assert np.array_equal(d1[1], uT) and np.array_equal(d1[2], du)
+    rng = np.random.default_rng(5)
+    t0, t1 = (rng.standard_normal((H, W)).astype(np.float32) for _ in range(2))
+    want = ost.loss_jvp(u0, tg, t0, t1, steps, rho=rho)
+    scale = np.linalg.norm(uTo - tg) * np.linalg.norm(t0)  # of the inner product's terms
+    assert abs(run_jvp(u0, tg, t0, t1, steps, rho) - want) <= 1e-5 * max(abs(want), scale)
+
+
+@pytest.mark.parametrize("scale", [0.1, 1.0, 100.0, 2.0 ** 14, 1e6, 1e20])
+def test_sine_of_the_non_linear_term(dev, scale):
+    """One step with c = 0 is u + rho sin(u): each way of reducing the argument.
+    The sine is within 2 units in the last place (2^-22 of its largest value) and
+    the sum rounds once more."""
+    from paper_2104_05372_amd import dex
+    H, W = 40, 72
+    rng = np.random.default_rng(3)
+    u = (rng.uniform(-1, 1, (H, W)) * scale).astype(np.float32)
+    u[0, 0], u[1, 1] = 0.0, np.float32(scale)
+    rho = 2.0 ** 40 if scale < 1e10 else 2.0 ** 100
+    d = dex.stencil_desc(H, W, 1, 1, 0.0, rho)
+    tu = torch.tensor(u, device=dev)
+    L, uT, ck = torch.empty(1, device=dev), torch.empty_like(tu), torch.empty_like(tu)
+    dex.dex_fwd(d, [tu, torch.zeros_like(tu)], [L, uT], [ck, uT],
+                dex.workspace(dex.dex_workspace_bytes(d, 0), dev))
+    u64 = u.astype(np.float64)
+    want = u64 + rho * np.sin(u64)
+    err = np.abs(uT.cpu().numpy() - want)
+    assert err.max() <= rho * 2.0 ** -21
