@@ -25,6 +25,7 @@ ARCH = "gfx950"
 UNITS = [
     ("abi.cpp", [], "abi.o"),
     ("gmm.hip", [], "gmm.o"),
+    ("gmm_f64.hip", [], "gmm_f64.o"),
     ("gmm_mfma_inst.hip", ["-DDEX_PREC=0"], "gmm_mfma_f32.o"),
     ("gmm_mfma_inst.hip", ["-DDEX_PREC=1"], "gmm_mfma_bf16.o"),
     ("gmm_mfma_inst.hip", ["-DDEX_PREC=2"], "gmm_mfma_bf16x3.o"),

@@ -86,17 +86,57 @@ DEX_DEV T xor_lane(T v, int mask) {
   return __shfl_xor(v, mask, kWave);
 }
 
+// Value of `v` at lane (lane ^ M), M < 16, by a DPP move within a row of 16 lanes,
+// for the steps of a butterfly (no LDS crossbar: a step costs a move or two instead
+// of a round trip). UP: steps M = 1, 2, 4, 8 in this order, so that aligned groups of
+// M lanes already hold equal values (quad permutations, half-row and row mirrors);
+// else M = 8, 4, 2, 1, after which lanes M apart do (row rotations by M). At 16 and
+// 32 the lane swaps, in either order.
+template <int M, bool UP, typename T>
+DEX_DEV T partner(T v) {
+  static_assert(sizeof(T) == 4 || sizeof(T) == 8, "one or two registers");
+  auto half = [](uint32_t w) -> uint32_t {
+    if constexpr (M == 32 || M == 16) {
+      const float f = __uint_as_float(w);
+      const LanePair p = M == 32 ? swap32(f, f) : swap16(f, f);
+      return __float_as_uint((threadIdx.x & M) ? p.first : p.second);
+    } else {
+      constexpr int ctrl = !UP ? 0x120 + M : M == 1 ? 0xB1 : M == 2 ? 0x4E : M == 4 ? 0x141 : 0x140;
+      return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, ctrl, 0xF, 0xF, false);
+    }
+  };
+  if constexpr (sizeof(T) == 4) {
+    return __builtin_bit_cast(T, half(__builtin_bit_cast(uint32_t, v)));
+  } else {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    return __builtin_bit_cast(T, (uint64_t)half((uint32_t)b) | ((uint64_t)half((uint32_t)(b >> 32)) << 32));
+  }
+}
+// (the ascending form, also for single steps 1 and 2, which hold for any values)
+template <int M, typename T>
+DEX_DEV T butterfly(T v) {
+  return partner<M, true>(v);
+}
+
+// v = op(v, partner's v) over the six steps, 32 first: every lane ends with the
+// same bits when op commutes.
+template <typename T, typename Op>
+DEX_DEV T wave_reduce(T v, Op op) {
+  v = op(v, partner<32, false>(v));
+  v = op(v, partner<16, false>(v));
+  v = op(v, partner<8, false>(v));
+  v = op(v, partner<4, false>(v));
+  v = op(v, partner<2, false>(v));
+  return op(v, partner<1, false>(v));
+}
+
 template <typename T>
 DEX_DEV T wave_sum(T v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v += xor_lane(v, m);
-  return v;
+  return wave_reduce(v, [](T a, T b) { return a + b; });
 }
 
 DEX_DEV float wave_max(float v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v = fmaxf(v, xor_lane(v, m));
-  return v;
+  return wave_reduce(v, [](float a, float b) { return fmaxf(a, b); });
 }
 
 // ---- compensated (Neumaier) accumulation ------------------------------------

@@ -1,159 +1,10 @@
-// GMM log-likelihood, one instance: host dispatch, the VALU forms (FP64 or
-// FP32, one thread per point) and the merge / finalize kernels shared with the
-// matrix-core forms (gmm_dev.h, gmm_mfma_inst.hip).
+// GMM log-likelihood, one instance: host dispatch, the vector-ALU forward mode
+// and the merge / finalize kernels of the FP32-storage forms (gmm_dev.h,
+// gmm_mfma_inst.hip); the FP64 forward and reverse are in gmm_f64.hip.
 #include "gmm_host.h"
 #include "internal.h"
 
 namespace dexk {
-
-// Forward, VALU: one thread per point, D <= DB. beta is stored [K][N].
-template <typename T, int DB>
-__global__ void __launch_bounds__(256) gmm_fwd_valu(const T* __restrict__ alphas,
-                                                    const T* __restrict__ means,
-                                                    const T* __restrict__ qd,
-                                                    const T* __restrict__ l,
-                                                    const T* __restrict__ x, int N, int D, int K,
-                                                    T* __restrict__ beta, T* __restrict__ f,
-                                                    T* __restrict__ fpart) {
-  const int p = blockIdx.x * 256 + threadIdx.x;
-  const bool valid = p < N;
-  const int L = D * (D - 1) / 2;
-  T xr[DB];
-#pragma unroll
-  for (int b = 0; b < DB; ++b) xr[b] = (valid && b < D) ? x[(size_t)p * D + b] : T(0);
-  T m = -INFINITY, ls = 0;
-  for (int k = 0; k < K; ++k) {
-    T r[DB];
-    T kap = alphas[k];
-#pragma unroll
-    for (int b = 0; b < DB; ++b) {
-      if (b < D) {
-        r[b] = xr[b] - means[(size_t)k * D + b];
-        kap += qd[(size_t)k * D + b];
-      } else {
-        r[b] = 0;
-      }
-    }
-    T s = 0;
-#pragma unroll
-    for (int a = 0; a < DB; ++a) {
-      if (a < D) {
-        T y = dexp<T>(qd[(size_t)k * D + a]) * r[a];
-#pragma unroll
-        for (int b = 0; b < a; ++b) y += l[(size_t)k * L + a * (a - 1) / 2 + b] * r[b];
-        s += y * y;
-      }
-    }
-    const T bv = kap - T(0.5) * s;
-    if (valid) beta[(size_t)k * N + p] = bv;
-    const T d = bv - m;
-    if (d > 0) {
-      ls = ls * dexp<T>(-d) + 1;
-      m = bv;
-    } else {
-      ls += dexp<T>(d);
-    }
-  }
-  T v = 0;
-  if (valid) {
-    v = m + dlog<T>(ls);
-    f[p] = v;
-  }
-  T s = 0, e = 0;
-  block_comp_sum<T>(v, s, e);
-  if (threadIdx.x == 0) {
-    fpart[2 * blockIdx.x] = s;
-    fpart[2 * blockIdx.x + 1] = e;
-  }
-}
-
-// Reverse, VALU: block (k, point chunk), 64-point tiles. Threads 0..63 put
-// w y and r of one point each in LDS; then every thread accumulates its share
-// of the D(D+1)/2 + D + 1 sums over the tile.
-template <typename T, int DB>
-__global__ void __launch_bounds__(256) gmm_bwd_valu(const T* __restrict__ means,
-                                                    const T* __restrict__ qd,
-                                                    const T* __restrict__ l,
-                                                    const T* __restrict__ x, int N, int D, int K,
-                                                    int chunk_pts, const T* __restrict__ beta,
-                                                    const T* __restrict__ f,
-                                                    const T* __restrict__ ct,
-                                                    T* __restrict__ part) {
-  constexpr int MAXE = (DB * (DB + 1) / 2 + DB + 1 + 255) / 256;
-  __shared__ T wy[64][DB + 1], rr[64][DB + 1], wsh[64];
-  const int k = blockIdx.x;
-  const int L = D * (D - 1) / 2;
-  const int nM = D * (D + 1) / 2, nE = nM + D + 1;
-  const int pbeg = blockIdx.y * chunk_pts, pend = min(N, pbeg + chunk_pts);
-  const T ctv = ct[0];
-  int ea[MAXE], eb[MAXE], kind[MAXE];
-  T acc[MAXE];
-#pragma unroll
-  for (int q = 0; q < MAXE; ++q) {
-    const int e = threadIdx.x + 256 * q;
-    acc[q] = 0;
-    kind[q] = 3;
-    ea[q] = eb[q] = 0;
-    if (e < nM) {
-      int a = 0;
-      while ((a + 1) * (a + 2) / 2 <= e) ++a;
-      ea[q] = a;
-      eb[q] = e - a * (a + 1) / 2;
-      kind[q] = 0;
-    } else if (e < nM + D) {
-      ea[q] = e - nM;
-      kind[q] = 1;
-    } else if (e < nE) {
-      kind[q] = 2;
-    }
-  }
-  for (int t0 = pbeg; t0 < pend; t0 += 64) {
-    __syncthreads();
-    if (threadIdx.x < 64) {
-      const int p = t0 + threadIdx.x;
-      const bool valid = p < pend;
-      T r[DB];
-      T w = 0;
-#pragma unroll
-      for (int b = 0; b < DB; ++b)
-        r[b] = (valid && b < D) ? x[(size_t)p * D + b] - means[(size_t)k * D + b] : T(0);
-      if (valid) w = dexp<T>(beta[(size_t)k * N + p] - f[p]) * ctv;
-#pragma unroll
-      for (int a = 0; a < DB; ++a) {
-        if (a < D) {
-          T y = dexp<T>(qd[(size_t)k * D + a]) * r[a];
-#pragma unroll
-          for (int b = 0; b < a; ++b) y += l[(size_t)k * L + a * (a - 1) / 2 + b] * r[b];
-          wy[threadIdx.x][a] = w * y;
-          rr[threadIdx.x][a] = r[a];
-        }
-      }
-      wsh[threadIdx.x] = w;
-    }
-    __syncthreads();
-    const int np = min(64, pend - t0);
-#pragma unroll
-    for (int q = 0; q < MAXE; ++q) {
-      if (kind[q] == 0) {
-        for (int pp = 0; pp < np; ++pp) acc[q] += wy[pp][ea[q]] * rr[pp][eb[q]];
-      } else if (kind[q] == 1) {
-        for (int pp = 0; pp < np; ++pp) acc[q] += wy[pp][ea[q]];
-      } else if (kind[q] == 2) {
-        for (int pp = 0; pp < np; ++pp) acc[q] += wsh[pp];
-      }
-    }
-  }
-  T* P = part + ((size_t)blockIdx.y * K + k) * ((size_t)D * D + D + 1);
-#pragma unroll
-  for (int q = 0; q < MAXE; ++q) {
-    if (kind[q] == 0)
-      P[(size_t)ea[q] * D + eb[q]] = acc[q];
-    else if (kind[q] == 1)
-      P[(size_t)D * D + ea[q]] = acc[q];
-    else if (kind[q] == 2)
-      P[(size_t)D * D + D] = acc[q];
-  }
-}
 
 template <typename T>
 __global__ void __launch_bounds__(256) k_merge_lse(const float2* __restrict__ ml, int Sk, int N,
@@ -359,8 +210,7 @@ __global__ void __launch_bounds__(256) k_jvp_final(const double* __restrict__ pa
   __syncthreads();
   {
     double m = am;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
+    m = wave_reduce(m, [](double a, double b) { return fmax(a, b); });
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
   }
   __syncthreads();
@@ -381,22 +231,6 @@ __global__ void __launch_bounds__(256) k_finalize_F(const T* __restrict__ fpart,
                                                     const T* __restrict__ alphas, int K, int64_t N,
                                                     T* __restrict__ F) {
   finalize_F_block<T>(fpart, nparts, alphas, K, N, F);
-}
-
-template <typename T, typename TP>
-__global__ void __launch_bounds__(256) k_bwd_finalize(const TP* __restrict__ part, size_t E, int S,
-                                                      int K, int D, int ld, int64_t N,
-                                                      const T* __restrict__ alphas,
-                                                      const T* __restrict__ qd,
-                                                      const T* __restrict__ l,
-                                                      const T* __restrict__ means,
-                                                      const T* __restrict__ ct,
-                                                      T* __restrict__ d_alphas,
-                                                      T* __restrict__ d_means, T* __restrict__ d_qd,
-                                                      T* __restrict__ d_l, int accumulate) {
-  const int k = blockIdx.x;
-  bwd_finalize_comp<T, TP>(part + (size_t)k * E, (size_t)K * E, S, k, K, D, ld, N, alphas, qd, l,
-                           means, ct[0], d_alphas, d_means, d_qd, d_l, accumulate);
 }
 
 // Component k's moment partials, already summed into slot 0 (S = 1); the
@@ -452,7 +286,6 @@ const FwdCfg kFwdF32[] = {{2, 0, 1}, {2, 0, 2}, {2, 2, 1}, {2, 1, 2}};
 // FP16 form: scaled rows double-buffered (default) or not)
 const BwdCfg kBwdBF[] = {{2, 0}, {3, 0}, {4, 0}, {2, 2}, {3, 2}, {4, 0, 0}, {2, 1}, {4, 1}};
 const BwdCfg kBwdF32[] = {{2, 0}, {1, 0}, {4, 0}, {2, 2}, {1, 2}};
-constexpr int kValuS = 16;
 
 int nfwd(const Shape& s) { return s.prec == PREC_BF16 ? 8 : 4; }
 int nbwd(const Shape& s) { return s.prec == PREC_F32 ? 5 : 8; }
@@ -518,47 +351,6 @@ MfmaOps ops_of(const Shape& s, const CacheLayout& cl, const char* cache) {
   return o;
 }
 
-template <typename T>
-void launch_fwd_valu(const Shape& s, const GmmPtrs& in, T* beta, T* f, T* fpart, hipStream_t st) {
-  dim3 grid((unsigned)((s.g.N + 255) / 256));
-#define DEX_FV(DB)                                                                         \
-  hipLaunchKernelGGL((gmm_fwd_valu<T, DB>), grid, dim3(256), 0, st, (const T*)in.alphas, \
-                     (const T*)in.means, (const T*)in.qd, (const T*)in.l, (const T*)in.x,  \
-                     (int)s.g.N, (int)s.g.D, (int)s.g.K, beta, f, fpart)
-  if (s.g.D <= 4)
-    DEX_FV(4);
-  else if (s.g.D <= 8)
-    DEX_FV(8);
-  else if (s.g.D <= 16)
-    DEX_FV(16);
-  else if (s.g.D <= 32)
-    DEX_FV(32);
-  else
-    DEX_FV(64);
-#undef DEX_FV
-}
-
-template <typename T>
-void launch_bwd_valu(const Shape& s, const GmmPtrs& in, const T* beta, const T* f, const T* ct,
-                     T* part, int chunk, hipStream_t st) {
-  dim3 grid((unsigned)s.g.K, (unsigned)((s.g.N + chunk - 1) / chunk));
-#define DEX_BV(DB)                                                                          \
-  hipLaunchKernelGGL((gmm_bwd_valu<T, DB>), grid, dim3(256), 0, st, (const T*)in.means,   \
-                     (const T*)in.qd, (const T*)in.l, (const T*)in.x, (int)s.g.N,         \
-                     (int)s.g.D, (int)s.g.K, chunk, beta, f, ct, part)
-  if (s.g.D <= 4)
-    DEX_BV(4);
-  else if (s.g.D <= 8)
-    DEX_BV(8);
-  else if (s.g.D <= 16)
-    DEX_BV(16);
-  else if (s.g.D <= 32)
-    DEX_BV(32);
-  else
-    DEX_BV(64);
-#undef DEX_BV
-}
-
 bool valid_shape(const Shape& s) {
   const GmmGeom& g = s.g;
   if (g.N < 1 || g.D < 1 || g.K < 1 || g.D > 64) return false;
@@ -613,15 +405,13 @@ size_t gmm_ws_bytes(const dex_desc& d, int role) {
   if (!valid_shape(s)) return 0;
   if (role == DEX_WS_RESID) return cache_layout(s).total;
   if (role == DEX_WS_JVP) return jvp_layout(s).total;
+  if (!s.mfma)
+    return role == DEX_WS_FWD ? gmm_f64_fwd_ws(s.g.N) : gmm_f64_bwd_ws(s.g.N, s.g.D, s.g.K);
   const size_t nparts = (size_t)(s.g.Npad / 64);  // objective partials (one per 64 points)
-  if (role == DEX_WS_FWD) {
-    size_t b = align256(nparts * 2 * s.tsize);
-    if (s.mfma) b += align256((size_t)fwd_max_slots(s.g.K) * s.g.Npad * sizeof(float2));
-    return b;
-  }
-  if (s.mfma)
-    return align256((size_t)bwd_max_slots(s.g.Npad, s.g.K) * s.g.K * mom_slot(s.g.DP) * 4);
-  return align256((size_t)kValuS * s.g.K * (s.g.D * s.g.D + s.g.D + 1) * s.tsize);
+  if (role == DEX_WS_FWD)
+    return align256(nparts * 2 * s.tsize) +
+           align256((size_t)fwd_max_slots(s.g.K) * s.g.Npad * sizeof(float2));
+  return align256((size_t)bwd_max_slots(s.g.Npad, s.g.K) * s.g.K * mom_slot(s.g.DP) * 4);
 }
 
 int gmm_num_configs(const dex_desc& d, int role) {
@@ -638,12 +428,9 @@ dex_status gmm_fwd(const dex_desc& d, int cfg, const GmmPtrs& in, void* F, void*
   char* cc = (char*)cache;
   const size_t nparts = (size_t)(s.g.Npad / 64);
   if (!s.mfma) {
-    double* fpart = (double*)ws;
-    launch_fwd_valu<double>(s, in, (double*)(cc + cl.beta), (double*)f, fpart, st);
-    hipLaunchKernelGGL((k_finalize_F<double>), dim3(1), dim3(256), 0, st, fpart,
-                       (int)((s.g.N + 255) / 256), (const double*)in.alphas, (int)s.g.K, s.g.N,
-                       (double*)F);
-    return check_hip(hipGetLastError(), "gmm_fwd (VALU)");
+    gmm_f64_fwd(s.g.N, s.g.D, s.g.K, in, (double*)(cc + cl.beta), (double*)f, (double*)ws,
+                (double*)F, st);
+    return check_hip(hipGetLastError(), "gmm_fwd (FP64)");
   }
   if (cfg < 0 || cfg >= nfwd(s)) return fail(DEX_ERR_INVALID_ARG, "GMM forward config %d out of range", cfg);
   const FwdCfg c = fwd_cfg(s, cfg);
@@ -717,17 +504,9 @@ dex_status gmm_vjp(const dex_desc& d, int cfg, const GmmPtrs& in, const void* f,
   CacheLayout cl = cache_layout(s);
   const char* cc = (const char*)cache;
   if (!s.mfma) {
-    const int chunk = (int)(((s.g.N + kValuS - 1) / kValuS + 63) / 64 * 64);
-    const int S = (int)((s.g.N + chunk - 1) / chunk);
-    launch_bwd_valu<double>(s, in, (const double*)(cc + cl.beta), (const double*)f,
-                            (const double*)ct, (double*)ws, chunk, st);
-    const size_t E = (size_t)s.g.D * s.g.D + s.g.D + 1;
-    hipLaunchKernelGGL((k_bwd_finalize<double, double>), dim3((unsigned)s.g.K), dim3(256), 0, st,
-                       (const double*)ws, E, S, (int)s.g.K, (int)s.g.D, (int)s.g.D, s.g.N,
-                       (const double*)in.alphas, (const double*)in.qd, (const double*)in.l,
-                       (const double*)nullptr, (const double*)ct, (double*)out.d_alphas, (double*)out.d_means,
-                       (double*)out.d_qd, (double*)out.d_l, accumulate ? 1 : 0);
-    return check_hip(hipGetLastError(), "gmm_vjp (VALU)");
+    gmm_f64_vjp(s.g.N, s.g.D, s.g.K, in, (const double*)(cc + cl.beta), (const double*)f,
+                (const double*)ct, out, accumulate, (double*)ws, st);
+    return check_hip(hipGetLastError(), "gmm_vjp (FP64)");
   }
   if (cfg < 0 || cfg >= nbwd(s)) return fail(DEX_ERR_INVALID_ARG, "GMM reverse config %d out of range", cfg);
   const BwdCfg c = bwd_cfg(s, cfg);

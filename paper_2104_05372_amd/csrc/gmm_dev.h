@@ -228,14 +228,15 @@ template <typename T>
 DEX_DEV void block_comp_sum(T v, T& out_s, T& out_e) {
   __shared__ T sh_s[16], sh_e[16];
   T s = v, e = 0;
-#pragma unroll
-  for (int m = 1; m < 64; m <<= 1) {
-    T os = xor_lane(s, m), oe = xor_lane(e, m);
+  auto step = [&](auto mc) {
+    constexpr int M = 1 << decltype(mc)::value;
+    const T os = butterfly<M>(s), oe = butterfly<M>(e);
     T ns, ne;
     two_sum(s, os, ns, ne);
     s = ns;
     e = e + oe + ne;
-  }
+  };
+  static_for<6>(step);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
   __syncthreads();
   if (lane == 0) {
@@ -1522,8 +1523,8 @@ DEX_DEV void bwd_finalize_mom(const float* __restrict__ part, size_t sstride, in
     float v = 0.f;
     if (a < D)
       for (int cc = r; cc <= a; cc += 4) v = fmaf(QT[cc][a], vq[cc], v);
-    v += xor_lane(v, 1);
-    v += xor_lane(v, 2);
+    v += butterfly<1>(v);
+    v += butterfly<2>(v);
     if (a < D && r == 0) bq[a] = v;
   }
   __syncthreads();
@@ -1532,8 +1533,8 @@ DEX_DEV void bwd_finalize_mom(const float* __restrict__ part, size_t sstride, in
     float gm = 0.f;
     if (d < D)
       for (int a = d + r; a < D; a += 4) gm = fmaf(QT[d][a], bq[a], gm);
-    gm += xor_lane(gm, 1);
-    gm += xor_lane(gm, 2);
+    gm += butterfly<1>(gm);
+    gm += butterfly<2>(gm);
     if (d < D && r == 0) {
       float* om = d_means + (size_t)k * D + d;
       *om = accumulate ? *om + gm : gm;
@@ -1644,11 +1645,7 @@ DEX_DEV void finalize_F_block(const T* __restrict__ fpart, int nparts, const T* 
   __shared__ T red[16];
   T m = -INFINITY;
   for (int k = threadIdx.x; k < K; k += blockDim.x) m = alphas[k] > m ? alphas[k] : m;
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    const T om = xor_lane(m, o);
-    m = om > m ? om : m;
-  }
+  m = wave_reduce(m, [](T a, T b) { return a > b ? a : b; });
   __syncthreads();
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
   __syncthreads();
@@ -1662,78 +1659,6 @@ DEX_DEV void finalize_F_block(const T* __restrict__ fpart, int nparts, const T* 
     const T lse = m + dlog<T>(zs + ze);
     F[0] = (s - (T)N * lse) + e;
   }
-}
-
-// Reverse, final step for component k: fixed-order compensated sum over the
-// S partial slots (stride `sstride` elements), then the gradient assembly.
-// Slot layout: M[a*ld + b] (a >= b), b[ld*ld + a], A at ld*ld + ld.
-// With `means` non-null the slots hold sum_i w y x~^T instead of M, and
-// M = that - b mu^T is formed here (the matrix-core reverse pass contracts
-// against x~, which does not depend on the component).
-template <typename T, typename TP>
-DEX_DEV void bwd_finalize_comp(const TP* __restrict__ part, size_t sstride, int S, int k, int K,
-                               int D, int ld, int64_t N, const T* __restrict__ alphas,
-                               const T* __restrict__ qd, const T* __restrict__ l,
-                               const T* __restrict__ means, T ctv, T* __restrict__ d_alphas,
-                               T* __restrict__ d_means, T* __restrict__ d_qd, T* __restrict__ d_l,
-                               int accumulate) {
-  __shared__ T bsh[64], mdiag[64], Ash;
-  const int L = D * (D - 1) / 2;
-  const int nM = D * (D + 1) / 2;
-  auto comp_sum = [&](size_t off) {
-    T s = 0, err = 0;
-    for (int sp = 0; sp < S; ++sp) {
-      T ns, ne;
-      two_sum<T>(s, (T)part[(size_t)sp * sstride + off], ns, ne);
-      s = ns;
-      err += ne;
-    }
-    return s + err;
-  };
-  __syncthreads();
-  for (int e = threadIdx.x; e <= D; e += blockDim.x) {
-    if (e < D)
-      bsh[e] = comp_sum((size_t)ld * ld + e);
-    else
-      Ash = comp_sum((size_t)ld * ld + ld);
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < nM; e += blockDim.x) {
-    int a = (int)((sqrtf(8.f * e + 1.f) - 1.f) * 0.5f);
-    while (a * (a + 1) / 2 > e) --a;
-    while ((a + 1) * (a + 2) / 2 <= e) ++a;
-    const int b = e - a * (a + 1) / 2;
-    T val = comp_sum((size_t)a * ld + b);
-    if (means) val -= bsh[a] * means[(size_t)k * D + b];
-    if (a > b) {
-      T* o = d_l + (size_t)k * L + a * (a - 1) / 2 + b;
-      *o = accumulate ? *o - val : -val;
-    } else {
-      mdiag[a] = val;
-    }
-  }
-  __syncthreads();
-  const T A = Ash;
-  for (int d = threadIdx.x; d < D; d += blockDim.x) {
-    const T eq = dexp<T>(qd[(size_t)k * D + d]);
-    const T gq = A - eq * mdiag[d];
-    T gm = eq * bsh[d];
-    for (int a = d + 1; a < D; ++a) gm += l[(size_t)k * L + a * (a - 1) / 2 + d] * bsh[a];
-    T* oq = d_qd + (size_t)k * D + d;
-    T* om = d_means + (size_t)k * D + d;
-    *oq = accumulate ? *oq + gq : gq;
-    *om = accumulate ? *om + gm : gm;
-  }
-  if (threadIdx.x == 0) {
-    T m = -INFINITY;
-    for (int j = 0; j < K; ++j) m = alphas[j] > m ? alphas[j] : m;
-    T z = 0;
-    for (int j = 0; j < K; ++j) z += dexp<T>(alphas[j] - m);
-    const T sm = dexp<T>(alphas[k] - m) / z;
-    const T ga = A - ctv * (T)N * sm;
-    d_alphas[k] = accumulate ? d_alphas[k] + ga : ga;
-  }
-  __syncthreads();
 }
 
 }  // namespace dexk

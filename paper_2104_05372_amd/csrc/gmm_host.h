@@ -8,6 +8,7 @@
 #include <algorithm>
 
 #include "gmm_dev.h"
+#include "internal.h"
 
 namespace dexi {
 
@@ -67,6 +68,16 @@ FlatSplit mfma_fwd(const GmmGeom& g, const FwdCfg& c, const dexk::MfmaOps& o, fl
 template <int PREC>
 FlatSplit mfma_bwd(const GmmGeom& g, const BwdCfg& c, const dexk::MfmaOps& o, const float* beta,
                    const float* f, const float* ct, float* part, hipStream_t st);
+
+// FP64 forms (gmm_f64.hip). beta: K x N. Workspaces: gmm_f64_fwd_ws bytes for the
+// objective's partials, gmm_f64_bwd_ws for the reverse's moments.
+size_t gmm_f64_fwd_ws(int64_t N);
+size_t gmm_f64_bwd_ws(int64_t N, int64_t D, int64_t K);
+void gmm_f64_fwd(int64_t N, int64_t D, int64_t K, const GmmPtrs& in, double* beta, double* f,
+                 double* fpart, double* F, hipStream_t st);
+void gmm_f64_vjp(int64_t N, int64_t D, int64_t K, const GmmPtrs& in, const double* beta,
+                 const double* f, const double* ct, const GmmGrads& out, bool accumulate,
+                 double* part, hipStream_t st);
 
 // Feature-product forward (BF16 variant, D = 64; defined with the BF16 kernels).
 // qf_prep: the origin (shift), x~^T, the per-tile scaled FP16 copy of x and

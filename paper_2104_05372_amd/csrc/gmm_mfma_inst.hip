@@ -281,8 +281,8 @@ DEX_DEV void qf_w_comp(int k, char* smem, const float* __restrict__ alphas,
     float v = 0.f;
 #pragma unroll 4
     for (int b = r; b < D; b += 4) v = fmaf(P[a][b], mus[b], v);
-    v += xor_lane(v, 1);
-    v += xor_lane(v, 2);
+    v += butterfly<1>(v);
+    v += butterfly<2>(v);
     if (r == 0) Pmu[a] = v;
   }
   __syncthreads();
@@ -450,10 +450,10 @@ DEX_DEV void qf_tan_comp(int k, char* smem, const float* __restrict__ means,
       s1 = fmaf(P[a][bb], dms[bb], s1);
       s2 = fmaf(G[a][bb], mus[bb], s2);
     }
-    s1 += xor_lane(s1, 1);
-    s1 += xor_lane(s1, 2);
-    s2 += xor_lane(s2, 1);
-    s2 += xor_lane(s2, 2);
+    s1 += butterfly<1>(s1);
+    s1 += butterfly<2>(s1);
+    s2 += butterfly<1>(s2);
+    s2 += butterfly<2>(s2);
     if (r == 0) {
       Pdm[a] = s1;
       dPm[a] = s2;

@@ -98,6 +98,22 @@ def test_fp64_shapes(dev, N, D, K):
     check(run_gmm(g, dex.DEX_F64, dex.DEX_GMM_PLAIN), oracle_gmm(g), 1e-10, f"fp64 {N},{D},{K}")
 
 
+# One point, tiles of 64 points and one over, the block that finishes its own sums
+# and the first that does not (1024 points at D <= 4, 256 above), more than sixteen
+# components a wave, one share of the points per component and several.
+@pytest.mark.parametrize("N,D,K", [(1, 1, 1), (63, 4, 2), (64, 5, 3), (65, 16, 40), (256, 16, 4),
+                                   (257, 16, 90), (1024, 4, 5), (1025, 4, 5), (1000, 3, 40),
+                                   (5000, 2, 700), (20011, 13, 25), (130, 64, 9), (9000, 33, 3)])
+def test_fp64_tiles_and_shares(dev, N, D, K):
+    from paper_2104_05372_amd import dex
+    g = workloads.gmm_inputs(N, D, K, 700 + N % 89)
+    want = oracle_gmm(g, -0.5)
+    check(run_gmm(g, dex.DEX_F64, dex.DEX_GMM_PLAIN, ct=-0.5), want, 1e-10, f"fp64 {N},{D},{K}")
+    base = [np.random.default_rng(q).standard_normal(a.shape) for q, a in enumerate(want[2])]
+    got = run_gmm(g, dex.DEX_F64, dex.DEX_GMM_PLAIN, ct=-0.5, accumulate_into=base)
+    check(got, (want[0], want[1], [a + b for a, b in zip(want[2], base)]), 1e-10, "accumulated")
+
+
 @pytest.mark.parametrize("N,D,K", [(257, 1, 3), (1000, 2, 5), (700, 7, 1), (1500, 16, 5),
                                    (999, 17, 6), (2048, 32, 3), (640, 33, 4), (3000, 64, 7),
                                    (513, 63, 2)])
