@@ -142,9 +142,12 @@ static dex_status ensure_device() {
 
 static int pick_config(const dex_desc& d, int role) {
   if (d.config > 0) return d.config - 1;
-  std::lock_guard<std::mutex> lk(g_mu);
-  auto it = g_tuned.find(tune_key(d, role));
-  return it == g_tuned.end() ? 0 : it->second;
+  {
+    std::lock_guard<std::mutex> lk(g_mu);
+    auto it = g_tuned.find(tune_key(d, role));
+    if (it != g_tuned.end()) return it->second;
+  }
+  return d.kind == DEX_GMM ? gmm_default_config(d, role) : 0;
 }
 
 static size_t dtype_size(int32_t dt) {

@@ -40,64 +40,84 @@ DEX_DEV void comp_add(float& s, float& err, float a) {
 
 // Fixed-order compensated sum of each component's partial moment slots (the
 // waves that owned part of its group's points), written back into slot 0, so
-// the per-component finalize reads a single slot. One thread per element.
-// Slots of component k: on each XCD x the waves that owned part of its
-// group's steps, in slots x * SX + rank; summed in (x, rank) order.
+// the per-component finalize reads a single slot. Slots of component k: on each
+// XCD x the waves that owned part of its group's steps, in slots x * SX + rank.
 DEX_DEV int mom_slots(int64_t kg, int x, int64_t nkg, int64_t nsteps, int Wx) {
   const int64_t nsx = (x + 1) * nsteps / 8 - x * nsteps / 8;
   return nsx == 0 ? 0 : split_slots(kg * nsx, nsx, nkg * nsx, min<int64_t>(Wx, nkg * nsx));
 }
 
-__global__ void __launch_bounds__(256) k_mom_reduce(float* __restrict__ part, int64_t E, int K,
-                                                    int gw, int64_t nsteps, int Wx, int SX) {
-  const int64_t i0 = (int64_t)blockIdx.x * 256, i = i0 + threadIdx.x;
-  const int64_t nkg = (K + gw - 1) / gw;
-  // slot counts: with E >= 256 a block meets at most two components, whose
-  // counts 16 threads compute once (64-bit divisions) and share
+// A block sums 64 consecutive elements, one per lane; its W waves share the
+// slots: 8 / W XCDs each in order (W = 4), or every W / 8-th slot of one XCD (W =
+// 16), and the waves' sums are added in wave order. Bound by the latency of the
+// slot loads, so they are spread over waves as far as there are few elements: with
+// few components there are many slots each (N = 1e5, D = 20, K = 5: 340) and one
+// thread per element walked them in 190 us.
+template <int W>
+__global__ void __launch_bounds__(64 * W) k_mom_reduce(float* __restrict__ part, int64_t E, int K,
+                                                       int gw, int64_t nsteps, int Wx, int SX) {
   __shared__ int Ssh[2][8];
+  __shared__ float ssh[W][64], esh[W][64];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int64_t i0 = (int64_t)blockIdx.x * 64, i = i0 + lane;
+  const int64_t nkg = (K + gw - 1) / gw;
+  // a block meets at most two components (E >= 256): their slot counts
   const int k0 = (int)(i0 / E);
-  const bool shared_counts = E >= 256;
-  if (shared_counts) {
-    if (threadIdx.x < 16) {
-      const int kk = k0 + (int)(threadIdx.x >> 3);
-      Ssh[threadIdx.x >> 3][threadIdx.x & 7] =
-          kk < K ? mom_slots(kk / gw, threadIdx.x & 7, nkg, nsteps, Wx) : 0;
-    }
-    __syncthreads();
+  if (threadIdx.x < 16) {
+    const int kk = k0 + (int)(threadIdx.x >> 3);
+    Ssh[threadIdx.x >> 3][threadIdx.x & 7] =
+        kk < K ? mom_slots(kk / gw, threadIdx.x & 7, nkg, nsteps, Wx) : 0;
   }
-  if (i >= (int64_t)K * E) return;
-  const int k = (int)(i / E);
-  const int64_t kg = k / gw;
+  __syncthreads();
+  const bool in = i < (int64_t)K * E;
+  const int kr = in && i >= (int64_t)(k0 + 1) * E ? 1 : 0;
   const size_t stride = (size_t)K * E;
-  // the first 5 slots of every XCD are loaded together (one round trip for
-  // the usual case: a group's waves on one XCD leave at most wx / groups + 2
-  // slots), then summed in (x, rank) order; slots past 5 follow in batches of 4
-  int S[8];
-  float v[8][5];
-#pragma unroll
-  for (int x = 0; x < 8; ++x) {
-    S[x] = shared_counts ? Ssh[k - k0][x] : mom_slots(kg, x, nkg, nsteps, Wx);
-    const float* base = part + (size_t)x * SX * stride + i;
-#pragma unroll
-    for (int u = 0; u < 5; ++u) v[x][u] = u < S[x] ? base[(size_t)u * stride] : 0.f;
-  }
+  constexpr int XW = W < 8 ? 8 / W : 1;   // XCDs of a wave
+  constexpr int SH = W < 8 ? 1 : W / 8;   // waves of an XCD
+  constexpr int U = 5;                    // slots of an XCD loaded together
+  const int xa = W < 8 ? wv * XW : wv / SH, r0 = W < 8 ? 0 : wv % SH;
   float s = 0.f, err = 0.f;
+  int S[XW];
+  float v[XW][U];
 #pragma unroll
-  for (int x = 0; x < 8; ++x) {
+  for (int q = 0; q < XW; ++q) {
+    S[q] = in ? Ssh[kr][xa + q] : 0;
+    const float* base = part + (size_t)(xa + q) * SX * stride + i;
 #pragma unroll
-    for (int u = 0; u < 5; ++u)
-      if (u < S[x]) comp_add(s, err, v[x][u]);
-    const float* base = part + (size_t)x * SX * stride + i;
-    for (int sp = 5; sp < S[x]; sp += 4) {
-      float w[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) w[u] = sp + u < S[x] ? base[(size_t)(sp + u) * stride] : 0.f;
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (sp + u < S[x]) comp_add(s, err, w[u]);
+    for (int u = 0; u < U; ++u) {
+      const int sp = r0 + u * SH;
+      v[q][u] = sp < S[q] ? base[(size_t)sp * stride] : 0.f;
     }
   }
-  part[i] = s + err;
+#pragma unroll
+  for (int q = 0; q < XW; ++q) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (r0 + u * SH < S[q]) comp_add(s, err, v[q][u]);
+    const float* base = part + (size_t)(xa + q) * SX * stride + i;
+    for (int sp0 = r0 + U * SH; sp0 < S[q]; sp0 += 8 * SH) {
+      float w[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int sp = sp0 + u * SH;
+        w[u] = sp < S[q] ? base[(size_t)sp * stride] : 0.f;
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (sp0 + u * SH < S[q]) comp_add(s, err, w[u]);
+    }
+  }
+  ssh[wv][lane] = s;
+  esh[wv][lane] = err;
+  __syncthreads();
+  if (wv == 0 && in) {
+#pragma unroll
+    for (int w = 1; w < W; ++w) {
+      comp_add(s, err, ssh[w][lane]);
+      err += esh[w][lane];
+    }
+    part[i] = s + err;
+  }
 }
 
 // Forward mode of the objective on the vector ALU (every D <= 64; FP64, or
@@ -420,6 +440,34 @@ int gmm_num_configs(const dex_desc& d, int role) {
   return role == DEX_WS_VJP ? nbwd(s) : nfwd(s);
 }
 
+// The configuration of an untuned call, by the form and by N K (the work per
+// element of a component's moments). Measured whole calls, us:
+//   forward FP32: two components a wave, two waves a SIMD, everywhere (N = 30011,
+//     K = 37, D = 20: 40 against 47 with all waves resident; N = 1e5, K = 200, D = 8:
+//     170 against 185); split BF16 at D > 32: one wave a SIMD and two tiles ahead (46
+//     against 50 at N = 1e5, K = 5).
+//   reverse 16-bit: below 1.5e6 two components and one wave a SIMD (D = 64, N =
+//     10000, K = 37: 37 against 41 with four components); above, four components (D =
+//     64, N = 1e5, K = 200: 0.123 ms a call against 0.19 with two), at D <= 16 from 1e7
+//     on with all waves resident (N = 1e5, K = 200, D = 8: 44 against 54).
+//   reverse FP32: one component and two waves a SIMD below 1.2e6 (D = 20, N = 30011,
+//     K = 37: 41 against 45 for two components, all resident), two and two below 5e6
+//     (N = 10000, K = 200: 56 against 58), two and all resident above.
+//   reverse split BF16: as 16-bit below 1.5e6 (35 against 41); above, three
+//     components and two waves a SIMD (D = 20, N = 30011, K = 200: 78 against 82), two
+//     at D > 32, where three need too many registers.
+int gmm_default_config(const dex_desc& d, int role) {
+  const Shape s = shape_of(d);
+  if (!s.mfma || !valid_shape(s)) return 0;
+  const double nk = (double)s.g.N * (double)s.g.K;
+  if (role != DEX_WS_VJP)
+    return s.prec == PREC_F32 ? 2 : s.prec == PREC_BF16X3 && s.g.DP == 64 ? 3 : 0;
+  if (s.prec == PREC_F32) return nk < 1.2e6 ? 4 : nk < 5e6 ? 3 : 0;
+  if (nk < 1.5e6) return 6;
+  if (s.prec == PREC_BF16X3) return s.g.DP == 64 ? 3 : 4;
+  return s.g.DP == 16 && nk >= 1e7 ? 2 : 7;
+}
+
 dex_status gmm_fwd(const dex_desc& d, int cfg, const GmmPtrs& in, void* F, void* f, void* cache,
                    void* ws, hipStream_t st) {
   Shape s = shape_of(d);
@@ -527,8 +575,13 @@ dex_status gmm_vjp(const dex_desc& d, int cfg, const GmmPtrs& in, const void* f,
   }
   pr.end(1);
   const int64_t E = (int64_t)mom_slot(s.g.DP);
-  hipLaunchKernelGGL(k_mom_reduce, dim3((unsigned)((s.g.K * E + 255) / 256)), dim3(256), 0, st,
-                     part, E, (int)s.g.K, sp.gw, sp.nsteps, sp.W, (int)sp.T);
+  const unsigned nb = (unsigned)((s.g.K * E + 63) / 64);
+  if (nb <= 512)
+    hipLaunchKernelGGL(k_mom_reduce<16>, dim3(nb), dim3(1024), 0, st, part, E, (int)s.g.K, sp.gw,
+                       sp.nsteps, sp.W, (int)sp.T);
+  else
+    hipLaunchKernelGGL(k_mom_reduce<4>, dim3(nb), dim3(256), 0, st, part, E, (int)s.g.K, sp.gw,
+                       sp.nsteps, sp.W, (int)sp.T);
   hipLaunchKernelGGL(k_bwd_finalize_mom, dim3((unsigned)s.g.K), dim3(256), 0, st, (const float*)part,
                      (size_t)E, 1, (int)s.g.K,
                      (int)s.g.D, s.g.DP, s.g.N, (const float*)in.alphas, (const float*)in.means,

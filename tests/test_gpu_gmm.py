@@ -135,6 +135,25 @@ def test_bf16_shapes(dev, variant, tol, N, D, K):
     check(got, want, tol, f"bf16 v{variant} {N},{D},{K}")
 
 
+# Few components over many points leave many moment slots per component (summed by
+# sixteen waves), many components few (four waves); one point short of a step, sizes
+# on either side of the default configurations' limits.
+# FP32 against the oracle; the 16-bit forms against their configuration 1 (other
+# slots, the same operands): sums of some thousand FP32 terms, 2e-6, magnified at
+# most some 200 times where A - exp(qd) M_dd cancels.
+@pytest.mark.parametrize("variant", [0, 1, 2])
+@pytest.mark.parametrize("N,D,K", [(30_011, 20, 1), (40_000, 2, 5), (20_003, 64, 3), (1500, 16, 211),
+                                   (31_999, 8, 47)])
+def test_many_and_few_moment_slots(dev, variant, N, D, K):
+    g = workloads.gmm_inputs(N, D, K, 900 + D, np.float32)
+    got = run_gmm(g, 2, variant)
+    if variant == 0:
+        check(got, oracle_gmm(g), 1e-5, f"slots {N},{D},{K}")
+    else:
+        for a, b in zip(got[2], run_gmm(g, 2, variant, bcfg=1)[2]):
+            assert rel(a, b) <= 1e-3
+
+
 @pytest.mark.parametrize("offset", [100.0, 1000.0])
 @pytest.mark.parametrize("D,variant", [(64, 1), (16, 1), (33, 1), (64, 0), (20, 2)])
 def test_data_far_from_origin(dev, offset, D, variant):
