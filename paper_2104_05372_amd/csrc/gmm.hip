@@ -120,8 +120,8 @@ __global__ void __launch_bounds__(64 * W) k_mom_reduce(float* __restrict__ part,
   }
 }
 
-// Forward mode of the objective on the vector ALU (every D <= 64; FP64, or
-// FP32 with x - mu formed exactly in FP64 and rounded once). Block
+// Forward mode of the objective on the vector ALU (FP64 at every D <= 64, FP32 at D
+// < 12, with x - mu formed exactly in FP64 and rounded once). Block
 // (256 points, chunk of kJvpKC components); the components of the chunk are
 // staged in LDS in turn. For point i and component k, with r = x_i - mu_k,
 //   y = Q_k r, dy = dQ_k r - Q_k dmu_k (dQ: diagonal exp(qd) dqd, strict lower
@@ -210,6 +210,148 @@ __global__ void __launch_bounds__(256) gmm_jvp_valu(
   }
   acc = block_sum(acc, sh);
   if (t == 0) part[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = acc;
+}
+
+// The same for FP32 on the matrix cores (16x16x4 FP32 products; D >= 12): a wave
+// takes 64 points and every KS-th component. Per component y = Q_k r and dy = dQ_k r
+// - Q_k dmu_k from r = x - mu_k (formed per component: the difference of two FP32
+// values, rounded once), with the strict lower parts read as they are stored and the
+// next component's loads issued before the current one's products; |y|^2 and y . dy
+// are summed over the lane groups so that lane p owns point p. Each wave writes its
+// FP64 sum to part[wave]. N = 20000, D = 32, K = 50: 53 us (one thread per point
+// and LDS broadcasts of Q and dQ: 163). Lane layout: A and B hold row / column c and
+// contraction values 16 ch + 4 g + j (element j), the result rows 4 g + i.
+template <int DP>
+__global__ void __launch_bounds__(256) gmm_jvp_mfma(
+    const float* __restrict__ alphas, const float* __restrict__ means, const float* __restrict__ qd,
+    const float* __restrict__ l, const float* __restrict__ x, const float* __restrict__ f, int N,
+    int D, int K, int KS, const float* __restrict__ da, const float* __restrict__ dm,
+    const float* __restrict__ dq, const float* __restrict__ dl, double* __restrict__ part) {
+  constexpr int NB = DP / 16, NQ = NB * (NB + 1) / 2;
+  const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
+  const int wave = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tiles = (N + 63) / 64;
+  const int ks = wave / tiles, tile = wave - ks * tiles;
+  if (ks >= KS) return;  // (no barrier follows)
+  const int p0 = tile * 64, p = p0 + lane;
+  const int64_t L = (int64_t)D * (D - 1) / 2;
+  f32x4 xb[4][NB];
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int ch = 0; ch < NB; ++ch) {
+      const float* row = x + (size_t)min(p0 + 16 * t + c, N - 1) * D;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int col = 16 * ch + 4 * g + j;
+        const float v = row[min(col, D - 1)];
+        xb[t][ch][j] = col < D ? v : 0.f;
+      }
+    }
+  const float fp = f[min(p, N - 1)];
+  // component k's operands as loaded: chunks (rb, ch <= rb) of l and dl, the
+  // diagonals of the lane's rows, the means and their tangents at its columns
+  struct Ops {
+    f32x4 q[NQ], dq[NQ], mu[NB], dmu[NB];
+    float qdr[NB], dqr[NB], al, da;
+  };
+  auto load = [&](int k, Ops& o) {
+    int n = 0;
+#pragma unroll
+    for (int rb = 0; rb < NB; ++rb) {
+      const int row = 16 * rb + c, rc = min(row, D - 1);
+      o.qdr[rb] = qd[(size_t)k * D + rc];
+      o.dqr[rb] = dq[(size_t)k * D + rc];
+#pragma unroll
+      for (int ch = 0; ch <= rb; ++ch, ++n)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int col = 16 * ch + 4 * g + j;
+          const int64_t e = k * L + (row < D && col < row ? row * (row - 1) / 2 + col : 0);
+          o.q[n][j] = l[e];
+          o.dq[n][j] = dl[e];
+        }
+    }
+#pragma unroll
+    for (int ch = 0; ch < NB; ++ch)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const size_t e = (size_t)k * D + min(16 * ch + 4 * g + j, D - 1);
+        o.mu[ch][j] = means[e];
+        o.dmu[ch][j] = dm[e];
+      }
+    o.al = alphas[k];
+    o.da = da[k];
+  };
+  double acc = 0.0;
+  auto compute = [&](const Ops& o) {
+    float s[4] = {0, 0, 0, 0}, sd[4] = {0, 0, 0, 0}, sq = 0.f, sdq = 0.f;
+    int n = 0;
+#pragma unroll
+    for (int rb = 0; rb < NB; ++rb) {
+      const int row = 16 * rb + c;
+      const bool rin = row < D;
+      sq += rin ? o.qdr[rb] : 0.f;
+      sdq += rin ? o.dqr[rb] : 0.f;
+      const float ed = expf(o.qdr[rb]), ded = ed * o.dqr[rb];
+      f32x4 y[4], dy[4], qm = f32x4{0.f, 0.f, 0.f, 0.f};  // qm: Q dmu, the same in every column
+#pragma unroll
+      for (int t = 0; t < 4; ++t) y[t] = dy[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ch = 0; ch <= rb; ++ch, ++n) {
+        f32x4 q = o.q[n], dqv = o.dq[n];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int col = 16 * ch + 4 * g + j;
+          if (ch == rb) {
+            q[j] = col < row ? q[j] : col == row ? ed : 0.f;
+            dqv[j] = col < row ? dqv[j] : col == row ? ded : 0.f;
+          }
+          q[j] = rin ? q[j] : 0.f;
+          dqv[j] = rin ? dqv[j] : 0.f;
+          const float mu = col < D ? o.mu[ch][j] : 0.f, dmu = col < D ? o.dmu[ch][j] : 0.f;
+          qm = __builtin_amdgcn_mfma_f32_16x16x4f32(q[j], dmu, qm, 0, 0, 0);
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            const float r = xb[t][ch][j] - mu;
+            y[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(q[j], r, y[t], 0, 0, 0);
+            dy[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(dqv[j], r, dy[t], 0, 0, 0);
+          }
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          s[t] = fmaf(y[t][i], y[t][i], s[t]);
+          sd[t] = fmaf(y[t][i], dy[t][i] - qm[i], sd[t]);
+        }
+    }
+    treduce_groups<4>(s);   // lane 16 t + c: point 16 t + c
+    treduce_groups<4>(sd);
+#define DEX_ROW16(v)          \
+  v += butterfly<1>(v);       \
+  v += butterfly<2>(v);       \
+  v += butterfly<4>(v);       \
+  v += butterfly<8>(v);
+    DEX_ROW16(sq)
+    DEX_ROW16(sdq)
+#undef DEX_ROW16
+    const float w = expf((o.al + sq) - 0.5f * s[0] - fp);
+    if (p < N) acc += (double)(w * ((o.da + sdq) - sd[0]));
+  };
+  Ops oa, ob;
+  load(ks, oa);
+  int k = ks;
+  for (; k + KS < K; k += 2 * KS) {
+    load(k + KS, ob);
+    compute(oa);
+    load(min(k + 2 * KS, K - 1), oa);
+    compute(ob);
+  }
+  if (k < K) compute(oa);
+  acc = wave_sum(acc);
+  if (lane == 0) part[wave] = acc;
 }
 
 // dF = (sum of the partials, fixed order) - N sum_k softmax(alpha)_k dalpha_k,
@@ -395,7 +537,23 @@ size_t gmm_cache_bytes(const dex_desc& d) {
 struct JvpLayout {
   size_t x16, texp, dW16, dkq, disc, part, total;
   int64_t nparts;
+  int ks;  // matrix-core FP32 form: waves sharing a tile's components (0: vector ALU)
 };
+// Waves that share a 64-point tile's components, for the least rounds of waves
+// (one per SIMD) times components each.
+static int jvp_shares(const GmmGeom& g) {
+  const int64_t tiles = (g.N + 63) / 64, simds = 4 * num_cus();
+  int best = 1;
+  int64_t cost = INT64_MAX;
+  for (int ks = 1; ks <= 64 && ks <= g.K; ++ks) {
+    const int64_t c = (tiles * ks + simds - 1) / simds * ((g.K + ks - 1) / ks + 1);
+    if (c < cost) {
+      cost = c;
+      best = ks;
+    }
+  }
+  return best;
+}
 static JvpLayout jvp_layout(const Shape& s) {
   JvpLayout j{};
   size_t o = 0;
@@ -412,6 +570,11 @@ static JvpLayout jvp_layout(const Shape& s) {
     j.dkq = take(Kp * 4);
     j.disc = take(Kp * 4);
     j.nparts = qf_tan_parts(s.g);
+  } else if (s.mfma && s.g.D >= 12) {
+    // (a 16x16 tile is mostly padding below: N = 1e5, K = 150, D = 8 takes the
+    // vector ALU 135 us and the matrix cores 237, D = 16 405 and 242)
+    j.ks = jvp_shares(s.g);
+    j.nparts = (s.g.N + 63) / 64 * j.ks;
   } else {
     j.nparts = ((s.g.N + 255) / 256) * ((s.g.K + kJvpKC - 1) / kJvpKC);
   }
@@ -600,16 +763,18 @@ static void launch_jvp_valu(const Shape& s, const GmmPtrs& in, const void* f, co
                      (const T*)in.means, (const T*)in.qd, (const T*)in.l, (const T*)in.x,     \
                      (const T*)f, (int)s.g.N, (int)s.g.D, (int)s.g.K, (const T*)t.d_alphas,   \
                      (const T*)t.d_means, (const T*)t.d_qd, (const T*)t.d_l, part)
-  if (s.g.D <= 4)
+  if (s.g.D <= 4) {
     DEX_JV(4);
-  else if (s.g.D <= 8)
+  } else if (s.g.D <= 8) {
     DEX_JV(8);
-  else if (s.g.D <= 16)
+  } else if (s.g.D <= 16) {
     DEX_JV(16);
-  else if (s.g.D <= 32)
-    DEX_JV(32);
-  else
-    DEX_JV(64);
+  } else if constexpr (sizeof(T) == 8) {  // (FP32 takes the matrix cores there)
+    if (s.g.D <= 32)
+      DEX_JV(32);
+    else
+      DEX_JV(64);
+  }
 #undef DEX_JV
 }
 
@@ -633,6 +798,23 @@ dex_status gmm_jvp(const dex_desc& d, int cfg, const GmmPtrs& in, const void* f,
     ProfRange pr(DEX_PROF_GMM_JVP, st);
     qf_jvp(s.g, w + jl.x16, w + jl.dW16, (const float*)(w + jl.dkq), (const float*)(w + jl.disc),
            (const int*)(w + jl.texp), (const float*)(cc + cl.beta), (const float*)f, part, st);
+    pr.end(1);
+  } else if (jl.ks) {
+    ProfRange pr(DEX_PROF_GMM_JVP, st);
+    const dim3 grid((unsigned)((jl.nparts + 3) / 4));
+#define DEX_JM(DP_)                                                                              \
+  hipLaunchKernelGGL((gmm_jvp_mfma<DP_>), grid, dim3(256), 0, st, (const float*)in.alphas,       \
+                     (const float*)in.means, (const float*)in.qd, (const float*)in.l,            \
+                     (const float*)in.x, (const float*)f, (int)s.g.N, (int)s.g.D, (int)s.g.K,    \
+                     jl.ks, (const float*)t.d_alphas, (const float*)t.d_means,                   \
+                     (const float*)t.d_qd, (const float*)t.d_l, part)
+    if (s.g.DP == 16)
+      DEX_JM(16);
+    else if (s.g.DP == 32)
+      DEX_JM(32);
+    else
+      DEX_JM(64);
+#undef DEX_JM
     pr.end(1);
   } else {
     ProfRange pr(DEX_PROF_GMM_JVP, st);

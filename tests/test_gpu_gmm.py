@@ -294,6 +294,19 @@ def test_forward_mode(dev, N, D, K, variant, tol):
     assert abs(got - want) <= tol * abs(want), (got, want)
 
 
+# FP32 matrix-core form: both sides of its smallest D and of the padded sizes, one
+# point and one over a tile, fewer and more components than waves share a tile.
+@pytest.mark.parametrize("N,D,K", [(1, 12, 1), (65, 11, 2), (64, 12, 9), (1000, 16, 70), (63, 17, 1),
+                                   (700, 32, 3), (130, 33, 5), (6000, 63, 2), (321, 64, 90)])
+def test_forward_mode_matrix_core_edges(dev, N, D, K):
+    from paper_2104_05372_amd import dex
+    g = workloads.gmm_inputs(N, D, K, 80 + D, np.float32)
+    tangent = along_gradient(g, 3 * D + K)
+    got, _ = run_gmm_jvp(g, dex.DEX_F32, dex.DEX_GMM_PLAIN, tangent)
+    want = ogmm.jvp(*g.params(), g.x, tangent)
+    assert abs(got - want) <= 1e-5 * abs(want), (got, want)
+
+
 @pytest.mark.parametrize("D,variant,tol", [(64, 1, TOL_MIXED16), (64, 0, 1e-5), (12, 1, TOL_MIXED16)])
 def test_forward_mode_far_from_origin(dev, D, variant, tol):
     from paper_2104_05372_amd import dex
