@@ -262,8 +262,11 @@ def row_scatter(torch, dex, workloads, dev, steps, scatter_config=1, check=True)
                             2: "block sort + run sums + atomics"}[scatter_config],
            "fwd_ms": round(f_ms, 4), "vjp_ms": round(b_ms, 4), "bwd_fwd_ratio": round(b_ms / f_ms, 3),
            "touched_rows": touched}
-    bytes_k = {"GATHER": 2 * n * 4 + 2 * n * R * 4, "SCATTER": 2 * n * 4 + n * R * 4 + touched * R * 4,
-               "GATHER_DW": 2 * n * R * 4 + 3 * n * 4}
+    bytes_k = {"GATHER": 2 * n * 4 + 2 * n * R * 4, "SCATTER": 2 * n * 4 + n * R * 4 + touched * R * 4}
+    if scatter_config == 1:  # the sorted form reads each touched row of T and writes dw as well
+        bytes_k["SCATTER"] += touched * R * 4 + n * 4
+    else:
+        bytes_k["GATHER_DW"] = 2 * n * R * 4 + 3 * n * 4
     if j_ms is not None:
         res["jvp_ms"] = round(j_ms, 4)
         bytes_k["GATHER_JVP"] = 3 * n * 4 + 3 * n * R * 4

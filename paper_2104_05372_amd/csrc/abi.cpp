@@ -597,15 +597,10 @@ dex_status dex_vjp(const dex_desc* d, const dex_buf* in, int32_t n_in, const dex
       DEX_TRY(ensure_device());
       // config 1 (default): radix sort + one owner per row; config 2: block sort +
       // run sums + atomics
-      const int path = cfg == 0 ? kScatterSorted : kScatterAtomic;
-      if (!acc) DEX_TRY(fill_zero(ct_in[0].ptr, (size_t)(V * R) * 4, s));
-      DEX_TRY(accum_scatter(ct_in[0].ptr, DEX_F32, V, R, in[1].ptr, DEX_I32, ct_out[0].ptr,
-                            (const float*)in[2].ptr, n, false, nullptr, workspace, ws_bytes_, path,
-                            s, !acc));
-      if (with_dw)
-        DEX_TRY(gather_dw((const float*)in[0].ptr, (const int32_t*)in[1].ptr,
-                          (const float*)ct_out[0].ptr, V, R, n, (float*)ct_in[1].ptr, acc, s));
-      return DEX_OK;
+      return gather_vjp((const float*)in[0].ptr, (const int32_t*)in[1].ptr, (const float*)in[2].ptr,
+                        (const float*)ct_out[0].ptr, V, R, n, (float*)ct_in[0].ptr,
+                        with_dw ? (float*)ct_in[1].ptr : nullptr, acc, cfg == 0, workspace, ws_bytes_,
+                        s);
     }
     case DEX_STENCIL5: {
       const int64_t n = d->dims[0] * d->dims[1];

@@ -70,14 +70,17 @@ size_t scatter_ws_bytes(int32_t acc_dtype, int64_t n_rows, int64_t row_len, int6
                         bool has_vals, bool deterministic);
 // path: kScatterAtomic (block sort + run sums + atomics, no workspace) or
 // kScatterSorted (radix sort + one owner per row, deterministic, workspace).
-// overwrite (sorted path): acc was cleared by the caller and untouched rows stay
-// zero, so a row's owner stores its sum without reading the row.
 constexpr int kScatterAtomic = 0, kScatterSorted = 1;
 dex_status accum_scatter(void* acc, int32_t acc_dtype, int64_t n_rows, int64_t row_len,
                          const void* idx, int32_t idx_dtype, const void* vals,
                          const float* scale, int64_t n, bool count_oob, int64_t* oob,
-                         void* ws, size_t ws_bytes, int path, hipStream_t s,
-                         bool overwrite = false);
+                         void* ws, size_t ws_bytes, int path, hipStream_t s);
+// Transpose of the gather: dT (=|+=) the scatter-accumulate of w[j] g[j, :], and,
+// where dw is given, dw (=|+=) <T[idx_j], g_j> (in the sorted form from the same
+// read of g).
+dex_status gather_vjp(const float* T, const int32_t* idx, const float* w, const float* g, int64_t V,
+                      int64_t R, int64_t n, float* dT, float* dw, bool accumulate, bool sorted,
+                      void* ws, size_t ws_bytes, hipStream_t s);
 dex_status gather_fwd(const float* T, const int32_t* idx, const float* w, int64_t V, int64_t R,
                       int64_t n, float* out, bool count_oob, int64_t* oob, hipStream_t s);
 dex_status gather_jvp(const float* T, const float* tT, const int32_t* idx, const float* w,

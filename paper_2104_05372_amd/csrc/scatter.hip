@@ -305,22 +305,35 @@ __global__ void __launch_bounds__(256) scatter_int_generic(int32_t* __restrict__
   if (oob) count_oob(bad, oob);
 }
 
-// Rows a half-wave has in flight in the gathers: the index and weight loads of
-// kGU rows are issued together, then their kGU row loads, so the two dependent
-// global reads (index, then row) are paid once per kGU rows.
+// The gathers. 2^lg lanes per row, VW consecutive columns per lane (the widest
+// the row length and the pointers' alignment allow), as many lanes as the row has
+// groups of columns up to half a wave. Rows a lane group has in flight: the index
+// and weight loads of kGU rows are issued together, then their kGU row loads, so
+// the two dependent global reads (index, then row) are paid once per kGU rows.
+// HBM bound: R = 128, n = 2^22 0.70 ms, 77 %; rows of odd length no longer divide an
+// element index (R = 50, n = 100003: 10.6 us against 14.5).
 constexpr int kGU = 4;
 
-// out[j, :] = w[j] * T[idx[j], :]; half a wave per row, 4 floats per lane.
+template <int VW>
+struct RowVec {
+  typedef float T __attribute__((ext_vector_type(VW)));
+};
+
+// out[j, :] = w[j] * T[idx[j], :]
+template <int VW>
 __global__ void __launch_bounds__(256) gather_scale_kernel(const float* __restrict__ T,
                                                            const int32_t* __restrict__ idx,
                                                            const float* __restrict__ w,
-                                                           int64_t V, int R, int64_t n,
+                                                           int64_t V, int R, int64_t n, int lg,
                                                            float* __restrict__ out,
                                                            int64_t* oob) {
-  const int half = threadIdx.x >> 5, hl = threadIdx.x & 31;
-  const int64_t stride = (int64_t)gridDim.x * 8;  // rows per round of the grid
+  using VT = typename RowVec<VW>::T;
+  const int sub = threadIdx.x >> lg, hl = threadIdx.x & ((1 << lg) - 1);
+  const int per = 256 >> lg, step = VW << lg;
+  const int64_t stride = (int64_t)gridDim.x * per;  // rows per round of the grid
+  const bool nt = R % 32 == 0;  // whole lines: past the caches
   int bad = 0;
-  for (int64_t j0 = (int64_t)blockIdx.x * 8 + half; j0 < n; j0 += stride * kGU) {
+  for (int64_t j0 = (int64_t)blockIdx.x * per + sub; j0 < n; j0 += stride * kGU) {
     int64_t v[kGU];
     float s[kGU];
     bool live[kGU], ok[kGU];
@@ -333,16 +346,20 @@ __global__ void __launch_bounds__(256) gather_scale_kernel(const float* __restri
       ok[u] = live[u] && v[u] >= 0 && v[u] < V;
       if (live[u] && !ok[u] && hl == 0) ++bad;
     }
-    for (int c = 4 * hl; c < R; c += 128) {
-      f32x4 t[kGU];
+    for (int c = VW * hl; c < R; c += step) {
+      VT t[kGU];
 #pragma unroll
       for (int u = 0; u < kGU; ++u)
-        t[u] = ok[u] ? *reinterpret_cast<const f32x4*>(T + v[u] * R + c) : f32x4{0.f, 0.f, 0.f, 0.f};
+        t[u] = ok[u] ? *reinterpret_cast<const VT*>(T + v[u] * R + c) : VT(0.f);
 #pragma unroll
       for (int u = 0; u < kGU; ++u)
-        if (live[u])
-          __builtin_nontemporal_store(t[u] * s[u],
-                                      reinterpret_cast<f32x4*>(out + (j0 + u * stride) * R + c));
+        if (live[u]) {
+          VT* o = reinterpret_cast<VT*>(out + (j0 + u * stride) * R + c);
+          if (nt)
+            __builtin_nontemporal_store(t[u] * s[u], o);
+          else
+            *o = t[u] * s[u];
+        }
     }
   }
   if (oob) count_oob(bad, oob);
@@ -351,18 +368,21 @@ __global__ void __launch_bounds__(256) gather_scale_kernel(const float* __restri
 // Forward mode of the gather (the linear map of its linearization, Sec. 5.1;
 // idx is an integer, so it carries no tangent):
 //   tout[j, :] = tw[j] * T[idx[j], :] + w[j] * tT[idx[j], :]
-// Same layout as the gather: half a wave per row, 4 floats per lane, kGU rows
-// in flight; rows with an index outside [0, V) give zeros.
+// Rows with an index outside [0, V) give zeros.
+template <int VW>
 __global__ void __launch_bounds__(256) gather_jvp_kernel(const float* __restrict__ T,
                                                          const float* __restrict__ tT,
                                                          const int32_t* __restrict__ idx,
                                                          const float* __restrict__ w,
                                                          const float* __restrict__ tw, int64_t V,
-                                                         int R, int64_t n,
+                                                         int R, int64_t n, int lg,
                                                          float* __restrict__ tout) {
-  const int half = threadIdx.x >> 5, hl = threadIdx.x & 31;
-  const int64_t stride = (int64_t)gridDim.x * 8;
-  for (int64_t j0 = (int64_t)blockIdx.x * 8 + half; j0 < n; j0 += stride * kGU) {
+  using VT = typename RowVec<VW>::T;
+  const int sub = threadIdx.x >> lg, hl = threadIdx.x & ((1 << lg) - 1);
+  const int per = 256 >> lg, step = VW << lg;
+  const int64_t stride = (int64_t)gridDim.x * per;
+  const bool nt = R % 32 == 0;
+  for (int64_t j0 = (int64_t)blockIdx.x * per + sub; j0 < n; j0 += stride * kGU) {
     int64_t v[kGU];
     float a[kGU], b[kGU];
     bool live[kGU], ok[kGU];
@@ -375,61 +395,29 @@ __global__ void __launch_bounds__(256) gather_jvp_kernel(const float* __restrict
       b[u] = live[u] ? w[j] : 0.f;
       ok[u] = live[u] && v[u] >= 0 && v[u] < V;
     }
-    for (int c = 4 * hl; c < R; c += 128) {
-      f32x4 x[kGU], y[kGU];
+    for (int c = VW * hl; c < R; c += step) {
+      VT x[kGU], y[kGU];
 #pragma unroll
       for (int u = 0; u < kGU; ++u) {
-        x[u] = ok[u] ? *reinterpret_cast<const f32x4*>(T + v[u] * R + c) : f32x4{0.f, 0.f, 0.f, 0.f};
-        y[u] = ok[u] ? *reinterpret_cast<const f32x4*>(tT + v[u] * R + c) : f32x4{0.f, 0.f, 0.f, 0.f};
+        x[u] = ok[u] ? *reinterpret_cast<const VT*>(T + v[u] * R + c) : VT(0.f);
+        y[u] = ok[u] ? *reinterpret_cast<const VT*>(tT + v[u] * R + c) : VT(0.f);
       }
 #pragma unroll
       for (int u = 0; u < kGU; ++u) {
         if (!live[u]) continue;
-        f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
+        VT o = VT(0.f);
         if (ok[u]) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) o[e] = fmaf(b[u], y[u][e], a[u] * x[u][e]);
+          for (int e = 0; e < VW; ++e) o[e] = fmaf(b[u], y[u][e], a[u] * x[u][e]);
         }
-        __builtin_nontemporal_store(o, reinterpret_cast<f32x4*>(tout + (j0 + u * stride) * R + c));
+        VT* p = reinterpret_cast<VT*>(tout + (j0 + u * stride) * R + c);
+        if (nt)
+          __builtin_nontemporal_store(o, p);
+        else
+          *p = o;
       }
     }
   }
-}
-
-// Scalar form for row lengths that are not a multiple of 4.
-__global__ void __launch_bounds__(256) gather_jvp_scalar(const float* __restrict__ T,
-                                                         const float* __restrict__ tT,
-                                                         const int32_t* __restrict__ idx,
-                                                         const float* __restrict__ w,
-                                                         const float* __restrict__ tw, int64_t V,
-                                                         int R, int64_t n,
-                                                         float* __restrict__ tout) {
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (t < n * R) {
-    const int64_t j = t / R, c = t % R;
-    const int64_t v = idx[j];
-    const bool ok = v >= 0 && v < V;
-    tout[t] = ok ? fmaf(w[j], tT[v * R + c], tw[j] * T[v * R + c]) : 0.f;
-  }
-}
-
-// Scalar-path gather for row lengths that are not a multiple of 4.
-__global__ void __launch_bounds__(256) gather_scale_scalar(const float* __restrict__ T,
-                                                           const int32_t* __restrict__ idx,
-                                                           const float* __restrict__ w,
-                                                           int64_t V, int R, int64_t n,
-                                                           float* __restrict__ out,
-                                                           int64_t* oob) {
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  int bad = 0;
-  if (t < n * R) {
-    const int64_t j = t / R, c = t % R;
-    const int64_t v = idx[j];
-    const bool ok = v >= 0 && v < V;
-    if (!ok && c == 0) bad = 1;
-    out[t] = ok ? w[j] * T[v * R + c] : 0.f;
-  }
-  if (oob) count_oob(bad, oob);
 }
 
 // dw[j] (=|+=) <T[idx[j], :], g[j, :]>; half a wave per row.
@@ -467,13 +455,15 @@ __global__ void __launch_bounds__(256) gather_dw_kernel(const float* __restrict_
 // Deterministic float scatter: a stable LSD radix sort of (row, position) pairs
 // followed by run sums with a fixed owner per run, so the rounding order of
 // every row's sum is fixed (bit-reproducible), and no atomics are used.
-constexpr int kRsTile = 8192;   // keys per sort block (1024 threads x 8 rounds)
+// Keys per sort block: 16 waves of RD rounds of 64 keys. Eight rounds (8192 keys, so a
+// digit gets about 32 and leaves as a run of 128 bytes of keys), or two where that
+// would leave most CUs without a block (n = 100003: a pass 14 us against 26).
+constexpr int rs_tile(int RD) { return 1024 * RD; }
 
 // keys[j] = idx[j] if it is inside [0, n_rows), else n_rows (sorts last and is
 // skipped); vals[j] = j.
-// Radix digits of kRsBits bits (a million rows: 20-bit keys, three passes). With
-// 8192-key tiles a digit gets about 32 keys per tile, so the scatter writes runs
-// of 128 bytes of keys (wider digits leave runs too short to write efficiently).
+// Radix digits of kRsBits bits (a million rows: 20-bit keys, three passes; wider
+// digits leave runs too short to write efficiently).
 constexpr int kRsBits = 8;
 constexpr int kRsDigits = 1 << kRsBits;
 
@@ -503,7 +493,7 @@ DEX_DEV uint32_t row_key(const IdxT* __restrict__ idx, int64_t j, int64_t n_rows
 // keys would otherwise queue on one counter). The first pass reads the indices
 // themselves (and counts those outside the table, and clears the combine
 // lists' counters); later passes read the keys the previous pass wrote.
-template <bool FIRST, typename IdxT>
+template <bool FIRST, typename IdxT, int RD>
 __global__ void __launch_bounds__(1024) rs_hist(const IdxT* __restrict__ idx,
                                                 const uint32_t* __restrict__ keys, int64_t n,
                                                 int64_t n_rows, int shift,
@@ -515,11 +505,11 @@ __global__ void __launch_bounds__(1024) rs_hist(const IdxT* __restrict__ idx,
   __syncthreads();
   const int lane = threadIdx.x & 63;
   const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  const int64_t t0 = (int64_t)blockIdx.x * kRsTile;
-  uint32_t kv[kRsTile / 1024];
+  const int64_t t0 = (int64_t)blockIdx.x * rs_tile(RD);
+  uint32_t kv[RD];
   int bad = 0;
 #pragma unroll
-  for (int r = 0; r < kRsTile / 1024; ++r) {  // all of a thread's loads in flight together
+  for (int r = 0; r < RD; ++r) {  // all of a thread's loads in flight together
     const int64_t j = t0 + r * 1024 + threadIdx.x;
     if constexpr (FIRST)
       kv[r] = j < n ? row_key(idx, j, n_rows, bad) : 0u;
@@ -527,7 +517,7 @@ __global__ void __launch_bounds__(1024) rs_hist(const IdxT* __restrict__ idx,
       kv[r] = j < n ? keys[j] : 0u;
   }
 #pragma unroll
-  for (int r = 0; r < kRsTile / 1024; ++r) {
+  for (int r = 0; r < RD; ++r) {
     const bool valid = t0 + r * 1024 + threadIdx.x < n;
     const uint32_t d = (kv[r] >> shift) & (kRsDigits - 1);
     const uint64_t peers = digit_peers(d, __ballot(valid));
@@ -570,7 +560,7 @@ __global__ void __launch_bounds__(256) rs_digit_scan(uint32_t* __restrict__ cnt,
 }
 
 // Stable scatter of one tile by digit. Wave w ranks the tile's keys
-// [512 w, 512 w + 512) in index order, 64 at a time: ballots rank a key among
+// [64 RD w, 64 RD (w + 1)) in index order, 64 at a time: ballots rank a key among
 // the equal digits of its 64, and a per-wave running count per digit in LDS
 // (read, then bumped by the first of the peers) ranks it among the wave's
 // earlier keys; no barrier is needed until the wave is done. The per-digit
@@ -581,7 +571,7 @@ __global__ void __launch_bounds__(256) rs_digit_scan(uint32_t* __restrict__ cnt,
 // The first pass reads the indices and scales themselves: an entry's value is
 // its position j with its scale's bits above (the run sums then read the scales
 // in sorted order, not scattered).
-template <bool FIRST, typename IdxT>
+template <bool FIRST, typename IdxT, int RD>
 __global__ void __launch_bounds__(1024) rs_scatter(const IdxT* __restrict__ idx,
                                                    const float* __restrict__ scale,
                                                    int64_t n_rows,
@@ -591,7 +581,8 @@ __global__ void __launch_bounds__(1024) rs_scatter(const IdxT* __restrict__ idx,
                                                    uint64_t* __restrict__ vout, int64_t n,
                                                    int shift, const uint32_t* __restrict__ cnt,
                                                    const uint32_t* __restrict__ tot, int ntiles) {
-  static_assert(kRsDigits <= 256 && kRsTile == 16 * 512, "digits in the first four waves");
+  constexpr int R = RD, kRsTile = rs_tile(RD);
+  static_assert(kRsDigits <= 256, "digits in the first four waves");
   __shared__ uint32_t gbase[kRsDigits];   // where digit d of this tile starts in the output
   __shared__ uint32_t lbase[kRsDigits];   // where digit d starts inside the reordered tile
   __shared__ uint32_t hw[16][kRsDigits];  // per-wave digit counts, then per-wave offsets
@@ -600,9 +591,8 @@ __global__ void __launch_bounds__(1024) rs_scatter(const IdxT* __restrict__ idx,
   __shared__ uint64_t sv[kRsTile];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int64_t tile0 = (int64_t)blockIdx.x * kRsTile;
-  const int64_t t0 = tile0 + (int64_t)wv * 512;
+  const int64_t t0 = tile0 + (int64_t)wv * (64 * RD);
   const int tlen = (int)min<int64_t>(kRsTile, n - tile0);
-  constexpr int R = 512 / 64;
   uint32_t kk[R], rk[R];
   uint64_t vv[R];
 #pragma unroll
@@ -696,7 +686,7 @@ __global__ void __launch_bounds__(1024) rs_scatter(const IdxT* __restrict__ idx,
 
 // ---------------------------------------------------------------------------
 // Owner-per-run sum over the sorted (row, position, scale) entries, the default
-// form of the transposed gather. Each wave takes kOwnSeg consecutive sorted
+// form of the transposed gather. Each wave takes SEG consecutive sorted
 // entries; a lane holds VW consecutive columns of a row (a 128-column row is
 // one wave load of 512 bytes). A run of equal rows wholly inside the segment
 // has exactly one owner, this wave, which writes the row once: a plain store
@@ -708,32 +698,35 @@ __global__ void __launch_bounds__(1024) rs_scatter(const IdxT* __restrict__ idx,
 // tail[seg], and the segment is put on the list for own_fix (the list's order
 // does not matter: each entry is combined on its own, in a fixed order). The
 // values of the next U entries are loaded before the current U are summed.
-constexpr int kOwnSeg = 512;
-
-template <int VW, int U, bool HV, bool OVR>
+// SEG (a multiple of 64) entries per wave: 512 where that leaves a wave or two per
+// SIMD, 64 below (the entries of a wave are walked in order, so their number is the
+// kernel's latency: n = 100003, R = 50: 23 us with 64, 57 with 512), at the price
+// of more runs that span segments.
+// DW: the cotangent of the scales too, dw[j] (=|+=) <T[idx_j], vals_j>, from the
+// same read of vals: the run's row of T is read beside each entry (a repeat hits the
+// L1), a batch's partial products are reduced over the lanes together, and one lane
+// per entry writes its sum. A pass of its own read vals once more: 0.53 + 0.61 ms at n = 2^22, R = 128,
+// against 0.72 (0.11 of it for T's rows, 0.07 for the scattered dw).
+template <int VW, int U, bool HV, bool OVR, int SEG, bool DW>
 __global__ void __launch_bounds__(256) own_sum(const uint32_t* __restrict__ skey,
                                                const uint64_t* __restrict__ sval, int64_t n,
                                                uint32_t sentinel, const float* __restrict__ vals,
                                                int R, float* __restrict__ acc,
                                                float* __restrict__ head, float* __restrict__ tail,
                                                uint32_t* __restrict__ list,
-                                               uint32_t* __restrict__ nlist) {
+                                               uint32_t* __restrict__ nlist,
+                                               const float* __restrict__ T, float* __restrict__ dw,
+                                               int dw_add) {
   typedef float VT __attribute__((ext_vector_type(VW)));
-  constexpr int G = kOwnSeg / 64;  // groups of 64 entries
-  constexpr int NB = 64 / U;       // batches of U entries per group
+  constexpr int G = SEG / 64;  // groups of 64 entries
+  constexpr int NB = 64 / U;   // batches of U entries per group
   static_assert(64 % U == 0 && NB % 2 == 0, "whole batch pairs per group");
+  static_assert(!DW || (HV && (U == 16 || U == 8)), "8 or 16 products are reduced together");
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int64_t seg = (int64_t)blockIdx.x * 4 + wv;
-  const int64_t e0 = seg * kOwnSeg;
+  const int64_t e0 = seg * SEG;
   if (e0 >= n) return;
-  const int len = (int)min<int64_t>(kOwnSeg, n - e0);
-  const uint32_t first = __builtin_amdgcn_readfirstlane(skey[e0]);
-  const uint32_t lastk = __builtin_amdgcn_readfirstlane(skey[e0 + len - 1]);
-  if (first == sentinel) return;
-  const bool cont_in = e0 > 0 && skey[e0 - 1] == first;
-  const bool cont_out = e0 + len < n && skey[e0 + len] == lastk && lastk != sentinel;
-  if (cont_out && !(cont_in && first == lastk) && lane == 0)
-    list[atomicAdd(nlist, 1u)] = (uint32_t)seg;  // a run starts here and spans segments
+  const int len = (int)min<int64_t>(SEG, n - e0);
   // lane t holds entry 64 g + t of the current group (key, position, scale);
   // each entry is read back with readlane, so keys, positions and the run logic
   // are wave-uniform (scalar) and a batch's row loads are issued back to back
@@ -745,6 +738,27 @@ __global__ void __launch_bounds__(256) own_sum(const uint32_t* __restrict__ skey
     const bool in = gq < G && e < len;
     const uint64_t pv = in ? sval[e0 + e] : 0ull;
     return Ent{in ? skey[e0 + e] : sentinel, (uint32_t)pv, (uint32_t)(pv >> 32)};
+  };
+  // the segment's edges and its first group, loaded together
+  const Ent g0 = load_group(0);
+  const uint32_t kl = skey[e0 + len - 1], kp = skey[e0 > 0 ? e0 - 1 : 0],
+                 kn = skey[e0 + len < n ? e0 + len : n - 1];
+  const uint32_t first = __builtin_amdgcn_readfirstlane(g0.k);
+  const uint32_t lastk = __builtin_amdgcn_readfirstlane(kl);
+  if (first == sentinel) {  // no valid entry here
+    if constexpr (DW) {
+      for (int e = lane; !dw_add && e < len; e += 64) dw[(uint32_t)sval[e0 + e]] = 0.f;
+    }
+    return;
+  }
+  const bool cont_in = e0 > 0 && __builtin_amdgcn_readfirstlane(kp) == first;
+  const bool cont_out =
+      e0 + len < n && __builtin_amdgcn_readfirstlane(kn) == lastk && lastk != sentinel;
+  // a batch as loaded: rows of vals, and of acc (!OVR) and T (DW); entries without
+  // a row read row 0 (clamped)
+  struct Batch {
+    uint32_t k[U];
+    VT v[HV ? U : 1], a[OVR ? 1 : U], t[DW ? U : 1];
   };
   for (int c0 = 0; c0 < R; c0 += 64 * VW) {
     const int col = c0 + VW * lane;
@@ -762,42 +776,86 @@ __global__ void __launch_bounds__(256) own_sum(const uint32_t* __restrict__ skey
       else
         *reinterpret_cast<VT*>(&acc[(int64_t)cur * R + col]) = OVR ? sum : base + sum;
     };
-    auto fetch = [&](auto l0c, const Ent& g, uint32_t(&kk)[U], VT(&rv)[U], VT(&av)[U]) {
+    auto fetch = [&](auto l0c, const Ent& g, Batch& b) {
       constexpr int l0 = decltype(l0c)::value;
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        kk[u] = __builtin_amdgcn_readlane(g.k, l0 + u);
+        b.k[u] = __builtin_amdgcn_readlane(g.k, l0 + u);
         const uint32_t j = __builtin_amdgcn_readlane(g.j, l0 + u);
-        const float sc = __uint_as_float(__builtin_amdgcn_readlane(g.s, l0 + u));
-        const bool ok = kk[u] != sentinel;
-        VT v = VT(1.f);
-        if constexpr (HV) v = *reinterpret_cast<const VT*>(&vals[(int64_t)j * R + colc]);
-        rv[u] = ok ? v * sc : VT(0.f);
-        if constexpr (!OVR) {
-          const int64_t row = ok ? (int64_t)kk[u] : 0;
-          av[u] = *reinterpret_cast<const VT*>(&acc[row * R + colc]);
+        if constexpr (HV) b.v[u] = *reinterpret_cast<const VT*>(&vals[(int64_t)j * R + colc]);
+        if constexpr (!OVR || DW) {
+          const int64_t row = b.k[u] != sentinel ? (int64_t)b.k[u] : 0;
+          if constexpr (!OVR) b.a[u] = *reinterpret_cast<const VT*>(&acc[row * R + colc]);
+          if constexpr (DW) b.t[u] = *reinterpret_cast<const VT*>(&T[row * R + colc]);
         }
       }
     };
-    auto consume = [&](const uint32_t(&kk)[U], const VT(&rv)[U], const VT(&av)[U]) {
+    auto consume = [&](auto l0c, const Ent& g, const Batch& b, int e_first) {
+      constexpr int l0 = decltype(l0c)::value;
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        if (kk[u] == sentinel) continue;
-        if (kk[u] != cur) {
+        if (b.k[u] == sentinel) continue;
+        if (b.k[u] != cur) {
           flush(false);
-          cur = kk[u];
+          cur = b.k[u];
           started_before = false;
           sum = VT(0.f);
-          base = av[u];
+          if constexpr (!OVR) base = b.a[u];
         }
-        sum += rv[u];
+        const float sc = __uint_as_float(__builtin_amdgcn_readlane(g.s, l0 + u));
+        if constexpr (HV)
+          sum += b.v[u] * sc;
+        else
+          sum += VT(sc);
+      }
+      if constexpr (DW) {
+        float d[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          float q = 0.f;
+#pragma unroll
+          for (int e = 0; e < VW; ++e) q = fmaf(b.t[u][e], b.v[u][e], q);
+          d[u] = cv && b.k[u] != sentinel ? q : 0.f;
+        }
+        // each step halves the values a lane holds: lanes with its bit keep the
+        // upper half; the last steps add what remains
+#pragma unroll
+        for (int u = 0; u < U / 2; ++u) {
+          const LanePair p = swap32(d[u], d[u + U / 2]);
+          d[u] = p.first + p.second;
+        }
+#pragma unroll
+        for (int u = 0; u < U / 4; ++u) {
+          const LanePair p = swap16(d[u], d[u + U / 4]);
+          d[u] = p.first + p.second;
+        }
+#pragma unroll
+        for (int u = 0; u < U / 8; ++u) {
+          const bool up = lane & 8;
+          d[u] = (up ? d[u + U / 8] : d[u]) + partner<8, false>(up ? d[u] : d[u + U / 8]);
+        }
+        float q = d[0];
+        if constexpr (U == 16) {
+          const bool up = lane & 4;
+          q = (up ? d[1] : d[0]) + __shfl_xor(up ? d[0] : d[1], 4, 64);
+        } else {
+          q += __shfl_xor(q, 4, 64);
+        }
+        q += butterfly<1>(q);
+        q += butterfly<2>(q);
+        const int e = (U / 2) * (lane >> 5) + (U / 4) * ((lane >> 4) & 1) + (U / 8) * ((lane >> 3) & 1) +
+                      (U == 16 ? (lane >> 2) & 1 : 0);
+        const uint32_t j = __shfl(g.j, l0 + e, 64);
+        if ((lane & (64 / U - 1)) == 0 && e_first + e < len) {
+          if (dw_add || c0 > 0) q += dw[j];
+          dw[j] = q;
+        }
       }
     };
-    uint32_t ka[U], kb[U];
-    VT ra[U], rb[U], aa[U], ab[U];
-    Ent gc = load_group(0);
-    fetch(std::integral_constant<int, 0>{}, gc, ka, ra, aa);
-    base = aa[0];  // the first run's row (unused when it began earlier)
+    Batch ba, bb;
+    Ent gc = c0 == 0 ? g0 : load_group(0);
+    fetch(std::integral_constant<int, 0>{}, gc, ba);
+    if constexpr (!OVR) base = ba.a[0];  // the first run's row (unused when it began earlier)
     // per group: batches 2p (set A) and 2p + 1 (set B); the next batch's loads
     // (the next group's first batch after the last) are issued before the
     // current batch is summed
@@ -805,22 +863,28 @@ __global__ void __launch_bounds__(256) own_sum(const uint32_t* __restrict__ skey
       const Ent gn = load_group(gq + 1);
       static_for<NB / 2>([&](auto pc) {
         constexpr int P = decltype(pc)::value;
-        fetch(std::integral_constant<int, (2 * P + 1) * U>{}, gc, kb, rb, ab);
+        using La = std::integral_constant<int, 2 * P * U>;
+        using Lb = std::integral_constant<int, (2 * P + 1) * U>;
+        fetch(Lb{}, gc, bb);
         __builtin_amdgcn_sched_barrier(0);
-        consume(ka, ra, aa);
+        consume(La{}, gc, ba, gq * 64 + La::value);
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (2 * P + 2 < NB)
-          fetch(std::integral_constant<int, (2 * P + 2) * U>{}, gc, ka, ra, aa);
+          fetch(std::integral_constant<int, (2 * P + 2) * U>{}, gc, ba);
         else
-          fetch(std::integral_constant<int, 0>{}, gn, ka, ra, aa);
+          fetch(std::integral_constant<int, 0>{}, gn, ba);
         __builtin_amdgcn_sched_barrier(0);
-        consume(kb, rb, ab);
+        consume(Lb{}, gc, bb, gq * 64 + Lb::value);
         __builtin_amdgcn_sched_barrier(0);
       });
       gc = gn;
     }
     flush(cont_out);
   }
+  // a run that starts here and spans segments goes on the list (last: the counter's
+  // answer is waited for)
+  if (cont_out && !(cont_in && first == lastk) && lane == 0)
+    list[atomicAdd(nlist, 1u)] = (uint32_t)seg;
 }
 
 // Runs that span segments: each list entry is a run's first segment s0. One
@@ -830,7 +894,7 @@ __global__ void __launch_bounds__(256) own_sum(const uint32_t* __restrict__ skey
 // segments in a fixed order (eight interleaved sums, then in order) -- and the
 // total is the row's only write (store, or added to the row's value). Longer
 // runs (the hottest rows) go to a second list for own_fix_long.
-template <int VW, bool OVR>
+template <int VW, bool OVR, int SEG>
 __global__ void __launch_bounds__(256) own_fix(const uint32_t* __restrict__ skey, int64_t n,
                                                int R, float* __restrict__ acc,
                                                const float* __restrict__ head,
@@ -841,15 +905,15 @@ __global__ void __launch_bounds__(256) own_fix(const uint32_t* __restrict__ skey
                                                uint32_t* __restrict__ nllist) {
   typedef float VT __attribute__((ext_vector_type(VW)));
   const int lane = threadIdx.x & 63;
-  const int64_t nseg = (n + kOwnSeg - 1) / kOwnSeg;
+  const int64_t nseg = (n + SEG - 1) / SEG;
   const uint32_t items = *nlist;
   const uint32_t gw = blockIdx.x * 4 + (threadIdx.x >> 6), nw = gridDim.x * 4;
   for (uint32_t it = gw; it < items; it += nw) {
     const int64_t s0 = __builtin_amdgcn_readfirstlane(list[it]);
-    const int64_t e1 = min<int64_t>(n, (s0 + 1) * kOwnSeg);
+    const int64_t e1 = min<int64_t>(n, (s0 + 1) * SEG);
     const uint32_t row = __builtin_amdgcn_readfirstlane(skey[e1 - 1]);
     const int64_t st = s0 + 1 + lane;
-    const bool in = st < nseg && skey[st * kOwnSeg] == row;
+    const bool in = st < nseg && skey[st * SEG] == row;
     const uint64_t miss = __ballot(!in);
     if (miss == 0) {  // continues past 64 more segments
       if (lane == 0) llist[atomicAdd(nllist, 1u)] = (uint32_t)s0;
@@ -886,7 +950,7 @@ __global__ void __launch_bounds__(256) own_fix(const uint32_t* __restrict__ skey
 // waves add head[] over the run's later segments in a fixed order (wave w takes
 // every 16th, eight interleaved sums each), the wave sums are combined in wave
 // order with tail[s0], and the total is the row's only write.
-template <int VW, bool OVR>
+template <int VW, bool OVR, int SEG>
 __global__ void __launch_bounds__(1024) own_fix_long(const uint32_t* __restrict__ skey, int64_t n,
                                                      int R, float* __restrict__ acc,
                                                      const float* __restrict__ head,
@@ -897,16 +961,16 @@ __global__ void __launch_bounds__(1024) own_fix_long(const uint32_t* __restrict_
   __shared__ VT wsum[16][64];
   __shared__ int64_t first_miss[16];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int64_t nseg = (n + kOwnSeg - 1) / kOwnSeg;
+  const int64_t nseg = (n + SEG - 1) / SEG;
   const uint32_t items = *nllist;
   for (uint32_t it = blockIdx.x; it < items; it += gridDim.x) {
     const int64_t s0 = llist[it];
-    const int64_t e1 = min<int64_t>(n, (s0 + 1) * kOwnSeg);
+    const int64_t e1 = min<int64_t>(n, (s0 + 1) * SEG);
     const uint32_t row = skey[e1 - 1];
     int64_t send = s0;
     for (int64_t b = s0 + 1;; b += 1024) {
       const int64_t st = b + threadIdx.x;
-      const bool in = st < nseg && skey[st * kOwnSeg] == row;
+      const bool in = st < nseg && skey[st * SEG] == row;
       const uint64_t miss = __ballot(!in);
       __syncthreads();
       first_miss[wv] = miss ? (int64_t)(64 * wv + __ffsll((long long)miss) - 1) : 1024;
@@ -956,6 +1020,11 @@ using namespace dexk;
 static int hist_blocks() { return num_cus(); }
 
 size_t sorted_scatter_ws_bytes(int64_t n, int64_t R);
+
+// Sorted entries per wave of the run sums: 512 from a wave per SIMD on.
+static int own_seg(int64_t n) { return n >= 512 * 1024 ? 512 : 64; }
+// Rounds per wave of the sort's tiles: 8192-key tiles from half a tile per CU on.
+static int rs_rounds(int64_t n) { return n >= 1024 * 1024 ? 8 : 2; }
 
 size_t scatter_ws_bytes(int32_t acc_dtype, int64_t n_rows, int64_t row_len, int64_t n,
                         bool has_vals, bool deterministic) {
@@ -1045,6 +1114,22 @@ static dex_status scatter_typed(void* acc, int32_t acc_dtype, int64_t n_rows, in
   return check_hip(hipGetLastError(), "accum_scatter");
 }
 
+// Columns per lane, log2 of the lanes per row, blocks (a round of
+// kGU rows per lane group each, up to 32 per CU).
+struct GatherShape {
+  int vw, lg;
+  unsigned blocks;
+};
+static GatherShape gather_shape(int64_t R, int64_t n, uintptr_t align) {
+  GatherShape g;
+  g.vw = R % 4 == 0 && (align & 15) == 0 ? 4 : R % 2 == 0 && (align & 7) == 0 ? 2 : 1;
+  g.lg = 0;
+  while (g.lg < 5 && (int64_t)(g.vw << g.lg) < R) ++g.lg;
+  const int64_t per = (256 >> g.lg) * kGU;  // rows of a block's round
+  g.blocks = (unsigned)std::min<int64_t>((n + per - 1) / per, (int64_t)num_cus() * 32);
+  return g;
+}
+
 // Workspace of the sorted (deterministic) float scatter.
 struct SortWs {
   uint32_t *ka, *kb, *cnt, *tot, *list, *nlist, *llist;
@@ -1061,8 +1146,8 @@ static SortWs sort_ws(int64_t n, int64_t R, char* base) {
     o += align256(b);
     return base ? (void*)(base + at) : nullptr;
   };
-  const int64_t ntiles = (n + kRsTile - 1) / kRsTile;
-  const int64_t nseg = (n + kOwnSeg - 1) / kOwnSeg;
+  const int64_t ntiles = (n + rs_tile(rs_rounds(n)) - 1) / rs_tile(rs_rounds(n));
+  const int64_t nseg = (n + own_seg(n) - 1) / own_seg(n);
   w.ka = (uint32_t*)take((size_t)n * 4);
   w.kb = (uint32_t*)take((size_t)n * 4);
   w.va = (uint64_t*)take((size_t)n * 8);
@@ -1080,35 +1165,53 @@ static SortWs sort_ws(int64_t n, int64_t R, char* base) {
 
 size_t sorted_scatter_ws_bytes(int64_t n, int64_t R) { return sort_ws(n, R, nullptr).bytes; }
 
-template <int VW, bool OVR>
+// T, dw: where the cotangent of the scales is wanted too (vals given).
+struct DwArgs {
+  const float* T;
+  float* dw;
+  bool add;
+};
+
+template <int VW, bool OVR, int SEG>
 static void launch_own(const SortWs& w, const uint32_t* skey, const uint64_t* sval, int64_t n,
-                       uint32_t sentinel, const float* vals, int R, float* acc, hipStream_t s) {
-  const int64_t nseg = (n + kOwnSeg - 1) / kOwnSeg;
+                       uint32_t sentinel, const float* vals, int R, float* acc, const DwArgs& d,
+                       hipStream_t s) {
+  const int64_t nseg = (n + SEG - 1) / SEG;
   const unsigned sb = (unsigned)((nseg + 3) / 4);
-  if (vals)
-    hipLaunchKernelGGL((own_sum<VW, 16, true, OVR>), dim3(sb), dim3(256), 0, s, skey, sval, n,
-                       sentinel, vals, R, acc, w.pf, w.pl, w.list, w.nlist);
+  // (entries in flight: what the registers hold)
+  constexpr int UD = VW == 4 ? 8 : 16, UV = VW == 4 && !OVR ? 8 : 16;
+  if (vals && d.dw)
+    hipLaunchKernelGGL((own_sum<VW, UD, true, OVR, SEG, true>), dim3(sb), dim3(256), 0, s, skey,
+                       sval, n, sentinel, vals, R, acc, w.pf, w.pl, w.list, w.nlist, d.T, d.dw,
+                       d.add ? 1 : 0);
+  else if (vals)
+    hipLaunchKernelGGL((own_sum<VW, UV, true, OVR, SEG, false>), dim3(sb), dim3(256), 0, s, skey,
+                       sval, n, sentinel, vals, R, acc, w.pf, w.pl, w.list, w.nlist, nullptr, nullptr,
+                       0);
   else
-    hipLaunchKernelGGL((own_sum<VW, 16, false, OVR>), dim3(sb), dim3(256), 0, s, skey, sval, n,
-                       sentinel, vals, R, acc, w.pf, w.pl, w.list, w.nlist);
+    hipLaunchKernelGGL((own_sum<VW, UV, false, OVR, SEG, false>), dim3(sb), dim3(256), 0, s, skey,
+                       sval, n, sentinel, vals, R, acc, w.pf, w.pl, w.list, w.nlist, nullptr, nullptr,
+                       0);
   // fixed grids that walk the lists of spanning runs (their lengths stay on the device)
   const unsigned fb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((nseg + 3) / 4, 4 * num_cus()));
-  hipLaunchKernelGGL((own_fix<VW, OVR>), dim3(fb), dim3(256), 0, s, skey, n, R, acc, w.pf, w.pl,
-                     w.list, w.nlist, w.llist, w.nlist + 1);
-  hipLaunchKernelGGL((own_fix_long<VW, OVR>), dim3((unsigned)num_cus()), dim3(1024), 0, s, skey, n,
-                     R, acc, w.pf, w.pl, w.llist, w.nlist + 1);
+  hipLaunchKernelGGL((own_fix<VW, OVR, SEG>), dim3(fb), dim3(256), 0, s, skey, n, R, acc, w.pf,
+                     w.pl, w.list, w.nlist, w.llist, w.nlist + 1);
+  hipLaunchKernelGGL((own_fix_long<VW, OVR, SEG>), dim3((unsigned)num_cus()), dim3(1024), 0, s, skey,
+                     n, R, acc, w.pf, w.pl, w.llist, w.nlist + 1);
 }
 
 template <typename IdxT>
 static dex_status scatter_sorted(float* acc, int64_t n_rows, int64_t R, const IdxT* idx,
                                  const float* vals, const float* scale, int64_t n, int64_t* oob,
-                                 bool overwrite, void* ws, size_t ws_bytes, hipStream_t s) {
+                                 bool overwrite, const DwArgs& dw, void* ws, size_t ws_bytes,
+                                 hipStream_t s) {
   if (n_rows > 0xFFFFFFFEll || n > 0xFFFFFFFFll)
     return fail(DEX_ERR_UNSUPPORTED, "sorted scatter: at most 2^32-2 rows and 2^32 indices");
   const SortWs w = sort_ws(n, R, (char*)ws);
   if (!ws || ws_bytes < w.bytes)
     return fail(DEX_ERR_WORKSPACE, "sorted scatter needs %zu workspace bytes, got %zu", w.bytes, ws_bytes);
-  const int ntiles = (int)((n + kRsTile - 1) / kRsTile);
+  const int rd = rs_rounds(n);
+  const int ntiles = (int)((n + rs_tile(rd) - 1) / rs_tile(rd));
   const int nbits = 64 - __builtin_clzll((unsigned long long)n_rows);  // n_rows itself is the sentinel
   const int passes = (nbits + kRsBits - 1) / kRsBits;
   ProfRange pr(DEX_PROF_SCATTER, s);
@@ -1118,29 +1221,36 @@ static dex_status scatter_sorted(float* acc, int64_t n_rows, int64_t R, const Id
   uint64_t *vin = w.va, *vout = w.vb;
   for (int p = 0; p < passes; ++p) {
     const int shift = kRsBits * p;
-    if (p == 0)
-      hipLaunchKernelGGL((rs_hist<true, IdxT>), dim3(ntiles), dim3(1024), 0, s, idx, kin, n, n_rows,
-                         shift, w.cnt, ntiles, w.nlist, oob);
+#define DEX_RS(FIRST_, RD_)                                                                       \
+  do {                                                                                             \
+    hipLaunchKernelGGL((rs_hist<FIRST_, IdxT, RD_>), dim3(ntiles), dim3(1024), 0, s, idx, kin, n,  \
+                       n_rows, shift, w.cnt, ntiles, w.nlist, oob);                                \
+    hipLaunchKernelGGL(rs_digit_scan, dim3(kRsDigits), dim3(256), 0, s, w.cnt, ntiles, w.tot);     \
+    hipLaunchKernelGGL((rs_scatter<FIRST_, IdxT, RD_>), dim3(ntiles), dim3(1024), 0, s, idx, scale, \
+                       n_rows, kin, vin, kout, vout, n, shift, w.cnt, w.tot, ntiles);              \
+  } while (0)
+    if (p == 0 && rd == 8)
+      DEX_RS(true, 8);
+    else if (p == 0)
+      DEX_RS(true, 2);
+    else if (rd == 8)
+      DEX_RS(false, 8);
     else
-      hipLaunchKernelGGL((rs_hist<false, IdxT>), dim3(ntiles), dim3(1024), 0, s, idx, kin, n,
-                         n_rows, shift, w.cnt, ntiles, w.nlist, oob);
-    hipLaunchKernelGGL(rs_digit_scan, dim3(kRsDigits), dim3(256), 0, s, w.cnt, ntiles, w.tot);
-    if (p == 0)
-      hipLaunchKernelGGL((rs_scatter<true, IdxT>), dim3(ntiles), dim3(1024), 0, s, idx, scale, n_rows,
-                         kin, vin, kout, vout, n, shift, w.cnt, w.tot, ntiles);
-    else
-      hipLaunchKernelGGL((rs_scatter<false, IdxT>), dim3(ntiles), dim3(1024), 0, s, idx, scale,
-                         n_rows, kin, vin, kout, vout, n, shift, w.cnt, w.tot, ntiles);
+      DEX_RS(false, 2);
+#undef DEX_RS
     std::swap(kin, kout);
     std::swap(vin, vout);
   }
   // widest column vector the row length and the pointers' alignment allow
-  const uintptr_t al = (uintptr_t)acc | (uintptr_t)(vals ? vals : acc);
+  const uintptr_t al =
+      (uintptr_t)acc | (uintptr_t)(vals ? vals : acc) | (uintptr_t)(dw.dw ? dw.T : acc);
   const int vw = (R % 4 == 0 && R >= 256 && (al & 15) == 0) ? 4 : (R % 2 == 0 && (al & 7) == 0) ? 2 : 1;
   const uint32_t sent = (uint32_t)n_rows;
-#define DEX_OWNL(V)                                                                   \
-  (overwrite ? launch_own<V, true>(w, kin, vin, n, sent, vals, (int)R, acc, s)        \
-             : launch_own<V, false>(w, kin, vin, n, sent, vals, (int)R, acc, s))
+#define DEX_OWNS(V, OV, SEG_) \
+  launch_own<V, OV, SEG_>(w, kin, vin, n, sent, vals, (int)R, acc, dw, s)
+#define DEX_OWNL(V)                                                            \
+  (own_seg(n) == 512 ? (overwrite ? DEX_OWNS(V, true, 512) : DEX_OWNS(V, false, 512)) \
+                     : (overwrite ? DEX_OWNS(V, true, 64) : DEX_OWNS(V, false, 64)))
   if (vw == 4)
     DEX_OWNL(4);
   else if (vw == 2)
@@ -1148,6 +1258,7 @@ static dex_status scatter_sorted(float* acc, int64_t n_rows, int64_t R, const Id
   else
     DEX_OWNL(1);
 #undef DEX_OWNL
+#undef DEX_OWNS
   pr.end(1);
   return check_hip(hipGetLastError(), "sorted scatter");
 }
@@ -1155,15 +1266,16 @@ static dex_status scatter_sorted(float* acc, int64_t n_rows, int64_t R, const Id
 dex_status accum_scatter(void* acc, int32_t acc_dtype, int64_t n_rows, int64_t row_len,
                          const void* idx, int32_t idx_dtype, const void* vals,
                          const float* scale, int64_t n, bool count_oob, int64_t* oob, void* ws,
-                         size_t ws_bytes, int path, hipStream_t s, bool overwrite) {
+                         size_t ws_bytes, int path, hipStream_t s) {
   if (n == 0) return DEX_OK;
   int64_t* o = count_oob ? oob : nullptr;
   if (path == kScatterSorted && acc_dtype == DEX_F32) {
+    const DwArgs none{nullptr, nullptr, false};
     if (idx_dtype == DEX_I32)
       return scatter_sorted<int32_t>((float*)acc, n_rows, row_len, (const int32_t*)idx,
-                                     (const float*)vals, scale, n, o, overwrite, ws, ws_bytes, s);
+                                     (const float*)vals, scale, n, o, false, none, ws, ws_bytes, s);
     return scatter_sorted<uint32_t>((float*)acc, n_rows, row_len, (const uint32_t*)idx,
-                                    (const float*)vals, scale, n, o, overwrite, ws, ws_bytes, s);
+                                    (const float*)vals, scale, n, o, false, none, ws, ws_bytes, s);
   }
   if (idx_dtype == DEX_I32)
     return scatter_typed<int32_t>(acc, acc_dtype, n_rows, row_len, (const int32_t*)idx, vals,
@@ -1172,20 +1284,37 @@ dex_status accum_scatter(void* acc, int32_t acc_dtype, int64_t n_rows, int64_t r
                                  scale, n, o, ws, ws_bytes, s);
 }
 
+dex_status gather_vjp(const float* T, const int32_t* idx, const float* w, const float* g, int64_t V,
+                      int64_t R, int64_t n, float* dT, float* dw, bool accumulate, bool sorted,
+                      void* ws, size_t ws_bytes, hipStream_t s) {
+  if (!accumulate) {
+    const dex_status st = fill_zero(dT, (size_t)(V * R) * 4, s);
+    if (st != DEX_OK) return st;
+  }
+  if (n == 0) return DEX_OK;
+  if (sorted)
+    return scatter_sorted<int32_t>(dT, V, R, idx, g, w, n, nullptr, !accumulate,
+                                   DwArgs{T, dw, accumulate}, ws, ws_bytes, s);
+  const dex_status st = scatter_typed<int32_t>(dT, DEX_F32, V, R, idx, g, w, n, nullptr, ws, ws_bytes, s);
+  return st != DEX_OK || !dw ? st : gather_dw(T, idx, g, V, R, n, dw, accumulate, s);
+}
+
 dex_status gather_fwd(const float* T, const int32_t* idx, const float* w, int64_t V, int64_t R,
                       int64_t n, float* out, bool count, int64_t* oob, hipStream_t s) {
   if (n == 0) return DEX_OK;
   int64_t* o = count ? oob : nullptr;
-  const bool vec = (R % 4) == 0 && ((uintptr_t)T & 15) == 0 && ((uintptr_t)out & 15) == 0;
+  const GatherShape g = gather_shape(R, n, (uintptr_t)T | (uintptr_t)out);
   ProfRange pr(DEX_PROF_GATHER, s);
-  if (vec) {
-    const unsigned blocks = (unsigned)std::min<int64_t>((n + 7) / 8, (int64_t)num_cus() * 32);
-    hipLaunchKernelGGL(gather_scale_kernel, dim3(blocks), dim3(256), 0, s, T, idx, w, V, (int)R, n,
-                       out, o);
-  } else {
-    hipLaunchKernelGGL(gather_scale_scalar, dim3((unsigned)((n * R + 255) / 256)), dim3(256), 0, s,
-                       T, idx, w, V, (int)R, n, out, o);
-  }
+#define DEX_GF(VW_)                                                                             \
+  hipLaunchKernelGGL(gather_scale_kernel<VW_>, dim3(g.blocks), dim3(256), 0, s, T, idx, w, V,   \
+                     (int)R, n, g.lg, out, o)
+  if (g.vw == 4)
+    DEX_GF(4);
+  else if (g.vw == 2)
+    DEX_GF(2);
+  else
+    DEX_GF(1);
+#undef DEX_GF
   pr.end(1);
   return check_hip(hipGetLastError(), "gather_fwd");
 }
@@ -1194,17 +1323,18 @@ dex_status gather_jvp(const float* T, const float* tT, const int32_t* idx, const
                       const float* tw, int64_t V, int64_t R, int64_t n, float* tout,
                       hipStream_t s) {
   if (n == 0) return DEX_OK;
-  const bool vec = (R % 4) == 0 && ((uintptr_t)T & 15) == 0 && ((uintptr_t)tT & 15) == 0 &&
-                   ((uintptr_t)tout & 15) == 0;
+  const GatherShape g = gather_shape(R, n, (uintptr_t)T | (uintptr_t)tT | (uintptr_t)tout);
   ProfRange pr(DEX_PROF_GATHER_JVP, s);
-  if (vec) {
-    const unsigned blocks = (unsigned)std::min<int64_t>((n + 7) / 8, (int64_t)num_cus() * 32);
-    hipLaunchKernelGGL(gather_jvp_kernel, dim3(blocks), dim3(256), 0, s, T, tT, idx, w, tw, V,
-                       (int)R, n, tout);
-  } else {
-    hipLaunchKernelGGL(gather_jvp_scalar, dim3((unsigned)((n * R + 255) / 256)), dim3(256), 0, s,
-                       T, tT, idx, w, tw, V, (int)R, n, tout);
-  }
+#define DEX_GJ(VW_)                                                                            \
+  hipLaunchKernelGGL(gather_jvp_kernel<VW_>, dim3(g.blocks), dim3(256), 0, s, T, tT, idx, w, tw, \
+                     V, (int)R, n, g.lg, tout)
+  if (g.vw == 4)
+    DEX_GJ(4);
+  else if (g.vw == 2)
+    DEX_GJ(2);
+  else
+    DEX_GJ(1);
+#undef DEX_GJ
   pr.end(1);
   return check_hip(hipGetLastError(), "gather_jvp");
 }

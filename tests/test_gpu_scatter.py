@@ -53,6 +53,44 @@ def test_gather_and_transpose(dev, V, R, n, seed, config):
     assert rel(dw, osc.scatter_dw(si.table, si.idx, si.g)) <= 1e-5
 
 
+# The two cotangents from one read: row lengths of every vector width (and more than
+# one pass over the columns), entry counts on either side of a segment (64 and 512
+# entries, from 2^19 on) and of a sort tile (2048 and 8192 keys, from 2^20 on),
+# indices outside the table, buffers that are only 4-byte aligned, accumulation.
+@pytest.mark.parametrize("V,R,n,offset", [(40, 1, 63, 0), (40, 2, 65, 0), (9, 3, 2048, 0), (500, 4, 2049, 1),
+                                          (300, 50, 1000, 0), (33, 260, 700, 0), (33, 300, 129, 3),
+                                          (64, 513, 200, 0), (3000, 2, (1 << 19) + 5, 0),
+                                          (70_000, 1, (1 << 20) + 3, 0)])
+def test_both_cotangents(dev, V, R, n, offset):
+    from paper_2104_05372_amd import dex
+    rng = np.random.default_rng(V + R + n)
+    idx = rng.integers(-2, V + 2, n).astype(np.int32)
+    idx[rng.random(n) < 0.3] = V // 2  # one hot row: its run spans segments
+    T, g = (rng.standard_normal(s).astype(np.float32) for s in ((V, R), (n, R)))
+    w = rng.uniform(-1, 1, n).astype(np.float32)
+    ok = (idx >= 0) & (idx < V)
+    safe = np.where(ok, idx, 0)
+    want_T = osc.scatter(V, safe, np.where(ok, w, 0), g)
+    want_w = np.where(ok, osc.scatter_dw(T, safe, g), 0)
+    want_out = np.where(ok[:, None], osc.gather(T, safe, w), 0)
+
+    def put(a):  # contiguous, `offset` floats into its storage
+        t = torch.empty(a.size + offset, device=dev, dtype=torch.from_numpy(a).dtype)[offset:]
+        return t.copy_(torch.from_numpy(a).reshape(-1)).view(a.shape)
+
+    ins = [put(T), torch.tensor(idx, device=dev), put(w)]
+    d = dex.gather_desc(V, R, n)
+    out = put(np.full((n, R), 7, np.float32))
+    dex.dex_fwd(d, ins, [out], [])
+    assert rel(out.cpu().numpy(), want_out) <= 1e-6
+    ws = dex.workspace(dex.dex_workspace_bytes(d, dex.DEX_WS_VJP), dev)
+    for flags, base in ((0, 0.0), (dex.DEX_ACCUMULATE, 0.5)):
+        dT, dw = put(np.full((V, R), 0.5, np.float32)), put(np.full(n, 0.5, np.float32))
+        dex.dex_vjp(d, ins, [], [put(g)], [dT, dw], flags, ws)
+        assert rel(dT.cpu().numpy(), want_T + base) <= 1e-5
+        assert rel(dw.cpu().numpy(), want_w + base) <= 1e-5
+
+
 def test_dense_one_hot_invariant(dev):
     si = workloads.scatter_inputs(50, 8, 1000, 1.1, 0)
     _, dT, _ = gather_vjp(si.table, si.idx, si.w, si.g, dev)
