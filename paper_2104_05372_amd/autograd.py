@@ -33,9 +33,7 @@ class GMMLogLik(torch.autograd.Function):
         dev = x.device
         F = torch.empty(1, dtype=x.dtype, device=dev)
         f = torch.empty(N, dtype=x.dtype, device=dev)
-        cache = torch.empty(max(1, dex.dex_workspace_bytes(d, dex.DEX_WS_RESID)), dtype=torch.uint8,
-                            device=dev)
-        cache_v = cache[: dex.dex_workspace_bytes(d, dex.DEX_WS_RESID)]
+        cache_v = torch.empty(dex.dex_workspace_bytes(d, dex.DEX_WS_RESID), dtype=torch.uint8, device=dev)
         ins = [t.contiguous() for t in (alphas, means, qd, l, x)]
         dex.dex_fwd(d, ins, [F], [f, cache_v], _ws(d, dex.DEX_WS_FWD, dev))
         ctx.save_for_backward(*ins, f, cache_v)

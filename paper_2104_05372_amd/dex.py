@@ -8,7 +8,9 @@ loaded, every call raises: there is no fallback.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
+import struct
 
 import numpy as np
 import torch
@@ -72,7 +74,7 @@ def lib():
             raise RuntimeError(f"{LIB_PATH} is missing: run `python -m paper_2104_05372_amd.build`")
         L = ctypes.CDLL(LIB_PATH)
         S, P, I32, I64, SZ = ctypes.c_int32, ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_size_t
-        DP, BP = ctypes.POINTER(DexDesc), ctypes.POINTER(DexBuf)
+        DP = ctypes.POINTER(DexDesc)
         L.dex_status_string.restype = ctypes.c_char_p
         L.dex_status_string.argtypes = [S]
         L.dex_last_error.restype = ctypes.c_char_p
@@ -82,6 +84,8 @@ def lib():
         L.dex_workspace_bytes.restype = S
         L.dex_num_configs.argtypes = [DP, I32, ctypes.POINTER(I32)]
         L.dex_num_configs.restype = S
+        # dex_buf lists: a ctypes array of DexBuf, or the same records packed into bytes
+        BP = P
         L.dex_fwd.argtypes = [DP, BP, I32, BP, I32, BP, I32, P, SZ, P]
         L.dex_fwd.restype = S
         L.dex_vjp.argtypes = [DP, BP, I32, BP, I32, BP, I32, BP, I32, ctypes.c_uint32, P, SZ, P]
@@ -132,10 +136,21 @@ def dtype_code(t: torch.Tensor) -> int:
     return _DT[t.dtype]
 
 
+_gpu = False
+
+
+def _have_gpu() -> bool:
+    """torch.cuda.is_available(), asked again only until it says yes."""
+    global _gpu
+    if not _gpu:
+        _gpu = torch.cuda.is_available()
+    return _gpu
+
+
 def _check_device(t: torch.Tensor, name: str = "buffer"):
     """Device buffers must live on the GPU. Without a visible GPU the library
     itself reports the missing device (after its host-side argument checks)."""
-    if t.numel() and not t.is_cuda and torch.cuda.is_available():
+    if not t.is_cuda and t.numel() and _have_gpu():
         raise ValueError(f"dex {name} must be a GPU tensor (got device {t.device})")
 
 
@@ -156,14 +171,51 @@ def bufs(ts, dtypes=None):
     return arr, len(ts)
 
 
-def stream_ptr(stream=None):
-    """The HIP stream to enqueue on: the given torch stream, else torch's current
-    one. Without a visible GPU this is the null stream, and the library then
-    reports the missing device itself."""
-    if stream is None and not torch.cuda.is_available():
+@functools.lru_cache(maxsize=None)
+def _packer(n: int):
+    """struct.pack for n dex_buf records (pointer, element count, dtype, 0)."""
+    return struct.Struct("@" + "Pqii" * n).pack
+
+
+def _pack(ts, dtypes=None) -> bytes | None:
+    """The dex_buf array of a list of tensors, as bytes: what bufs() gives, in one
+    packing call (a small call's cost is mostly its argument lists: 20 buffers by
+    ctypes fields 24 us, packed 9)."""
+    v = []
+    for i, t in enumerate(ts):
+        if t is None:
+            v += (0, 0, (dtypes[i] if dtypes is not None else None) or DEX_F32, 0)
+            continue
+        if not t.is_contiguous():
+            raise ValueError("dex buffers must be contiguous")
+        n = t.numel()
+        if not t.is_cuda:
+            _check_device(t)
+        dt = dtypes[i] if dtypes is not None else None
+        v += (t.data_ptr() if n else 0, n, _DT[t.dtype] if dt is None else dt, 0)
+    return _packer(len(ts))(*v) if v else None
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream(stream=None):
+    """The HIP stream to enqueue on, as an integer: the given torch stream, else
+    torch's current one. Without a visible GPU this is the null stream (None), and
+    the library then reports the missing device itself."""
+    if stream is not None:
+        return stream.cuda_stream
+    if not _have_gpu():
         return None
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    if _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
+
+
+def stream_ptr(stream=None):
+    """_stream as a ctypes pointer (None for the null stream without a GPU)."""
+    s = _stream(stream)
+    return None if s is None else ctypes.c_void_p(s)
 
 
 # ---- descriptors --------------------------------------------------------------
@@ -219,33 +271,31 @@ def workspace(nbytes: int, device) -> torch.Tensor:
 def dex_fwd(d: DexDesc, ins, outs, resid, ws: torch.Tensor | None = None, stream=None,
             dtypes=None):
     """ins/outs/resid: lists of tensors. dtypes: optional override per list."""
-    a, na = bufs(ins, dtypes and dtypes.get("in"))
-    o, no = bufs(outs, dtypes and dtypes.get("out"))
-    r, nr = bufs(resid, dtypes and dtypes.get("resid"))
-    wp = ctypes.c_void_p(ws.data_ptr()) if ws is not None else None
-    wb = ws.numel() if ws is not None else 0
-    check(lib().dex_fwd(ctypes.byref(d), a, na, o, no, r, nr, wp, wb, stream_ptr(stream)))
+    g = dtypes.get if dtypes else _no_dtypes
+    check(lib().dex_fwd(ctypes.byref(d), _pack(ins, g("in")), len(ins), _pack(outs, g("out")),
+                        len(outs), _pack(resid, g("resid")), len(resid), _ptr(ws),
+                        ws.numel() if ws is not None else 0, _stream(stream)))
 
 
 def dex_jvp(d: DexDesc, ins, t_in, t_out, ws: torch.Tensor | None = None, stream=None,
             resid=(), dtypes=None):
     """Forward mode: t_out = the linearization of f at ins applied to t_in
     (resid: dex_fwd's residuals, for DEX_GMM)."""
-    a, na = bufs(ins, dtypes and dtypes.get("in"))
-    r, nr = bufs(list(resid), dtypes and dtypes.get("resid"))
-    ti, nti = bufs(t_in)
-    to, nto = bufs(t_out)
-    wp = ctypes.c_void_p(ws.data_ptr()) if ws is not None else None
-    wb = ws.numel() if ws is not None else 0
-    check(lib().dex_jvp(ctypes.byref(d), a, na, r, nr, ti, nti, to, nto, wp, wb,
-                        stream_ptr(stream)))
+    g = dtypes.get if dtypes else _no_dtypes
+    check(lib().dex_jvp(ctypes.byref(d), _pack(ins, g("in")), len(ins), _pack(resid, g("resid")),
+                        len(resid), _pack(t_in), len(t_in), _pack(t_out), len(t_out), _ptr(ws),
+                        ws.numel() if ws is not None else 0, _stream(stream)))
 
 
 DEX_REDUCE_WS_BYTES = 8192
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
+
+
+def _no_dtypes(_):
+    return None
 
 
 def _f32_buffer(t, name):
@@ -268,7 +318,7 @@ def dex_reduce_rows(out: torch.Tensor, values: torch.Tensor, flags=0, stream=Non
     rows, cols = values.shape
     if out.numel() != rows:
         raise ValueError(f"out must hold {rows} values (one per row), got {out.numel()}")
-    check(lib().dex_reduce_rows(_ptr(out), _ptr(values), rows, cols, flags, stream_ptr(stream)))
+    check(lib().dex_reduce_rows(_ptr(out), _ptr(values), rows, cols, flags, _stream(stream)))
 
 
 def dex_reduce_all(out: torch.Tensor, values: torch.Tensor, ws: torch.Tensor, flags=0,
@@ -285,7 +335,7 @@ def dex_reduce_all(out: torch.Tensor, values: torch.Tensor, ws: torch.Tensor, fl
         raise ValueError(f"ws must hold at least {DEX_REDUCE_WS_BYTES} bytes, got {ws.numel()}")
     _check_device(ws, "ws")
     check(lib().dex_reduce_all(_ptr(out), _ptr(values), values.numel(), flags, _ptr(ws),
-                               ws.numel(), stream_ptr(stream)))
+                               ws.numel(), _stream(stream)))
 
 
 def dex_reduce_all_noalloc(out: torch.Tensor, values: torch.Tensor, flags=0, stream=None):
@@ -297,19 +347,15 @@ def dex_reduce_all_noalloc(out: torch.Tensor, values: torch.Tensor, flags=0, str
     if out.numel() != 1:
         raise ValueError(f"out must hold one value, got {out.numel()}")
     check(lib().dex_reduce_all_noalloc(_ptr(out), _ptr(values), values.numel(), flags,
-                                       stream_ptr(stream)))
+                                       _stream(stream)))
 
 
 def dex_vjp(d: DexDesc, ins, resid, ct_out, ct_in, flags=0, ws: torch.Tensor | None = None,
             stream=None, dtypes=None):
-    a, na = bufs(ins, dtypes and dtypes.get("in"))
-    r, nr = bufs(resid, dtypes and dtypes.get("resid"))
-    co, nco = bufs(ct_out)
-    ci, nci = bufs(ct_in, dtypes and dtypes.get("ct_in"))
-    wp = ctypes.c_void_p(ws.data_ptr()) if ws is not None else None
-    wb = ws.numel() if ws is not None else 0
-    check(lib().dex_vjp(ctypes.byref(d), a, na, r, nr, co, nco, ci, nci, flags, wp, wb,
-                        stream_ptr(stream)))
+    g = dtypes.get if dtypes else _no_dtypes
+    check(lib().dex_vjp(ctypes.byref(d), _pack(ins, g("in")), len(ins), _pack(resid, g("resid")),
+                        len(resid), _pack(ct_out), len(ct_out), _pack(ct_in, g("ct_in")), len(ct_in),
+                        flags, _ptr(ws), ws.numel() if ws is not None else 0, _stream(stream)))
 
 
 def dex_accum_scatter_workspace_bytes(acc_dtype, n_rows, row_len, n, has_vals, flags=0) -> int:
@@ -338,12 +384,8 @@ def dex_accum_scatter(acc: torch.Tensor, idx: torch.Tensor, vals: torch.Tensor |
                 raise ValueError("dex buffers must be contiguous")
             _check_device(t)
     check(lib().dex_accum_scatter(
-        ctypes.c_void_p(acc.data_ptr()), acc_dt, n_rows, row_len, ctypes.c_void_p(idx.data_ptr()),
-        idt, ctypes.c_void_p(vals.data_ptr()) if vals is not None else None,
-        ctypes.c_void_p(scale.data_ptr()) if scale is not None else None, n, flags,
-        ctypes.c_void_p(oob.data_ptr()) if oob is not None else None,
-        ctypes.c_void_p(ws.data_ptr()) if ws is not None else None,
-        ws.numel() if ws is not None else 0, stream_ptr(stream)))
+        _ptr(acc), acc_dt, n_rows, row_len, _ptr(idx), idt, _ptr(vals), _ptr(scale), n, flags,
+        _ptr(oob), _ptr(ws), ws.numel() if ws is not None else 0, _stream(stream)))
 
 
 def dex_gmm_batched_plan(shapes: np.ndarray, variant: int = DEX_GMM_PLAIN):

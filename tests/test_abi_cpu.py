@@ -287,3 +287,21 @@ def test_undersized_workspace_rejected_on_host(dex):
     L_ = dex.lib()
     assert L_.dex_reduce_all(ctypes.c_void_p(16), ctypes.c_void_p(16), 5, 0, None, 0, None) \
         == dex.DEX_ERR_WORKSPACE
+
+
+def test_packed_buffer_lists_match_the_ctypes_records():
+    """The packed form of a buffer list is byte for byte the array of dex_buf."""
+    import torch
+    from paper_2104_05372_amd import dex
+    if torch.cuda.is_available():
+        pytest.skip("CPU tensors stand in for device buffers here")
+    ts = [torch.zeros(3, 4), None, torch.zeros(5, dtype=torch.float64), torch.zeros(0),
+          torch.zeros(7, dtype=torch.int32), torch.zeros(2, dtype=torch.uint8)]
+    for dtypes in (None, [None, dex.DEX_U8, None, None, dex.DEX_U32, None]):
+        arr, n = dex.bufs(ts, dtypes)
+        assert dex._pack(ts, dtypes) == bytes(arr)[: n * 24]
+    assert dex._pack([]) is None
+    with pytest.raises(ValueError):
+        dex._pack([torch.zeros(4, 4).t()])
+    with pytest.raises(KeyError):
+        dex._pack([torch.zeros(2, dtype=torch.float16)])
