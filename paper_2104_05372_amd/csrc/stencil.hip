@@ -255,31 +255,29 @@ __global__ void __launch_bounds__(256) stencil_step_vec(const float* __restrict_
 // 2 TB rows read ahead of a chunk's first output row. All indices are periodic,
 // so any H, W >= 1 is accepted. Measured per step, 4096^2, against one step per
 // launch: forward 6.5 us (24.0), adjoint 6.2 us (23.3); with the non-linear term
-// forward 10.5 us (25.8), adjoint with its recomputation 49 us (62); 601 x 333:
+// forward 10.6 us (25.8), adjoint 27.6 us (62; stencil_fused); 601 x 333:
 // 0.77 us (3.0). Bound by issuing the vector instructions (5 a cell, halo and
 // row overlap on top: 1.75 times the cells are computed at 4096^2).
 //
-// MODE   FWD   u -> u after TB steps; `snap` (if given) receives the input rows
-//        REC   FWD, and rho cos(u) of every level, which is all the adjoint
-//              steps read of the states they linearize about
-//        ADJ   cotangent back through TB steps (reads what REC wrote)
+// MODE   FWD   u -> u after TB steps; `snap` (if given) receives the input rows,
+//              `mid` (TB = 8) the state after four
+//        ADJ   cotangent back through TB linear steps
 //        ADJI  ADJ, the first cotangent dL (u_T - target) formed on the fly
 //        TAN   a state and its tangent together (forward mode)
-// NL: rho != 0. Products and sums are written as explicit fused
-// multiply-adds in the order of the one-step kernels, so every TB, VW and MODE
-// rounds alike and results do not depend on how the steps are grouped.
-enum { TB_FWD = 0, TB_REC = 1, TB_ADJ = 2, TB_ADJI = 3, TB_TAN = 4 };
+// NL: rho != 0 (its adjoint is stencil_fused). Products and sums are written as
+// explicit fused multiply-adds in the order of the one-step kernels, so every TB, VW
+// and MODE rounds alike and results do not depend on how the steps are grouped.
+enum { TB_FWD = 0, TB_ADJ = 1, TB_ADJI = 2, TB_TAN = 3 };
 
 struct TbArgs {
-  const float* in;    // level 0 (ADJI: u_T; TAN: the state)
-  const float* in2;   // ADJI: target; TAN: the tangent
-  float* out;         // level TB; may be null for REC (only the rho cos(u) are wanted)
+  const float* in;    // level 0 (ADJI: u_T; TAN: the state; stencil_fused: the cotangent or u_T)
+  const float* in2;   // ADJI: target; TAN: the tangent; stencil_fused: the state TB steps back
+  const float* in3;   // stencil_fused, first cotangent: target
+  float* out;         // level TB
   float* out2;        // TAN: the tangent's
   float* snap;        // FWD: copy of level 0, or null
-  float* rc;          // REC: rho cos(u) of level 0 (level t at rc + t rcs); ADJ*: of the first
-                      // step taken back (step t at rc - t rcs)
-  const float* dL;    // ADJI
-  int64_t rcs;        // elements between the levels of rc
+  float* mid;         // FWD, TB = 8: level 4, or null
+  const float* dL;    // first cotangent
   int H, W, RB, strips, accumulate;
   float c, rho;
 };
@@ -314,35 +312,25 @@ struct UVec<1> {
   typedef float T;
 };
 
-template <int TB, int VW, int MODE, bool NL>
-__global__ void __launch_bounds__(256) stencil_tb(TbArgs a) {
-  constexpr bool kAdj = MODE == TB_ADJ || MODE == TB_ADJI;
-  constexpr bool kTwo = MODE == TB_TAN || MODE == TB_ADJI;  // a second input field
-  constexpr bool kTan = MODE == TB_TAN;
-  constexpr bool kRc = kAdj && NL;
-  constexpr int HL = (TB + VW - 1) / VW, WV = VW * (64 - 2 * HL);
+// A wave's strip of columns: x0 + VW (lane - HL) onwards, taken modulo W for the
+// loads; lanes HL .. 63 - HL store theirs where they lie inside the grid.
+template <int VW>
+struct Strip {
   using C = Cells<VW>;
   using U = typename UVec<VW>::T;
-  const int lane = threadIdx.x & 63;
-  const int wave = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int chunk = wave / a.strips, strip = wave - chunk * a.strips;
-  const int y0 = chunk * a.RB;
-  if (y0 >= a.H) return;  // (no barrier follows)
-  const int H = a.H, W = a.W;
-  const int total = min(a.RB, H - y0) + 2 * TB;  // level-0 rows this wave needs
-  // the lane's columns: xc .. xc + VW - 1, taken modulo W for the loads
-  const int xc = strip * WV + VW * (lane - HL);
-  int col[VW];
+  int W, xc, col[VW], nmine;  // nmine: columns this lane stores
+  bool whole, even;           // no lane straddles the wrap; every lane stores all or none
+  DEX_DEV Strip(int lane, int x0, int HL, int W_) : W(W_), xc(x0 + VW * (lane - HL)) {
 #pragma unroll
-  for (int e = 0; e < VW; ++e) {
-    int m = (xc + e) % W;
-    col[e] = m < 0 ? m + W : m;
+    for (int e = 0; e < VW; ++e) {
+      const int m = (xc + e) % W;
+      col[e] = m < 0 ? m + W : m;
+    }
+    whole = __all(col[VW - 1] - col[0] == VW - 1);
+    nmine = lane >= HL && lane < 64 - HL && xc < W ? min(VW, W - xc) : 0;
+    even = __all(nmine == 0 || nmine == VW);
   }
-  const bool whole = __all(col[VW - 1] - col[0] == VW - 1);  // no lane straddles the wrap
-  const bool mine = lane >= HL && lane < 64 - HL && xc < W;
-  const int nmine = mine ? min(VW, W - xc) : 0;  // columns this lane stores
-  const bool even = __all(nmine == 0 || nmine == VW);
-  auto load = [&](const float* f, int y) {
+  DEX_DEV C load(const float* f, int y) const {
     C r;
     const float* row = f + (int64_t)y * W;
     if (VW == 1 || whole) {
@@ -358,8 +346,8 @@ __global__ void __launch_bounds__(256) stencil_tb(TbArgs a) {
       for (int e = 0; e < VW; ++e) r.v[e] = row[col[e]];
     }
     return r;
-  };
-  auto store = [&](float* f, int y, const C& r) {
+  }
+  DEX_DEV void store(float* f, int y, const C& r) const {
     float* row = f + (int64_t)y * W + xc;
     if (VW == 1 || even) {
       if (nmine) {
@@ -377,25 +365,40 @@ __global__ void __launch_bounds__(256) stencil_tb(TbArgs a) {
       for (int e = 0; e < VW; ++e)
         if (e < nmine) row[e] = r.v[e];
     }
-  };
+  }
+  // r += the row's present values
+  DEX_DEV void add(const float* f, int y, C& r) const {
+    const float* row = f + (int64_t)y * W + xc;
+#pragma unroll
+    for (int e = 0; e < VW; ++e)
+      if (e < nmine) r.v[e] += row[e];
+  }
+};
+
+template <int TB, int VW, int MODE, bool NL>
+__global__ void __launch_bounds__(256) stencil_tb(TbArgs a) {
+  constexpr bool kAdj = MODE == TB_ADJ || MODE == TB_ADJI;
+  constexpr bool kTwo = MODE == TB_TAN || MODE == TB_ADJI;  // a second input field
+  constexpr bool kTan = MODE == TB_TAN;
+  static_assert(!(kAdj && NL), "the non-linear adjoint is stencil_fused");
+  constexpr int HL = (TB + VW - 1) / VW;
+  using C = Cells<VW>;
+  const int lane = threadIdx.x & 63;
+  const int wave = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int chunk = wave / a.strips, strip = wave - chunk * a.strips;
+  const int y0 = chunk * a.RB;
+  if (y0 >= a.H) return;  // (no barrier follows)
+  const Strip<VW> sp(lane, strip * VW * (64 - 2 * HL), HL, a.W);
+  const int H = a.H;
+  const int total = min(a.RB, H - y0) + 2 * TB;  // level-0 rows this wave needs
   const float cw = a.c, rho = a.rho, ac = 1.f - 4.f * a.c;
   const float dL = MODE == TB_ADJI ? a.dL[0] : 0.f;
-
-  // rows y of the next loads, and of the first level's centre row, modulo H
-  int yl = (y0 - TB) % H;
+  int yl = (y0 - TB) % H;  // row of the next load, modulo H
   if (yl < 0) yl += H;
   auto next = [&](int y) { return y + 1 == H ? 0 : y + 1; };
-  // level t's row i - 1 - t has y = (yc - t) mod H at row i
-  int yc = yl == 0 ? H - 1 : yl - 1;
-  auto back = [&](int y, int t) {
-    int r = y - t;
-    while (r < 0) r += H;
-    return r;
-  };
 
   C sl[2][TB], sl2[2][TB];     // the last two rows of every level (sl2: the tangent's)
   C pf[2], pf2[2];             // rows loaded two ahead
-  C rp[2][kRc ? TB : 1];       // rho cos(u) rows, loaded two ahead
 #pragma unroll
   for (int q = 0; q < 2; ++q)
 #pragma unroll
@@ -404,47 +407,34 @@ __global__ void __launch_bounds__(256) stencil_tb(TbArgs a) {
       for (int e = 0; e < VW; ++e) sl[q][t].v[e] = sl2[q][t].v[e] = 0.f;
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
-    pf[q] = load(a.in, yl);
-    if constexpr (kTwo) pf2[q] = load(a.in2, yl);
-    if constexpr (kRc) {
-      int y = yc;
-      if (q) y = next(y);
-#pragma unroll
-      for (int t = 0; t < TB; ++t) rp[q][t] = load(a.rc - t * a.rcs, back(y, t));
-    }
+    pf[q] = sp.load(a.in, yl);
+    if constexpr (kTwo) pf2[q] = sp.load(a.in2, yl);
     yl = next(yl);
   }
-  int yc2 = next(next(yc));
 
   // row i of level 0: P = i % 2; FULL: every level has its rows
   auto advance = [&](auto pc, auto fullc, int i) {
     constexpr int P = decltype(pc)::value;
     constexpr bool FULL = decltype(fullc)::value;
     C s = pf[P], s2;
-    C rc[kRc ? TB : 1];
-    pf[P] = load(a.in, yl);
+    pf[P] = sp.load(a.in, yl);
     if constexpr (kTwo) {
       s2 = pf2[P];
-      pf2[P] = load(a.in2, yl);
-    }
-    if constexpr (kRc) {
-#pragma unroll
-      for (int t = 0; t < TB; ++t) {
-        rc[t] = rp[P][t];
-        rp[P][t] = load(a.rc - t * a.rcs, back(yc2, t));
-      }
+      pf2[P] = sp.load(a.in2, yl);
     }
     yl = next(yl);
-    if constexpr (kRc) yc2 = next(yc2);
     if constexpr (MODE == TB_ADJI) {
 #pragma unroll
       for (int e = 0; e < VW; ++e) s.v[e] = dL * (s.v[e] - s2.v[e]);
     }
     if constexpr (MODE == TB_FWD) {
-      if (a.snap && i >= TB && i < total - TB) store(a.snap, y0 + i - TB, s);
+      if (a.snap && i >= TB && i < total - TB) sp.store(a.snap, y0 + i - TB, s);
     }
     static_for<TB>([&](auto tc) {
       constexpr int t = decltype(tc)::value;
+      if constexpr (MODE == TB_FWD && TB == 8 && t == 4) {  // s: row i - 4 of level 4
+        if (a.mid && i - 4 >= TB && i - 4 < total - TB) sp.store(a.mid, y0 + i - 4 - TB, s);
+      }
       if (!FULL && i < 2 * (t + 1)) {  // (uniform) level t + 1 has no complete row yet
         if (i >= 2 * t) {
           sl[P][t] = s;
@@ -456,13 +446,10 @@ __global__ void __launch_bounds__(256) stencil_tb(TbArgs a) {
       C o = neighbours<VW>(sl[P][t], c, s), o2;
       if constexpr (kAdj) {
 #pragma unroll
-        for (int e = 0; e < VW; ++e) {
-          o.v[e] = fmaf(ac, c.v[e], cw * o.v[e]);
-          if constexpr (NL) o.v[e] = fmaf(rc[t].v[e], c.v[e], o.v[e]);
-        }
+        for (int e = 0; e < VW; ++e) o.v[e] = fmaf(ac, c.v[e], cw * o.v[e]);
       } else {
         C sn, cs;
-        if constexpr (NL) trig<true, MODE == TB_REC || kTan, VW>(c, sn, cs);
+        if constexpr (NL) trig<true, kTan, VW>(c, sn, cs);
         if constexpr (kTan) {
           const C c2 = sl2[P ^ 1][t];
           o2 = neighbours<VW>(sl2[P][t], c2, s2);
@@ -474,14 +461,8 @@ __global__ void __launch_bounds__(256) stencil_tb(TbArgs a) {
           o.v[e] = fmaf(cw, fmaf(-4.f, c.v[e], o.v[e]), c.v[e]);
           if constexpr (NL) {
             o.v[e] = fmaf(rho, sn.v[e], o.v[e]);
-            if constexpr (MODE == TB_REC || kTan) cs.v[e] = rho * cs.v[e];
-            if constexpr (kTan) o2.v[e] = fmaf(cs.v[e], sl2[P ^ 1][t].v[e], o2.v[e]);
+            if constexpr (kTan) o2.v[e] = fmaf(rho * cs.v[e], sl2[P ^ 1][t].v[e], o2.v[e]);
           }
-        }
-        if constexpr (MODE == TB_REC) {
-          // the centre row of level t: row i - 1 - t of the loaded ones
-          const int q = i - 1 - t;
-          if (q >= TB && q < total - TB) store(a.rc + t * a.rcs, y0 + q - TB, cs);
         }
       }
       sl[P][t] = s;
@@ -493,16 +474,9 @@ __global__ void __launch_bounds__(256) stencil_tb(TbArgs a) {
     });
     if constexpr (FULL) {
       const int y = y0 + i - 2 * TB;
-      if (MODE != TB_REC || a.out) {
-        if (kAdj && a.accumulate && nmine) {
-          const float* row = a.out + (int64_t)y * W + xc;
-#pragma unroll
-          for (int e = 0; e < VW; ++e)
-            if (e < nmine) s.v[e] += row[e];
-        }
-        store(a.out, y, s);
-        if constexpr (kTan) store(a.out2, y, s2);
-      }
+      if (kAdj && a.accumulate) sp.add(a.out, y, s);
+      sp.store(a.out, y, s);
+      if constexpr (kTan) sp.store(a.out2, y, s2);
     }
   };
   using F = std::integral_constant<bool, false>;
@@ -516,6 +490,114 @@ __global__ void __launch_bounds__(256) stencil_tb(TbArgs a) {
   for (int i = 2 * TB; i < total; i += 2) {
     advance(P0{}, T{}, i);
     if (i + 1 < total) advance(P1{}, T{}, i + 1);
+  }
+}
+
+// The non-linear adjoint through TB steps, the states it linearizes about rebuilt
+// in the same pass from the state TB steps back: nothing but that state and the two
+// cotangents crosses memory (storing rho cos(u) of every step cost 2 fields a step,
+// 49 us at 4096^2 against 27.6). Forward levels as in stencil_tb; when the centre
+// row of level t is complete its sine carries the state on and rho cos(u_t) waits
+// in registers for the adjoint level j = TB - 1 - t, which reaches that row 2 j
+// row-times later (chains of two-row delays, so that a loop of two rows needs a
+// move only between links). Row i of the state, row i - TB + 1 of the first
+// cotangent and row i - 2 TB + 1 of the last belong together. Halo: 2 (TB - 1)
+// columns, U rows ahead of the first output row. TB = 4: at 8 the delays take 112
+// registers and the halo a quarter of the columns.
+template <int TB, int VW, bool INIT>
+__global__ void __launch_bounds__(256) stencil_fused(TbArgs a) {
+  constexpr int U = 2 * (TB - 1) > TB ? 2 * (TB - 1) : TB;
+  constexpr int HL = (U + VW - 1) / VW;
+  using C = Cells<VW>;
+  const int lane = threadIdx.x & 63;
+  const int wave = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int chunk = wave / a.strips, strip = wave - chunk * a.strips;
+  const int y0 = chunk * a.RB;
+  if (y0 >= a.H) return;  // (no barrier follows)
+  const Strip<VW> sp(lane, strip * VW * (64 - 2 * HL), HL, a.W);
+  const int H = a.H;
+  const int total = U + 2 * TB - 1 + min(a.RB, H - y0);
+  const float cw = a.c, rho = a.rho, ac = 1.f - 4.f * a.c;
+  const float dL = INIT ? a.dL[0] : 0.f;
+  auto wrap = [&](int y) {
+    y %= H;
+    return y < 0 ? y + H : y;
+  };
+  auto next = [&](int y) { return y + 1 == H ? 0 : y + 1; };
+  int yu = wrap(y0 - U), yl = wrap(y0 - U - TB + 1);  // rows of the next loads
+  C us[2][TB], ls[2][TB];           // the last two rows of every level
+  C dl[2][TB * (TB - 1) / 2 + 1];   // delays: level j's links at j (j - 1) / 2 ...
+  C pu[2], pl[2], pt[2];            // rows loaded two ahead
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+#pragma unroll
+    for (int e = 0; e < VW; ++e) {
+#pragma unroll
+      for (int t = 0; t < TB; ++t) us[q][t].v[e] = ls[q][t].v[e] = 0.f;
+#pragma unroll
+      for (int t = 0; t <= TB * (TB - 1) / 2; ++t) dl[q][t].v[e] = 0.f;
+    }
+    pu[q] = sp.load(a.in2, yu);
+    pl[q] = sp.load(a.in, yl);
+    if constexpr (INIT) pt[q] = sp.load(a.in3, yl);
+    yu = next(yu);
+    yl = next(yl);
+  }
+  auto advance = [&](auto pc, int i) {
+    constexpr int P = decltype(pc)::value;
+    C s = pu[P], g = pl[P];
+    if constexpr (INIT) {
+#pragma unroll
+      for (int e = 0; e < VW; ++e) g.v[e] = dL * (g.v[e] - pt[P].v[e]);
+      pt[P] = sp.load(a.in3, yl);
+    }
+    pu[P] = sp.load(a.in2, yu);
+    pl[P] = sp.load(a.in, yl);
+    yu = next(yu);
+    yl = next(yl);
+    C rc[TB];  // rho cos(u) of level t at its centre row
+    static_for<TB>([&](auto tc) {
+      constexpr int t = decltype(tc)::value;
+      const C c = us[P ^ 1][t];
+      C sn, o;
+      trig<(t < TB - 1), true, VW>(c, sn, rc[t]);
+#pragma unroll
+      for (int e = 0; e < VW; ++e) rc[t].v[e] *= rho;
+      if constexpr (t < TB - 1) {
+        o = neighbours<VW>(us[P][t], c, s);
+#pragma unroll
+        for (int e = 0; e < VW; ++e)
+          o.v[e] = fmaf(rho, sn.v[e], fmaf(cw, fmaf(-4.f, c.v[e], o.v[e]), c.v[e]));
+      }
+      us[P][t] = s;
+      s = o;
+    });
+    static_for<TB>([&](auto jc) {
+      constexpr int j = decltype(jc)::value;
+      C r = rc[TB - 1 - j];
+#pragma unroll
+      for (int q = 0; q < j; ++q) {  // two row-times per link
+        const C old = dl[P][j * (j - 1) / 2 + q];
+        dl[P][j * (j - 1) / 2 + q] = r;
+        r = old;
+      }
+      const C c = ls[P ^ 1][j];
+      C o = neighbours<VW>(ls[P][j], c, g);
+#pragma unroll
+      for (int e = 0; e < VW; ++e)
+        o.v[e] = fmaf(r.v[e], c.v[e], fmaf(ac, c.v[e], cw * o.v[e]));
+      ls[P][j] = g;
+      g = o;
+    });
+    const int y = y0 + i - (U + 2 * TB - 1);
+    if (y >= y0) {
+      if (a.accumulate) sp.add(a.out, y, g);
+      sp.store(a.out, y, g);
+    }
+  };
+  for (int i = 0; i < total; i += 2) {
+    advance(std::integral_constant<int, 0>{}, i);
+    if (i + 1 < total) advance(std::integral_constant<int, 1>{}, i + 1);
   }
 }
 
@@ -721,8 +803,8 @@ int tb_pieces(int n) { return n / kTB + __builtin_popcount(n % kTB); }
 
 template <int MODE, int TB, int VW>
 void tb_launch(const TbArgs& a, bool nl, int blocks, hipStream_t st) {
-  if constexpr (MODE == TB_REC) {
-    hipLaunchKernelGGL((stencil_tb<TB, VW, MODE, true>), dim3(blocks), dim3(256), 0, st, a);
+  if constexpr (MODE == TB_ADJ || MODE == TB_ADJI) {
+    hipLaunchKernelGGL((stencil_tb<TB, VW, MODE, false>), dim3(blocks), dim3(256), 0, st, a);
   } else {
     if (nl)
       hipLaunchKernelGGL((stencil_tb<TB, VW, MODE, true>), dim3(blocks), dim3(256), 0, st, a);
@@ -731,32 +813,46 @@ void tb_launch(const TbArgs& a, bool nl, int blocks, hipStream_t st) {
   }
 }
 
+template <int TB, int VW>
+void fused_launch(const TbArgs& a, int blocks, hipStream_t st) {
+  if (a.in3)
+    hipLaunchKernelGGL((stencil_fused<TB, VW, true>), dim3(blocks), dim3(256), 0, st, a);
+  else
+    hipLaunchKernelGGL((stencil_fused<TB, VW, false>), dim3(blocks), dim3(256), 0, st, a);
+}
+
 // Launch shape of a tb-step launch on a grid: columns per lane, rows per wave,
 // strips.
 struct TbShape {
   int vw, rb, strips;
 };
-TbShape tb_shape(const St& s, int tb) {
+TbShape tb_shape(const St& s, int tb, bool fused) {
   const bool nl = s.rho != 0.f;
-  // Columns per lane (1 or 2) and rows per wave: the least modelled time. A wave
-  // takes rb + 3/2 tb row-times (the 2 tb rows ahead of its first output cost half),
-  // tb levels each; a level is about ins vector instructions, which one wave of a
-  // SIMD issues every 9 cycles or so (a dependent chain) and several waves every
-  // 4.4. Wide lanes waste fewer halo columns (112 of 128 kept against 48 of 64 at
-  // tb = 8), narrow ones give small grids more waves. Measured per step at tb = 8,
-  // rho = 0: 4096^2 two columns x 32 rows 6.2 us (one x 72: 6.2, one x 32: 6.4, two x
-  // 64: 6.5; four columns per lane, 32 rows: 6.9); 1024^2 one x 12 1.30 us (two x 8:
-  // 1.47); 601 x 333 one x 4 0.77 us (two x 4: 0.90, one x 16: 1.1).
+  const int halo = fused ? std::max(2 * (tb - 1), tb) : tb;
+  const double warm = fused ? halo + 2.0 * tb - 1.0 : 1.5 * tb;
+  // Columns per lane (1 or 2) and rows per wave: the least modelled time, over the
+  // heights that give every SIMD the same whole number n of waves. A wave takes rb +
+  // warm row-times, tb levels each; a level is about ins vector instructions, which
+  // several waves of a SIMD issue every 4.4 cycles and one wave by itself (a dependent
+  // chain, nothing to hide its loads) every 14 or so. Wide lanes waste fewer halo
+  // columns (112 of 128 kept against 48 of 64 at tb = 8), narrow ones give small grids
+  // more waves. Measured per step (forward rho = 0; rho != 0; adjoint rho != 0), for
+  // the lone wave's interval taken as 7, 14 +- 2 and 22: 4096^2 7.6, 6.5, 6.3; 11.9,
+  // 10.7, 10.2; 31.5, 27.6, 29.7 us; 1024^2 1.30, 1.30, 1.39; 2.60, 2.54, 2.78; 5.77,
+  // 5.57, 6.35 us; 601 x 333 within 2% throughout. Heights from a fixed list, which
+  // leave the last waves of a SIMD alone: 4096^2 6.3, 10.5 and 32.7 us.
   const int simds = 4 * num_cus();
   TbShape g{2, 32, 0};
   double best = 1e300;
   for (int v = 1; v <= 2; ++v) {
-    const int wv = v * (64 - 2 * ((tb + v - 1) / v));
+    const int wv = v * (64 - 2 * ((halo + v - 1) / v));
     const int64_t strips = (s.W + wv - 1) / wv;
-    const double ins = nl ? 14.0 * v + 6.0 : 5.5 * v + 2.5;
-    for (int r = 4; r <= 128; r += r < 32 ? 4 : 16) {
+    const double ins = fused ? 27.0 * v + 8.0 : nl ? 14.0 * v + 6.0 : 5.5 * v + 2.5;
+    for (int n = 1; n <= 16; ++n) {  // waves per SIMD
+      const int64_t chunks = std::max<int64_t>(1, (int64_t)n * simds / strips);
+      const int r = (int)std::max<int64_t>(4, (s.H + chunks - 1) / chunks);
       const int64_t per_simd = (strips * ((s.H + r - 1) / r) + simds - 1) / simds;
-      const double t = (r + 1.5 * tb) * tb * ins * std::max(9.0, 4.4 * (double)per_simd);
+      const double t = (r + warm) * tb * ins * std::max(14.0, 4.4 * (double)per_simd);
       if (t < best) {
         best = t;
         g = {v, r, (int)strips};
@@ -769,30 +865,31 @@ TbShape tb_shape(const St& s, int tb) {
 // The shapes of one call's launches, found once per number of steps.
 struct TbPlan {
   const St& s;
-  TbShape shape[4];
+  TbShape shape[2][4];
   explicit TbPlan(const St& s_) : s(s_), shape{} {}
-  const TbShape& at(int tb) {
-    TbShape& g = shape[__builtin_ctz(tb)];
-    if (!g.vw) g = tb_shape(s, tb);
+  const TbShape& at(int tb, bool fused) {
+    TbShape& g = shape[fused][__builtin_ctz(tb)];
+    if (!g.vw) g = tb_shape(s, tb, fused);
     return g;
+  }
+  // The launch's arguments from its shape; returns its blocks.
+  int fill(const TbShape& g, TbArgs& a) const {
+    a.H = s.H;
+    a.W = s.W;
+    a.c = s.c;
+    a.rho = s.rho;
+    a.RB = g.rb;
+    a.strips = g.strips;
+    return (int)(((int64_t)g.strips * ((s.H + g.rb - 1) / g.rb) + 3) / 4);
   }
 };
 
 // One launch of tb steps (a power of two up to kTB).
 template <int MODE>
 void tb_steps(TbPlan& plan, int tb, TbArgs a, hipStream_t st) {
-  const St& s = plan.s;
-  const TbShape& g = plan.at(tb);
-  const bool nl = s.rho != 0.f;
-  const int vw = g.vw;
-  a.H = s.H;
-  a.W = s.W;
-  a.c = s.c;
-  a.rho = s.rho;
-  a.RB = g.rb;
-  a.strips = g.strips;
-  const int64_t waves = (int64_t)g.strips * ((s.H + g.rb - 1) / g.rb);
-  const int blocks = (int)((waves + 3) / 4);
+  const TbShape& g = plan.at(tb, false);
+  const bool nl = plan.s.rho != 0.f;
+  const int vw = g.vw, blocks = plan.fill(g, a);
 #define DEX_TB(T_)                                     \
   (vw == 2 ? tb_launch<MODE, T_, 2>(a, nl, blocks, st) \
            : tb_launch<MODE, T_, 1>(a, nl, blocks, st))
@@ -810,6 +907,22 @@ void tb_steps(TbPlan& plan, int tb, TbArgs a, hipStream_t st) {
       DEX_TB(1);
   }
 #undef DEX_TB
+}
+
+// One launch of the non-linear adjoint through tb steps (4, 2 or 1).
+constexpr int kFused = 4;
+void fused_steps(TbPlan& plan, int tb, TbArgs a, hipStream_t st) {
+  const TbShape& g = plan.at(tb, true);
+  const int blocks = plan.fill(g, a);
+#define DEX_FU(T_) \
+  (g.vw == 2 ? fused_launch<T_, 2>(a, blocks, st) : fused_launch<T_, 1>(a, blocks, st))
+  if (tb == 4)
+    DEX_FU(4);
+  else if (tb == 2)
+    DEX_FU(2);
+  else
+    DEX_FU(1);
+#undef DEX_FU
 }
 
 // One step of the vector kernels (a tuning configuration).
@@ -949,7 +1062,7 @@ dex_status stencil_vjp(const dex_desc& d, int cfg, const float* u0, const float*
   float* lamA = (float*)ws;
   float* lamB = (float*)((char*)ws + fb);
   // recompute: a segment's states u_{s0+1} .. u_{s0+len-1} (vector and scatter
-  // forms), or rho cos(u) of its states u_{s0} .. u_{s0+len-1} (time-blocked form)
+  // forms), or those its pieces start from (time-blocked form)
   float* seg = (float*)((char*)ws + 2 * fb);
   const unsigned nb = (unsigned)((s.n + 255) / 256);
   if (s.T == 0) {
@@ -973,48 +1086,59 @@ dex_status stencil_vjp(const dex_desc& d, int cfg, const float* u0, const float*
     ProfRange pr(DEX_PROF_STENCIL_VJP, st);
     TbPlan plan(s);
     const bool nl = s.rho != 0.f;
-    const int64_t rcs = (int64_t)(fb / 4);
+    const int64_t fe = (int64_t)(fb / 4);
     bool first = true;
     for (int sg = s.nck - 1; sg >= 0; --sg) {
       const int s0 = sg * s.every;
       const int len = std::min(s.every, s.T - s0);
+      const float* ck = ckpt + (int64_t)sg * s.n;
+      // With rho = 0 the adjoint steps read no state, and none is rebuilt. Else
+      // the segment goes in pieces of kFused steps and the binary digits of the
+      // rest; the states they start from (the first is the checkpoint, the m-th
+      // seg + (m - 1) fe) are rebuilt first, two pieces a launch where they can.
+      const int lim = nl ? kFused : kTB;
       if (nl) {
-        // the segment's states again, from its checkpoint, keeping only what the
-        // adjoint steps read: rho cos(u_t). With rho = 0 they read no state, and
-        // none is rebuilt. The states between launches alternate between the
-        // cotangent field that is free here and the last rc field, which only
-        // the last launch fills: the state that launch reads is in the former.
-        const float* cur = ckpt + (int64_t)sg * s.n;
-        int pieces = tb_pieces(len);
-        for (int done = 0; done < len; --pieces) {
-          const int tb = tb_of(len - done);
+        const int full = len / kFused;  // pieces of kFused steps
+        const int starts = full + __builtin_popcount(len % kFused);
+        for (int m = 1; m < starts;) {
           TbArgs a{};
-          a.in = cur;
-          a.rc = seg + done * rcs;
-          a.rcs = rcs;
-          done += tb;
-          a.out = done == len ? nullptr : pieces % 2 == 0 ? o : seg + (len - 1) * rcs;
-          tb_steps<TB_REC>(plan, tb, a, st);
-          cur = a.out;
+          a.in = m == 1 ? ck : seg + (m - 2) * fe;
+          int tb = kFused;
+          if (m + 1 < starts && m + 1 <= full) {
+            tb = 2 * kFused;
+            a.mid = seg + (m - 1) * fe;
+            ++m;
+          } else if (m > full) {
+            tb = 1 << (31 - __builtin_clz(len % kFused));
+          }
+          a.out = seg + (m - 1) * fe;
+          ++m;
+          tb_steps<TB_FWD>(plan, tb, a, st);
           launches += tb;
         }
       }
-      for (int left = len; left > 0;) {
-        const int tb = tb_of(left);
-        TbArgs a{};
-        a.rc = nl ? seg + (left - 1) * rcs : nullptr;
-        a.rcs = rcs;
+      // pieces from the segment's end: the smallest digit of the rest first
+      for (int left = len, m = nl ? len / kFused + __builtin_popcount(len % kFused) - 1 : 0; left > 0; --m) {
+        int tb;
+        if (nl)
+          tb = left % lim ? left & -left : lim;
+        else
+          tb = tb_of(left);
         left -= tb;
         const bool last = sg == 0 && left == 0;
+        TbArgs a{};
+        a.in = first ? uT_in : g;
         a.out = last ? du0 : o;
         a.accumulate = last && accumulate;
-        if (first) {
-          a.in = uT_in;
+        a.dL = dL;
+        if (nl) {
+          a.in2 = m == 0 ? ck : seg + (m - 1) * fe;
+          a.in3 = first ? target : nullptr;
+          fused_steps(plan, tb, a, st);
+        } else if (first) {
           a.in2 = target;
-          a.dL = dL;
           tb_steps<TB_ADJI>(plan, tb, a, st);
         } else {
-          a.in = g;
           tb_steps<TB_ADJ>(plan, tb, a, st);
         }
         first = false;
