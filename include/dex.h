@@ -340,8 +340,8 @@ dex_status dex_accum_scatter_workspace_bytes(int32_t acc_dtype, int64_t n_rows,
 
 /*
  * Host-side plan for DEX_GMM_BATCHED. `shapes` is host memory, B rows of
- * (N, D, K) int64 with 1 <= D <= 32, N >= 1, K >= 1 (D <= 8 runs on the vector
- * units, 9..16 and 17..32 on matrix-core tiles padded to 16 and 32); variant
+ * (N, D, K) int64 with 1 <= D <= 32, N >= 1, K >= 1 (D is padded to a
+ * multiple of 8, in the F16X3 forward to 16 or 32); variant
  * DEX_GMM_PLAIN or DEX_GMM_F16X3 (fixed in the plan and the descriptor; the
  * operand cache of F16X3 holds the split parts). Fills *desc_out and
  * writes the plan (instance table and work lists, longest work first) into

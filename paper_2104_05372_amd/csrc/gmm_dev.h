@@ -827,6 +827,43 @@ __host__ __device__ inline size_t mom_slot(int DP) {
   return (size_t)(nb * (nb + 1) / 2) * 256 + DP + 4;
 }
 
+// Packed moments (D <= 32): the products x_a x_b and the coordinates x_a, each once,
+// in tiles of 16. D8: D rounded up to a multiple of 8. Order: (a, a + d mod D8) for
+// d = 0 .. D8/2 - 1 and every a; (a, a + D8/2) for a < D8/2; x_a.
+template <int D8>
+struct MomPack {
+  static constexpr int NQ = D8 * D8 / 32;                 // tiles of 16 features, d < D8/2
+  static constexpr int NT = NQ + (3 * D8 / 2 + 15) / 16;  // and of the rest
+  static constexpr int P = D8 == 24 ? 3 : D8 == 32 ? 2 : 1;  // tiles until (a) recurs
+  static constexpr int M = 16 * P / D8;                   // steps of d in that many tiles
+  static constexpr int NH = D8 >= 24 ? 4 : D8 == 16 ? 2 : 1;  // waves that share the tiles
+  static constexpr int TH = (NT + NH - 1) / NH;           // tiles per wave, of which
+  static constexpr int TE = TH * NH - NQ;                 // with two addresses of their own
+  static constexpr int NPW = 4 / NH;                      // waves that share the points
+  // points staged at a time; 16-point steps of them a wave multiplies, and weighs; LDS
+  // row length (rows 16 bytes x odd apart: the 16-byte reads of neighbouring rows meet
+  // no bank twice)
+  static constexpr int TP = D8 >= 24 ? 64 : D8 == 16 ? 128 : 256;
+  static constexpr int SPT = TP / 16 / NPW, SW = TP / 64;
+  static constexpr int ST = TP + 4;
+  static constexpr int ROWS = 3 * D8 / 2 + 2;             // last two: ones, zeros
+  static constexpr int NL = TP * D8 / 256;                // staged loads per thread
+  static constexpr int BUF = ROWS * ST + (NH > 1 ? TP * 16 : 0);  // coordinates, weights
+  static constexpr int SLOT = TH * NH * 16 + 4;           // the features, then the weight sum
+  static constexpr int RED = TH * NH * 256 + 64;          // floats of the waves' exchange
+};
+__host__ __device__ constexpr int mom_pack_slot(int D8) {
+  return D8 == 8    ? MomPack<8>::SLOT
+         : D8 == 16 ? MomPack<16>::SLOT
+         : D8 == 24 ? MomPack<24>::SLOT
+                    : MomPack<32>::SLOT;
+}
+// position of the moment of x_a x_b (a <= b < D8), and of x_a
+__host__ __device__ constexpr int mom_pack_quad(int D8, int a, int b) {
+  return b - a < D8 / 2 ? (b - a) * D8 + a
+                        : b - a == D8 / 2 ? D8 * D8 / 2 + a : (D8 - (b - a)) * D8 + b;
+}
+__host__ __device__ constexpr int mom_pack_lin(int D8, int a) { return D8 * D8 / 2 + D8 / 2 + a; }
 // FP16 moments with the point weights computed ahead (software pipelined).
 // Step s (32 points) computes the weights of step s + 2 from beta and f loaded
 // two steps earlier and writes them to LDS buffer s % 2, reads back those of
@@ -1293,7 +1330,8 @@ DEX_DEV void bwd_mom_unit(const void* xT_hi, const void* xT_lo, int N, int Npad,
 // summed second moments, first moments and weight sum are multiplied by m2, m1
 // and m0 (the undoing of a scaled form's operand scales and a cotangent left
 // out of its weights).
-template <int DPM = 64>
+// PACK: the slots are in MomPack's order.
+template <int DPM = 64, bool PACK = false>
 DEX_DEV void bwd_finalize_mom(const float* __restrict__ part, size_t sstride, int S, int k, int K,
                               int D, int DP, int64_t N, const float* __restrict__ alphas,
                               const float* __restrict__ means, const float* __restrict__ qd,
@@ -1343,7 +1381,10 @@ DEX_DEV void bwd_finalize_mom(const float* __restrict__ part, size_t sstride, in
   __shared__ float Ps[NBLKM * 256 + DPM + 4];  // summed slot: S blocks, u, A
   // Every global input is loaded first, each thread's loads issued together,
   // so the block waits for memory once instead of once per phase.
-  const int NE = NBLK * 256 + DP + 1;
+  const int D8 = (D + 7) & ~7;
+  const int eu = PACK ? mom_pack_lin(D8, 0) : NBLK * 256;        // u
+  const int ea = PACK ? mom_pack_slot(D8) - 4 : NBLK * 256 + DP;  // A
+  const int NE = ea + 1;
   float pv[NPV], qv[NQV], av[4];
   if (S == 1) {  // one slot (already reduced): plain loads, issued together
 #pragma unroll
@@ -1428,7 +1469,7 @@ DEX_DEV void bwd_finalize_mom(const float* __restrict__ part, size_t sstride, in
 #pragma unroll
   for (int i = 0; i < NPV; ++i) {
     const int e = t + 256 * i;
-    pv[i] *= e < NBLK * 256 ? m2 : e < NBLK * 256 + DP ? m1 : m0;
+    pv[i] *= e < eu ? m2 : e < ea ? m1 : m0;
     if (e < NE) Ps[e] = pv[i];
   }
   // QT and C: rows and columns past D stay zero
@@ -1449,12 +1490,22 @@ DEX_DEV void bwd_finalize_mom(const float* __restrict__ part, size_t sstride, in
   for (int j = t + 1024; j < K; j += 256) az += expf(alphas[j] - am);
   az = wave_sum(az);
   if ((t & 63) == 0) red[4 + (t >> 6)] = az;
-  if (t < D) us[t] = Ps[NBLK * 256 + t];
-  if (t == 0) Ash = Ps[NBLK * 256 + DP];
+  if (t < D) us[t] = Ps[eu + t];
+  if (t == 0) Ash = Ps[ea];
   __syncthreads();
   az = red[4] + red[5] + red[6] + red[7];
   const float A = Ash;
-  {
+  if constexpr (PACK) {
+    // C = S - u mu^T - mu u^T + A mu mu^T
+    for (int e = t; e < D8 * D8; e += 256) {
+      const int r = e / D8, s2 = e - r * D8;
+      if (s2 >= D || r > s2) continue;
+      const float v =
+          Ps[mom_pack_quad(D8, r, s2)] - us[r] * mus[s2] - mus[r] * us[s2] + A * mus[r] * mus[s2];
+      C[r][s2] = v;
+      C[s2][r] = v;
+    }
+  } else {
     // C = S - u mu^T - mu u^T + A mu mu^T over the stored lower blocks: the
     // thread's entry of block q = (ab, bb) is pv[q] (element t of the block),
     // at row r = 16 bb + (t/4 % 16) and column s = 16 ab + 4 (t/64) + t % 4

@@ -221,3 +221,19 @@ def test_full_batch_every_instance(dev):
             if done % 128 == 127:
                 print(f"  {done + 1} instances checked", flush=True)
     assert not bad, bad[:5]
+
+
+# Packed forward and moments: every padded dimension filled and not (24 has a
+# layout of its own), groups of 4 and of 16 components full, just over and single,
+# points at, under and over the staged tiles (64, 128, 256) and the reverse's chunks.
+PACKED_SHAPES = np.array([[256, 8, 4], [257, 7, 5], [513, 8, 33], [1025, 16, 16], [127, 15, 17],
+                          [64, 24, 8], [2113, 24, 19], [65, 23, 1], [1, 32, 2], [2560, 32, 48],
+                          [1087, 31, 3], [4609, 17, 6]], np.int64)
+
+
+@pytest.mark.parametrize("fcfg,bcfg", [(0, 0), (2, 2), (1, 4)])
+def test_packed_edges(dev, fcfg, bcfg):
+    """FP32 sums of at most 4609 terms: the bound of the tests above."""
+    insts = workloads.batched_inputs(PACKED_SHAPES, seed=77)
+    got = run_batched(PACKED_SHAPES, insts, fcfg, bcfg)
+    check_instances(PACKED_SHAPES, insts, got, range(len(insts)))
