@@ -30,6 +30,7 @@ UNITS = [
     ("gmm_mfma_inst.hip", ["-DDEX_PREC=1"], "gmm_mfma_bf16.o"),
     ("gmm_mfma_inst.hip", ["-DDEX_PREC=2"], "gmm_mfma_bf16x3.o"),
     ("gmm_batched.hip", [], "gmm_batched.o"),
+    ("gmm_f32.hip", [], "gmm_f32.o"),
     ("scatter.hip", [], "scatter.o"),
     ("stencil.hip", [], "stencil.o"),
     ("reduce.hip", [], "reduce.o"),

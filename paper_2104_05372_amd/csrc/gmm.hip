@@ -120,8 +120,7 @@ __global__ void __launch_bounds__(64 * W) k_mom_reduce(float* __restrict__ part,
   }
 }
 
-// Forward mode of the objective on the vector ALU (FP64 at every D <= 64, FP32 at D
-// < 12, with x - mu formed exactly in FP64 and rounded once). Block
+// Forward mode of the FP64 objective on the vector ALU. Block
 // (256 points, chunk of kJvpKC components); the components of the chunk are
 // staged in LDS in turn. For point i and component k, with r = x_i - mu_k,
 //   y = Q_k r, dy = dQ_k r - Q_k dmu_k (dQ: diagonal exp(qd) dqd, strict lower
@@ -131,32 +130,33 @@ __global__ void __launch_bounds__(64 * W) k_mom_reduce(float* __restrict__ part,
 // blockIdx.x].
 constexpr int kJvpKC = 8;
 
-template <typename T, int DB>
+template <int DB>
 __global__ void __launch_bounds__(256) gmm_jvp_valu(
-    const T* __restrict__ alphas, const T* __restrict__ means, const T* __restrict__ qd,
-    const T* __restrict__ l, const T* __restrict__ x, const T* __restrict__ f, int N, int D, int K,
-    const T* __restrict__ da, const T* __restrict__ dm, const T* __restrict__ dq,
-    const T* __restrict__ dl, double* __restrict__ part) {
-  __shared__ T Qs[DB][DB + 1], dQs[DB][DB + 1];
-  __shared__ T mus[DB], qdm[DB], kap[2];
+    const double* __restrict__ alphas, const double* __restrict__ means,
+    const double* __restrict__ qd, const double* __restrict__ l, const double* __restrict__ x,
+    const double* __restrict__ f, int N, int D, int K, const double* __restrict__ da,
+    const double* __restrict__ dm, const double* __restrict__ dq, const double* __restrict__ dl,
+    double* __restrict__ part) {
+  __shared__ double Qs[DB][DB + 1], dQs[DB][DB + 1];
+  __shared__ double mus[DB], qdm[DB], kap[2];
   __shared__ double sh[32];
   const int t = threadIdx.x, p = blockIdx.x * 256 + t;
   const bool valid = p < N;
   const int L = D * (D - 1) / 2;
-  T xr[DB];
+  double xr[DB];
 #pragma unroll
-  for (int b = 0; b < DB; ++b) xr[b] = (valid && b < D) ? x[(size_t)p * D + b] : T(0);
-  const T fp = valid ? f[p] : T(0);
+  for (int b = 0; b < DB; ++b) xr[b] = (valid && b < D) ? x[(size_t)p * D + b] : 0.0;
+  const double fp = valid ? f[p] : 0.0;
   double acc = 0.0;
   const int k0 = blockIdx.y * kJvpKC, k1 = min(K, k0 + kJvpKC);
   for (int k = k0; k < k1; ++k) {
     __syncthreads();
     for (int e = t; e < DB * DB; e += 256) {
       const int a = e / DB, b = e % DB;
-      T q = 0, dqv = 0;
+      double q = 0, dqv = 0;
       if (a < D && b < D) {
         if (a == b) {
-          const T ev = dexp<T>(qd[(size_t)k * D + a]);
+          const double ev = exp(qd[(size_t)k * D + a]);
           q = ev;
           dqv = ev * dq[(size_t)k * D + a];
         } else if (a > b) {
@@ -168,9 +168,9 @@ __global__ void __launch_bounds__(256) gmm_jvp_valu(
       Qs[a][b] = q;
       dQs[a][b] = dqv;
     }
-    if (t < DB) mus[t] = t < D ? means[(size_t)k * D + t] : T(0);
+    if (t < DB) mus[t] = t < D ? means[(size_t)k * D + t] : 0.0;
     if (t < 64) {
-      T s = 0, ds = 0;
+      double s = 0, ds = 0;
       for (int d = t; d < D; d += 64) {
         s += qd[(size_t)k * D + d];
         ds += dq[(size_t)k * D + d];
@@ -184,19 +184,19 @@ __global__ void __launch_bounds__(256) gmm_jvp_valu(
     }
     __syncthreads();
     if (t < DB) {  // Q_k dmu_k
-      T v = 0;
+      double v = 0;
       for (int b = 0; b <= t && b < D; ++b) v += Qs[t][b] * dm[(size_t)k * D + b];
       qdm[t] = v;
     }
     __syncthreads();
-    T r[DB];
+    double r[DB];
 #pragma unroll
-    for (int b = 0; b < DB; ++b) r[b] = b < D ? (T)((double)xr[b] - (double)mus[b]) : T(0);
-    T s = 0, sd = 0;
+    for (int b = 0; b < DB; ++b) r[b] = b < D ? xr[b] - mus[b] : 0.0;
+    double s = 0, sd = 0;
 #pragma unroll
     for (int a = 0; a < DB; ++a) {
       if (a < D) {
-        T y = 0, dy = -qdm[a];
+        double y = 0, dy = -qdm[a];
 #pragma unroll
         for (int b = 0; b <= a; ++b) {
           y += Qs[a][b] * r[b];
@@ -206,28 +206,28 @@ __global__ void __launch_bounds__(256) gmm_jvp_valu(
         sd += y * dy;
       }
     }
-    if (valid) acc += (double)(dexp<T>(kap[0] - T(0.5) * s - fp) * (kap[1] - sd));
+    if (valid) acc += exp(kap[0] - 0.5 * s - fp) * (kap[1] - sd);
   }
   acc = block_sum(acc, sh);
   if (t == 0) part[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = acc;
 }
 
-// The same for FP32 on the matrix cores (16x16x4 FP32 products; D >= 12): a wave
+// The same for FP32 storage and D > 32 on the matrix cores (16x16x4 FP32 products; D
+// <= 32: on quads of components): a wave
 // takes 64 points and every KS-th component. Per component y = Q_k r and dy = dQ_k r
 // - Q_k dmu_k from r = x - mu_k (formed per component: the difference of two FP32
 // values, rounded once), with the strict lower parts read as they are stored and the
 // next component's loads issued before the current one's products; |y|^2 and y . dy
 // are summed over the lane groups so that lane p owns point p. Each wave writes its
-// FP64 sum to part[wave]. N = 20000, D = 32, K = 50: 53 us (one thread per point
-// and LDS broadcasts of Q and dQ: 163). Lane layout: A and B hold row / column c and
+// FP64 sum to part[wave]. (N = 20000, D = 32, K = 50: 63 us a launch, 37 on quads; one
+// thread per point and LDS broadcasts of Q and dQ 163.) Lane layout: A and B hold row / column c and
 // contraction values 16 ch + 4 g + j (element j), the result rows 4 g + i.
-template <int DP>
 __global__ void __launch_bounds__(256) gmm_jvp_mfma(
     const float* __restrict__ alphas, const float* __restrict__ means, const float* __restrict__ qd,
     const float* __restrict__ l, const float* __restrict__ x, const float* __restrict__ f, int N,
     int D, int K, int KS, const float* __restrict__ da, const float* __restrict__ dm,
     const float* __restrict__ dq, const float* __restrict__ dl, double* __restrict__ part) {
-  constexpr int NB = DP / 16, NQ = NB * (NB + 1) / 2;
+  constexpr int NB = 4, NQ = NB * (NB + 1) / 2;
   const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
   const int wave = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int tiles = (N + 63) / 64;
@@ -455,6 +455,9 @@ size_t mom_es(const Shape& s) { return s.prec == PREC_F32 ? 4 : 2; }
 FwdCfg fwd_cfg(const Shape& s, int i) { return s.prec == PREC_BF16 ? kFwdBF[i] : kFwdF32[i]; }
 BwdCfg bwd_cfg(const Shape& s, int i) { return s.prec == PREC_F32 ? kBwdF32[i] : kBwdBF[i]; }
 
+// FP32 operands and D <= 32: the forward on quads of components
+bool quads(const Shape& s) { return s.mfma && s.prec == PREC_F32 && s.g.D <= 32; }
+
 struct CacheLayout {
   size_t xh, xl, xhT, xlT, Qh, Ql, negc, kappa, beta, shift, total;
   // feature-product forward (BF16, D = 64): coefficient operand, kappa',
@@ -474,11 +477,11 @@ CacheLayout cache_layout(const Shape& s) {
   if (s.mfma) {
     const size_t es = s.prec == PREC_F32 ? 4 : 2;
     const bool lo = s.prec == PREC_BF16X3;
-    c.xh = take(g.Npad * g.DP * es);
+    c.xh = quads(s) ? 0 : take(g.Npad * g.DP * es);
     c.xl = lo ? take(g.Npad * g.DP * es) : 0;
     c.xhT = take(g.Npad * g.DP * mom_es(s));
     c.xlT = lo ? take(g.Npad * g.DP * mom_es(s)) : 0;
-    c.Qh = take(g.K * g.DP * g.DP * es);
+    c.Qh = take(quads(s) ? quad_rec_bytes(g) : g.K * g.DP * g.DP * es);
     c.Ql = lo ? take(g.K * g.DP * g.DP * es) : 0;
     c.negc = take(g.K * g.DP * 4);
     c.kappa = take(g.K * 4);
@@ -533,11 +536,13 @@ size_t gmm_cache_bytes(const dex_desc& d) {
 // Forward-mode workspace. Feature-product form (16-bit variant, D = 64): the
 // scaled FP16 x~ and its tile exponents, the tangent coefficient operand,
 // dkq' and rescale factors, one FP64 partial per (pass, tile). Vector-ALU
-// form: one FP64 partial per (point block, component chunk).
+// form: one FP64 partial per (point block, component chunk). Quads: both records, the
+// origin, one partial per (tile, share).
 struct JvpLayout {
-  size_t x16, texp, dW16, dkq, disc, part, total;
+  size_t x16, texp, dW16, dkq, disc, rec, trec, shift, part, total;
   int64_t nparts;
-  int ks;  // matrix-core FP32 form: waves sharing a tile's components (0: vector ALU)
+  QuadSplit quad;  // quads of components (D <= 32; no tiles: not)
+  int ks;  // D > 32: waves sharing a tile's components
 };
 // Waves that share a 64-point tile's components, for the least rounds of waves
 // (one per SIMD) times components each.
@@ -570,9 +575,13 @@ static JvpLayout jvp_layout(const Shape& s) {
     j.dkq = take(Kp * 4);
     j.disc = take(Kp * 4);
     j.nparts = qf_tan_parts(s.g);
-  } else if (s.mfma && s.g.D >= 12) {
-    // (a 16x16 tile is mostly padding below: N = 1e5, K = 150, D = 8 takes the
-    // vector ALU 135 us and the matrix cores 237, D = 16 405 and 242)
+  } else if (s.mfma && s.g.D <= 32) {
+    j.quad = quad_jvp_split(s.g);
+    j.rec = take(quad_rec_bytes(s.g));
+    j.trec = take(quad_rec_bytes(s.g));
+    j.shift = take(64 * 4);
+    j.nparts = j.quad.tiles * j.quad.ks;
+  } else if (s.mfma) {
     j.ks = jvp_shares(s.g);
     j.nparts = (s.g.N + 63) / 64 * j.ks;
   } else {
@@ -605,10 +614,9 @@ int gmm_num_configs(const dex_desc& d, int role) {
 
 // The configuration of an untuned call, by the form and by N K (the work per
 // element of a component's moments). Measured whole calls, us:
-//   forward FP32: two components a wave, two waves a SIMD, everywhere (N = 30011,
-//     K = 37, D = 20: 40 against 47 with all waves resident; N = 1e5, K = 200, D = 8:
-//     170 against 185); split BF16 at D > 32: one wave a SIMD and two tiles ahead (46
-//     against 50 at N = 1e5, K = 5).
+//   forward FP32, D > 32 (at D <= 32 every configuration is the quads'): two
+//     components a wave, two waves a SIMD; split BF16 at D > 32: one wave a SIMD and two
+//     tiles ahead (46 against 50 at N = 1e5, K = 5).
 //   reverse 16-bit: below 1.5e6 two components and one wave a SIMD (D = 64, N =
 //     10000, K = 37: 37 against 41 with four components); above, four components (D =
 //     64, N = 1e5, K = 200: 0.123 ms a call against 0.19 with two), at D <= 16 from 1e7
@@ -685,6 +693,15 @@ dex_status gmm_fwd(const dex_desc& d, int cfg, const GmmPtrs& in, void* F, void*
       }
       break;
     default:
+      if (quads(s)) {
+        const QuadSplit q = quad_fwd_split(s.g);
+        quad_prep(s.g, in, (float*)xhT, (float*)Qh, shift, st);
+        ProfRange pr(DEX_PROF_GMM_FWD, st);
+        quad_fwd(s.g, q, x, (const float*)Qh, shift, beta, ml, st);
+        sp.sk = q.ks;
+        pr.end(1);
+        break;
+      }
       mfma_prep<PREC_F32>(s.g, x, al, mu, qd, l, xh, xl, xhT, xlT, Qh, Ql, negc, kappa, shift,
                           st);
       {
@@ -754,26 +771,25 @@ dex_status gmm_vjp(const dex_desc& d, int cfg, const GmmPtrs& in, const void* f,
   return check_hip(hipGetLastError(), "gmm_vjp (MFMA)");
 }
 
-template <typename T>
+// FP64
 static void launch_jvp_valu(const Shape& s, const GmmPtrs& in, const void* f, const GmmGrads& t,
                             double* part, hipStream_t st) {
   dim3 grid((unsigned)((s.g.N + 255) / 256), (unsigned)((s.g.K + kJvpKC - 1) / kJvpKC));
 #define DEX_JV(DB)                                                                            \
-  hipLaunchKernelGGL((gmm_jvp_valu<T, DB>), grid, dim3(256), 0, st, (const T*)in.alphas,     \
-                     (const T*)in.means, (const T*)in.qd, (const T*)in.l, (const T*)in.x,     \
-                     (const T*)f, (int)s.g.N, (int)s.g.D, (int)s.g.K, (const T*)t.d_alphas,   \
-                     (const T*)t.d_means, (const T*)t.d_qd, (const T*)t.d_l, part)
+  hipLaunchKernelGGL((gmm_jvp_valu<DB>), grid, dim3(256), 0, st, (const double*)in.alphas,     \
+                     (const double*)in.means, (const double*)in.qd, (const double*)in.l, (const double*)in.x,     \
+                     (const double*)f, (int)s.g.N, (int)s.g.D, (int)s.g.K, (const double*)t.d_alphas,   \
+                     (const double*)t.d_means, (const double*)t.d_qd, (const double*)t.d_l, part)
   if (s.g.D <= 4) {
     DEX_JV(4);
   } else if (s.g.D <= 8) {
     DEX_JV(8);
   } else if (s.g.D <= 16) {
     DEX_JV(16);
-  } else if constexpr (sizeof(T) == 8) {  // (FP32 takes the matrix cores there)
-    if (s.g.D <= 32)
-      DEX_JV(32);
-    else
-      DEX_JV(64);
+  } else if (s.g.D <= 32) {
+    DEX_JV(32);
+  } else {
+    DEX_JV(64);
   }
 #undef DEX_JV
 }
@@ -799,29 +815,23 @@ dex_status gmm_jvp(const dex_desc& d, int cfg, const GmmPtrs& in, const void* f,
     qf_jvp(s.g, w + jl.x16, w + jl.dW16, (const float*)(w + jl.dkq), (const float*)(w + jl.disc),
            (const int*)(w + jl.texp), (const float*)(cc + cl.beta), (const float*)f, part, st);
     pr.end(1);
+  } else if (jl.quad.tiles) {
+    ProfRange pr(DEX_PROF_GMM_JVP, st);
+    quad_jvp(s.g, jl.quad, in, t, (const float*)f, (float*)(w + jl.rec), (float*)(w + jl.trec),
+             (float*)(w + jl.shift), part, st);
+    pr.end(1);
   } else if (jl.ks) {
     ProfRange pr(DEX_PROF_GMM_JVP, st);
     const dim3 grid((unsigned)((jl.nparts + 3) / 4));
-#define DEX_JM(DP_)                                                                              \
-  hipLaunchKernelGGL((gmm_jvp_mfma<DP_>), grid, dim3(256), 0, st, (const float*)in.alphas,       \
-                     (const float*)in.means, (const float*)in.qd, (const float*)in.l,            \
-                     (const float*)in.x, (const float*)f, (int)s.g.N, (int)s.g.D, (int)s.g.K,    \
-                     jl.ks, (const float*)t.d_alphas, (const float*)t.d_means,                   \
-                     (const float*)t.d_qd, (const float*)t.d_l, part)
-    if (s.g.DP == 16)
-      DEX_JM(16);
-    else if (s.g.DP == 32)
-      DEX_JM(32);
-    else
-      DEX_JM(64);
-#undef DEX_JM
+    hipLaunchKernelGGL(gmm_jvp_mfma, grid, dim3(256), 0, st, (const float*)in.alphas,
+                       (const float*)in.means, (const float*)in.qd, (const float*)in.l,
+                       (const float*)in.x, (const float*)f, (int)s.g.N, (int)s.g.D, (int)s.g.K,
+                       jl.ks, (const float*)t.d_alphas, (const float*)t.d_means,
+                       (const float*)t.d_qd, (const float*)t.d_l, part);
     pr.end(1);
   } else {
     ProfRange pr(DEX_PROF_GMM_JVP, st);
-    if (s.tsize == 8)
-      launch_jvp_valu<double>(s, in, f, t, part, st);
-    else
-      launch_jvp_valu<float>(s, in, f, t, part, st);
+    launch_jvp_valu(s, in, f, t, part, st);
     pr.end(1);
   }
   if (s.tsize == 8)

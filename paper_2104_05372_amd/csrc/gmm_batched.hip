@@ -55,7 +55,7 @@ struct PlanHeader {
   int64_t B;
   int64_t inst_off;
   int64_t prepx_off, n_prepx;
-  int64_t prepq_off, n_prepq;  // (instance, component), or quads of a FP32 instance
+  int64_t prepq_off, n_prepq;  // (instance, component), those that fill up a quad too
   int64_t merge_off, n_merge;
   int64_t fwd_off[kBFwdCfgs], n_fwd[kBFwdCfgs];
   int64_t bwd_off[kBBwdCfgs], n_bwd[kBBwdCfgs];
@@ -192,19 +192,6 @@ __global__ void __launch_bounds__(256) k_bprep_x(const char* __restrict__ plan,
     prep_x_tile_split<32>(x + I.x_off, I.N, I.D, (int)I.Npad, w.a * 64, sh, xh, xl, ts);
 }
 
-// fn(integral_constant D8)
-template <typename F>
-DEX_DEV void with_d8(int D, F&& fn) {
-  if (D <= 8)
-    fn(std::integral_constant<int, 8>{});
-  else if (D <= 16)
-    fn(std::integral_constant<int, 16>{});
-  else if (D <= 24)
-    fn(std::integral_constant<int, 24>{});
-  else
-    fn(std::integral_constant<int, 32>{});
-}
-
 __global__ void __launch_bounds__(256) k_bprep_q(const char* __restrict__ plan,
                                                  const float* __restrict__ alphas,
                                                  const float* __restrict__ means,
@@ -231,8 +218,11 @@ __global__ void __launch_bounds__(256) k_bprep_q(const char* __restrict__ plan,
   float* Q = (float*)(cache + I.Q_off);
   const float* sh = (const float*)(cache + I.sh_off);
   with_d8(I.D, [&](auto d8) {
-    prep_quad<decltype(d8)::value>(alphas + I.a_off, means + I.m_off, qd + I.m_off, l + I.l_off,
-                                   I.D, I.K, w.a, sh, Q);
+    QuadPrep<decltype(d8)::value, false> p;
+    const typename decltype(p)::Src src{alphas + I.a_off, means + I.m_off, qd + I.m_off,
+                                        l + I.l_off};
+    p.load(src, src, I.D, I.K, w.a);
+    p.store(I.D, I.K, w.a, sh, Q, Q);
   });
 }
 
@@ -286,7 +276,7 @@ __global__ void __launch_bounds__(256, SPLIT ? 3 : 4) k_bgmm_fwd(const char* __r
     auto quads = [&](auto d8) {
       fwd_quads<decltype(d8)::value, CB>(x + I.x_off, (const float*)(cache + I.sh_off), I.N, I.D,
                                          (int)I.Npad, w.a * 64 * CB, (const float*)(cache + I.Q_off),
-                                         I.K, beta, ml + I.ml_off, lds);
+                                         0, (I.K + 3) / 4, beta, ml + I.ml_off, lds);
     };
     if constexpr (SPLIT)
       quads(std::integral_constant<int, 8>{});  // (D <= 8: the others are split)
@@ -441,7 +431,7 @@ PlanBuild build_plan(const int64_t* shapes, int64_t B, int32_t variant) {
     I.fpart_off = fp;
     fp += I.nblk;
     for (int t = 0; I.split && t < I.Npad / 64; ++t) p.prepx.push_back({(int32_t)b, t, 0, 0});
-    for (int k = 0; k < (I.split ? I.K : nq); ++k) p.prepq.push_back({(int32_t)b, k, 0, 0});
+    for (int k = 0; k < (I.split ? I.K : 4 * nq); ++k) p.prepq.push_back({(int32_t)b, k, 0, 0});
     for (int k = 0; k < I.K; ++k) p.comp.push_back({(int32_t)b, k, 0, 0});
     for (int t = 0; t < I.nblk; ++t) p.merge.push_back({(int32_t)b, t, 0, 0});
   }

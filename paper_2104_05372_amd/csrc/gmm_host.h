@@ -79,6 +79,24 @@ void gmm_f64_vjp(int64_t N, int64_t D, int64_t K, const GmmPtrs& in, const doubl
                  const double* f, const double* ct, const GmmGrads& out, bool accumulate,
                  double* part, hipStream_t st);
 
+// FP32, D <= 32, on quads of components (gmm_f32.hip): tiles of points, shares of a
+// tile's quads (the forward: log-sum-exp partials per point; the forward mode: one FP64
+// partial per tile and share). rec, trec: quad_rec_bytes.
+struct QuadSplit {
+  int64_t tiles = 0;
+  int ks = 1;
+};
+QuadSplit quad_fwd_split(const GmmGeom& g);
+QuadSplit quad_jvp_split(const GmmGeom& g);
+size_t quad_rec_bytes(const GmmGeom& g);
+void quad_prep(const GmmGeom& g, const GmmPtrs& in, float* xhT, float* rec, float* shift,
+               hipStream_t st);
+void quad_fwd(const GmmGeom& g, const QuadSplit& q, const float* x, const float* rec,
+              const float* shift, float* beta, float2* ml, hipStream_t st);
+void quad_jvp(const GmmGeom& g, const QuadSplit& q, const GmmPtrs& in, const GmmGrads& t,
+              const float* f, float* rec, float* trec, float* shift, double* part,
+              hipStream_t st);
+
 // Feature-product forward (BF16 variant, D = 64; defined with the BF16 kernels).
 // qf_prep: the origin (shift), x~^T, the per-tile scaled FP16 copy of x and
 // its exponents, the coefficient operand, kappa' and rescale factors. qf_fwd: beta and the per-pass

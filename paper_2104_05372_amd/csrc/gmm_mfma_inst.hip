@@ -844,12 +844,15 @@ void mfma_prep<P>(const GmmGeom& g, const float* x, const float* alphas, const f
                   const float* qd, const float* l, void* xh, void* xl, void* xhT, void* xlT,
                   void* Qh, void* Ql, float* negc, float* kappa, float* shift,
                   hipStream_t st) {
-  if (g.DP == 16)
-    prep_dp<16>(g, x, alphas, means, qd, l, xh, xl, xhT, xlT, Qh, Ql, negc, kappa, shift, st);
-  else if (g.DP == 32)
-    prep_dp<32>(g, x, alphas, means, qd, l, xh, xl, xhT, xlT, Qh, Ql, negc, kappa, shift, st);
-  else
-    prep_dp<64>(g, x, alphas, means, qd, l, xh, xl, xhT, xlT, Qh, Ql, negc, kappa, shift, st);
+  if constexpr (P != PREC_F32) {
+    if (g.DP == 16)
+      return prep_dp<16>(g, x, alphas, means, qd, l, xh, xl, xhT, xlT, Qh, Ql, negc, kappa, shift,
+                         st);
+    if (g.DP == 32)
+      return prep_dp<32>(g, x, alphas, means, qd, l, xh, xl, xhT, xlT, Qh, Ql, negc, kappa, shift,
+                         st);
+  }
+  prep_dp<64>(g, x, alphas, means, qd, l, xh, xl, xhT, xlT, Qh, Ql, negc, kappa, shift, st);
 }
 
 // Resident 256-thread blocks of `kernel` per CU.
@@ -901,8 +904,10 @@ static FlatSplit fwd_dp(const GmmGeom& g, const FwdCfg& c, const MfmaOps& o, flo
 template <>
 FlatSplit mfma_fwd<P>(const GmmGeom& g, const FwdCfg& c, const MfmaOps& o, float* beta,
                       float2* ml, hipStream_t st) {
-  if (g.DP == 16) return fwd_dp<16>(g, c, o, beta, ml, st);
-  if (g.DP == 32) return fwd_dp<32>(g, c, o, beta, ml, st);
+  if constexpr (P != PREC_F32) {  // (FP32: D > 32, see gmm_f32.hip)
+    if (g.DP == 16) return fwd_dp<16>(g, c, o, beta, ml, st);
+    if (g.DP == 32) return fwd_dp<32>(g, c, o, beta, ml, st);
+  }
   return fwd_dp<64>(g, c, o, beta, ml, st);
 }
 

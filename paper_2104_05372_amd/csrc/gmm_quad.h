@@ -17,6 +17,19 @@
 
 namespace dexk {
 
+// fn(integral_constant D8)
+template <typename F>
+__host__ __device__ inline void with_d8(int D, F&& fn) {
+  if (D <= 8)
+    fn(std::integral_constant<int, 8>{});
+  else if (D <= 16)
+    fn(std::integral_constant<int, 16>{});
+  else if (D <= 24)
+    fn(std::integral_constant<int, 24>{});
+  else
+    fn(std::integral_constant<int, 32>{});
+}
+
 // ---------------------------------------------------------------------------
 // Forward. Four components ("a quad") share the rows of a product: its 16 rows are
 // rows 4r .. 4r+3 of the four factors, which are zero past column 4r+3, so row
@@ -31,57 +44,98 @@ __host__ __device__ constexpr int quad_groups(int D8) { return (quad_products(D8
 __host__ __device__ constexpr int quad_neg(int D8) { return quad_groups(D8) * 256; }
 __host__ __device__ constexpr int quad_floats(int D8) { return quad_neg(D8) + 4 * D8 + 4; }
 
-// Record of components 4q .. 4q + 3; those past K have zero factors and kappa -inf, so
-// that their log-densities add nothing. (256 threads)
-template <int D8>
-DEX_DEV void prep_quad(const float* __restrict__ alphas, const float* __restrict__ means,
-                       const float* __restrict__ qd, const float* __restrict__ l, int D, int K,
-                       int q, const float* __restrict__ shift, float* __restrict__ rec) {
-  __shared__ float qs[4][D8][D8 + 1];
-  __shared__ float mus[4][D8], qds[4][D8];
-  const int L = D * (D - 1) / 2, t = threadIdx.x;
-  rec += (size_t)q * quad_floats(D8);
-  __syncthreads();
-  if (t < 4 * D8) {
-    const int j = t / D8, a = t % D8, k = 4 * q + j;
-    const bool in = k < K && a < D;
-    mus[j][a] = in ? means[(size_t)k * D + a] - shift[a] : 0.f;
-    qds[j][a] = in ? qd[(size_t)k * D + a] : 0.f;
-  }
-  __syncthreads();
-  for (int e = t; e < 4 * D8 * D8; e += 256) {
-    const int j = e / (D8 * D8), a = e / D8 % D8, b = e % D8, k = 4 * q + j;
-    float v = 0.f;
-    if (k < K && a < D && b <= a)
-      v = a == b ? expf(qds[j][a]) : l[(size_t)k * L + a * (a - 1) / 2 + b];
-    qs[j][a][b] = v;
-  }
-  __syncthreads();
-  for (int e = t; e < quad_neg(D8); e += 256) {
-    const int m = e / 256 * 4 + e % 4, n = e % 256 / 4;
-    float v = 0.f;
-    if (m < quad_products(D8)) {
-      int r = 0, ch = m;
-      while (ch > r) ch -= ++r;
-      v = qs[(n & 15) >> 2][4 * r + (n & 3)][4 * ch + (n >> 4)];
-    }
-    rec[e] = v;
-  }
-  if (t < 4 * D8) {
-    const int j = t / D8, a = t % D8;
-    float c = 0.f;
-    for (int b = 0; b <= a; ++b) c = fmaf(qs[j][a][b], mus[j][b], c);
-    rec[quad_neg(D8) + t] = -c;
-  }
-  // wave j: the log-determinant of component j, by a tree (it enters beta whole)
-  const int j = t >> 6, k = 4 * q + j;
-  const float s = wave_sum((t & 63) < D8 ? qds[j][t & 63] : 0.f);
-  if ((t & 63) == 0) rec[quad_neg(D8) + 4 * D8 + j] = k < K ? alphas[k] + s : -INFINITY;
-}
+// Component k's part of its quad's record, and of the tangent record with TAN (dQ,
+// exp(qd) dqd on its diagonal; -(dQ (mu - shift) + Q dmu); dkappa). The components that
+// fill up the last quad get zero factors, kappa -inf and dkappa 0, so that they add
+// nothing. 256 threads; load() issues every load (branch-free, at clamped addresses:
+// N = 20000, D = 32, K = 50 prepared both records quad by quad, a load at a time, in 21
+// us, this way in 6), store() may come after the block has found the shift.
+template <int D8, bool TAN>
+struct QuadPrep {
+  static constexpr int NL = (D8 * D8 + 255) / 256;
+  struct Src {
+    const float *al, *mu, *qd, *l;
+  };
+  float lv[NL], dv[NL], mu, qd, al;
+  float tlv[TAN ? NL : 1], tdv[TAN ? NL : 1], tmu, tqd, tal;
 
-// One block: 64 CB points from the tile's first, all K components; wave v takes 16 CB
-// points. beta has rows for ceil(K/4) 4 components (the last may hold values nobody
-// reads, as do points N <= p < Npad). Lane 16 g + c holds points CB c .. CB c + CB - 1
+  DEX_DEV static void load_one(const Src& s, int D, size_t kc, float (&lv)[NL], float (&dv)[NL],
+                               float& mu, float& qd, float& al) {
+    const int t = threadIdx.x, L = D * (D - 1) / 2, tc = min(t % D8, D - 1);
+    const float* lsrc = L > 0 ? s.l + kc * L : s.qd + kc * D;  // (D = 1: not used)
+#pragma unroll
+    for (int r = 0; r < NL; ++r) {
+      const int e = t + 256 * r, a = e / D8, b = e % D8;
+      lv[r] = lsrc[a < D && b < a ? a * (a - 1) / 2 + b : 0];
+      dv[r] = s.qd[kc * D + min(a, D - 1)];
+    }
+    mu = s.mu[kc * D + tc];
+    qd = s.qd[kc * D + tc];
+    al = s.al[kc];
+  }
+  DEX_DEV void load(const Src& p, const Src& tp, int D, int K, int k) {
+    const size_t kc = min(k, K - 1);
+    load_one(p, D, kc, lv, dv, mu, qd, al);
+    if constexpr (TAN) load_one(tp, D, kc, tlv, tdv, tmu, tqd, tal);
+  }
+  DEX_DEV void store(int D, int K, int k, const float* shift, float* rec, float* trec) {
+    __shared__ float qs[D8][D8 + 1], ds[TAN ? D8 : 1][D8 + 1];
+    __shared__ float mus[D8], dms[D8];
+    const int t = threadIdx.x, j = k & 3;
+    rec += (size_t)(k >> 2) * quad_floats(D8);
+    trec += (size_t)(k >> 2) * quad_floats(D8);
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < NL; ++r) {
+      const int e = t + 256 * r, a = e / D8, b = e % D8;
+      const bool in = k < K && a < D && b <= a;
+      const float ev = expf(dv[r]);
+      if (e < D8 * D8) {
+        qs[a][b] = !in ? 0.f : a == b ? ev : lv[r];
+        if constexpr (TAN) ds[a][b] = !in ? 0.f : a == b ? ev * tdv[r] : tlv[r];
+      }
+    }
+    const bool own = t < D8 && t < D && k < K;
+    if (t < D8) {
+      mus[t] = own ? mu - shift[t] : 0.f;
+      if constexpr (TAN) dms[t] = own ? tmu : 0.f;
+    }
+    // the log-determinant by a tree (it enters beta whole)
+    const float s = wave_sum(own ? qd : 0.f);
+    if (t == 0) rec[quad_neg(D8) + 4 * D8 + j] = k < K ? al + s : -INFINITY;
+    if constexpr (TAN) {
+      const float ts = wave_sum(own ? tqd : 0.f);
+      if (t == 0) trec[quad_neg(D8) + 4 * D8 + j] = k < K ? tal + ts : 0.f;
+    }
+    __syncthreads();
+    // the quad's operands of lanes 16 g + 4 j + i, rows 4 r + i, columns 4 ch + g
+    for (int e = t; e < quad_groups(D8) * 64; e += 256) {
+      const int m = e / 64 * 4 + e % 4, n = e / 4 % 16, g = n / 4, i = n % 4;
+      const int o = e / 64 * 256 + 4 * (16 * g + 4 * j + i) + m % 4;
+      int r = (int)((sqrtf(8.f * (float)m + 1.f) - 1.f) * 0.5f);  // (m < 36: exact after this)
+      if ((r + 1) * (r + 2) / 2 <= m) ++r;
+      if (r * (r + 1) / 2 > m) --r;
+      const int ch = m - r * (r + 1) / 2;
+      const bool in = m < quad_products(D8);
+      const int row = in ? 4 * r + i : 0, col = in ? 4 * ch + g : 0;
+      rec[o] = in ? qs[row][col] : 0.f;
+      if constexpr (TAN) trec[o] = in ? ds[row][col] : 0.f;
+    }
+    if (t < D8) {
+      float c = 0.f, tc = 0.f;
+      for (int b = 0; b <= t; ++b) {
+        c = fmaf(qs[t][b], mus[b], c);
+        if constexpr (TAN) tc = fmaf(ds[t][b], mus[b], fmaf(qs[t][b], dms[b], tc));
+      }
+      rec[quad_neg(D8) + j * D8 + t] = -c;
+      if constexpr (TAN) trec[quad_neg(D8) + j * D8 + t] = -tc;
+    }
+  }
+};
+
+// One block: 64 CB points from the tile's first, quads qa .. qb - 1; wave v takes 16 CB
+// points. beta has rows for whole quads (the last may hold values nobody reads, as do
+// points N <= p < Npad). Lane 16 g + c holds points CB c .. CB c + CB - 1
 // of the wave's and, quad by quad, component 4q + g. A maximum starts at the lowest
 // finite number, so that -inf log-weights (a component with alpha = -inf) leave the
 // sums as they are. The records go through LDS, QB quads at a time (the four waves
@@ -93,7 +147,7 @@ constexpr int kQuadLds = 5016;  // floats: the largest 2 quad_batch() quad_float
 
 template <int D8, int CB>
 DEX_DEV void fwd_quads(const float* __restrict__ x, const float* __restrict__ shift, int N, int D,
-                       int Npad, int tile0, const float* __restrict__ rec, int K,
+                       int Npad, int tile0, const float* __restrict__ rec, int qa, int qb,
                        float* __restrict__ beta, float2* __restrict__ ml, float* lds) {
   constexpr int R = D8 / 4, NG = quad_groups(D8), QB = quad_batch<D8>(), RS = quad_floats(D8);
   constexpr int NL = (QB * RS / 4 + 255) / 256;  // 16-byte loads per thread and batch
@@ -104,10 +158,9 @@ DEX_DEV void fwd_quads(const float* __restrict__ x, const float* __restrict__ sh
   asm volatile("" : "+v"(t));
   const int lane = t & 63, g = lane >> 4, c = lane & 15;
   const int p0 = tile0 + (t >> 6) * 16 * CB;
-  const int nq = (K + 3) / 4;
   f32x4 sv[NL];
   auto fetch = [&](int q) {
-    const int last = min(QB, nq - q) * (RS / 4) - 1;
+    const int last = min(QB, qb - q) * (RS / 4) - 1;
     const f32x4* src = reinterpret_cast<const f32x4*>(rec + (size_t)q * RS);
 #pragma unroll
     for (int i = 0; i < NL; ++i) sv[i] = src[min(t + 256 * i, last)];
@@ -117,7 +170,7 @@ DEX_DEV void fwd_quads(const float* __restrict__ x, const float* __restrict__ sh
     for (int i = 0; i < NL; ++i)
       if (t + 256 * i < QB * RS / 4) reinterpret_cast<f32x4*>(b)[t + 256 * i] = sv[i];
   };
-  fetch(0);
+  fetch(qa);
   float xb[CB][R];
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb) {
@@ -190,14 +243,14 @@ DEX_DEV void fwd_quads(const float* __restrict__ x, const float* __restrict__ sh
   };
   __syncthreads();  // (the item before has left the LDS)
   stage(lds);
-  if (QB < nq) fetch(QB);
-  for (int q0 = 0, buf = 0; q0 < nq; q0 += QB, buf ^= 1) {
+  if (qa + QB < qb) fetch(qa + QB);
+  for (int q0 = qa, buf = 0; q0 < qb; q0 += QB, buf ^= 1) {
     __syncthreads();
-    if (q0 + QB < nq) {
+    if (q0 + QB < qb) {
       stage(lds + (buf ^ 1) * QB * RS);
-      if (q0 + 2 * QB < nq) fetch(q0 + 2 * QB);
+      if (q0 + 2 * QB < qb) fetch(q0 + 2 * QB);
     }
-    for (int j = 0; j < QB && q0 + j < nq; ++j) compute(q0 + j, lds + (buf * QB + j) * RS);
+    for (int j = 0; j < QB && q0 + j < qb; ++j) compute(q0 + j, lds + (buf * QB + j) * RS);
   }
   // the four lane groups' sums of a point
 #pragma unroll
@@ -209,6 +262,132 @@ DEX_DEV void fwd_quads(const float* __restrict__ x, const float* __restrict__ sh
     v += xor_lane(v, 32);
     if (g == 0) ml[p0 + CB * c + cb] = make_float2(mx, v);
   }
+}
+
+// ---------------------------------------------------------------------------
+// Forward mode: y and ty = dQ (x - shift) - (dQ (mu - shift) + Q dmu) of four components
+// at a time, each row group's products in turn; the derivative of a log-density is
+// dkappa - y . ty.
+template <int D8>
+__host__ __device__ constexpr int quad_tan_batch() { return D8 == 8 ? 4 : D8 == 16 ? 2 : 1; }
+constexpr int kQuadTanLds = 9744;  // floats: the largest 4 quad_tan_batch() quad_floats()
+
+// One block: as fwd_quads; the lane's FP64 sum of exp(beta - f) dbeta over its points
+// and components.
+template <int D8, int CB>
+DEX_DEV double jvp_quads(const float* __restrict__ x, const float* __restrict__ shift, int N, int D,
+                         int tile0, const float* __restrict__ rec, const float* __restrict__ trec,
+                         int qa, int qb, const float* __restrict__ f, float* lds) {
+  constexpr int R = D8 / 4, NG = quad_groups(D8), QB = quad_tan_batch<D8>(), RS = quad_floats(D8);
+  constexpr int NL = (QB * RS / 4 + 255) / 256;
+  static_assert(4 * QB * RS <= kQuadTanLds && RS % 4 == 0, "LDS");
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));  // (as in fwd_quads)
+  const int lane = t & 63, g = lane >> 4, c = lane & 15;
+  const int p0 = tile0 + (t >> 6) * 16 * CB;
+  f32x4 sv[2][NL];
+  auto fetch = [&](int q) {
+    const int last = min(QB, qb - q) * (RS / 4) - 1;
+    const f32x4* a = reinterpret_cast<const f32x4*>(rec + (size_t)q * RS);
+    const f32x4* b = reinterpret_cast<const f32x4*>(trec + (size_t)q * RS);
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      sv[0][i] = a[min(t + 256 * i, last)];
+      sv[1][i] = b[min(t + 256 * i, last)];
+    }
+  };
+  auto stage = [&](float* b) {
+#pragma unroll
+    for (int i = 0; i < NL; ++i)
+      if (t + 256 * i < QB * RS / 4) {
+        reinterpret_cast<f32x4*>(b)[t + 256 * i] = sv[0][i];
+        reinterpret_cast<f32x4*>(b + QB * RS)[t + 256 * i] = sv[1][i];
+      }
+  };
+  fetch(qa);
+  float xb[CB][R], fp[CB];
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb) {
+    const int p = p0 + CB * c + cb;
+    fp[cb] = f[min(p, N - 1)];
+#pragma unroll
+    for (int ch = 0; ch < R; ++ch) xb[cb][ch] = x[(size_t)min(p, N - 1) * D + min(4 * ch + g, D - 1)];
+  }
+#pragma unroll
+  for (int ch = 0; ch < R; ++ch) {
+    const float sh = shift[4 * ch + g];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+      xb[cb][ch] = p0 + CB * c + cb < N && 4 * ch + g < D ? xb[cb][ch] - sh : 0.f;
+  }
+  double sum = 0.0;
+  auto compute = [&](const float* o, const float* to) {
+    const f32x4 *oq = reinterpret_cast<const f32x4*>(o) + lane,
+                *tq = reinterpret_cast<const f32x4*>(to) + lane;
+    const int no = quad_neg(D8) + g * D8;
+    float s[CB], sd[CB];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) s[cb] = sd[cb] = 0.f;
+    f32x4 qv[2], tv[2], nv[2], ntv[2], acc[2][CB], tacc[2][CB];
+    qv[0] = oq[0];
+    tv[0] = tq[0];
+    nv[0] = *reinterpret_cast<const f32x4*>(o + no);
+    ntv[0] = *reinterpret_cast<const f32x4*>(to + no);
+    const float kap = o[quad_neg(D8) + 4 * D8 + g], dkap = to[quad_neg(D8) + 4 * D8 + g];
+    auto squares = [&](int r) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+          s[cb] = fmaf(acc[r & 1][cb][i], acc[r & 1][cb][i], s[cb]);
+          sd[cb] = fmaf(acc[r & 1][cb][i], tacc[r & 1][cb][i], sd[cb]);
+        }
+    };
+    int n = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (r + 1 < R) {
+        nv[(r + 1) & 1] = *reinterpret_cast<const f32x4*>(o + no + 4 * (r + 1));
+        ntv[(r + 1) & 1] = *reinterpret_cast<const f32x4*>(to + no + 4 * (r + 1));
+      }
+#pragma unroll
+      for (int ch = 0; ch <= r; ++ch, ++n) {
+        if (n % 4 == 0 && n / 4 + 1 < NG) {
+          qv[(n / 4 + 1) & 1] = oq[(n / 4 + 1) * 64];
+          tv[(n / 4 + 1) & 1] = tq[(n / 4 + 1) * 64];
+          __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+          acc[r & 1][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+              qv[(n / 4) & 1][n % 4], xb[cb][ch], ch == 0 ? nv[r & 1] : acc[r & 1][cb], 0, 0, 0);
+          tacc[r & 1][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+              tv[(n / 4) & 1][n % 4], xb[cb][ch], ch == 0 ? ntv[r & 1] : tacc[r & 1][cb], 0, 0, 0);
+        }
+        if (ch == 0 && r > 0) squares(r - 1);
+        if (n % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    squares(R - 1);
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+      const float v = expf(kap - 0.5f * s[cb] - fp[cb]) * (dkap - sd[cb]);
+      if (p0 + CB * c + cb < N) sum += (double)v;
+    }
+  };
+  __syncthreads();  // (the tile before has left the LDS)
+  stage(lds);
+  if (qa + QB < qb) fetch(qa + QB);
+  for (int q0 = qa, buf = 0; q0 < qb; q0 += QB, buf ^= 1) {
+    __syncthreads();
+    float* cur = lds + buf * 2 * QB * RS;
+    if (q0 + QB < qb) {
+      stage(lds + (buf ^ 1) * 2 * QB * RS);
+      if (q0 + 2 * QB < qb) fetch(q0 + 2 * QB);
+    }
+    for (int j = 0; j < QB && q0 + j < qb; ++j) compute(cur + j * RS, cur + (QB + j) * RS);
+  }
+  return sum;
 }
 
 // ---------------------------------------------------------------------------

@@ -307,6 +307,35 @@ def test_forward_mode_matrix_core_edges(dev, N, D, K):
     assert abs(got - want) <= 1e-5 * abs(want), (got, want)
 
 
+# FP32, D <= 32, four components at a time: every padded dimension filled and not, quads
+# full, just over and single, one point and tiles of 64 and 128 just under and over,
+# components shared among blocks and not; data at the origin and far from it.
+@pytest.mark.parametrize("offset", [0.0, 100.0])
+@pytest.mark.parametrize("N,D,K", [(1, 1, 1), (63, 8, 4), (64, 9, 5), (65, 16, 3), (127, 17, 8),
+                                   (129, 24, 9), (257, 25, 33), (2049, 32, 17), (40_000, 7, 130)])
+def test_quads_of_components(dev, N, D, K, offset):
+    from paper_2104_05372_amd import dex
+    g = workloads.gmm_inputs(N, D, K, 90 + D)
+    g = workloads.GMMInputs(g.alphas, g.means + offset, g.qd, g.l, g.x + offset).astype(np.float32)
+    check(run_gmm(g, dex.DEX_F32, dex.DEX_GMM_PLAIN), oracle_gmm(g), 1e-5)
+    tangent = along_gradient(g, 5 * D + K)
+    got, _ = run_gmm_jvp(g, dex.DEX_F32, dex.DEX_GMM_PLAIN, tangent)
+    want = ogmm.jvp(*g.params(), g.x, tangent)
+    assert abs(got - want) <= 1e-5 * abs(want), (got, want)
+
+
+@pytest.mark.parametrize("dead", [0, 1, 6])
+def test_component_of_no_weight(dev, dead):
+    """alpha = -inf takes a component out, wherever it stands in its quad."""
+    from paper_2104_05372_amd import dex
+    g = workloads.gmm_inputs(300, 12, 7, 95, np.float32)
+    keep = [k for k in range(7) if k != dead]
+    want = ogmm.objective(g.alphas[keep], g.means[keep], g.qd[keep], g.l[keep], g.x)
+    g.alphas[dead] = -np.inf
+    F, f, _ = run_gmm(g, dex.DEX_F32, dex.DEX_GMM_PLAIN)
+    assert abs(F - want[0]) <= 1e-5 * abs(want[0]) and rel(f, want[1]) <= 1e-5
+
+
 @pytest.mark.parametrize("D,variant,tol", [(64, 1, TOL_MIXED16), (64, 0, 1e-5), (12, 1, TOL_MIXED16)])
 def test_forward_mode_far_from_origin(dev, D, variant, tol):
     from paper_2104_05372_amd import dex
