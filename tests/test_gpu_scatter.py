@@ -212,6 +212,26 @@ def test_histogram_single_hot_bin_drains(dev):
     assert h.sum() == keys.size
 
 
+@pytest.mark.parametrize("bins", [1, 2, 3, 1001, 65535, 65536])
+def test_histogram_full_rounds(dev, bins):
+    """Enough keys for whole rounds in every block, most of them on the two bins of one
+    counter word (both are emptied several times a block) and on its neighbours, and a
+    few out of range."""
+    from paper_2104_05372_amd import dex
+    rng = np.random.default_rng(bins)
+    n, half = (1 << 23) + 5, (bins + 1) // 2
+    hot = np.array([0, half, 1, bins - 1])[rng.integers(0, 4, n)] % bins
+    keys = np.where(rng.random(n) < 0.8, hot, rng.integers(0, bins, n)).astype(np.int32)
+    keys[::100_003] = bins
+    keys[1::100_003] = -1
+    h = torch.zeros(bins, dtype=torch.int32, device=dev)
+    oob = torch.zeros(1, dtype=torch.int64, device=dev)
+    dex.dex_accum_scatter(h, torch.tensor(keys, device=dev), flags=dex.DEX_CHECK_BOUNDS, oob=oob)
+    ok = (keys >= 0) & (keys < bins)
+    assert oob.item() == np.count_nonzero(~ok)
+    assert np.array_equal(h.cpu().numpy(), np.bincount(keys[ok], minlength=bins))
+
+
 def test_histogram_out_of_range_keys(dev):
     from paper_2104_05372_amd import dex
     keys = np.array([1, 2, 70_000, 2, 65_535, 65_536], np.uint32)
