@@ -80,7 +80,7 @@ struct QuadPrep {
   }
   DEX_DEV void store(int D, int K, int k, const float* shift, float* rec, float* trec) {
     __shared__ float qs[D8][D8 + 1], ds[TAN ? D8 : 1][D8 + 1];
-    __shared__ float mus[D8], dms[D8];
+    __shared__ double mus[D8], dms[D8];
     const int t = threadIdx.x, j = k & 3;
     rec += (size_t)(k >> 2) * quad_floats(D8);
     trec += (size_t)(k >> 2) * quad_floats(D8);
@@ -97,15 +97,16 @@ struct QuadPrep {
     }
     const bool own = t < D8 && t < D && k < K;
     if (t < D8) {
-      mus[t] = own ? mu - shift[t] : 0.f;
-      if constexpr (TAN) dms[t] = own ? tmu : 0.f;
+      mus[t] = own ? (double)mu - (double)shift[t] : 0.0;
+      if constexpr (TAN) dms[t] = own ? (double)tmu : 0.0;
     }
-    // the log-determinant by a tree (it enters beta whole)
-    const float s = wave_sum(own ? qd : 0.f);
-    if (t == 0) rec[quad_neg(D8) + 4 * D8 + j] = k < K ? al + s : -INFINITY;
+    // What every point of the component shares is summed in FP64 and rounded once: its
+    // error would not average out over the points.
+    const double s = wave_sum(own ? (double)qd : 0.0);
+    if (t == 0) rec[quad_neg(D8) + 4 * D8 + j] = k < K ? (float)((double)al + s) : -INFINITY;
     if constexpr (TAN) {
-      const float ts = wave_sum(own ? tqd : 0.f);
-      if (t == 0) trec[quad_neg(D8) + 4 * D8 + j] = k < K ? tal + ts : 0.f;
+      const double ts = wave_sum(own ? (double)tqd : 0.0);
+      if (t == 0) trec[quad_neg(D8) + 4 * D8 + j] = k < K ? (float)((double)tal + ts) : 0.f;
     }
     __syncthreads();
     // the quad's operands of lanes 16 g + 4 j + i, rows 4 r + i, columns 4 ch + g
@@ -122,13 +123,14 @@ struct QuadPrep {
       if constexpr (TAN) trec[o] = in ? ds[row][col] : 0.f;
     }
     if (t < D8) {
-      float c = 0.f, tc = 0.f;
+      double c = 0.0, tc = 0.0;
       for (int b = 0; b <= t; ++b) {
-        c = fmaf(qs[t][b], mus[b], c);
-        if constexpr (TAN) tc = fmaf(ds[t][b], mus[b], fmaf(qs[t][b], dms[b], tc));
+        c = fma((double)qs[t][b], mus[b], c);
+        if constexpr (TAN)
+          tc = fma((double)ds[t][b], mus[b], fma((double)qs[t][b], dms[b], tc));
       }
-      rec[quad_neg(D8) + j * D8 + t] = -c;
-      if constexpr (TAN) trec[quad_neg(D8) + j * D8 + t] = -tc;
+      rec[quad_neg(D8) + j * D8 + t] = (float)-c;
+      if constexpr (TAN) trec[quad_neg(D8) + j * D8 + t] = (float)-tc;
     }
   }
 };
