@@ -471,7 +471,10 @@ def row_stencil(torch, dex, workloads, dev, steps):
     gen = torch.Generator(device=dev).manual_seed(c["seed"])
     u0 = torch.randn(H, W, device=dev, generator=gen)
     tg = torch.randn(H, W, device=dev, generator=gen)
-    out = {"workload": f"{H}x{W} f32 periodic 5-point diffusion, {T} steps, checkpoint every {every}"}
+    out = {"workload": f"{H}x{W} f32 periodic 5-point diffusion, {T} steps, checkpoint every {every}",
+           "rates": "bytes of one step at a time (the fields read and written each step); the "
+                    "default kernels take up to 8 steps per pass over memory, so their rates "
+                    "can exceed the HBM's"}
     for name, variant, fc, vc in (("recompute", dex.DEX_STENCIL_RECOMPUTE, 0, 0),
                                   ("linear", dex.DEX_STENCIL_LINEAR, 0, 0),
                                   ("recompute_vector_kernels", dex.DEX_STENCIL_RECOMPUTE, 2, 3)):
