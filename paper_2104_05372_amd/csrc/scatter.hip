@@ -10,7 +10,7 @@
 // Work stays O(n * row_len) and every update is applied once; rows that never
 // appear are not touched.
 //
-// Histogram: one block per compute unit keeps a private histogram of 16-bit
+// Histogram: one block per compute unit (fewer for few keys) keeps a private histogram of 16-bit
 // counters packed two per LDS word. A counter that has reached 2^14 is emptied into
 // the table by whoever sees it (an LDS AND that returns what it held, one global
 // atomic of that), so a counter never overflows however skewed the keys are. At
@@ -268,6 +268,7 @@ __global__ void __launch_bounds__(1024) hist_private_kernel(int32_t* __restrict_
 // loads issued together) and adds the two bins' totals with integer atomics:
 // integer addition is exact, so the result does not depend on their order.
 constexpr int kHistGroup = 32;
+constexpr int64_t kHistRound = 16 * 1024;  // keys of a block's round
 __global__ void __launch_bounds__(256) hist_reduce_kernel(int32_t* __restrict__ acc, int n_bins,
                                                           const uint32_t* __restrict__ partial,
                                                           int nblocks) {
@@ -1056,7 +1057,11 @@ static dex_status scatter_typed(void* acc, int32_t acc_dtype, int64_t n_rows, in
                                 const IdxT* idx, const void* vals, const float* scale, int64_t n,
                                 int64_t* oob, void* ws, size_t ws_bytes, hipStream_t s) {
   if (acc_dtype == DEX_I32 && R == 1 && !vals && n_rows <= 65536) {
-    const int nb = hist_blocks();
+    // A block has a round's keys at least, and as many as it has counters, which it
+    // clears, writes and has added up: 65536 bins, 1000 keys 8.3 us (a block per CU:
+    // 27), 2^20 12 (27; 16384 keys a block 12.8), 5 2^20 17 (27; 27).
+    const int64_t least = std::max<int64_t>(kHistRound, n_rows);
+    const int nb = (int)std::max<int64_t>(1, std::min<int64_t>(hist_blocks(), (n + least - 1) / least));
     const size_t need = scatter_ws_bytes(acc_dtype, n_rows, R, n, false, false);
     if (!ws || ws_bytes < need)
       return fail(DEX_ERR_WORKSPACE, "histogram needs %zu workspace bytes, got %zu", need, ws_bytes);

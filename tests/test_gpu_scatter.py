@@ -202,6 +202,16 @@ def test_histogram_bit_exact(dev, n, bins, seed):
     assert np.array_equal(h1, want) and np.array_equal(h2, want)
 
 
+@pytest.mark.parametrize("n,bins", [(1, 65536), (16_384, 10), (16_385, 10), (65_536, 65536),
+                                    (65_537, 65536), (3 * 65_535 + 3, 65535)])
+def test_histogram_few_blocks(dev, n, bins):
+    """Both sides of where a second (third, fourth) block takes part."""
+    from paper_2104_05372_amd import autograd
+    keys = np.random.default_rng(n).integers(0, bins, n).astype(np.int32)
+    h = autograd.histogram(torch.tensor(keys, device=dev), bins).cpu().numpy()
+    assert np.array_equal(h, np.bincount(keys, minlength=bins))
+
+
 def test_histogram_single_hot_bin_drains(dev):
     """All keys equal: the LDS counter crosses the drain threshold many times."""
     from paper_2104_05372_amd import autograd
