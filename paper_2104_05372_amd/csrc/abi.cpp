@@ -147,7 +147,9 @@ static int pick_config(const dex_desc& d, int role) {
     auto it = g_tuned.find(tune_key(d, role));
     if (it != g_tuned.end()) return it->second;
   }
-  return d.kind == DEX_GMM ? gmm_default_config(d, role) : 0;
+  return d.kind == DEX_GMM           ? gmm_default_config(d, role)
+         : d.kind == DEX_GMM_BATCHED ? gmm_batched_default_config(d, role)
+                                     : 0;
 }
 
 static size_t dtype_size(int32_t dt) {

@@ -41,14 +41,15 @@ struct BItem {
 
 constexpr int kBFwdCfgs = 2;
 constexpr int kBBwdCfgs = 4;
-// Points per reverse work item (a block, 16 components). Configuration 0: 4096,
-// halved down to 512 while the batch has fewer than kBItems items (a small batch
-// then still fills the chip); the work list says what was chosen.
+// Points per reverse work item (a block, 16 components). Configuration 0: 4096, halved
+// down to 512 while the batch has fewer than kBItems items, so that a small batch still
+// fills the chip (64 mixtures of 10000 points, chunks of 512, 1024, 2048, 8192: 238,
+// 222, 253, 690 us; 12 of 2000: 73, 116, 193, 230). The plan says what was chosen.
 inline int64_t bbwd_chunk(int i) {
   const int64_t t[kBBwdCfgs] = {4096, 1024, 2048, 8192};
   return t[i];
 }
-constexpr int64_t kBItems = 4096;
+constexpr int64_t kBItems = 2048;
 __host__ __device__ inline int bfwd_cb(int i) { return i == 0 ? 4 : 2; }
 
 struct PlanHeader {
@@ -586,6 +587,13 @@ size_t gmm_batched_ws_bytes(const dex_desc& d, int role) {
 int gmm_batched_num_configs(const dex_desc& d, int role) {
   (void)d;
   return role == DEX_WS_VJP ? kBBwdCfgs : kBFwdCfgs;
+}
+
+// FP32 forward of an untuned call: 128 points a block below 2^21 points in all (12
+// mixtures of 2000: 75 us, 256 points 99; 64 of 10000: 196, 204; 512 of 25000: 3.53 ms,
+// 3.44).
+int gmm_batched_default_config(const dex_desc& d, int role) {
+  return role != DEX_WS_VJP && d.variant == DEX_GMM_PLAIN && d.dims[1] < (int64_t(1) << 21) ? 1 : 0;
 }
 
 // Blocks of the persistent launches: as many as a CU holds.
