@@ -57,7 +57,10 @@ DEX_DEV double lane_value(double v, int lane) {
               __builtin_amdgcn_readlane(__double2hiint(v), lane));
 }
 
-// One update of a running log-sum-exp (m, s).
+// One update of a running log-sum-exp (m, s). m starts at the lowest finite number, not
+// at -inf: a wave's first component may have beta = -inf (alpha = -inf), and -inf - -inf
+// would make its sum NaN.
+constexpr double kLowest = -1.7976931348623157e308;
 DEX_DEV void lse_add(double& m, double& s, double b) {
   const double d = b - m;
   const double e = exp(-fabs(d));
@@ -96,7 +99,7 @@ __global__ void __launch_bounds__(64 * f64_fwd_waves(DP)) k_f64_fwd(
     az = wave_sum(az);
     if (lane == 0) lse_alpha = am + log(az);
   }
-  double m = -INFINITY, s = 0;
+  double m = kLowest, s = 0;
   if (p0 < N) {
     if constexpr (DP == 4) {
       double xr[4];

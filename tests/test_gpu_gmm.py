@@ -336,6 +336,25 @@ def test_component_of_no_weight(dev, dead):
     assert abs(F - want[0]) <= 1e-5 * abs(want[0]) and rel(f, want[1]) <= 1e-5
 
 
+# FP64: one wave a tile (N = 1024 at D <= 4, 256 above), fewer waves than components and
+# as many; the dead component first, second, last and first of a wave's share.
+@pytest.mark.parametrize("N,D,K", [(1024, 3, 5), (256, 16, 4), (5000, 2, 40), (3000, 16, 25),
+                                   (60, 2, 5), (60, 20, 3), (700, 40, 6)])
+def test_component_of_no_weight_fp64(dev, N, D, K):
+    """alpha = -inf: the objective, f and every gradient are those of the other
+    components, and the dead component's gradient is zero."""
+    from paper_2104_05372_amd import dex
+    for dead in sorted({0, 1, 3 % K, K - 1}):
+        g = workloads.gmm_inputs(N, D, K, 96 + D)
+        keep = [k for k in range(K) if k != dead]
+        want = oracle_gmm(workloads.GMMInputs(g.alphas[keep], g.means[keep], g.qd[keep], g.l[keep], g.x))
+        g.alphas[dead] = -np.inf
+        F, f, grads = run_gmm(g, dex.DEX_F64, dex.DEX_GMM_PLAIN)
+        for a in grads:
+            assert not np.any(a[dead])
+        check((F, f, [a[keep] for a in grads]), want, 1e-10, f"dead {dead} of {K}")
+
+
 @pytest.mark.parametrize("D,variant,tol", [(64, 1, TOL_MIXED16), (64, 0, 1e-5), (12, 1, TOL_MIXED16)])
 def test_forward_mode_far_from_origin(dev, D, variant, tol):
     from paper_2104_05372_amd import dex
