@@ -349,6 +349,7 @@ __global__ void __launch_bounds__(256) gather_scale_kernel(const float* __restri
       v[u] = live[u] ? (int64_t)idx[j] : 0;
       s[u] = live[u] ? w[j] : 0.f;
       ok[u] = live[u] && v[u] >= 0 && v[u] < V;
+      if (!ok[u]) s[u] = 0.f;  // (a zero row whatever its weight)
       if (live[u] && !ok[u] && hl == 0) ++bad;
     }
     for (int c = VW * hl; c < R; c += step) {

@@ -352,6 +352,24 @@ def test_gather_forward_mode_out_of_range_rows(dev):
     assert np.array_equal(got, osc.gather_jvp(T, idx, w, tT, tw).astype(np.float32))
 
 
+@pytest.mark.parametrize("R", [1, 3, 4, 6, 50, 128])
+def test_out_of_range_rows_are_zero_whatever_their_weight(dev, R):
+    """A row of zeros for an index outside the table, also where its weight is an
+    infinity or NaN (every width of the gather's vectors)."""
+    from paper_2104_05372_amd import dex
+    rng = np.random.default_rng(R)
+    T = rng.standard_normal((9, R)).astype(np.float32)
+    idx = np.array([-1, 3, 9, 8, 1 << 30, 0, -5], dtype=np.int32)
+    w = np.array([np.inf, 2, np.nan, -1, -np.inf, 0.5, 1], dtype=np.float32)
+    out = torch.full((7, R), 7.0, device=dev)
+    dex.dex_fwd(dex.gather_desc(9, R, 7),
+                [torch.tensor(a, device=dev) for a in (T, idx, w)], [out], [])
+    ok = (idx >= 0) & (idx < 9)
+    want = np.zeros((7, R), np.float32)
+    want[ok] = osc.gather(T, idx[ok], w[ok])
+    assert np.array_equal(out.cpu().numpy(), want)
+
+
 def test_full_size_gather_forward_mode_sampled(dev):
     """The benchmarked 1e6 x 128 table with 2^22 Zipf(1.1) indices; sampled rows."""
     c = workloads.SCATTER
