@@ -191,16 +191,15 @@ __global__ void __launch_bounds__(1024) hist_private_kernel(int32_t* __restrict_
   auto add = [&](uint32_t k) {
     return atomicAdd(&cnt[word(k)], k >= nwords ? 0x10000u : 1u);
   };
+  // What is there by now goes to the table whether it is still full or not: put back, it
+  // would come on top of what others have added since, and no schedule bounds the sum.
   auto drain = [&](uint32_t k, uint32_t old) {
     const uint32_t m = k >= nwords ? 0xFFFF0000u : 0xFFFFu;
     uint32_t* c = &cnt[word(k)];
     // (most of those that saw it full come after the one that emptied it)
     if (!(old & kFull & m) || !(*(volatile uint32_t*)c & kFull & m)) return;
     const uint32_t o = atomicAnd(c, ~m) & m;
-    if (o & kFull)
-      atomicAdd(&acc[k], (int32_t)(k >= nwords ? o >> 16 : o));
-    else if (o)
-      atomicAdd(c, o);
+    if (o) atomicAdd(&acc[k], (int32_t)(k >= nwords ? o >> 16 : o));
   };
   auto bump = [&](int64_t kv) {
     if (kv < 0 || kv >= n_bins)
