@@ -12,11 +12,11 @@
 //
 // Histogram: one block per compute unit (fewer for few keys) keeps a private histogram of 16-bit
 // counters packed two per LDS word. A counter that has reached 2^14 is emptied into
-// the table by whoever sees it (an LDS AND that returns what it held, one global
-// atomic of that), so a counter never overflows however skewed the keys are. At
-// the end each block writes its counters to the workspace and a second kernel
-// adds them per bin. Integer addition is exact, so the result is identical
-// under any schedule.
+// the table by the first that sees it (an LDS AND that returns what it held, one global
+// atomic of that), at 1.5 2^14 by everyone who does, so a counter never overflows
+// however skewed the keys are. At the end each block writes its counters to the
+// workspace and a second kernel adds them per bin. Integer addition is exact, so the
+// result is identical under any schedule.
 #include <algorithm>
 #include <type_traits>
 #include <utility>
@@ -27,7 +27,10 @@
 namespace dexk {
 
 constexpr int kChunk = 2048;          // indices per block for the row scatter
-constexpr uint32_t kFull = 0xC000C000u;  // histogram: a counter of the word has reached 2^14
+// Histogram: a counter is full at kDrain (kFull: one of the word's is); at most 2^14
+// additions after kLate it is empty again, so it stays below 2^16 under any schedule.
+constexpr uint32_t kDrain = 1u << 14, kLate = kDrain + kDrain / 2;
+constexpr uint32_t kFull = 0xC000C000u;
 
 __global__ void fill_zero_kernel(uint32_t* p, size_t nwords) {
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -191,70 +194,97 @@ __global__ void __launch_bounds__(1024) hist_private_kernel(int32_t* __restrict_
   auto add = [&](uint32_t k) {
     return atomicAdd(&cnt[word(k)], k >= nwords ? 0x10000u : 1u);
   };
-  // What is there by now goes to the table whether it is still full or not: put back, it
-  // would come on top of what others have added since, and no schedule bounds the sum.
-  auto drain = [&](uint32_t k, uint32_t old) {
-    const uint32_t m = k >= nwords ? 0xFFFF0000u : 0xFFFFu;
+  // After an addition that found `old`: the first to find the counter full empties it into
+  // the table (`window`: how far one addition may have carried it), and, should that one be
+  // late, everyone who finds it past kLate does. What is there by then goes to the table,
+  // full or not (put back, it would come on top of what others have added since, and no
+  // schedule bounds the sum).
+  auto drain = [&](uint32_t k, uint32_t old, uint32_t window) {
+    const bool up = k >= nwords;
+    const uint32_t h = up ? old >> 16 : old & 0xFFFFu, m = up ? 0xFFFF0000u : 0xFFFFu;
     uint32_t* c = &cnt[word(k)];
-    // (most of those that saw it full come after the one that emptied it)
-    if (!(old & kFull & m) || !(*(volatile uint32_t*)c & kFull & m)) return;
+    if (h - kDrain >= window && (h < kLate || !(*(volatile uint32_t*)c & kFull & m))) return;
     const uint32_t o = atomicAnd(c, ~m) & m;
-    if (o) atomicAdd(&acc[k], (int32_t)(k >= nwords ? o >> 16 : o));
+    if (o) atomicAdd(&acc[k], (int32_t)(up ? o >> 16 : o));
   };
-  auto bump = [&](int64_t kv) {
-    if (kv < 0 || kv >= n_bins)
-      ++bad;
-    else
-      drain((uint32_t)kv, add((uint32_t)kv));
+  // Counts keys outside the table (negative ones are large here) ...
+  auto add_inside = [&](uint32_t k) -> uint32_t {
+    const bool ok = k < (uint32_t)n_bins;
+    bad += !ok;
+    return ok ? add(k) : 0u;
   };
-  if constexpr (sizeof(IdxT) == 4) {
-    // vectorised body on the aligned middle part: rounds of 16 keys per thread, the
-    // next round's loads issued before this round's LDS additions
-    int64_t a0 = (b0 + 3) & ~int64_t(3);
-    int64_t a1 = b1 & ~int64_t(3);
-    if (a1 < a0) a1 = a0;
-    for (int64_t j = b0 + threadIdx.x; j < min(a0, b1); j += blockDim.x) bump(load_index(keys, j));
-    const u32x4* k4 = reinterpret_cast<const u32x4*>(keys);
-    const int64_t step = (int64_t)blockDim.x;
-    const int64_t rounds = (a1 - a0) / (16 * step);
-    u32x4 vn[4];
-    auto load4 = [&](int64_t r) {
-      const u32x4* src = k4 + a0 / 4 + r * 4 * step + threadIdx.x;
+  // ... and the lanes that hold the first lane's key add once for all of them (one after
+  // the other they queue on the counter's word: 2^25 times one key 118 us, 38 this way).
+  const int lane = threadIdx.x & 63;
+  auto add_crowd = [&](uint32_t k) -> uint32_t {
+    const bool ok = k < (uint32_t)n_bins;
+    bad += !ok;
+    const uint32_t first = __builtin_amdgcn_readfirstlane(k);
+    const uint64_t same = __ballot(ok && k == first);
+    const bool one = k != first || lane == __ffsll((long long)same) - 1;
+    const uint32_t c = k != first ? 1u : (uint32_t)__popcll(same);
+    return ok && one ? atomicAdd(&cnt[word(k)], k >= nwords ? c << 16 : c) : 0u;
+  };
+  auto crowded = [&](uint32_t k) {  // a quarter of the wave's keys alike (few bins, skew)
+    return __popcll(__ballot(k == (uint32_t)__builtin_amdgcn_readfirstlane(k))) >= 16;
+  };
+  auto bump = [&](uint32_t k) {
+    const bool crowd = crowded(k);
+    const uint32_t old = crowd ? add_crowd(k) : add_inside(k);
+    if (old & kFull) drain(k, old, crowd ? 64 : 1);
+  };
+  static_assert(sizeof(IdxT) == 4, "keys are read as 32-bit words");
+  // vectorised body on the aligned middle part: rounds of 16 keys per thread, the
+  // next round's loads issued before this round's LDS additions
+  int64_t a0 = (b0 + 3) & ~int64_t(3);
+  int64_t a1 = b1 & ~int64_t(3);
+  if (a1 < a0) a1 = a0;
+  for (int64_t j = b0 + threadIdx.x; j < min(a0, b1); j += blockDim.x) bump((uint32_t)keys[j]);
+  const u32x4* k4 = reinterpret_cast<const u32x4*>(keys);
+  const int64_t step = (int64_t)blockDim.x;
+  const int64_t rounds = (a1 - a0) / (16 * step);
+  u32x4 vn[4];
+  auto load4 = [&](int64_t r) {
+    const u32x4* src = k4 + a0 / 4 + r * 4 * step + threadIdx.x;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) vn[i] = __builtin_nontemporal_load(src + i * step);
-    };
-    if (rounds > 0) load4(0);
-    for (int64_t r = 0; r < rounds; ++r) {
-      uint32_t k[16], mx = 0u;
+    for (int i = 0; i < 4; ++i) vn[i] = __builtin_nontemporal_load(src + i * step);
+  };
+  if (rounds > 0) load4(0);
+  for (int64_t r = 0; r < rounds; ++r) {
+    uint32_t k[16], mx = 0u;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        k[i] = vn[i / 4][i % 4];
-        mx = max(mx, k[i]);
-      }
-      if (r + 1 < rounds) load4(r + 1);
-      // (negative keys are large here)
-      if (mx < (uint32_t)n_bins) {
-        // the 16 additions back to back, one test of all that they return: a counter
-        // takes at most 16 more per thread (2^14 in all) before it is emptied
-        uint32_t old[16], any = 0u;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) old[i] = add(k[i]);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) any |= old[i];
-        if (any & kFull) {
-#pragma unroll
-          for (int i = 0; i < 16; ++i) drain(k[i], old[i]);
-        }
-      } else {
-#pragma unroll 1
-        for (int i = 0; i < 16; ++i)
-          bump(load_index(keys, a0 + 4 * (r * 4 * step + i / 4 * step + threadIdx.x) + i % 4));
-      }
+    for (int i = 0; i < 16; ++i) {
+      k[i] = vn[i / 4][i % 4];
+      mx = max(mx, k[i]);
     }
-    for (int64_t j = a0 + rounds * 16 * step + threadIdx.x; j < b1; j += blockDim.x)
-      bump(load_index(keys, j));
-  } else {
-    for (int64_t j = b0 + threadIdx.x; j < b1; j += blockDim.x) bump(load_index(keys, j));
+    if (r + 1 < rounds) load4(r + 1);
+    // the 16 additions back to back, one test of all that they return: past kLate a
+    // counter takes at most 16 more per thread before it is emptied
+    uint32_t old[16], any = 0u;
+    const bool crowd = crowded(k[0]);
+    if (crowd) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) old[i] = add_crowd(k[i]);
+    } else if (__all(mx < (uint32_t)n_bins)) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) old[i] = add(k[i]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) old[i] = add_inside(k[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) any |= old[i];
+    if (any & kFull) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (old[i]) drain(k[i], old[i], crowd ? 64 : 1);
+    }
+  }
+  int64_t j = a0 + rounds * 16 * step + threadIdx.x;
+  for (uint32_t kn = j < b1 ? (uint32_t)keys[j] : 0u; j < b1; j += step) {
+    const uint32_t k = kn;
+    if (j + step < b1) kn = (uint32_t)keys[j + step];
+    bump(k);
   }
   if (oob) count_oob(bad, oob);
   __syncthreads();
@@ -1059,7 +1089,8 @@ static dex_status scatter_typed(void* acc, int32_t acc_dtype, int64_t n_rows, in
   if (acc_dtype == DEX_I32 && R == 1 && !vals && n_rows <= 65536) {
     // A block has a round's keys at least, and as many as it has counters, which it
     // clears, writes and has added up: 65536 bins, 1000 keys 8.3 us (a block per CU:
-    // 27), 2^20 12 (27; 16384 keys a block 12.8), 5 2^20 17 (27; 27).
+    // 27), 2^20 12 (27; 16384 keys a block 12.8), 5 2^20 17 (27; 27); one key 1e5 and
+    // 3e6 times 20 and 28 (27 and 34).
     const int64_t least = std::max<int64_t>(kHistRound, n_rows);
     const int nb = (int)std::max<int64_t>(1, std::min<int64_t>(hist_blocks(), (n + least - 1) / least));
     const size_t need = scatter_ws_bytes(acc_dtype, n_rows, R, n, false, false);

@@ -242,6 +242,23 @@ def test_histogram_full_rounds(dev, bins):
     assert np.array_equal(h.cpu().numpy(), np.bincount(keys[ok], minlength=bins))
 
 
+# Waves whose lanes share a key (some, most, all), with keys outside the table among
+# them: full rounds, the keys left over, both halves of a word.
+@pytest.mark.parametrize("hot", [0.2, 0.6, 0.97, 1.0])
+@pytest.mark.parametrize("n,bins", [(1000, 3), (16_384 * 3 + 77, 65_535), ((1 << 22) + 3, 1)])
+def test_histogram_crowded_waves(dev, n, bins, hot):
+    from paper_2104_05372_amd import dex
+    rng = np.random.default_rng(n + int(100 * hot))
+    for key in (0, bins - 1, bins, -1):
+        keys = np.where(rng.random(n) < hot, key, rng.integers(-3, bins + 3, n)).astype(np.int32)
+        h = torch.zeros(bins, dtype=torch.int32, device=dev)
+        oob = torch.zeros(1, dtype=torch.int64, device=dev)
+        dex.dex_accum_scatter(h, torch.tensor(keys, device=dev), flags=dex.DEX_CHECK_BOUNDS, oob=oob)
+        ok = (keys >= 0) & (keys < bins)
+        assert oob.item() == np.count_nonzero(~ok)
+        assert np.array_equal(h.cpu().numpy(), np.bincount(keys[ok], minlength=bins))
+
+
 def test_histogram_out_of_range_keys(dev):
     from paper_2104_05372_amd import dex
     keys = np.array([1, 2, 70_000, 2, 65_535, 65_536], np.uint32)
