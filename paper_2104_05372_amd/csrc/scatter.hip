@@ -353,8 +353,18 @@ struct RowVec {
   typedef float T __attribute__((ext_vector_type(VW)));
 };
 
+// NT: past the caches (chosen at compile time: an `if` over both kinds of store is merged
+// into the ordinary one); see gather_shape.
+template <bool NT, typename VT>
+DEX_DEV void store_row(VT v, float* p) {
+  if constexpr (NT)
+    __builtin_nontemporal_store(v, reinterpret_cast<VT*>(p));
+  else
+    *reinterpret_cast<VT*>(p) = v;
+}
+
 // out[j, :] = w[j] * T[idx[j], :]
-template <int VW>
+template <int VW, bool NT>
 __global__ void __launch_bounds__(256) gather_scale_kernel(const float* __restrict__ T,
                                                            const int32_t* __restrict__ idx,
                                                            const float* __restrict__ w,
@@ -365,7 +375,6 @@ __global__ void __launch_bounds__(256) gather_scale_kernel(const float* __restri
   const int sub = threadIdx.x >> lg, hl = threadIdx.x & ((1 << lg) - 1);
   const int per = 256 >> lg, step = VW << lg;
   const int64_t stride = (int64_t)gridDim.x * per;  // rows per round of the grid
-  const bool nt = R % 32 == 0;  // whole lines: past the caches
   int bad = 0;
   for (int64_t j0 = (int64_t)blockIdx.x * per + sub; j0 < n; j0 += stride * kGU) {
     int64_t v[kGU];
@@ -388,13 +397,7 @@ __global__ void __launch_bounds__(256) gather_scale_kernel(const float* __restri
         t[u] = ok[u] ? *reinterpret_cast<const VT*>(T + v[u] * R + c) : VT(0.f);
 #pragma unroll
       for (int u = 0; u < kGU; ++u)
-        if (live[u]) {
-          VT* o = reinterpret_cast<VT*>(out + (j0 + u * stride) * R + c);
-          if (nt)
-            __builtin_nontemporal_store(t[u] * s[u], o);
-          else
-            *o = t[u] * s[u];
-        }
+        if (live[u]) store_row<NT>(t[u] * s[u], out + (j0 + u * stride) * R + c);
     }
   }
   if (oob) count_oob(bad, oob);
@@ -404,7 +407,7 @@ __global__ void __launch_bounds__(256) gather_scale_kernel(const float* __restri
 // idx is an integer, so it carries no tangent):
 //   tout[j, :] = tw[j] * T[idx[j], :] + w[j] * tT[idx[j], :]
 // Rows with an index outside [0, V) give zeros.
-template <int VW>
+template <int VW, bool NT>
 __global__ void __launch_bounds__(256) gather_jvp_kernel(const float* __restrict__ T,
                                                          const float* __restrict__ tT,
                                                          const int32_t* __restrict__ idx,
@@ -416,7 +419,6 @@ __global__ void __launch_bounds__(256) gather_jvp_kernel(const float* __restrict
   const int sub = threadIdx.x >> lg, hl = threadIdx.x & ((1 << lg) - 1);
   const int per = 256 >> lg, step = VW << lg;
   const int64_t stride = (int64_t)gridDim.x * per;
-  const bool nt = R % 32 == 0;
   for (int64_t j0 = (int64_t)blockIdx.x * per + sub; j0 < n; j0 += stride * kGU) {
     int64_t v[kGU];
     float a[kGU], b[kGU];
@@ -445,11 +447,7 @@ __global__ void __launch_bounds__(256) gather_jvp_kernel(const float* __restrict
 #pragma unroll
           for (int e = 0; e < VW; ++e) o[e] = fmaf(b[u], y[u][e], a[u] * x[u][e]);
         }
-        VT* p = reinterpret_cast<VT*>(tout + (j0 + u * stride) * R + c);
-        if (nt)
-          __builtin_nontemporal_store(o, p);
-        else
-          *p = o;
+        store_row<NT>(o, tout + (j0 + u * stride) * R + c);
       }
     }
   }
@@ -1154,19 +1152,27 @@ static dex_status scatter_typed(void* acc, int32_t acc_dtype, int64_t n_rows, in
   return check_hip(hipGetLastError(), "accum_scatter");
 }
 
-// Columns per lane, log2 of the lanes per row, blocks (a round of
-// kGU rows per lane group each, up to 32 per CU).
+// Columns per lane, log2 of the lanes per row, blocks, stores past the caches.
 struct GatherShape {
   int vw, lg;
   unsigned blocks;
+  bool nt;
 };
 static GatherShape gather_shape(int64_t R, int64_t n, uintptr_t align) {
   GatherShape g;
   g.vw = R % 4 == 0 && (align & 15) == 0 ? 4 : R % 2 == 0 && (align & 7) == 0 ? 2 : 1;
   g.lg = 0;
   while (g.lg < 5 && (int64_t)(g.vw << g.lg) < R) ++g.lg;
-  const int64_t per = (256 >> g.lg) * kGU;  // rows of a block's round
+  // A block has kGU rows per lane group, up to 32 blocks per CU; one row where a row
+  // takes a lane group several turns (R = 500, n = 40000: forward mode 41 us with four,
+  // 38; R = 50, n = 100003: forward 10.2, 11.5 with one).
+  const int64_t groups = 256 >> g.lg, per = R > (g.vw << g.lg) ? groups : groups * kGU;
   g.blocks = (unsigned)std::min<int64_t>((n + per - 1) / per, (int64_t)num_cus() * 32);
+  // Stores past the caches keep the table in them, but a line that two rows share is then
+  // written twice: for rows of whole lines (V = 100000, R = 128, n = 2e6, sorted indices
+  // 206 us, ordinary stores 309), and for results larger than the last-level cache (R =
+  // 300: 360 MB, forward mode, sorted 129 us, 139; 240 MB 84, 43).
+  g.nt = g.vw == 4 && (R % 32 == 0 || n * R > (int64_t(1) << 26));
   return g;
 }
 
@@ -1345,15 +1351,17 @@ dex_status gather_fwd(const float* T, const int32_t* idx, const float* w, int64_
   int64_t* o = count ? oob : nullptr;
   const GatherShape g = gather_shape(R, n, (uintptr_t)T | (uintptr_t)out);
   ProfRange pr(DEX_PROF_GATHER, s);
-#define DEX_GF(VW_)                                                                             \
-  hipLaunchKernelGGL(gather_scale_kernel<VW_>, dim3(g.blocks), dim3(256), 0, s, T, idx, w, V,   \
+#define DEX_GF(VW_, NT_)                                                                            \
+  hipLaunchKernelGGL((gather_scale_kernel<VW_, NT_>), dim3(g.blocks), dim3(256), 0, s, T, idx, w, V,   \
                      (int)R, n, g.lg, out, o)
-  if (g.vw == 4)
-    DEX_GF(4);
+  if (g.nt)
+    DEX_GF(4, true);
+  else if (g.vw == 4)
+    DEX_GF(4, false);
   else if (g.vw == 2)
-    DEX_GF(2);
+    DEX_GF(2, false);
   else
-    DEX_GF(1);
+    DEX_GF(1, false);
 #undef DEX_GF
   pr.end(1);
   return check_hip(hipGetLastError(), "gather_fwd");
@@ -1365,15 +1373,17 @@ dex_status gather_jvp(const float* T, const float* tT, const int32_t* idx, const
   if (n == 0) return DEX_OK;
   const GatherShape g = gather_shape(R, n, (uintptr_t)T | (uintptr_t)tT | (uintptr_t)tout);
   ProfRange pr(DEX_PROF_GATHER_JVP, s);
-#define DEX_GJ(VW_)                                                                            \
-  hipLaunchKernelGGL(gather_jvp_kernel<VW_>, dim3(g.blocks), dim3(256), 0, s, T, tT, idx, w, tw, \
+#define DEX_GJ(VW_, NT_)                                                                           \
+  hipLaunchKernelGGL((gather_jvp_kernel<VW_, NT_>), dim3(g.blocks), dim3(256), 0, s, T, tT, idx, w, tw, \
                      V, (int)R, n, g.lg, tout)
-  if (g.vw == 4)
-    DEX_GJ(4);
+  if (g.nt)
+    DEX_GJ(4, true);
+  else if (g.vw == 4)
+    DEX_GJ(4, false);
   else if (g.vw == 2)
-    DEX_GJ(2);
+    DEX_GJ(2, false);
   else
-    DEX_GJ(1);
+    DEX_GJ(1, false);
 #undef DEX_GJ
   pr.end(1);
   return check_hip(hipGetLastError(), "gather_jvp");
