@@ -731,10 +731,8 @@ __global__ void __launch_bounds__(1024) rs_scatter(const IdxT* __restrict__ idx,
 // tail[seg], and the segment is put on the list for own_fix (the list's order
 // does not matter: each entry is combined on its own, in a fixed order). The
 // values of the next U entries are loaded before the current U are summed.
-// SEG (a multiple of 64) entries per wave: 512 where that leaves a wave or two per
-// SIMD, 64 below (the entries of a wave are walked in order, so their number is the
-// kernel's latency: n = 100003, R = 50: 23 us with 64, 57 with 512), at the price
-// of more runs that span segments.
+// SEG (a multiple of 64) entries per wave, walked in order: their number is the kernel's
+// latency (see own_seg).
 // DW: the cotangent of the scales too, dw[j] (=|+=) <T[idx_j], vals_j>, from the
 // same read of vals: the run's row of T is read beside each entry (a repeat hits the
 // L1), a batch's partial products are reduced over the lanes together, and one lane
@@ -1054,8 +1052,13 @@ static int hist_blocks() { return num_cus(); }
 
 size_t sorted_scatter_ws_bytes(int64_t n, int64_t R);
 
-// Sorted entries per wave of the run sums: 512 from a wave per SIMD on.
-static int own_seg(int64_t n) { return n >= 512 * 1024 ? 512 : 64; }
+// Sorted entries per wave of the run sums: enough waves for every SIMD, and as few
+// segments as that allows, whose partials are written, read and combined. Whole
+// transposes, us, with 64 / 256 / 512 (dT only, even indices): R = 50, n = 100003 53 / 58 /
+// 76, n = 300000 92 / 68 / 75, n = 400000 114 / 72 / 77, n = 520000 139 / 83 / 81; R = 300,
+// n = 300000 148 / 175 / 168. (Skewed indices, R = 1, both cotangents: n = 300000 76 / 83 /
+// 112, n = 400000 85 / 84 / 112.)
+static int own_seg(int64_t n) { return n >= 512 * 1024 ? 512 : n >= 320 * 1024 ? 256 : 64; }
 // Rounds per wave of the sort's tiles: 8192-key tiles from half a tile per CU on.
 static int rs_rounds(int64_t n) { return n >= 1024 * 1024 ? 8 : 2; }
 
@@ -1294,15 +1297,17 @@ static dex_status scatter_sorted(float* acc, int64_t n_rows, int64_t R, const Id
   const uint32_t sent = (uint32_t)n_rows;
 #define DEX_OWNS(V, OV, SEG_) \
   launch_own<V, OV, SEG_>(w, kin, vin, n, sent, vals, (int)R, acc, dw, s)
-#define DEX_OWNL(V)                                                            \
-  (own_seg(n) == 512 ? (overwrite ? DEX_OWNS(V, true, 512) : DEX_OWNS(V, false, 512)) \
-                     : (overwrite ? DEX_OWNS(V, true, 64) : DEX_OWNS(V, false, 64)))
+#define DEX_OWNL(V, SEG_) (overwrite ? DEX_OWNS(V, true, SEG_) : DEX_OWNS(V, false, SEG_))
+#define DEX_OWNV(V) \
+  (seg == 512 ? DEX_OWNL(V, 512) : seg == 256 ? DEX_OWNL(V, 256) : DEX_OWNL(V, 64))
+  const int seg = own_seg(n);
   if (vw == 4)
-    DEX_OWNL(4);
+    DEX_OWNV(4);
   else if (vw == 2)
-    DEX_OWNL(2);
+    DEX_OWNV(2);
   else
-    DEX_OWNL(1);
+    DEX_OWNV(1);
+#undef DEX_OWNV
 #undef DEX_OWNL
 #undef DEX_OWNS
   pr.end(1);

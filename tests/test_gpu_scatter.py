@@ -189,6 +189,18 @@ def test_integer_rows_exact(dev):
         assert np.array_equal(acc.cpu().numpy(), want)
 
 
+# Segments of 256 entries (from 320 K of them): a hot row over many segments, one column a
+# lane, two and four.
+@pytest.mark.parametrize("V,R,n", [(700, 3, 320 * 1024), (50, 66, 320 * 1024 + 257),
+                                   (9, 260, 320 * 1024 + 1)])
+def test_transpose_middle_segments(dev, V, R, n):
+    si = workloads.scatter_inputs(V, R, n, 1.1, 14)
+    idx = np.where(np.random.default_rng(n).random(n) < 0.4, V - 1, si.idx).astype(np.int32)
+    _, dT, dw = gather_vjp(si.table, idx, si.w, si.g, dev, config=1)
+    assert rel(dT, osc.scatter(V, idx, si.w, si.g)) <= 1e-5
+    assert rel(dw, osc.scatter_dw(si.table, idx, si.g)) <= 1e-5
+
+
 @pytest.mark.parametrize("n,bins,seed", [(1 << 20, 65536, 0), (100_003, 17, 1), (5, 65536, 2),
                                          (300_000, 1, 3), (1 << 18, 1000, 4)])
 def test_histogram_bit_exact(dev, n, bins, seed):
