@@ -1343,11 +1343,16 @@ dex_status gather_vjp(const float* T, const int32_t* idx, const float* w, const 
     if (st != DEX_OK) return st;
   }
   if (n == 0) return DEX_OK;
-  if (sorted)
-    return scatter_sorted<int32_t>(dT, V, R, idx, g, w, n, nullptr, !accumulate,
-                                   DwArgs{T, dw, accumulate}, ws, ws_bytes, s);
-  const dex_status st = scatter_typed<int32_t>(dT, DEX_F32, V, R, idx, g, w, n, nullptr, ws, ws_bytes, s);
-  return st != DEX_OK || !dw ? st : gather_dw(T, idx, g, V, R, n, dw, accumulate, s);
+  // In one pass where no row of T is written on the way; a table updated in place (dT over
+  // T) gives dw from what it holds afterwards, in a pass of its own, as the atomic form does.
+  const char *t0 = (const char*)T, *d0 = (const char*)dT;
+  const int64_t bytes = V * R * 4;
+  const bool fused = sorted && dw && (t0 + bytes <= d0 || d0 + bytes <= t0);
+  const dex_status st =
+      sorted ? scatter_sorted<int32_t>(dT, V, R, idx, g, w, n, nullptr, !accumulate,
+                                       DwArgs{T, fused ? dw : nullptr, accumulate}, ws, ws_bytes, s)
+             : scatter_typed<int32_t>(dT, DEX_F32, V, R, idx, g, w, n, nullptr, ws, ws_bytes, s);
+  return st != DEX_OK || !dw || fused ? st : gather_dw(T, idx, g, V, R, n, dw, accumulate, s);
 }
 
 dex_status gather_fwd(const float* T, const int32_t* idx, const float* w, int64_t V, int64_t R,

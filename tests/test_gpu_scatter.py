@@ -201,6 +201,23 @@ def test_transpose_middle_segments(dev, V, R, n):
     assert rel(dw, osc.scatter_dw(si.table, idx, si.g)) <= 1e-5
 
 
+@pytest.mark.parametrize("config", [1, 2])
+def test_table_updated_in_place(dev, config):
+    """dT over T itself with DEX_ACCUMULATE (a step of w = -rate, in place): the table
+    takes the transposed gather, and dw is formed with the table it has become."""
+    from paper_2104_05372_amd import dex
+    si = workloads.scatter_inputs(300, 50, 5000, 1.1, 15)
+    T, idx, w, g = (torch.tensor(a, device=dev) for a in (si.table, si.idx, si.w, si.g))
+    d = dex.gather_desc(300, 50, 5000)
+    d.config = config
+    dw = torch.zeros_like(w)
+    dex.dex_vjp(d, [T, idx, w], [], [g], [T, dw], dex.DEX_ACCUMULATE,
+                dex.workspace(dex.dex_workspace_bytes(d, dex.DEX_WS_VJP), dev))
+    want = si.table + osc.scatter(300, si.idx, si.w, si.g)
+    assert rel(T.cpu().numpy(), want) <= 1e-5
+    assert rel(dw.cpu().numpy(), osc.scatter_dw(want, si.idx, si.g)) <= 1e-5
+
+
 @pytest.mark.parametrize("n,bins,seed", [(1 << 20, 65536, 0), (100_003, 17, 1), (5, 65536, 2),
                                          (300_000, 1, 3), (1 << 18, 1000, 4)])
 def test_histogram_bit_exact(dev, n, bins, seed):
