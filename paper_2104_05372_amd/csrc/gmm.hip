@@ -550,7 +550,7 @@ static int jvp_shares(const GmmGeom& g) {
   const int64_t tiles = (g.N + 63) / 64, simds = 4 * num_cus();
   int best = 1;
   int64_t cost = INT64_MAX;
-  for (int ks = 1; ks <= 64 && ks <= g.K; ++ks) {
+  for (int ks = 1; ks <= kMaxShares && ks <= g.K; ++ks) {
     const int64_t c = (tiles * ks + simds - 1) / simds * ((g.K + ks - 1) / ks + 1);
     if (c < cost) {
       cost = c;
@@ -587,7 +587,12 @@ static JvpLayout jvp_layout(const Shape& s) {
   } else {
     j.nparts = ((s.g.N + 255) / 256) * ((s.g.K + kJvpKC - 1) / kJvpKC);
   }
-  j.part = take((size_t)j.nparts * 8);
+  // the partials of the most shares any smaller N or K may have, so that scratch sized for
+  // the largest call serves all
+  const int64_t most = j.quad.tiles ? j.quad.tiles * std::min<int64_t>(kMaxShares, (s.g.K + 3) / 4)
+                       : j.ks       ? j.nparts / j.ks * std::min<int64_t>(kMaxShares, s.g.K)
+                                    : j.nparts;
+  j.part = take((size_t)most * 8);
   j.total = o;
   return j;
 }

@@ -97,7 +97,7 @@ static QuadSplit quad_split(const GmmGeom& g, int cb, int per_cu) {
   const int64_t nq = (g.K + 3) / 4, resident = (int64_t)per_cu * num_cus();
   q.tiles = (g.N + 64 * cb - 1) / (64 * cb);
   int64_t best = INT64_MAX;
-  for (int64_t ks = 1; ks <= nq && ks <= 64; ++ks) {
+  for (int64_t ks = 1; ks <= nq && ks <= kMaxShares; ++ks) {
     const int64_t t = (q.tiles * ks + resident - 1) / resident * ((nq + ks - 1) / ks + 1);
     if (t < best) {
       best = t;

@@ -579,9 +579,12 @@ int f64_shares(int64_t N, int64_t D, int64_t K) {
 }  // namespace
 
 size_t gmm_f64_fwd_ws(int64_t N) { return align256((size_t)((N + 63) / 64) * 2 * 8); }
+// S K slots, and what any smaller N or K may need too (S K is at most 511 + K, and S 1
+// from K = 512 on), so that scratch sized for the largest call serves all.
 size_t gmm_f64_bwd_ws(int64_t N, int64_t D, int64_t K) {
-  const int S = f64_shares(N, D, K);
-  return S == 1 ? 0 : align256((size_t)S * K * f64_slot(f64_dp(D)) * 8);
+  const int64_t k = std::min<int64_t>(K, 511), one = f64_shares(N, D, 1);
+  if (one == 1) return 0;
+  return align256((size_t)std::min(511 + k, one * k) * f64_slot(f64_dp(D)) * 8);
 }
 
 #define DEX_F64_DP(DP_, CALL) \

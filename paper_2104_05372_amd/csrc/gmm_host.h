@@ -86,6 +86,7 @@ struct QuadSplit {
   int64_t tiles = 0;
   int ks = 1;
 };
+constexpr int kMaxShares = 64;  // of a tile's quads, or of its components where D > 32
 QuadSplit quad_fwd_split(const GmmGeom& g);
 QuadSplit quad_jvp_split(const GmmGeom& g);
 size_t quad_rec_bytes(const GmmGeom& g);

@@ -1058,9 +1058,11 @@ size_t sorted_scatter_ws_bytes(int64_t n, int64_t R);
 // 76, n = 300000 92 / 68 / 75, n = 400000 114 / 72 / 77, n = 520000 139 / 83 / 81; R = 300,
 // n = 300000 148 / 175 / 168. (Skewed indices, R = 1, both cotangents: n = 300000 76 / 83 /
 // 112, n = 400000 85 / 84 / 112.)
-static int own_seg(int64_t n) { return n >= 512 * 1024 ? 512 : n >= 320 * 1024 ? 256 : 64; }
+constexpr int64_t kSeg256 = 320 * 1024, kSeg512 = 512 * 1024;
+static int own_seg(int64_t n) { return n >= kSeg512 ? 512 : n >= kSeg256 ? 256 : 64; }
 // Rounds per wave of the sort's tiles: 8192-key tiles from half a tile per CU on.
-static int rs_rounds(int64_t n) { return n >= 1024 * 1024 ? 8 : 2; }
+constexpr int64_t kTile8 = 1024 * 1024;
+static int rs_rounds(int64_t n) { return n >= kTile8 ? 8 : 2; }
 
 size_t scatter_ws_bytes(int32_t acc_dtype, int64_t n_rows, int64_t row_len, int64_t n,
                         bool has_vals, bool deterministic) {
@@ -1212,7 +1214,14 @@ static SortWs sort_ws(int64_t n, int64_t R, char* base) {
   return w;
 }
 
-size_t sorted_scatter_ws_bytes(int64_t n, int64_t R) { return sort_ws(n, R, nullptr).bytes; }
+// What any smaller n may need too, so that scratch sized for the largest call serves all
+// (segments and tiles grow at these n, and their number falls).
+size_t sorted_scatter_ws_bytes(int64_t n, int64_t R) {
+  size_t b = sort_ws(n, R, nullptr).bytes;
+  for (const int64_t t : {kSeg256, kSeg512, kTile8})
+    if (n >= t) b = std::max(b, sort_ws(t - 1, R, nullptr).bytes);
+  return b;
+}
 
 // T, dw: where the cotangent of the scales is wanted too (vals given).
 struct DwArgs {

@@ -126,6 +126,26 @@ def test_workspace_sizes(dex):
     assert dex.dex_num_configs(d, dex.DEX_WS_VJP) >= 2
 
 
+def test_scratch_for_the_largest_call_serves_smaller_ones(dex):
+    """Scratch sizes do not fall as the points, components or indices grow: a program
+    may size one workspace for its largest batch."""
+    def rises(sizes):
+        assert all(a <= b for a, b in zip(sizes, sizes[1:])), sizes
+
+    edges = [(k << 10) + o for k in (1, 64, 320, 512, 1024, 4096) for o in (-1, 0, 1)]
+    for R in (1, 50, 300):
+        rises([dex.dex_workspace_bytes(dex.gather_desc(1000, R, n), dex.DEX_WS_VJP) for n in edges])
+        rises([dex.dex_accum_scatter_workspace_bytes(dex.DEX_F32, 1000, R, n, True, dex.DEX_DETERMINISTIC)
+               for n in edges])
+    for dt, D in ((dex.DEX_F32, 8), (dex.DEX_F32, 32), (dex.DEX_F32, 48), (dex.DEX_F64, 3), (dex.DEX_F64, 16)):
+        ws = lambda N, K, role: dex.dex_workspace_bytes(dex.gmm_desc(N, D, K, dt, dex.DEX_GMM_PLAIN), role)
+        rises([ws(N, 60, dex.DEX_WS_JVP) for N in range(1, 300_000, 1777)])
+        rises([ws(9000, K, dex.DEX_WS_JVP) for K in range(1, 600)])
+        rises([ws(N, 60, dex.DEX_WS_VJP) for N in range(1, 300_000, 1777)])
+        if dt == dex.DEX_F64:
+            rises([ws(9000, K, dex.DEX_WS_VJP) for K in range(1, 600)])
+
+
 def test_batched_plan(dex):
     shapes = workloads.batched_shapes(64, seed=3)
     d, plan = dex.dex_gmm_batched_plan(shapes)
