@@ -281,7 +281,7 @@ def dex_jvp(d: DexDesc, ins, t_in, t_out, ws: torch.Tensor | None = None, stream
             resid=(), dtypes=None):
     """Forward mode: t_out = the linearization of f at ins applied to t_in
     (resid: dex_fwd's residuals, for DEX_GMM)."""
-    g = dtypes.get if dtypes else _no_dtypes
+    g, resid = dtypes.get if dtypes else _no_dtypes, list(resid)
     check(lib().dex_jvp(ctypes.byref(d), _pack(ins, g("in")), len(ins), _pack(resid, g("resid")),
                         len(resid), _pack(t_in), len(t_in), _pack(t_out), len(t_out), _ptr(ws),
                         ws.numel() if ws is not None else 0, _stream(stream)))

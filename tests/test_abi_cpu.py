@@ -146,6 +146,19 @@ def test_scratch_for_the_largest_call_serves_smaller_ones(dex):
             rises([ws(9000, K, dex.DEX_WS_VJP) for K in range(1, 600)])
 
 
+def test_forward_mode_takes_any_iterable_of_residuals(dex):
+    """An iterator over the residuals gives what their list gives (here: the library's
+    own answer on buffers of the wrong count)."""
+    import torch
+    d = dex.gmm_desc(10, 2, 3, dex.DEX_F32, dex.DEX_GMM_PLAIN)
+    t = [torch.zeros(m) for m in (3, 6, 6, 3, 20)]
+    if torch.cuda.is_available():
+        t = [a.cuda() for a in t]
+    status = [_status(lambda: dex.dex_jvp(d, t, t[:4], t[:1], resid=r))
+              for r in ([t[0]], iter([t[0]]), (a for a in t[:1]))]
+    assert status == [dex.DEX_ERR_INVALID_ARG] * 3
+
+
 def test_batched_plan(dex):
     shapes = workloads.batched_shapes(64, seed=3)
     d, plan = dex.dex_gmm_batched_plan(shapes)
