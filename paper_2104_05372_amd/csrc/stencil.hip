@@ -761,6 +761,12 @@ __global__ void __launch_bounds__(256) copy_f32(const float* __restrict__ a, flo
   if (i < n) b[i] = a[i];
 }
 
+__global__ void __launch_bounds__(256) add_f32(const float* __restrict__ a, float* __restrict__ b,
+                                               int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) b[i] += a[i];
+}
+
 }  // namespace dexk
 
 // ===========================================================================
@@ -1051,6 +1057,11 @@ dex_status stencil_jvp(const dex_desc& d, const float* u0, const float* target, 
   return check_hip(hipGetLastError(), "stencil_jvp");
 }
 
+// [a, a + na) and [b, b + nb) do not meet.
+static bool apart_from(const float* a, int64_t na, const float* b, int64_t nb) {
+  return (uintptr_t)(a + na) <= (uintptr_t)b || (uintptr_t)(b + nb) <= (uintptr_t)a;
+}
+
 // uT_in: the forward's final state (second residual).
 dex_status stencil_vjp(const dex_desc& d, int cfg, const float* u0, const float* target,
                        const float* ckpt, const float* uT_in, const float* dL, float* du0,
@@ -1077,6 +1088,10 @@ dex_status stencil_vjp(const dex_desc& d, int cfg, const float* u0, const float*
     return check_hip(hipGetLastError(), "stencil_vjp");
   }
   const bool recompute = d.variant == DEX_STENCIL_RECOMPUTE;
+  // du0 over a buffer that the last time-blocked launch reads (its rows feed other waves'
+  // cells): that launch writes scratch, from where the field is copied or added
+  const bool apart = apart_from(du0, s.n, uT_in, s.n) && apart_from(du0, s.n, target, s.n) &&
+                     apart_from(du0, s.n, ckpt, (int64_t)s.nck * s.n);
   if (!recompute && s.rho != 0.f)
     return fail(DEX_ERR_INVALID_ARG, "the no-recompute reverse pass needs rho == 0");
   float* g = lamA;
@@ -1128,8 +1143,8 @@ dex_status stencil_vjp(const dex_desc& d, int cfg, const float* u0, const float*
         const bool last = sg == 0 && left == 0;
         TbArgs a{};
         a.in = first ? uT_in : g;
-        a.out = last ? du0 : o;
-        a.accumulate = last && accumulate;
+        a.out = last && apart ? du0 : o;
+        a.accumulate = last && apart && accumulate;
         a.dL = dL;
         if (nl) {
           a.in2 = m == 0 ? ck : seg + (m - 1) * fe;
@@ -1145,6 +1160,12 @@ dex_status stencil_vjp(const dex_desc& d, int cfg, const float* u0, const float*
         launches += tb;
         std::swap(g, o);
       }
+    }
+    if (!apart) {  // (g: the last launch's field)
+      if (accumulate)
+        hipLaunchKernelGGL(add_f32, dim3(nb), dim3(256), 0, st, g, du0, s.n);
+      else
+        hipLaunchKernelGGL(copy_f32, dim3(nb), dim3(256), 0, st, g, du0, s.n);
     }
     pr.end(launches);
     return check_hip(hipGetLastError(), "stencil_vjp");

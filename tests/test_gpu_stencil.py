@@ -219,3 +219,43 @@ def test_sine_of_the_non_linear_term(dev, scale):
     want = u64 + rho * np.sin(u64)
     err = np.abs(uT.cpu().numpy() - want)
     assert err.max() <= rho * 2.0 ** -21
+
+
+# Reverse: DEX_ACCUMULATE in every form, and du0 over a buffer that the call reads (the
+# linear adjoint's target and final state, the non-linear one's first checkpoint too).
+@pytest.mark.parametrize("rho", [0.0, -0.2])
+@pytest.mark.parametrize("H,W,steps,every", [(70, 130, 8, 8), (33, 47, 3, 4), (40, 256, 21, 6), (9, 9, 1, 1)])
+def test_reverse_accumulates_and_in_place(dev, H, W, steps, every, rho):
+    from paper_2104_05372_amd import dex
+    u0, tg = workloads.stencil_inputs(H, W, 23)
+    want = ost.loss_and_grad(u0, tg, steps, rho=rho)[2]
+    d = dex.stencil_desc(H, W, steps, every, 0.2, rho)
+    tu, tt = torch.tensor(u0, device=dev), torch.tensor(tg, device=dev)
+    L, uT = torch.empty(1, device=dev), torch.empty_like(tu)
+    ck = torch.empty((steps + every - 1) // every, H, W, device=dev)
+    dex.dex_fwd(d, [tu, tt], [L, uT], [ck, uT], dex.workspace(dex.dex_workspace_bytes(d, 0), dev))
+    ws, one = dex.workspace(dex.dex_workspace_bytes(d, 1), dev), torch.ones(1, device=dev)
+
+    def vjp(du, flags, target, cks, last, cfg=0):
+        d.config = cfg
+        print(f"  stencil vjp {H}x{W} rho={rho} cfg={cfg} flags={flags}", flush=True)
+        dex.dex_vjp(d, [tu, target], [cks, last], [one], [du], flags, ws)
+        return du.cpu().numpy()
+
+    plain = vjp(torch.empty_like(tu), 0, tt, ck, uT)
+    assert rel(plain, want) <= 1e-5
+    # added to 0.5: the gather forms round the sum once, the scatter form each of five
+    # additions to a value below 2 (2^-24 each) and what it adds
+    for cfg in (1, 3):
+        alone = vjp(torch.empty_like(tu), 0, tt, ck, uT, cfg)
+        got = vjp(torch.full_like(tu, 0.5), dex.DEX_ACCUMULATE, tt, ck, uT, cfg)
+        assert np.array_equal(got, np.float32(0.5) + alone)
+    got = vjp(torch.full_like(tu, 0.5), dex.DEX_ACCUMULATE, tt, ck, uT, 2)
+    assert np.abs(got - (0.5 + plain.astype(np.float64))).max() <= 5 * 2.0 ** -23
+    for flags in (0, dex.DEX_ACCUMULATE):
+        for where in ("target", "last", "checkpoint"):
+            t2, c2, l2 = tt.clone(), ck.clone(), uT.clone()
+            du = {"target": t2, "last": l2, "checkpoint": c2[0]}[where]
+            base = du.cpu().numpy() if flags else 0.0
+            # the same sum, rounded once more where it is added
+            assert np.array_equal(vjp(du, flags, t2, c2, l2), base + plain), where
