@@ -320,14 +320,18 @@ struct Strip {
   using U = typename UVec<VW>::T;
   int W, xc, col[VW], nmine;  // nmine: columns this lane stores
   bool whole, even;           // no lane straddles the wrap; every lane stores all or none
-  DEX_DEV Strip(int lane, int x0, int HL, int W_) : W(W_), xc(x0 + VW * (lane - HL)) {
+  // (x0 + 64 VW may pass 2^31 where W is just below it: unsigned, and compared with W - x0)
+  DEX_DEV Strip(int lane, int x0, int HL, int W_) : W(W_) {
+    const int off = VW * (lane - HL);
+    xc = (int)((uint32_t)x0 + (uint32_t)off);
 #pragma unroll
     for (int e = 0; e < VW; ++e) {
-      const int m = (xc + e) % W;
-      col[e] = m < 0 ? m + W : m;
+      const bool below = off + e < 0 && x0 + off + e < 0;
+      const uint32_t a = (uint32_t)x0 + (uint32_t)(off + e), m = (below ? 0u - a : a) % (uint32_t)W;
+      col[e] = below && m ? W - (int)m : (int)m;
     }
     whole = __all(col[VW - 1] - col[0] == VW - 1);
-    nmine = lane >= HL && lane < 64 - HL && xc < W ? min(VW, W - xc) : 0;
+    nmine = lane >= HL && lane < 64 - HL && off < W - x0 ? min(VW, W - x0 - off) : 0;
     even = __all(nmine == 0 || nmine == VW);
   }
   DEX_DEV C load(const float* f, int y) const {
@@ -852,7 +856,9 @@ TbShape tb_shape(const St& s, int tb, bool fused) {
   double best = 1e300;
   for (int v = 1; v <= 2; ++v) {
     const int wv = v * (64 - 2 * ((halo + v - 1) / v));
-    const int64_t strips = (s.W + wv - 1) / wv;
+    const int64_t strips = ((int64_t)s.W + wv - 1) / wv;
+    // (a launch of 2^31 threads and more runs only in part; wide lanes stay below)
+    if (v == 1 && strips * 64 > (int64_t(1) << 30)) continue;
     const double ins = fused ? 27.0 * v + 8.0 : nl ? 14.0 * v + 6.0 : 5.5 * v + 2.5;
     for (int n = 1; n <= 16; ++n) {  // waves per SIMD
       const int64_t chunks = std::max<int64_t>(1, (int64_t)n * simds / strips);
