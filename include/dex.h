@@ -190,7 +190,9 @@ typedef struct dex_buf {
  *   configs: fwd 1 time-blocked kernel, several steps per launch (default), 2
  *   vector kernel, one step per launch; vjp 1 gather-form adjoint, time-blocked
  *   (default), 2 scatter-form adjoint (atomics), 3 gather form with vector
- *   kernels. All configs compute the same values.
+ *   kernels. On grids of few columns or rows the time-blocked forms go one step
+ *   per launch where that is faster. All configs compute the same values, the
+ *   gather forms and the forward ones bit for bit.
  */
 
 /* Message for a status code (static storage). */

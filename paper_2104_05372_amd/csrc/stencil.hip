@@ -5,7 +5,8 @@
 // where every read is of the previous field (`get` yields a value, Sec. 5.3.2),
 // so each step is a Jacobi sweep into a second buffer. Every `every`-th state
 // (t = 0, every, 2 every, ...) is a checkpoint. By default up to eight steps run
-// per launch, the levels in between held in registers (stencil_tb).
+// per launch, the levels in between held in registers (stencil_tb); on grids of a few
+// columns or rows one step does (TbPlan::one_step).
 // Loss L = 1/2 ||u_T - target||^2.
 //
 // Reverse (ForTranspose runs the loop backwards; GetTranspose/PutTranspose carry
@@ -209,6 +210,11 @@ DEX_DEV float cos1(float x) {
   return c.v[0];
 }
 
+// One step of a cell from the sum of its neighbours, and its adjoint; the fused
+// multiply-adds are written out, so that every kernel rounds alike.
+DEX_DEV float step1(float u, float sum, float c) { return fmaf(c, fmaf(-4.f, u, sum), u); }
+DEX_DEV float adj1(float g, float sum, float c) { return fmaf(1.f - 4.f * c, g, c * sum); }
+
 // One forward step, 4 cells per thread (W % 4 == 0, W >= 8).
 __global__ void __launch_bounds__(256) stencil_step_vec(const float* __restrict__ u,
                                                         float* __restrict__ un,
@@ -226,15 +232,17 @@ __global__ void __launch_bounds__(256) stencil_step_vec(const float* __restrict_
   const float lf = u[(int64_t)y * W + (x0 == 0 ? W - 1 : x0 - 1)];
   const float rt = u[(int64_t)y * W + (x0 + 4 == W ? 0 : x0 + 4)];
   float4 o;
-  o.x = cc.x + c * (((ss.x + nn.x) + cc.y) + lf - 4.f * cc.x);
-  o.y = cc.y + c * (((ss.y + nn.y) + cc.z) + cc.x - 4.f * cc.y);
-  o.z = cc.z + c * (((ss.z + nn.z) + cc.w) + cc.y - 4.f * cc.z);
-  o.w = cc.w + c * (((ss.w + nn.w) + rt) + cc.z - 4.f * cc.w);
+  o.x = step1(cc.x, ((ss.x + nn.x) + cc.y) + lf, c);
+  o.y = step1(cc.y, ((ss.y + nn.y) + cc.z) + cc.x, c);
+  o.z = step1(cc.z, ((ss.z + nn.z) + cc.w) + cc.y, c);
+  o.w = step1(cc.w, ((ss.w + nn.w) + rt) + cc.z, c);
   if (rho != 0.f) {
-    o.x += rho * sin1(cc.x);
-    o.y += rho * sin1(cc.y);
-    o.z += rho * sin1(cc.z);
-    o.w += rho * sin1(cc.w);
+    Cells<4> sn, cs;
+    trig<true, false, 4>(Cells<4>{{cc.x, cc.y, cc.z, cc.w}}, sn, cs);
+    o.x = fmaf(rho, sn.v[0], o.x);
+    o.y = fmaf(rho, sn.v[1], o.y);
+    o.z = fmaf(rho, sn.v[2], o.z);
+    o.w = fmaf(rho, sn.v[3], o.w);
   }
   *reinterpret_cast<float4*>(un + (int64_t)y * W + x0) = o;
   if (snap) *reinterpret_cast<float4*>(snap + (int64_t)y * W + x0) = cc;
@@ -615,11 +623,37 @@ __global__ void __launch_bounds__(256) stencil_step_scalar(const float* __restri
   const int yn = y == 0 ? H - 1 : y - 1, ys = y == H - 1 ? 0 : y + 1;
   const int xl = x == 0 ? W - 1 : x - 1, xr = x == W - 1 ? 0 : x + 1;
   const float cc = u[t];
-  float o = cc + c * (((u[(int64_t)ys * W + x] + u[(int64_t)yn * W + x]) + u[(int64_t)y * W + xr]) +
-                      u[(int64_t)y * W + xl] - 4.f * cc);
-  if (rho != 0.f) o += rho * sin1(cc);
+  float o = step1(cc, ((u[(int64_t)ys * W + x] + u[(int64_t)yn * W + x]) + u[(int64_t)y * W + xr]) +
+                          u[(int64_t)y * W + xl], c);
+  if (rho != 0.f) o = fmaf(rho, sin1(cc), o);
   un[t] = o;
   if (snap) snap[t] = cc;
+}
+
+// Forward mode, one step of the state and its tangent; one cell per thread.
+__global__ void __launch_bounds__(256) stencil_tan_step(const float* __restrict__ u,
+                                                        const float* __restrict__ du,
+                                                        float* __restrict__ un,
+                                                        float* __restrict__ dun, int H, int W,
+                                                        float c, float rho) {
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (t >= (int64_t)H * W) return;
+  const int y = (int)(t / W), x = (int)(t % W);
+  const int yn = y == 0 ? H - 1 : y - 1, ys = y == H - 1 ? 0 : y + 1;
+  const int xl = x == 0 ? W - 1 : x - 1, xr = x == W - 1 ? 0 : x + 1;
+  const int64_t is = (int64_t)ys * W + x, in = (int64_t)yn * W + x;
+  const int64_t ir = (int64_t)y * W + xr, il = (int64_t)y * W + xl;
+  const float cc = u[t], dc = du[t];
+  float o = step1(cc, ((u[is] + u[in]) + u[ir]) + u[il], c);
+  float d = step1(dc, ((du[is] + du[in]) + du[ir]) + du[il], c);
+  if (rho != 0.f) {
+    Cells<1> sn, cs;
+    trig<true, true, 1>(Cells<1>{{cc}}, sn, cs);
+    o = fmaf(rho, sn.v[0], o);
+    d = fmaf(rho * cs.v[0], dc, d);
+  }
+  un[t] = o;
+  dun[t] = d;
 }
 
 // Adjoint step, gather form: lam = S^T g + rho cos(u) g  (=|+= into out).
@@ -634,10 +668,9 @@ __global__ void __launch_bounds__(256) stencil_adj_gather(const float* __restric
   const int xl = x == 0 ? W - 1 : x - 1, xr = x == W - 1 ? 0 : x + 1;
   const float gc = g[t];
   // cell (y+1, x) read u[y, x] as its north neighbour, etc.
-  float v = (1.f - 4.f * c) * gc +
-            c * (((g[(int64_t)ys * W + x] + g[(int64_t)yn * W + x]) + g[(int64_t)y * W + xr]) +
-                 g[(int64_t)y * W + xl]);
-  if (rho != 0.f) v += rho * cos1(u[t]) * gc;
+  float v = adj1(gc, ((g[(int64_t)ys * W + x] + g[(int64_t)yn * W + x]) + g[(int64_t)y * W + xr]) +
+                         g[(int64_t)y * W + xl], c);
+  if (rho != 0.f) v = fmaf(rho * cos1(u[t]), gc, v);
   out[t] = accumulate ? out[t] + v : v;
 }
 
@@ -658,18 +691,19 @@ __global__ void __launch_bounds__(256) stencil_adj_gather_vec(const float* __res
   const float4 ss = *reinterpret_cast<const float4*>(g + (int64_t)ys * W + x0);
   const float lf = g[(int64_t)y * W + (x0 == 0 ? W - 1 : x0 - 1)];
   const float rt = g[(int64_t)y * W + (x0 + 4 == W ? 0 : x0 + 4)];
-  const float a = 1.f - 4.f * c;
   float4 v;
-  v.x = a * cc.x + c * (((ss.x + nn.x) + cc.y) + lf);
-  v.y = a * cc.y + c * (((ss.y + nn.y) + cc.z) + cc.x);
-  v.z = a * cc.z + c * (((ss.z + nn.z) + cc.w) + cc.y);
-  v.w = a * cc.w + c * (((ss.w + nn.w) + rt) + cc.z);
+  v.x = adj1(cc.x, ((ss.x + nn.x) + cc.y) + lf, c);
+  v.y = adj1(cc.y, ((ss.y + nn.y) + cc.z) + cc.x, c);
+  v.z = adj1(cc.z, ((ss.z + nn.z) + cc.w) + cc.y, c);
+  v.w = adj1(cc.w, ((ss.w + nn.w) + rt) + cc.z, c);
   if (rho != 0.f) {
     const float4 uu = *reinterpret_cast<const float4*>(u + (int64_t)y * W + x0);
-    v.x += rho * cos1(uu.x) * cc.x;
-    v.y += rho * cos1(uu.y) * cc.y;
-    v.z += rho * cos1(uu.z) * cc.z;
-    v.w += rho * cos1(uu.w) * cc.w;
+    Cells<4> sn, cs;
+    trig<false, true, 4>(Cells<4>{{uu.x, uu.y, uu.z, uu.w}}, sn, cs);
+    v.x = fmaf(rho * cs.v[0], cc.x, v.x);
+    v.y = fmaf(rho * cs.v[1], cc.y, v.y);
+    v.z = fmaf(rho * cs.v[2], cc.z, v.z);
+    v.w = fmaf(rho * cs.v[3], cc.w, v.w);
   }
   float4* o = reinterpret_cast<float4*>(out + (int64_t)y * W + x0);
   if (accumulate) {
@@ -803,7 +837,7 @@ St st_of(const dex_desc& d) {
 
 // Steps per launch are powers of two up to kTB: a stretch of n steps runs as
 // n / kTB launches of kTB steps and the binary digits of the rest.
-constexpr int kTB = 8;
+constexpr int kTB = 8, kFused = 4;  // (kFused: the non-linear adjoint)
 int tb_of(int left) {
   int tb = kTB;
   while (tb > left) tb >>= 1;
@@ -832,9 +866,10 @@ void fused_launch(const TbArgs& a, int blocks, hipStream_t st) {
 }
 
 // Launch shape of a tb-step launch on a grid: columns per lane, rows per wave,
-// strips.
+// strips; and the modelled time of one of its steps.
 struct TbShape {
   int vw, rb, strips;
+  double us;
 };
 TbShape tb_shape(const St& s, int tb, bool fused) {
   const bool nl = s.rho != 0.f;
@@ -852,7 +887,7 @@ TbShape tb_shape(const St& s, int tb, bool fused) {
   // 5.57, 6.35 us; 601 x 333 within 2% throughout. Heights from a fixed list, which
   // leave the last waves of a SIMD alone: 4096^2 6.3, 10.5 and 32.7 us.
   const int simds = 4 * num_cus();
-  TbShape g{2, 32, 0};
+  TbShape g{2, 32, 0, 0.0};
   double best = 1e300;
   for (int v = 1; v <= 2; ++v) {
     const int wv = v * (64 - 2 * ((halo + v - 1) / v));
@@ -867,7 +902,9 @@ TbShape tb_shape(const St& s, int tb, bool fused) {
       const double t = (r + warm) * tb * ins * std::max(14.0, 4.4 * (double)per_simd);
       if (t < best) {
         best = t;
-        g = {v, r, (int)strips};
+        // (what the levels compute: the forward ones skip the rows they do not have yet)
+        const double rows = std::min(r, s.H) + (fused ? warm : tb - 1.0);
+        g = {v, r, (int)strips, rows * ins * std::max(14.0, 4.4 * (double)per_simd) / 2800.0};
       }
     }
   }
@@ -883,6 +920,32 @@ struct TbPlan {
     TbShape& g = shape[fused][__builtin_ctz(tb)];
     if (!g.vw) g = tb_shape(s, tb, fused);
     return g;
+  }
+  // Whether a call whose stretches are of `len` steps goes one step a launch. A strip is
+  // 48 or 112 columns and a halo, and a chunk some rows and 2 tb more, so on columns or
+  // rows by themselves the time-blocked kernels compute many times their cells: 1.6e7 x 1
+  // cells 196 us a step (one-step kernel 34), 4e6 x 4 with the sine 107 (35), 1 x 1.6e7
+  // with the sine 55 (22). Modelled, us a step: one-step kernels by a launch and what they
+  // read and write (four cells a thread, or one), the others by their instructions; the
+  // factors are those of measured grids from 1 x 1e6 to 4096^2. One step by itself gains
+  // nothing from levels, but only the sine's adjoint loses by them (601 x 333, a
+  // checkpoint every step: 3.3 us a step, 4.0).
+  enum Pass { FWD, TAN, ADJ };
+  bool one_step(int len, Pass pass) {
+    const int tb = tb_of(len);
+    const bool nl = s.rho != 0.f;
+    if (tb <= 1) return pass == ADJ && nl;
+    auto one = [&](double fields, bool vec) {
+      return std::max(3.0, 2.2 + (double)s.n * fields * (vec ? 0.72e-6 : 1.05e-6));
+    };
+    const double blocked = at(tb, false).us;
+    if (pass == TAN) return blocked * (nl ? 1.5 : 2.1) > one(nl ? 3.1 : 2.7, false);
+    if (pass == FWD || !nl) return blocked > one(2.0, s.vec);
+    // the sine's adjoint, with the states it rebuilds
+    const int tf = std::min(tb, kFused);
+    const double again = (double)((len + tf - 1) / tf - 1) * tf / len;
+    return at(tf, true).us + again * blocked >
+           one(3.0, s.vec) + (len - 1.0) / len * one(2.0, s.vec);
   }
   // The launch's arguments from its shape; returns its blocks.
   int fill(const TbShape& g, TbArgs& a) const {
@@ -921,8 +984,7 @@ void tb_steps(TbPlan& plan, int tb, TbArgs a, hipStream_t st) {
 #undef DEX_TB
 }
 
-// One launch of the non-linear adjoint through tb steps (4, 2 or 1).
-constexpr int kFused = 4;
+// One launch of the non-linear adjoint through tb steps (up to kFused).
 void fused_steps(TbPlan& plan, int tb, TbArgs a, hipStream_t st) {
   const TbShape& g = plan.at(tb, true);
   const int blocks = plan.fill(g, a);
@@ -949,7 +1011,7 @@ void step(const St& s, const float* u, float* un, float* snap, hipStream_t st) {
   }
 }
 
-// One adjoint step; form: 1 scatter, 2 gather (vector kernel).
+// One adjoint step; form: 1 scatter, else gather.
 void adj(const St& s, int form, const float* g, const float* u, float* out, bool accumulate,
          hipStream_t st) {
   const unsigned nb = (unsigned)((s.n + 255) / 256);
@@ -994,8 +1056,8 @@ dex_status stencil_fwd(const dex_desc& d, int cfg, const float* u0, const float*
   double* part = (double*)((char*)ws + align256((size_t)s.n * 4));
   const float* cur = u0;
   ProfRange pr(DEX_PROF_STENCIL_FWD, st);
-  if (cfg == 0) {
-    TbPlan plan(s);
+  TbPlan plan(s);
+  if (cfg == 0 && !plan.one_step(std::min(s.every, s.T), TbPlan::FWD)) {
     // each stretch between checkpoints ends in the next one's storage (the last
     // in uT); its inner launches alternate between uT and the workspace field,
     // the one before uT's writing the workspace. The first launch also copies
@@ -1045,15 +1107,20 @@ dex_status stencil_jvp(const dex_desc& d, const float* u0, const float* target, 
   double* part = (double*)((char*)ws + 4 * fb);
   const float *u = u0, *du = du0;
   TbPlan plan(s);
+  const bool one = plan.one_step(s.T, TbPlan::TAN);
   for (int left = s.T, q = 0; left > 0; q ^= 1) {
-    const int tb = tb_of(left);
+    const int tb = one ? 1 : tb_of(left);
     left -= tb;
     TbArgs a{};
     a.in = u;
     a.in2 = du;
     a.out = buf[q][0];
     a.out2 = buf[q][1];
-    tb_steps<TB_TAN>(plan, tb, a, st);
+    if (one)
+      hipLaunchKernelGGL(stencil_tan_step, dim3((unsigned)((s.n + 255) / 256)), dim3(256), 0, st, u,
+                         du, a.out, a.out2, s.H, s.W, s.c, s.rho);
+    else
+      tb_steps<TB_TAN>(plan, tb, a, st);
     u = a.out;
     du = a.out2;
   }
@@ -1103,10 +1170,10 @@ dex_status stencil_vjp(const dex_desc& d, int cfg, const float* u0, const float*
   float* g = lamA;
   float* o = lamB;
   int64_t launches = 0;
-  if (form == 0) {
+  TbPlan plan(s);
+  const bool nl = s.rho != 0.f;
+  if (form == 0 && !plan.one_step(std::min(s.every, s.T), TbPlan::ADJ)) {
     ProfRange pr(DEX_PROF_STENCIL_VJP, st);
-    TbPlan plan(s);
-    const bool nl = s.rho != 0.f;
     const int64_t fe = (int64_t)(fb / 4);
     bool first = true;
     for (int sg = s.nck - 1; sg >= 0; --sg) {
@@ -1182,7 +1249,8 @@ dex_status stencil_vjp(const dex_desc& d, int cfg, const float* u0, const float*
     const int s0 = sg * s.every;
     const int len = std::min(s.every, s.T - s0);
     const float* ck = ckpt + (int64_t)sg * s.n;
-    if (recompute) {
+    const bool rebuild = recompute && (nl || form != 0);
+    if (rebuild) {
       // rebuild u_{s0+1} .. u_{s0+len-1} from the checkpoint
       const float* cur = ck;
       for (int q = 1; q < len; ++q) {
@@ -1195,7 +1263,7 @@ dex_status stencil_vjp(const dex_desc& d, int cfg, const float* u0, const float*
     for (int q = len - 1; q >= 0; --q) {
       const int t = s0 + q;
       const float* ut = nullptr;
-      if (recompute) ut = q == 0 ? ck : seg + (int64_t)(q - 1) * (fb / 4);
+      if (rebuild) ut = q == 0 ? ck : seg + (int64_t)(q - 1) * (fb / 4);
       const bool last = (t == 0);
       float* dst = last ? du0 : o;
       adj(s, form, g, ut, dst, last && accumulate, st);

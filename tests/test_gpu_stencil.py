@@ -221,6 +221,27 @@ def test_sine_of_the_non_linear_term(dev, scale):
     assert err.max() <= rho * 2.0 ** -21
 
 
+# Grids that the default forms take in blocks of steps and one step a launch (few columns,
+# few rows, a stretch of one step): the same bits as the one-step configurations, and the
+# oracle's forward mode.
+@pytest.mark.parametrize("rho", [0.0, -0.2])
+@pytest.mark.parametrize("H,W,steps,every", [(120_000, 1, 9, 4), (150_000, 3, 10, 8), (40_000, 16, 11, 8),
+                                             (1, 300_000, 8, 8), (2, 90_001, 7, 3), (64, 256, 6, 1),
+                                             (130, 130, 17, 8), (61, 67, 1, 8)])
+def test_forms_round_alike(dev, H, W, steps, every, rho):
+    u0, tg = workloads.stencil_inputs(H, W, 41)
+    a = run(u0, tg, steps, every, rho=rho)
+    b = run(u0, tg, steps, every, rho=rho, fcfg=2, vcfg=3)
+    assert a[0] == b[0]
+    assert all(np.array_equal(p, q) for p, q in zip(a[1:], b[1:]))
+    assert rel(a[2], ost.loss_and_grad(u0, tg, steps, rho=rho)[2]) <= 1e-5
+    rng = np.random.default_rng(6)
+    t0, t1 = (rng.standard_normal((H, W)).astype(np.float32) for _ in range(2))
+    want = ost.loss_jvp(u0, tg, t0, t1, steps, rho=rho)
+    scale = np.linalg.norm(a[1].astype(np.float64) - tg) * np.linalg.norm(t0)  # of the terms
+    assert abs(run_jvp(u0, tg, t0, t1, steps, rho) - want) <= 1e-5 * max(abs(want), scale)
+
+
 # Reverse: DEX_ACCUMULATE in every form, and du0 over a buffer that the call reads (the
 # linear adjoint's target and final state, the non-linear one's first checkpoint too).
 @pytest.mark.parametrize("rho", [0.0, -0.2])
