@@ -589,11 +589,18 @@ int gmm_batched_num_configs(const dex_desc& d, int role) {
   return role == DEX_WS_VJP ? kBBwdCfgs : kBFwdCfgs;
 }
 
-// FP32 forward of an untuned call: 128 points a block below 2^21 points in all (12
-// mixtures of 2000: 75 us, 256 points 99; 64 of 10000: 196, 204; 512 of 25000: 3.53 ms,
-// 3.44).
+// FP32 forward of an untuned call: 256 points a block, which reads its records and its
+// item once for more of them (100 mixtures of 20000 points, 256 and 128, us: D = 8, K = 2
+// 130, 218; D = 16, K = 30 253, 268; D = 24, K = 17 303, 311; D = 32, K = 10 329, 309), but
+// 128 where the batch is small and each point's products are many, for an even end (12
+// mixtures of 2000, D to 32, K to 100: 99, 75; 64 of 10000: 204, 196; 512 of 25000: 3.39
+// ms, 3.53), and where it is smaller still (10 of 300, D = 9, K = 5: 29.2, 27.5).
 int gmm_batched_default_config(const dex_desc& d, int role) {
-  return role != DEX_WS_VJP && d.variant == DEX_GMM_PLAIN && d.dims[1] < (int64_t(1) << 21) ? 1 : 0;
+  if (role == DEX_WS_VJP || d.variant != DEX_GMM_PLAIN) return 0;
+  const int64_t B = d.dims[0], sumN = d.dims[1], sumK = d.dims[2], sumKD = d.dims[3];
+  const int D8 = (int)((sumKD / std::max<int64_t>(sumK, 1) + 7) / 8 * 8);
+  const bool heavy = (double)sumK / (4.0 * B) * quad_products(D8) >= 88.0;
+  return sumN < (int64_t(1) << 17) || (sumN < (int64_t(1) << 21) && heavy) ? 1 : 0;
 }
 
 // Blocks of the persistent launches: as many as a CU holds.
