@@ -44,12 +44,14 @@ constexpr int kBBwdCfgs = 4;
 // Points per reverse work item (a block, 16 components). Configuration 0: 4096, halved
 // down to 512 while the batch has fewer than kBItems items, so that a small batch still
 // fills the chip (64 mixtures of 10000 points, chunks of 512, 1024, 2048, 8192: 238,
-// 222, 253, 690 us; 12 of 2000: 73, 116, 193, 230). The plan says what was chosen.
+// 222, 253, 690 us; 12 of 2000: 73, 116, 193, 230), and no instance more than kBChunks
+// chunks, whose moments one block adds up (1e6 points, D = 2, K = 3: 141, 93, 76, 134).
+// The plan says what was chosen.
 inline int64_t bbwd_chunk(int i) {
   const int64_t t[kBBwdCfgs] = {4096, 1024, 2048, 8192};
   return t[i];
 }
-constexpr int64_t kBItems = 2048;
+constexpr int64_t kBItems = 2048, kBChunks = 512;
 __host__ __device__ inline int bfwd_cb(int i) { return i == 0 ? 4 : 2; }
 
 struct PlanHeader {
@@ -440,9 +442,12 @@ PlanBuild build_plan(const int64_t* shapes, int64_t B, int32_t variant) {
   for (int c = 0; c < kBBwdCfgs; ++c) {
     int64_t ch = bbwd_chunk(c);
     for (; c == 0 && ch > 512; ch /= 2) {
-      int64_t items = 0;
-      for (const BInst& I : p.inst) items += (I.K + 15) / 16 * ((I.Npad + ch - 1) / ch);
-      if (items >= kBItems) break;
+      int64_t items = 0, most = 0;
+      for (const BInst& I : p.inst) {
+        items += (I.K + 15) / 16 * ((I.Npad + ch - 1) / ch);
+        most = std::max(most, (I.Npad + ch / 2 - 1) / (ch / 2));
+      }
+      if (items >= kBItems || most > kBChunks) break;
     }
     p.h.bwd_chunk[c] = ch;
     minch = std::min(minch, ch);

@@ -89,6 +89,14 @@ def test_any_dimension(dev, fcfg, bcfg):
     check_instances(shapes, insts, got, range(len(insts)))
 
 
+def test_many_chunks_of_one_instance(dev):
+    """A long instance of few components: no more than 512 chunks, and the sums over them."""
+    shapes = np.array([[600_001, 2, 3], [70, 3, 2]], np.int64)
+    insts = workloads.batched_inputs(shapes, seed=62)
+    got = run_batched(shapes, insts)
+    check_instances(shapes, insts, got, range(len(insts)))
+
+
 SPLIT_SHAPES = np.array([[1000, 8, 10], [1537, 16, 3], [2049, 32, 7], [600, 12, 15], [800, 20, 11],
                          [1000, 31, 6], [450, 9, 40], [3001, 32, 12], [999, 16, 25], [300, 2, 1]],
                         np.int64)
