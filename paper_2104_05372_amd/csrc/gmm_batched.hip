@@ -24,7 +24,9 @@ struct BInst {
   int32_t N, D, K, DP;
   int64_t Npad;
   int64_t a_off, m_off, l_off, x_off, f_off;       // packed inputs / f (elements)
-  int64_t xh_off, xhT_off, Q_off, negc_off, kappa_off, beta_off;  // cache (bytes)
+  // cache (bytes); xhT_off: of instances whose moments go component by component
+  // (blocks_pay), else 0
+  int64_t xh_off, xhT_off, Q_off, negc_off, kappa_off, beta_off;
   int64_t ml_off;     // ws float2 elements
   int64_t fpart_off;  // ws float pairs
   int64_t part_off;   // ws floats
@@ -67,6 +69,7 @@ struct PlanHeader {
   int64_t ws_ml, ws_fpart, ws_counter, ws_part;  // byte offsets into ws
   int64_t comp_off, n_comp;      // (instance, component)
   int64_t bwd_chunk[kBBwdCfgs];  // points per reverse item
+  int64_t blk_off[kBBwdCfgs], n_blk[kBBwdCfgs];  // items of 8 components, one by one
 };
 
 __device__ inline const PlanHeader* hdr(const char* plan) { return (const PlanHeader*)plan; }
@@ -186,6 +189,16 @@ __global__ void __launch_bounds__(256) k_bprep_x(const char* __restrict__ plan,
   const BItem w = ((const BItem*)(plan + h->prepx_off))[blockIdx.x];
   const BInst I = ((const BInst*)(plan + h->inst_off))[w.inst];
   const float* sh = (const float*)(cache + I.sh_off);
+  if (I.xhT_off) {
+    float* xhT = (float*)(cache + I.xhT_off);
+    if (I.DP == 16)
+      prep_x_tile<PREC_F32, 16>(x + I.x_off, I.N, I.D, (int)I.Npad, w.a * 64, nullptr, nullptr, xhT,
+                                nullptr, nullptr, sh);
+    else
+      prep_x_tile<PREC_F32, 32>(x + I.x_off, I.N, I.D, (int)I.Npad, w.a * 64, nullptr, nullptr, xhT,
+                                nullptr, nullptr, sh);
+  }
+  if (!I.split) return;
   _Float16* xh = (_Float16*)(cache + I.xh_off);
   _Float16* xl = (_Float16*)(cache + I.xl_off);
   float* ts = (float*)(cache + I.ts_off);
@@ -341,6 +354,39 @@ __global__ void __launch_bounds__(256, 3) k_bgmm_bwd(const char* __restrict__ pl
   }
 }
 
+// The items of instances whose moments go component by component: eight components, two
+// a wave, from x~^T.
+__global__ void __launch_bounds__(256) k_bgmm_bwd_blocks(const char* __restrict__ plan, int cfg,
+                                                         const char* cache,
+                                                         const float* __restrict__ f, char* ws) {
+  const PlanHeader* h = hdr(plan);
+  const BInst* inst = (const BInst*)(plan + h->inst_off);
+  const BItem* items = (const BItem*)(plan + h->blk_off[cfg]);
+  const int n = (int)h->n_blk[cfg];
+  const int64_t chunk = h->bwd_chunk[cfg];
+  int* counter = (int*)(ws + h->ws_counter) + 2;
+  for (;;) {
+    const int it = next_item(counter);
+    if (it >= n) break;
+    const BItem w = items[it];
+    const BInst I = inst[w.inst];
+    const int pbeg = (int)(w.b * chunk);
+    const int pend = (int)std::min<int64_t>(I.Npad, pbeg + chunk);
+    const size_t E = mom_slot(I.DP);
+    float* P = (float*)(ws + h->ws_part) + I.part_off + (size_t)w.b * I.K * E;
+    const float* beta = (const float*)(cache + I.beta_off);
+    const int kw = w.a * 8 + (threadIdx.x >> 6) * 2;
+    if (I.DP == 16)
+      bwd_mom_unit<16, MP_F32, 2>(cache + I.xhT_off, nullptr, I.N, (int)I.Npad, I.K, kw, pbeg, pend,
+                                  beta, f + I.f_off, 1.f, P, E);
+    else
+      bwd_mom_unit<32, MP_F32, 2>(cache + I.xhT_off, nullptr, I.N, (int)I.Npad, I.K, kw, pbeg, pend,
+                                  beta, f + I.f_off, 1.f, P, E);
+  }
+}
+
+// PACK: the instances of the packed moments, else the others.
+template <bool PACK>
 __global__ void __launch_bounds__(256) k_bbwd_finalize(const char* __restrict__ plan, int cfg,
                                                        const char* ws, const char* cache,
                                                        const float* __restrict__ alphas,
@@ -355,12 +401,13 @@ __global__ void __launch_bounds__(256) k_bbwd_finalize(const char* __restrict__ 
   const PlanHeader* h = hdr(plan);
   const BItem w = ((const BItem*)(plan + h->comp_off))[blockIdx.x];
   const BInst I = ((const BInst*)(plan + h->inst_off))[w.inst];
+  if (PACK == (I.xhT_off != 0)) return;
   const int nch = ((const int32_t*)(plan + h->nch_off))[cfg * h->B + w.inst];
-  const size_t E = mom_pack_slot((I.D + 7) & ~7);
+  const size_t E = PACK ? mom_pack_slot((I.D + 7) & ~7) : mom_slot(I.DP);
   const float* part = (const float*)(ws + h->ws_part) + I.part_off + (size_t)w.a * E;
   // moments of x - shift without the cotangent
   const float c = ct[w.inst];
-  bwd_finalize_mom<32, true>(part, (size_t)I.K * E, nch, w.a, I.K, I.D, I.DP, I.N, alphas + I.a_off,
+  bwd_finalize_mom<32, PACK>(part, (size_t)I.K * E, nch, w.a, I.K, I.D, I.DP, I.N, alphas + I.a_off,
                              means + I.m_off, qd + I.m_off, l + I.l_off, c, d_alphas + I.a_off,
                              d_means + I.m_off, d_qd + I.m_off, d_l + I.l_off, accumulate,
                              (const float*)(cache + I.sh_off), c, c, c);
@@ -378,10 +425,24 @@ struct PlanBuild {
   PlanHeader h{};
   std::vector<BInst> inst;
   std::vector<BItem> prepx, prepq, comp, merge;
-  std::vector<BItem> fwd[kBFwdCfgs], bwd[kBBwdCfgs];
+  std::vector<BItem> fwd[kBFwdCfgs], bwd[kBBwdCfgs], blk[kBBwdCfgs];
   std::vector<int32_t> nch;  // [cfg][B]
   size_t bytes = 0;
 };
+
+// Matrix products per 4 points of an instance's moments: packed, 16 components at a time
+// however many there are; and component by component, the 16x16 blocks of each (a third
+// dearer apiece) with the weights and, in the forward, x~^T to prepare. 100 mixtures of
+// 20000 points, forward and reverse, us: D = 25, K = 3 155 + 390 packed, 246 + 172; D = 32,
+// K = 5 250 + 373, 341 + 223; D = 24, K = 3 145 + 267, 227 + 172; D = 16, K = 3 134 + 135,
+// 177 + 104.
+double packed_cost(const BInst& I) {
+  return (double)(mom_pack_slot((I.D + 7) & ~7) / 16) * ((I.K + 15) / 16);
+}
+double blocks_cost(const BInst& I) {
+  return I.DP == 16 ? 1.34 * I.K + 7.7 : 1.34 * 3 * I.K + 12.2;
+}
+bool blocks_pay(const BInst& I) { return I.D > 8 && blocks_cost(I) < packed_cost(I); }
 
 PlanBuild build_plan(const int64_t* shapes, int64_t B, int32_t variant) {
   PlanBuild p;
@@ -393,6 +454,8 @@ PlanBuild build_plan(const int64_t* shapes, int64_t B, int32_t variant) {
     cache += (int64_t)align256((size_t)bytes);
     return at;
   };
+  // A second kind of launch for some instances is worth it where it saves a tenth of all.
+  double packed = 0.0, best = 0.0;
   for (int64_t b = 0; b < B; ++b) {
     BInst& I = p.inst[b];
     I.N = (int32_t)shapes[3 * b];
@@ -400,6 +463,12 @@ PlanBuild build_plan(const int64_t* shapes, int64_t B, int32_t variant) {
     I.K = (int32_t)shapes[3 * b + 2];
     I.DP = I.D <= 16 ? 16 : 32;
     I.Npad = (I.N + 255) / 256 * 256;
+    packed += I.Npad * packed_cost(I);
+    best += I.Npad * (blocks_pay(I) ? blocks_cost(I) : packed_cost(I));
+  }
+  const bool some_blocks = best < 0.9 * packed;
+  for (int64_t b = 0; b < B; ++b) {
+    BInst& I = p.inst[b];
     I.nblk = (int32_t)(I.Npad / 256);
     I.a_off = a;
     I.m_off = m;
@@ -429,11 +498,12 @@ PlanBuild build_plan(const int64_t* shapes, int64_t B, int32_t variant) {
       I.kappa_off = take((int64_t)I.K * 4);
     }
     I.beta_off = take(4 * nq * I.Npad * 4);
+    if (some_blocks && blocks_pay(I)) I.xhT_off = take(I.Npad * I.DP * 4);  // (never at 0)
     I.ml_off = ml;
     ml += I.Npad;
     I.fpart_off = fp;
     fp += I.nblk;
-    for (int t = 0; I.split && t < I.Npad / 64; ++t) p.prepx.push_back({(int32_t)b, t, 0, 0});
+    for (int t = 0; (I.split || I.xhT_off) && t < I.Npad / 64; ++t) p.prepx.push_back({(int32_t)b, t, 0, 0});
     for (int k = 0; k < (I.split ? I.K : 4 * nq); ++k) p.prepq.push_back({(int32_t)b, k, 0, 0});
     for (int k = 0; k < I.K; ++k) p.comp.push_back({(int32_t)b, k, 0, 0});
     for (int t = 0; t < I.nblk; ++t) p.merge.push_back({(int32_t)b, t, 0, 0});
@@ -454,7 +524,8 @@ PlanBuild build_plan(const int64_t* shapes, int64_t B, int32_t variant) {
   }
   for (BInst& I : p.inst) {
     I.part_off = part;
-    part += (I.Npad + minch - 1) / minch * I.K * (int64_t)mom_pack_slot((I.D + 7) & ~7);
+    part += (I.Npad + minch - 1) / minch * I.K *
+            (int64_t)(I.xhT_off ? mom_slot(I.DP) : mom_pack_slot((I.D + 7) & ~7));
     part = (part + 63) / 64 * 64;
   }
   // forward work lists, longest first
@@ -473,18 +544,26 @@ PlanBuild build_plan(const int64_t* shapes, int64_t B, int32_t variant) {
   p.nch.assign((size_t)kBBwdCfgs * B, 0);
   for (int c = 0; c < kBBwdCfgs; ++c) {
     const int64_t chunk = p.h.bwd_chunk[c];
-    std::vector<std::pair<int64_t, BItem>> v;
+    std::vector<std::pair<int64_t, BItem>> v, vb;
     for (int64_t b = 0; b < B; ++b) {
       const BInst& I = p.inst[b];
       const int nch = (int)((I.Npad + chunk - 1) / chunk);
       p.nch[(size_t)c * B + b] = nch;
-      for (int g = 0; g < (I.K + 15) / 16; ++g)
-        for (int s = 0; s < nch; ++s)
-          v.push_back({std::min<int64_t>(chunk, I.Npad - s * chunk) * mom_pack_slot((I.D + 7) & ~7),
-                       BItem{(int32_t)b, g, s, 0}});
+      const int per = I.xhT_off ? 8 : 16;
+      for (int g = 0; g < (I.K + per - 1) / per; ++g)
+        for (int s = 0; s < nch; ++s) {
+          const int64_t pts = std::min<int64_t>(chunk, I.Npad - s * chunk);
+          const BItem it{(int32_t)b, g, s, 0};
+          if (I.xhT_off)
+            vb.push_back({std::min(2, I.K - 8 * g) * pts * (I.DP == 16 ? 1 : 3), it});
+          else
+            v.push_back({pts * mom_pack_slot((I.D + 7) & ~7), it});
+        }
     }
-    std::stable_sort(v.begin(), v.end(), [](auto& x, auto& y) { return x.first > y.first; });
+    for (auto* l : {&v, &vb})
+      std::stable_sort(l->begin(), l->end(), [](auto& x, auto& y) { return x.first > y.first; });
     for (auto& e : v) p.bwd[c].push_back(e.second);
+    for (auto& e : vb) p.blk[c].push_back(e.second);
   }
   // layout of the plan bytes
   size_t o = align256(sizeof(PlanHeader));
@@ -509,6 +588,8 @@ PlanBuild build_plan(const int64_t* shapes, int64_t B, int32_t variant) {
   for (int c = 0; c < kBBwdCfgs; ++c) {
     p.h.bwd_off[c] = place(p.bwd[c].size() * sizeof(BItem));
     p.h.n_bwd[c] = (int64_t)p.bwd[c].size();
+    p.h.blk_off[c] = place(p.blk[c].size() * sizeof(BItem));
+    p.h.n_blk[c] = (int64_t)p.blk[c].size();
   }
   p.h.nch_off = place(p.nch.size() * sizeof(int32_t));
   p.bytes = o;
@@ -560,9 +641,10 @@ dex_status gmm_batched_plan(const int64_t* shapes, int64_t B, int32_t variant, d
   d->dims[5] = sumND;
   d->dims[6] = (int64_t)p.bytes;
   d->dims[7] = p.h.cache_bytes;
-  // item counts for the launches: prepx, merge, ws bytes, prepq; the persistent
-  // lists' lengths are read on the device
-  d->fparams[0] = (double)p.h.n_prepx;
+  // item counts for the launches: prepx (negative where some moments go component by
+  // component), merge, ws bytes, prepq; the persistent lists' lengths are read on the
+  // device
+  d->fparams[0] = p.h.n_blk[0] ? -(double)p.h.n_prepx : (double)p.h.n_prepx;
   d->fparams[1] = (double)p.h.n_merge;
   d->fparams[2] = (double)p.h.ws_bytes;
   d->fparams[3] = (double)p.h.n_prepq;
@@ -578,8 +660,10 @@ dex_status gmm_batched_plan(const int64_t* shapes, int64_t B, int32_t variant, d
   memcpy(o + p.h.merge_off, p.merge.data(), p.merge.size() * sizeof(BItem));
   for (int c = 0; c < kBFwdCfgs; ++c)
     memcpy(o + p.h.fwd_off[c], p.fwd[c].data(), p.fwd[c].size() * sizeof(BItem));
-  for (int c = 0; c < kBBwdCfgs; ++c)
+  for (int c = 0; c < kBBwdCfgs; ++c) {
     memcpy(o + p.h.bwd_off[c], p.bwd[c].data(), p.bwd[c].size() * sizeof(BItem));
+    memcpy(o + p.h.blk_off[c], p.blk[c].data(), p.blk[c].size() * sizeof(BItem));
+  }
   memcpy(o + p.h.nch_off, p.nch.data(), p.nch.size() * sizeof(int32_t));
   return DEX_OK;
 }
@@ -615,7 +699,7 @@ dex_status gmm_batched_fwd(const dex_desc& d, int cfg, const void* plan, const G
                            void* F, void* f, void* cache, void* ws, hipStream_t st) {
   if (cfg < 0 || cfg >= kBFwdCfgs) return fail(DEX_ERR_INVALID_ARG, "batched forward config");
   const int64_t B = d.dims[0];
-  const int64_t n_prepx = (int64_t)d.fparams[0], n_merge = (int64_t)d.fparams[1];
+  const int64_t n_prepx = std::abs((int64_t)d.fparams[0]), n_merge = (int64_t)d.fparams[1];
   const int64_t n_prepq = (int64_t)d.fparams[3];
   if (n_prepq < 1) return fail(DEX_ERR_INVALID_ARG, "batched GMM: plan of another library version");
   const char* pl = (const char*)plan;
@@ -664,12 +748,20 @@ dex_status gmm_batched_vjp(const dex_desc& d, int cfg, const void* plan, const G
   ProfRange pr(DEX_PROF_BGMM_VJP, st);
   hipLaunchKernelGGL(k_bgmm_bwd, dim3(persistent_blocks(3)), dim3(256), 0, st, pl, cfg,
                      (const float*)in.x, (const char*)cache, (const float*)f, w);
-  pr.end(1);
-  hipLaunchKernelGGL(k_bbwd_finalize, dim3((unsigned)sumK), dim3(256), 0, st, pl, cfg,
-                     (const char*)w, (const char*)cache, (const float*)in.alphas, (const float*)in.qd,
-                     (const float*)in.l, (const float*)in.means, (const float*)ct,
-                     (float*)out.d_alphas,
-                     (float*)out.d_means, (float*)out.d_qd, (float*)out.d_l, accumulate ? 1 : 0);
+  const bool blocks = d.fparams[0] < 0;
+  if (blocks)
+    hipLaunchKernelGGL(k_bgmm_bwd_blocks, dim3(persistent_blocks(4)), dim3(256), 0, st, pl, cfg,
+                       (const char*)cache, (const float*)f, w);
+  pr.end(blocks ? 2 : 1);
+#define DEX_BFIN(PACK_)                                                                           \
+  hipLaunchKernelGGL(k_bbwd_finalize<PACK_>, dim3((unsigned)sumK), dim3(256), 0, st, pl, cfg,     \
+                     (const char*)w, (const char*)cache, (const float*)in.alphas,                 \
+                     (const float*)in.qd, (const float*)in.l, (const float*)in.means,             \
+                     (const float*)ct, (float*)out.d_alphas, (float*)out.d_means,                 \
+                     (float*)out.d_qd, (float*)out.d_l, accumulate ? 1 : 0)
+  DEX_BFIN(true);
+  if (blocks) DEX_BFIN(false);
+#undef DEX_BFIN
   return check_hip(hipGetLastError(), "gmm_batched_vjp");
 }
 

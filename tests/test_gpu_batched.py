@@ -89,6 +89,23 @@ def test_any_dimension(dev, fcfg, bcfg):
     check_instances(shapes, insts, got, range(len(insts)))
 
 
+# Instances of few components (moments component by component) among others of the packed
+# form, both padded dimensions; every chunk.
+FEW = np.array([[1300, 32, 3], [700, 24, 1], [2049, 31, 5], [900, 12, 1], [513, 17, 2], [600, 20, 17],
+                [400, 32, 6], [256, 9, 1], [300, 16, 40], [500, 8, 3]], np.int64)
+
+
+@pytest.mark.parametrize("variant", [0, 3])
+@pytest.mark.parametrize("fcfg,bcfg", [(0, 0), (1, 1), (2, 2), (1, 3), (2, 4)])
+def test_few_components(dev, fcfg, bcfg, variant):
+    from paper_2104_05372_amd import dex
+    assert dex.dex_gmm_batched_plan(FEW, variant)[0].fparams[0] < 0  # (both forms in the plan)
+    insts = workloads.batched_inputs(FEW, seed=61)
+    ct = np.linspace(-2, 1, len(insts)).astype(np.float32)
+    got = run_batched(FEW, insts, fcfg, bcfg, ct=ct, variant=variant)
+    check_instances(FEW, insts, got, range(len(insts)), ct)
+
+
 def test_many_chunks_of_one_instance(dev):
     """A long instance of few components: no more than 512 chunks, and the sums over them."""
     shapes = np.array([[600_001, 2, 3], [70, 3, 2]], np.int64)
