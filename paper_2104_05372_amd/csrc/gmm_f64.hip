@@ -146,7 +146,9 @@ __global__ void __launch_bounds__(64 * f64_fwd_waves(DP)) k_f64_fwd(
         lse_add(m, s, bv);
       }
     } else {
-      constexpr int NRB = DP / 16, NCH = DP / 4, NQ = 2 * NRB * (NRB + 1);
+      // NCHR: chunks of row block rb (DP = 8: the two that hold columns)
+      constexpr int NRB = (DP + 15) / 16, NCH = DP / 4, NQ = DP == 8 ? 2 : 2 * NRB * (NRB + 1);
+      auto NCHR = [](int rb) { return 4 * (rb + 1) < NCH ? 4 * (rb + 1) : NCH; };
       double xb[4][NCH];
 #pragma unroll
       for (int t = 0; t < 4; ++t)
@@ -166,7 +168,7 @@ __global__ void __launch_bounds__(64 * f64_fwd_waves(DP)) k_f64_fwd(
           const int row = 16 * rb + c;
           o.qdr[rb] = qd[(size_t)k * D + min(row, D - 1)];
 #pragma unroll
-          for (int ch = 0; ch < 4 * (rb + 1); ++ch) {
+          for (int ch = 0; ch < NCHR(rb); ++ch) {
             const int col = 4 * ch + g;
             const bool in = row < D && col < row;
             o.q[n++] = l[k * L + (in ? row * (row - 1) / 2 + col : 0)];
@@ -187,7 +189,7 @@ __global__ void __launch_bounds__(64 * f64_fwd_waves(DP)) k_f64_fwd(
           const double ed = exp(o.qdr[rb]);
           f64x4 acc[4] = {{0, 0, 0, 0}, {0, 0, 0, 0}, {0, 0, 0, 0}, {0, 0, 0, 0}};
 #pragma unroll
-          for (int ch = 0; ch < 4 * (rb + 1); ++ch) {
+          for (int ch = 0; ch < NCHR(rb); ++ch) {
             const int col = 4 * ch + g;
             double q = o.q[n++];
             if (4 * ch >= 16 * rb)  // the chunk meets the diagonal
@@ -604,19 +606,25 @@ size_t gmm_f64_bwd_ws(int64_t N, int64_t D, int64_t K) {
 
 void gmm_f64_fwd(int64_t N, int64_t D, int64_t K, const GmmPtrs& in, double* beta, double* f,
                  double* fpart, double* F, hipStream_t st) {
-  const int dp = f64_dp(D), maxw = f64_fwd_waves(dp);
+  // (D = 5 .. 8: two chunks of four columns instead of four: N = 1e6, D = 8, K = 3 59 us
+  // for 76, with the blocks below 45)
+  const int dp = D > 4 && D <= 8 ? 8 : f64_dp(D), maxw = f64_fwd_waves(dp);
   const int64_t tiles = (N + 63) / 64;
   // One block, which also finishes F, where its waves' components take no longer
   // than the launch it saves (about 10 000 cycles; cycles per 64 points and
   // component by padded dimension); else one tile per block and enough waves
   // sharing its components to fill the chip (about four per SIMD).
-  const int64_t cost = dp == 4 ? 500 : dp == 16 ? 900 : dp == 32 ? 2200 : 6000;
+  const int64_t cost = dp == 4 ? 500 : dp == 8 ? 700 : dp == 16 ? 900 : dp == 32 ? 2200 : 6000;
   int64_t tt = 1, ks;
   if (tiles <= maxw && ((K + maxw / tiles - 1) / (maxw / tiles)) * cost <= 10000) {
     tt = tiles;
     ks = std::min<int64_t>(maxw / tiles, K);
   } else {
     ks = std::min<int64_t>({(4096 + tiles - 1) / tiles, maxw, K});
+    // with a wave a tile, four tiles a block, so that starting blocks does not bound the
+    // small ones (N = 1e6, D = 1, K = 2 45 us with one tile, 26; D = 16, K = 3 78, 69; D =
+    // 32, K = 2 155, 190)
+    if (tiles >= 4096 && dp <= 16) tt = 4;
   }
   const unsigned blocks = (unsigned)((tiles + tt - 1) / tt), threads = (unsigned)(64 * tt * ks);
   const double *al = (const double*)in.alphas, *mu = (const double*)in.means,
@@ -624,7 +632,10 @@ void gmm_f64_fwd(int64_t N, int64_t D, int64_t K, const GmmPtrs& in, double* bet
 #define DEX_F64_FWD(DP_)                                                                    \
   hipLaunchKernelGGL((k_f64_fwd<DP_>), dim3(blocks), dim3(threads), 0, st, al, mu, qd, l, x, \
                      (int)N, (int)D, (int)K, (int)ks, beta, f, fpart, F)
-  DEX_F64_DP(dp, DEX_F64_FWD)
+  if (dp == 8)
+    DEX_F64_FWD(8);
+  else
+    DEX_F64_DP(dp, DEX_F64_FWD)
 #undef DEX_F64_FWD
   if (blocks > 1)
     hipLaunchKernelGGL(k_f64_finalize_F, dim3(1), dim3(256), 0, st, fpart, (int)blocks, al, (int)K, N,

@@ -154,6 +154,15 @@ def test_many_and_few_moment_slots(dev, variant, N, D, K):
             assert rel(a, b) <= 1e-3
 
 
+# A wave a tile and four tiles a block (2^18 points and more), D of one vector-ALU form, of
+# half a matrix block and of a whole one; the last block short.
+@pytest.mark.parametrize("N,D,K", [(262_081, 3, 3), (262_200, 7, 2), (262_145, 13, 2), (262_144, 8, 1)])
+def test_fp64_tiles_by_four(dev, N, D, K):
+    from paper_2104_05372_amd import dex
+    g = workloads.gmm_inputs(N, D, K, 930 + D)
+    check(run_gmm(g, dex.DEX_F64, dex.DEX_GMM_PLAIN), oracle_gmm(g), 1e-10, f"fp64 {N},{D},{K}")
+
+
 @pytest.mark.parametrize("offset", [100.0, 1000.0])
 @pytest.mark.parametrize("D,variant", [(64, 1), (16, 1), (33, 1), (64, 0), (20, 2)])
 def test_data_far_from_origin(dev, offset, D, variant):
