@@ -48,11 +48,12 @@ DEX_DEV int mom_slots(int64_t kg, int x, int64_t nkg, int64_t nsteps, int Wx) {
 }
 
 // A block sums 64 consecutive elements, one per lane; its W waves share the
-// slots: 8 / W XCDs each in order (W = 4), or every W / 8-th slot of one XCD (W =
+// slots: 8 / W XCDs each in order (W = 4, 1), or every W / 8-th slot of one XCD (W =
 // 16), and the waves' sums are added in wave order. Bound by the latency of the
 // slot loads, so they are spread over waves as far as there are few elements: with
 // few components there are many slots each (N = 1e5, D = 20, K = 5: 340) and one
-// thread per element walked them in 190 us.
+// thread per element walked them in 190 us. With very many elements one wave takes
+// all eight XCDs (reverse pass at N = 100, D = 64, K = 1000: 94 us with W = 4, 82).
 template <int W>
 __global__ void __launch_bounds__(64 * W) k_mom_reduce(float* __restrict__ part, int64_t E, int K,
                                                        int gw, int64_t nsteps, int Wx, int SX) {
@@ -761,7 +762,10 @@ dex_status gmm_vjp(const dex_desc& d, int cfg, const GmmPtrs& in, const void* f,
   pr.end(1);
   const int64_t E = (int64_t)mom_slot(s.g.DP);
   const unsigned nb = (unsigned)((s.g.K * E + 63) / 64);
-  if (nb <= 512)
+  if (nb > 16384)
+    hipLaunchKernelGGL(k_mom_reduce<1>, dim3(nb), dim3(64), 0, st, part, E, (int)s.g.K, sp.gw,
+                       sp.nsteps, sp.W, (int)sp.T);
+  else if (nb <= 512)
     hipLaunchKernelGGL(k_mom_reduce<16>, dim3(nb), dim3(1024), 0, st, part, E, (int)s.g.K, sp.gw,
                        sp.nsteps, sp.W, (int)sp.T);
   else

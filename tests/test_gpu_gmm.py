@@ -154,6 +154,14 @@ def test_many_and_few_moment_slots(dev, variant, N, D, K):
             assert rel(a, b) <= 1e-3
 
 
+@pytest.mark.parametrize("N,D,K", [(300, 64, 420), (900, 16, 3900)])
+def test_very_many_moments(dev, N, D, K):
+    """More than 2^20 moment elements: their slots summed by one wave each."""
+    from paper_2104_05372_amd import dex
+    g = workloads.gmm_inputs(N, D, K, 920 + D, np.float32)
+    check(run_gmm(g, dex.DEX_F32, dex.DEX_GMM_PLAIN), oracle_gmm(g), 1e-5, f"moments {N},{D},{K}")
+
+
 # A wave a tile and four tiles a block (2^18 points and more), D of one vector-ALU form, of
 # half a matrix block and of a whole one; the last block short.
 @pytest.mark.parametrize("N,D,K", [(262_081, 3, 3), (262_200, 7, 2), (262_145, 13, 2), (262_144, 8, 1)])
