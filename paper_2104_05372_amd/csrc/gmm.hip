@@ -121,7 +121,9 @@ __global__ void __launch_bounds__(64 * W) k_mom_reduce(float* __restrict__ part,
   }
 }
 
-// Forward mode of the FP64 objective on the vector ALU. Block
+// Forward mode on the vector ALU: FP64, and FP32 at D <= 4 with few components, where
+// quads of components are mostly padding and the start of their blocks (N = 1e6, D = 2, K =
+// 5: 27 us, quads 42; K = 64: 217, 153). Block
 // (256 points, chunk of kJvpKC components); the components of the chunk are
 // staged in LDS in turn. For point i and component k, with r = x_i - mu_k,
 //   y = Q_k r, dy = dQ_k r - Q_k dmu_k (dQ: diagonal exp(qd) dqd, strict lower
@@ -131,33 +133,33 @@ __global__ void __launch_bounds__(64 * W) k_mom_reduce(float* __restrict__ part,
 // blockIdx.x].
 constexpr int kJvpKC = 8;
 
-template <int DB>
+template <typename T, int DB>
 __global__ void __launch_bounds__(256) gmm_jvp_valu(
-    const double* __restrict__ alphas, const double* __restrict__ means,
-    const double* __restrict__ qd, const double* __restrict__ l, const double* __restrict__ x,
-    const double* __restrict__ f, int N, int D, int K, const double* __restrict__ da,
-    const double* __restrict__ dm, const double* __restrict__ dq, const double* __restrict__ dl,
+    const T* __restrict__ alphas, const T* __restrict__ means,
+    const T* __restrict__ qd, const T* __restrict__ l, const T* __restrict__ x,
+    const T* __restrict__ f, int N, int D, int K, const T* __restrict__ da,
+    const T* __restrict__ dm, const T* __restrict__ dq, const T* __restrict__ dl,
     double* __restrict__ part) {
-  __shared__ double Qs[DB][DB + 1], dQs[DB][DB + 1];
-  __shared__ double mus[DB], qdm[DB], kap[2];
+  __shared__ T Qs[DB][DB + 1], dQs[DB][DB + 1];
+  __shared__ T mus[DB], qdm[DB], kap[2];
   __shared__ double sh[32];
   const int t = threadIdx.x, p = blockIdx.x * 256 + t;
   const bool valid = p < N;
   const int L = D * (D - 1) / 2;
-  double xr[DB];
+  T xr[DB];
 #pragma unroll
-  for (int b = 0; b < DB; ++b) xr[b] = (valid && b < D) ? x[(size_t)p * D + b] : 0.0;
-  const double fp = valid ? f[p] : 0.0;
+  for (int b = 0; b < DB; ++b) xr[b] = (valid && b < D) ? x[(size_t)p * D + b] : T(0);
+  const T fp = valid ? f[p] : T(0);
   double acc = 0.0;
   const int k0 = blockIdx.y * kJvpKC, k1 = min(K, k0 + kJvpKC);
   for (int k = k0; k < k1; ++k) {
     __syncthreads();
     for (int e = t; e < DB * DB; e += 256) {
       const int a = e / DB, b = e % DB;
-      double q = 0, dqv = 0;
+      T q = 0, dqv = 0;
       if (a < D && b < D) {
         if (a == b) {
-          const double ev = exp(qd[(size_t)k * D + a]);
+          const T ev = dexp<T>(qd[(size_t)k * D + a]);
           q = ev;
           dqv = ev * dq[(size_t)k * D + a];
         } else if (a > b) {
@@ -169,9 +171,9 @@ __global__ void __launch_bounds__(256) gmm_jvp_valu(
       Qs[a][b] = q;
       dQs[a][b] = dqv;
     }
-    if (t < DB) mus[t] = t < D ? means[(size_t)k * D + t] : 0.0;
+    if (t < DB) mus[t] = t < D ? means[(size_t)k * D + t] : T(0);
     if (t < 64) {
-      double s = 0, ds = 0;
+      T s = 0, ds = 0;
       for (int d = t; d < D; d += 64) {
         s += qd[(size_t)k * D + d];
         ds += dq[(size_t)k * D + d];
@@ -185,19 +187,19 @@ __global__ void __launch_bounds__(256) gmm_jvp_valu(
     }
     __syncthreads();
     if (t < DB) {  // Q_k dmu_k
-      double v = 0;
+      T v = 0;
       for (int b = 0; b <= t && b < D; ++b) v += Qs[t][b] * dm[(size_t)k * D + b];
       qdm[t] = v;
     }
     __syncthreads();
-    double r[DB];
+    T r[DB];
 #pragma unroll
-    for (int b = 0; b < DB; ++b) r[b] = b < D ? xr[b] - mus[b] : 0.0;
-    double s = 0, sd = 0;
+    for (int b = 0; b < DB; ++b) r[b] = b < D ? xr[b] - mus[b] : T(0);
+    T s = 0, sd = 0;
 #pragma unroll
     for (int a = 0; a < DB; ++a) {
       if (a < D) {
-        double y = 0, dy = -qdm[a];
+        T y = 0, dy = -qdm[a];
 #pragma unroll
         for (int b = 0; b <= a; ++b) {
           y += Qs[a][b] * r[b];
@@ -207,7 +209,7 @@ __global__ void __launch_bounds__(256) gmm_jvp_valu(
         sd += y * dy;
       }
     }
-    if (valid) acc += exp(kap[0] - 0.5 * s - fp) * (kap[1] - sd);
+    if (valid) acc += (double)(dexp<T>(kap[0] - T(0.5) * s - fp) * (kap[1] - sd));
   }
   acc = block_sum(acc, sh);
   if (t == 0) part[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = acc;
@@ -560,6 +562,9 @@ static int jvp_shares(const GmmGeom& g) {
   }
   return best;
 }
+static int64_t valu_parts(const GmmGeom& g) {
+  return (g.N + 255) / 256 * ((g.K + kJvpKC - 1) / kJvpKC);
+}
 static JvpLayout jvp_layout(const Shape& s) {
   JvpLayout j{};
   size_t o = 0;
@@ -576,6 +581,8 @@ static JvpLayout jvp_layout(const Shape& s) {
     j.dkq = take(Kp * 4);
     j.disc = take(Kp * 4);
     j.nparts = qf_tan_parts(s.g);
+  } else if (s.mfma && s.g.D <= 4 && s.g.K <= 10) {
+    j.nparts = valu_parts(s.g);
   } else if (s.mfma && s.g.D <= 32) {
     j.quad = quad_jvp_split(s.g);
     j.rec = take(quad_rec_bytes(s.g));
@@ -586,7 +593,7 @@ static JvpLayout jvp_layout(const Shape& s) {
     j.ks = jvp_shares(s.g);
     j.nparts = (s.g.N + 63) / 64 * j.ks;
   } else {
-    j.nparts = ((s.g.N + 255) / 256) * ((s.g.K + kJvpKC - 1) / kJvpKC);
+    j.nparts = valu_parts(s.g);
   }
   // the partials of the most shares any smaller N or K may have, so that scratch sized for
   // the largest call serves all
@@ -780,25 +787,26 @@ dex_status gmm_vjp(const dex_desc& d, int cfg, const GmmPtrs& in, const void* f,
   return check_hip(hipGetLastError(), "gmm_vjp (MFMA)");
 }
 
-// FP64
 static void launch_jvp_valu(const Shape& s, const GmmPtrs& in, const void* f, const GmmGrads& t,
                             double* part, hipStream_t st) {
   dim3 grid((unsigned)((s.g.N + 255) / 256), (unsigned)((s.g.K + kJvpKC - 1) / kJvpKC));
-#define DEX_JV(DB)                                                                            \
-  hipLaunchKernelGGL((gmm_jvp_valu<DB>), grid, dim3(256), 0, st, (const double*)in.alphas,     \
-                     (const double*)in.means, (const double*)in.qd, (const double*)in.l, (const double*)in.x,     \
-                     (const double*)f, (int)s.g.N, (int)s.g.D, (int)s.g.K, (const double*)t.d_alphas,   \
-                     (const double*)t.d_means, (const double*)t.d_qd, (const double*)t.d_l, part)
-  if (s.g.D <= 4) {
-    DEX_JV(4);
+#define DEX_JV(T, DB)                                                                             \
+  hipLaunchKernelGGL((gmm_jvp_valu<T, DB>), grid, dim3(256), 0, st, (const T*)in.alphas,          \
+                     (const T*)in.means, (const T*)in.qd, (const T*)in.l, (const T*)in.x,         \
+                     (const T*)f, (int)s.g.N, (int)s.g.D, (int)s.g.K, (const T*)t.d_alphas,       \
+                     (const T*)t.d_means, (const T*)t.d_qd, (const T*)t.d_l, part)
+  if (s.mfma) {
+    DEX_JV(float, 4);
+  } else if (s.g.D <= 4) {
+    DEX_JV(double, 4);
   } else if (s.g.D <= 8) {
-    DEX_JV(8);
+    DEX_JV(double, 8);
   } else if (s.g.D <= 16) {
-    DEX_JV(16);
+    DEX_JV(double, 16);
   } else if (s.g.D <= 32) {
-    DEX_JV(32);
+    DEX_JV(double, 32);
   } else {
-    DEX_JV(64);
+    DEX_JV(double, 64);
   }
 #undef DEX_JV
 }

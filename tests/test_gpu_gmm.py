@@ -341,6 +341,19 @@ def test_quads_of_components(dev, N, D, K, offset):
     assert abs(got - want) <= 1e-5 * abs(want), (got, want)
 
 
+# FP32 forward mode at D <= 4: the vector ALU up to ten components (one and two chunks of
+# eight), quads above; every variant takes it.
+@pytest.mark.parametrize("variant,tol", [(0, 1e-5), (1, TOL_MIXED16), (2, TOL_BF16X3)])
+@pytest.mark.parametrize("N,D,K", [(1, 1, 1), (255, 2, 8), (257, 3, 9), (5000, 4, 10), (5000, 4, 11)])
+def test_forward_mode_few_dimensions(dev, N, D, K, variant, tol):
+    from paper_2104_05372_amd import dex
+    g = workloads.gmm_inputs(N, D, K, 940 + D, np.float32)
+    tangent = along_gradient(g, 7 * D + K)
+    got, _ = run_gmm_jvp(g, dex.DEX_F32, variant, tangent)
+    want = ogmm.jvp(*g.params(), g.x, tangent)
+    assert abs(got - want) <= tol * abs(want), (got, want)
+
+
 @pytest.mark.parametrize("dead", [0, 1, 6])
 def test_component_of_no_weight(dev, dead):
     """alpha = -inf takes a component out, wherever it stands in its quad."""
