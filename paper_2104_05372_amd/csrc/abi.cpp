@@ -712,6 +712,7 @@ dex_status dex_autotune(const dex_desc* d, int32_t role, const dex_buf* in, int3
   DEX_TRY(ensure_device());
   int32_t nc = 1;
   DEX_TRY(dex_num_configs(d, role, &nc));
+  if (d->kind == DEX_GMM) nc = gmm_tuned_configs(*d, role);
   hipStream_t s = (hipStream_t)hip_stream;
   hipEvent_t e0, e1;
   DEX_TRY(check_hip(hipEventCreate(&e0), "event"));

@@ -625,6 +625,11 @@ int gmm_num_configs(const dex_desc& d, int role) {
   return role == DEX_WS_VJP ? nbwd(s) : nfwd(s);
 }
 
+// (Quads have one form: every configuration of the FP32 forward at D <= 32 launches it.)
+int gmm_tuned_configs(const dex_desc& d, int role) {
+  return role != DEX_WS_VJP && quads(shape_of(d)) ? 1 : gmm_num_configs(d, role);
+}
+
 // The configuration of an untuned call, by the form and by N K (the work per
 // element of a component's moments). Measured whole calls, us:
 //   forward FP32, D > 32 (at D <= 32 every configuration is the quads'): two

@@ -42,6 +42,7 @@ size_t gmm_cache_bytes(const dex_desc& d);
 size_t gmm_ws_bytes(const dex_desc& d, int role);
 int gmm_num_configs(const dex_desc& d, int role);
 int gmm_default_config(const dex_desc& d, int role);  // of an untuned call
+int gmm_tuned_configs(const dex_desc& d, int role);   // the first so many that differ
 int gmm_batched_default_config(const dex_desc& d, int role);
 dex_status gmm_fwd(const dex_desc& d, int cfg, const GmmPtrs& in, void* F, void* f,
                    void* cache, void* ws, hipStream_t s);

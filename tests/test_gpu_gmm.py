@@ -459,3 +459,29 @@ def test_nan_point_propagates_and_leaves_no_state(dev, variant, D):
     for a, b in zip(got[2], go):
         assert np.array_equal(np.isnan(a), np.isnan(np.asarray(b).reshape(a.shape)))
     check(run_gmm(g, 2, variant), oracle_gmm(g), tol, "clean call after a NaN call")
+
+
+def test_autotuner_times_each_form_once(dev):
+    """The FP32 forward at D <= 32 has one form, whatever its configuration: the tuner runs
+    it as one candidate (a warm-up and three timed calls), and every number stays accepted."""
+    from paper_2104_05372_amd import dex
+    g = workloads.gmm_inputs(500, 16, 5, 97, np.float32)
+    t = [torch.tensor(np.ascontiguousarray(a), device=dev) for a in (g.alphas, g.means, g.qd, g.l, g.x)]
+    d = dex.gmm_desc(500, 16, 5, dex.DEX_F32, dex.DEX_GMM_PLAIN)
+    F, f = torch.empty(1, device=dev), torch.empty(500, device=dev)
+    cache = torch.empty(dex.dex_workspace_bytes(d, dex.DEX_WS_RESID), dtype=torch.uint8, device=dev)
+    ws = dex.workspace(dex.dex_workspace_bytes(d, dex.DEX_WS_FWD), dev)
+    dex.dex_profile_enable(True)
+    dex.dex_profile_reset()
+    try:
+        assert dex.dex_autotune(d, dex.DEX_WS_FWD, t, [F], [f, cache], [], [], ws) == 1
+        assert dex.dex_profile_read("GMM_FWD")[1] == 4
+    finally:
+        dex.dex_profile_enable(False)
+        dex.dex_profile_reset()
+        dex.dex_autotune_reset()
+    want = F.item()
+    for c in range(1, dex.dex_num_configs(d, dex.DEX_WS_FWD) + 1):
+        d.config = c
+        dex.dex_fwd(d, t, [F.zero_()], [f, cache], ws)
+        assert F.item() == want
