@@ -486,8 +486,8 @@ CacheLayout cache_layout(const Shape& s) {
     c.xlT = lo ? take(g.Npad * g.DP * mom_es(s)) : 0;
     c.Qh = take(quads(s) ? quad_rec_bytes(g) : g.K * g.DP * g.DP * es);
     c.Ql = lo ? take(g.K * g.DP * g.DP * es) : 0;
-    c.negc = take(g.K * g.DP * 4);
-    c.kappa = take(g.K * 4);
+    c.negc = quads(s) ? 0 : take(g.K * g.DP * 4);  // (quads: in their records)
+    c.kappa = quads(s) ? 0 : take(g.K * 4);
     c.shift = take(64 * 4);
     c.beta = take(beta_rows(g.K) * g.Npad * 4);
     if (qf_eligible(g, s.prec)) {
