@@ -485,3 +485,40 @@ def test_autotuner_times_each_form_once(dev):
         d.config = c
         dex.dex_fwd(d, t, [F.zero_()], [f, cache], ws)
         assert F.item() == want
+
+
+# The 16-bit and split forms at sizes with many and few moment slots, against the oracle
+# (the 16-bit one where its bound is meant: with 700 points a component its d_qd is off by
+# 1.25e-2 whatever the slots), and two configurations against each other to what their
+# sums' order can change: 2e-6 of FP32 sums magnified some 200 times.
+@pytest.mark.parametrize("N,D,K,variant,tol", [(30_011, 20, 1, 1, TOL_MIXED16), (40_000, 2, 5, 1, TOL_MIXED16),
+                                               (20_003, 64, 3, 1, TOL_MIXED16), (31_999, 8, 47, 1, None),
+                                               (30_011, 20, 1, 2, TOL_BF16X3), (40_000, 2, 5, 2, TOL_BF16X3),
+                                               (20_003, 64, 3, 2, TOL_BF16X3), (31_999, 8, 47, 2, TOL_BF16X3)])
+def test_moment_slots_against_oracle(dev, N, D, K, variant, tol):
+    g = workloads.gmm_inputs(N, D, K, 900 + D, np.float32)
+    got = run_gmm(g, 2, variant)
+    if tol is not None:
+        check(got, oracle_gmm(g), tol, f"slots v{variant} {N},{D},{K}")
+    for a, b in zip(got[2], run_gmm(g, 2, variant, bcfg=1)[2]):
+        assert rel(a, b) <= 4e-4
+
+
+# A NaN coordinate and an infinite one in the kernels of every form: the point's f and every
+# gradient entry of the objective are NaN where the oracle's are, and only there.
+@pytest.mark.parametrize("dtype,N,D,K", [(1, 700, 3, 5), (1, 700, 8, 4), (1, 700, 16, 30), (1, 9000, 40, 3),
+                                         (2, 700, 8, 5), (2, 700, 24, 9), (2, 700, 32, 4)])
+def test_non_finite_points(dev, dtype, N, D, K):
+    g = workloads.gmm_inputs(N, D, K, 78, np.float64 if dtype == 1 else np.float32)
+    tol = 1e-10 if dtype == 1 else 1e-5
+    fo = oracle_gmm(g)[1]
+    others = np.delete(np.arange(N), 123)
+    for bad in (np.nan, np.inf):
+        x = g.x.copy()
+        x[123, D - 1] = bad
+        F, f, grads = run_gmm(workloads.GMMInputs(g.alphas, g.means, g.qd, g.l, x), dtype, 0)
+        assert not np.isfinite(F) and not np.isfinite(f[123])
+        assert np.all(np.isfinite(f[others])) and rel(f[others], fo[others]) <= tol
+        if np.isnan(bad):
+            assert all(np.all(np.isnan(a)) for a in grads)
+    check(run_gmm(g, dtype, 0), oracle_gmm(g), tol, "clean call afterwards")
