@@ -717,37 +717,43 @@ dex_status dex_autotune(const dex_desc* d, int32_t role, const dex_buf* in, int3
   hipEvent_t e0, e1;
   DEX_TRY(check_hip(hipEventCreate(&e0), "event"));
   DEX_TRY(check_hip(hipEventCreate(&e1), "event"));
-  float best_ms = 1e30f;
-  int best_c = 0;
-  dex_status last = DEX_OK;
-  for (int c = 0; c < nc; ++c) {
+  auto run = [&](int c) -> dex_status {
     dex_desc dc = *d;
     dc.config = c + 1;
-    auto run = [&]() -> dex_status {
-      if (role == DEX_WS_FWD)
-        return dex_fwd(&dc, in, n_in, out, n_out, resid, n_resid, workspace, ws_bytes_, hip_stream);
-      return dex_vjp(&dc, in, n_in, resid, n_resid, ct_out, n_ct_out, ct_in, n_ct_in, 0, workspace,
-                     ws_bytes_, hip_stream);
-    };
-    dex_status st = run();  // warm-up
-    if (st != DEX_OK) {
-      last = st;
-      continue;
-    }
-    std::vector<float> ts;
-    for (int r = 0; r < 3; ++r) {
+    if (role == DEX_WS_FWD)
+      return dex_fwd(&dc, in, n_in, out, n_out, resid, n_resid, workspace, ws_bytes_, hip_stream);
+    return dex_vjp(&dc, in, n_in, resid, n_resid, ct_out, n_ct_out, ct_in, n_ct_in, 0, workspace,
+                   ws_bytes_, hip_stream);
+  };
+  // a warm-up of each candidate, then three rounds over all of them: timed one candidate
+  // after the other, the first paid for the clocks (512 mixtures, 256 points a block: 3.57
+  // ms at first, 3.28 in turn with 128 points at 3.41)
+  dex_status last = DEX_OK;
+  std::vector<std::vector<float>> ts(nc);
+  std::vector<bool> runs(nc, false);
+  for (int c = 0; c < nc; ++c) {
+    const dex_status st = run(c);
+    runs[c] = st == DEX_OK;
+    if (st != DEX_OK) last = st;
+  }
+  for (int r = 0; r < 3; ++r)
+    for (int c = 0; c < nc; ++c) {
+      if (!runs[c]) continue;
       hipEventRecord(e0, s);
-      st = run();
+      const dex_status st = run(c);
       hipEventRecord(e1, s);
       hipEventSynchronize(e1);
       float ms = 0.f;
       hipEventElapsedTime(&ms, e0, e1);
-      if (st == DEX_OK) ts.push_back(ms);
+      if (st == DEX_OK) ts[c].push_back(ms);
     }
-    if (ts.empty()) continue;
-    std::sort(ts.begin(), ts.end());
-    if (ts[ts.size() / 2] < best_ms) {
-      best_ms = ts[ts.size() / 2];
+  float best_ms = 1e30f;
+  int best_c = 0;
+  for (int c = 0; c < nc; ++c) {
+    if (ts[c].empty()) continue;
+    std::sort(ts[c].begin(), ts[c].end());
+    if (ts[c][ts[c].size() / 2] < best_ms) {
+      best_ms = ts[c][ts[c].size() / 2];
       best_c = c;
     }
   }
