@@ -866,12 +866,13 @@ void fused_launch(const TbArgs& a, int blocks, hipStream_t st) {
 }
 
 // Launch shape of a tb-step launch on a grid: columns per lane, rows per wave,
-// strips; and the modelled time of one of its steps.
+// strips; and the modelled time of one of its steps. row: the least cycles that a wave
+// spends on a row, whatever its levels.
 struct TbShape {
   int vw, rb, strips;
   double us;
 };
-TbShape tb_shape(const St& s, int tb, bool fused) {
+TbShape tb_shape(const St& s, int tb, bool fused, double row) {
   const bool nl = s.rho != 0.f;
   const int halo = fused ? std::max(2 * (tb - 1), tb) : tb;
   const double warm = fused ? halo + 2.0 * tb - 1.0 : 1.5 * tb;
@@ -899,7 +900,8 @@ TbShape tb_shape(const St& s, int tb, bool fused) {
       const int64_t chunks = std::max<int64_t>(1, (int64_t)n * simds / strips);
       const int r = (int)std::max<int64_t>(4, (s.H + chunks - 1) / chunks);
       const int64_t per_simd = (strips * ((s.H + r - 1) / r) + simds - 1) / simds;
-      const double t = (r + warm) * tb * ins * std::max(14.0, 4.4 * (double)per_simd);
+      const double t =
+          (r + warm) * std::max(row, tb * ins * std::max(14.0, 4.4 * (double)per_simd));
       if (t < best) {
         best = t;
         // (what the levels compute: the forward ones skip the rows they do not have yet)
@@ -913,12 +915,25 @@ TbShape tb_shape(const St& s, int tb, bool fused) {
 
 // The shapes of one call's launches, found once per number of steps.
 struct TbPlan {
+  // A wave of the forward kernel is taken to need 900 cycles for a row, as long as its
+  // load and its store (with one or two levels there is no more to do meanwhile), so that
+  // short stretches get more waves: a checkpoint every step at 4096^2 32 steps 1036 us
+  // (0: 1220, 600: 1096, 1400: 1036) and 1106 with the sine (1230, 1231, 1108), 1000^2
+  // 146 (153), every 7th at 1500 x 700 77 (81), every 5th at 4096^2 392 (394; 1400: 414).
+  // The adjoint reads a row as far ahead as its levels let it and loses by it (4096^2
+  // every step 865 us, 794 without).
+  static constexpr double kFwdRow = 900.0;
   const St& s;
-  TbShape shape[2][4];
+  TbShape shape[3][4];
   explicit TbPlan(const St& s_) : s(s_), shape{} {}
   const TbShape& at(int tb, bool fused) {
     TbShape& g = shape[fused][__builtin_ctz(tb)];
-    if (!g.vw) g = tb_shape(s, tb, fused);
+    if (!g.vw) g = tb_shape(s, tb, fused, 0.0);
+    return g;
+  }
+  const TbShape& fwd_at(int tb) {
+    TbShape& g = shape[2][__builtin_ctz(tb)];
+    if (!g.vw) g = tb_shape(s, tb, false, kFwdRow);
     return g;
   }
   // Whether a call whose stretches are of `len` steps goes one step a launch. A strip is
@@ -962,7 +977,7 @@ struct TbPlan {
 // One launch of tb steps (a power of two up to kTB).
 template <int MODE>
 void tb_steps(TbPlan& plan, int tb, TbArgs a, hipStream_t st) {
-  const TbShape& g = plan.at(tb, false);
+  const TbShape& g = MODE == TB_FWD ? plan.fwd_at(tb) : plan.at(tb, false);
   const bool nl = plan.s.rho != 0.f;
   const int vw = g.vw, blocks = plan.fill(g, a);
 #define DEX_TB(T_)                                     \
