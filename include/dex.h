@@ -258,9 +258,11 @@ dex_status dex_vjp(const dex_desc* d,
  *     16-bit variant at D = 64: dbeta comes from one FP16 matrix-core product
  *     of the forward's second-order features with tangent coefficients (built
  *     from dP = dQ^T Q + Q^T dQ), weighted by the forward's beta residual.
- *     Every other form: one vector-ALU pass in the descriptor dtype (FP32 forms
- *     compute in FP32). The per-block sums and the final sum are FP64 in a
- *     fixed order. Workspace: DEX_WS_JVP bytes.
+ *     Every other form with FP32 storage: y and dy by FP32 matrix-core products,
+ *     D <= 32 four components at a time, D > 32 component by component; D <= 4
+ *     with at most 10 components, and FP64, one vector-ALU pass in the descriptor
+ *     dtype. The per-wave or per-block sums and the final sum are FP64 in a fixed
+ *     order. Workspace: DEX_WS_JVP bytes.
  *   Other kinds: DEX_ERR_UNSUPPORTED.
  * All buffers are device memory owned by the caller; t_out is overwritten.
  * Argument errors are reported before anything is enqueued; the call enqueues
@@ -382,10 +384,12 @@ void dex_autotune_reset(void);
  */
 #define DEX_PROF_GMM_FWD      0 /* matrix-core forward tile kernel            */
 #define DEX_PROF_GMM_VJP      1 /* matrix-core reverse tile kernel            */
-#define DEX_PROF_SCATTER      2 /* float row scatter (sort + segmented sum)   */
+#define DEX_PROF_SCATTER      2 /* float row scatter (sort + segmented sum; in the
+                                 * gather's reverse with the weights' cotangent) */
 #define DEX_PROF_HIST         3 /* LDS-private histogram kernel               */
 #define DEX_PROF_GATHER       4 /* gather-scale forward                       */
-#define DEX_PROF_GATHER_DW    5 /* cotangent of the gather weights            */
+#define DEX_PROF_GATHER_DW    5 /* cotangent of the gather weights in a pass of its
+                                 * own (atomic form, or dT overlapping T)     */
 #define DEX_PROF_BGMM_FWD     6 /* batched forward persistent kernel          */
 #define DEX_PROF_BGMM_VJP     7 /* batched reverse persistent kernel          */
 #define DEX_PROF_STENCIL_FWD  8 /* forward steps (one range per dex_fwd)      */

@@ -1,6 +1,7 @@
-// GMM log-likelihood, one instance: host dispatch, the vector-ALU forward mode
-// and the merge / finalize kernels of the FP32-storage forms (gmm_dev.h,
-// gmm_mfma_inst.hip); the FP64 forward and reverse are in gmm_f64.hip.
+// GMM log-likelihood, one instance: host dispatch, the forward mode (but for the
+// 16-bit variant's at D = 64 and that on quads of components, gmm_f32.hip) and the
+// merge / finalize kernels of the FP32-storage forms (gmm_dev.h, gmm_mfma_inst.hip);
+// the FP64 forward and reverse are in gmm_f64.hip.
 #include "gmm_host.h"
 #include "internal.h"
 
@@ -215,16 +216,16 @@ __global__ void __launch_bounds__(256) gmm_jvp_valu(
   if (t == 0) part[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = acc;
 }
 
-// The same for FP32 storage and D > 32 on the matrix cores (16x16x4 FP32 products; D
-// <= 32: on quads of components): a wave
-// takes 64 points and every KS-th component. Per component y = Q_k r and dy = dQ_k r
-// - Q_k dmu_k from r = x - mu_k (formed per component: the difference of two FP32
-// values, rounded once), with the strict lower parts read as they are stored and the
-// next component's loads issued before the current one's products; |y|^2 and y . dy
-// are summed over the lane groups so that lane p owns point p. Each wave writes its
-// FP64 sum to part[wave]. (N = 20000, D = 32, K = 50: 63 us a launch, 37 on quads; one
-// thread per point and LDS broadcasts of Q and dQ 163.) Lane layout: A and B hold row / column c and
-// contraction values 16 ch + 4 g + j (element j), the result rows 4 g + i.
+// The same for FP32 storage and D > 32 on the matrix cores (16x16x4 FP32 products;
+// smaller D goes on quads of components): a wave takes 64 points and every KS-th
+// component. Per component y = Q_k r and dy = dQ_k r - Q_k dmu_k from r = x - mu_k
+// (formed per component: the difference of two FP32 values, rounded once), with the
+// strict lower parts read as they are stored and the next component's loads issued
+// before the current one's products; |y|^2 and y . dy are summed over the lane groups
+// so that lane p owns point p. Each wave writes its FP64 sum to part[wave]. (N = 20000,
+// D = 32, K = 50: 63 us a launch, 37 on quads; one thread per point and LDS broadcasts
+// of Q and dQ 163.) Lane layout: A and B hold row / column c and contraction values
+// 16 ch + 4 g + j (element j), the result rows 4 g + i.
 __global__ void __launch_bounds__(256) gmm_jvp_mfma(
     const float* __restrict__ alphas, const float* __restrict__ means, const float* __restrict__ qd,
     const float* __restrict__ l, const float* __restrict__ x, const float* __restrict__ f, int N,

@@ -6,8 +6,9 @@
 // ordered longest first; the forward and reverse phases each run as one
 // persistent launch whose blocks take items from an atomic counter until the
 // list is exhausted, so the smallest instances do not pay a launch each.
-// FP32 units: gmm_quad.h, D padded to a multiple of 8. Split-FP16 forward (D > 8):
-// tiles of 16-deep contraction chunks, D padded to 16 or 32.
+// FP32 units: gmm_quad.h, D padded to a multiple of 8; the moments of instances that
+// fill few quads go component by component, D padded to 16 or 32 (blocks_pay).
+// Split-FP16 forward (D > 8): tiles of 16-deep contraction chunks, D padded likewise.
 #include <string.h>
 
 #include <algorithm>

@@ -1,5 +1,5 @@
 // GMM log-likelihood in FP64 (one instance): forward and reverse on the FP64
-// matrix cores (16x16x4 products; D <= 4 on the vector ALU).
+// matrix cores (16x16x4 products; the forward at D <= 4 on the vector ALU).
 //
 // Forward: y = Q_k (x - mu_k) for 64 points at a time, Q_k's lower-triangular
 // chunks as the A operand and x - mu_k, formed per component, as B. Reverse:

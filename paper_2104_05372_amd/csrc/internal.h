@@ -47,8 +47,9 @@ int gmm_batched_default_config(const dex_desc& d, int role);
 dex_status gmm_fwd(const dex_desc& d, int cfg, const GmmPtrs& in, void* F, void* f,
                    void* cache, void* ws, hipStream_t s);
 // Forward mode of the scalar objective: the linearized loop run forward over
-// the tangents (matrix-core tangent products for the 16-bit variant at D = 64,
-// a vector-ALU pass otherwise), FP64 fixed-order sums.
+// the tangents (matrix-core tangent products for the 16-bit variant at D = 64 and
+// FP32 products for other FP32 storage, a vector-ALU pass for FP64 and for few
+// dimensions and components), FP64 fixed-order sums.
 dex_status gmm_jvp(const dex_desc& d, int cfg, const GmmPtrs& in, const void* f,
                    const void* cache, const GmmGrads& t, void* dF, void* ws, hipStream_t st);
 dex_status gmm_vjp(const dex_desc& d, int cfg, const GmmPtrs& in, const void* f,
