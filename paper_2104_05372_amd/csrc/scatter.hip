@@ -172,7 +172,7 @@ __global__ void __launch_bounds__(256) scatter_rows_kernel(T* __restrict__ acc, 
 // bins w and w + nwords (neighbours, which skewed keys favour together, are in
 // different words). Bound by the vector instructions per key and the LDS unit (a wave's
 // hits on one word go one after the other) as much as by reading the keys: 2^26 keys,
-// Zipf(1.1), 65536 bins: 51 us, 43 to read them and 6 to write the
+// Zipf(1.1), 65536 bins: 53 us, 43 to read them and 6 to write the
 // counters; with a test and a shift of its own for every key and its result, 58.
 template <typename IdxT>
 __global__ void __launch_bounds__(1024) hist_private_kernel(int32_t* __restrict__ acc,
