@@ -215,13 +215,24 @@ DEX_DEV float cos1(float x) {
 DEX_DEV float step1(float u, float sum, float c) { return fmaf(c, fmaf(-4.f, u, sum), u); }
 DEX_DEV float adj1(float g, float sum, float c) { return fmaf(1.f - 4.f * c, g, c * sum); }
 
+// Which 256 of a one-step launch's threads a block is. Blocks go to the XCDs in turn; of
+// every 512 among the first `runs` an XCD takes 64 that follow each other, so that a row's
+// neighbours come from its own L2. Non-linear adjoint, a checkpoint every step, 24 steps,
+// in turn / runs of 16 / 64 / 128 / an eighth of the grid: 4096^2 1042 / 899 / 849 / 905 /
+// 1019 us, 2048^2 344 / 268 / 259 / 269 / 266.
+constexpr unsigned kRun = 64;
+DEX_DEV int64_t own_block(unsigned runs) {
+  const unsigned b = blockIdx.x, in = b % (8 * kRun);
+  return b < runs ? b - in + (in & 7) * kRun + (in >> 3) : b;
+}
+
 // One forward step, 4 cells per thread (W % 4 == 0, W >= 8).
 __global__ void __launch_bounds__(256) stencil_step_vec(const float* __restrict__ u,
                                                         float* __restrict__ un,
                                                         float* __restrict__ snap, int H, int W,
-                                                        float c, float rho) {
+                                                        float c, float rho, unsigned runs) {
   const int W4 = W >> 2;
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t t = own_block(runs) * 256 + threadIdx.x;
   if (t >= (int64_t)H * W4) return;
   const int y = (int)(t / W4), x4 = (int)(t % W4);
   const int yn = y == 0 ? H - 1 : y - 1, ys = y == H - 1 ? 0 : y + 1;
@@ -616,8 +627,9 @@ __global__ void __launch_bounds__(256) stencil_fused(TbArgs a) {
 __global__ void __launch_bounds__(256) stencil_step_scalar(const float* __restrict__ u,
                                                            float* __restrict__ un,
                                                            float* __restrict__ snap, int H,
-                                                           int W, float c, float rho) {
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+                                                           int W, float c, float rho,
+                                                           unsigned runs) {
+  const int64_t t = own_block(runs) * 256 + threadIdx.x;
   if (t >= (int64_t)H * W) return;
   const int y = (int)(t / W), x = (int)(t % W);
   const int yn = y == 0 ? H - 1 : y - 1, ys = y == H - 1 ? 0 : y + 1;
@@ -635,8 +647,8 @@ __global__ void __launch_bounds__(256) stencil_tan_step(const float* __restrict_
                                                         const float* __restrict__ du,
                                                         float* __restrict__ un,
                                                         float* __restrict__ dun, int H, int W,
-                                                        float c, float rho) {
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+                                                        float c, float rho, unsigned runs) {
+  const int64_t t = own_block(runs) * 256 + threadIdx.x;
   if (t >= (int64_t)H * W) return;
   const int y = (int)(t / W), x = (int)(t % W);
   const int yn = y == 0 ? H - 1 : y - 1, ys = y == H - 1 ? 0 : y + 1;
@@ -660,8 +672,9 @@ __global__ void __launch_bounds__(256) stencil_tan_step(const float* __restrict_
 __global__ void __launch_bounds__(256) stencil_adj_gather(const float* __restrict__ g,
                                                           const float* __restrict__ u,
                                                           float* __restrict__ out, int H, int W,
-                                                          float c, float rho, int accumulate) {
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+                                                          float c, float rho, int accumulate,
+                                                          unsigned runs) {
+  const int64_t t = own_block(runs) * 256 + threadIdx.x;
   if (t >= (int64_t)H * W) return;
   const int y = (int)(t / W), x = (int)(t % W);
   const int yn = y == 0 ? H - 1 : y - 1, ys = y == H - 1 ? 0 : y + 1;
@@ -679,9 +692,9 @@ __global__ void __launch_bounds__(256) stencil_adj_gather_vec(const float* __res
                                                               const float* __restrict__ u,
                                                               float* __restrict__ out, int H,
                                                               int W, float c, float rho,
-                                                              int accumulate) {
+                                                              int accumulate, unsigned runs) {
   const int W4 = W >> 2;
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t t = own_block(runs) * 256 + threadIdx.x;
   if (t >= (int64_t)H * W4) return;
   const int y = (int)(t / W4), x4 = (int)(t % W4);
   const int yn = y == 0 ? H - 1 : y - 1, ys = y == H - 1 ? 0 : y + 1;
@@ -917,11 +930,10 @@ TbShape tb_shape(const St& s, int tb, bool fused, double row) {
 struct TbPlan {
   // A wave of the forward kernel is taken to need 900 cycles for a row, as long as its
   // load and its store (with one or two levels there is no more to do meanwhile), so that
-  // short stretches get more waves: a checkpoint every step at 4096^2 32 steps 1036 us
-  // (0: 1220, 600: 1096, 1400: 1036) and 1106 with the sine (1230, 1231, 1108), 1000^2
-  // 146 (153), every 7th at 1500 x 700 77 (81), every 5th at 4096^2 392 (394; 1400: 414).
-  // The adjoint reads a row as far ahead as its levels let it and loses by it (4096^2
-  // every step 865 us, 794 without).
+  // short stretches get more waves: a checkpoint every step, 24 steps of 4096 x 4095 794 us
+  // (0: 921), 8192 x 2047 798 (906), 1536 x 1535 182 (174); every 5th, 2048^2 139 (151); every
+  // 2nd, 2048^2 132 (122), 1024^2 68 (71). The adjoint reads a row as far ahead as its levels
+  // let it and loses by it.
   static constexpr double kFwdRow = 900.0;
   const St& s;
   TbShape shape[3][4];
@@ -942,9 +954,9 @@ struct TbPlan {
   // cells 196 us a step (one-step kernel 34), 4e6 x 4 with the sine 107 (35), 1 x 1.6e7
   // with the sine 55 (22). Modelled, us a step: one-step kernels by a launch and what they
   // read and write (four cells a thread, or one), the others by their instructions; the
-  // factors are those of measured grids from 1 x 1e6 to 4096^2. One step by itself gains
-  // nothing from levels, but only the sine's adjoint loses by them (601 x 333, a
-  // checkpoint every step: 3.3 us a step, 4.0).
+  // factors are those of measured grids from 1 x 1e6 to 4096^2. The sine's adjoint of one
+  // step by itself only loses by the blocked form (a checkpoint every step, 24 steps of
+  // 601 x 333: 69 us, 93).
   enum Pass { FWD, TAN, ADJ };
   bool one_step(int len, Pass pass) {
     const int tb = tb_of(len);
@@ -1014,15 +1026,23 @@ void fused_steps(TbPlan& plan, int tb, TbArgs a, hipStream_t st) {
 #undef DEX_FU
 }
 
-// One step of the vector kernels (a tuning configuration).
+// Blocks of a one-step launch that go in runs (own_block): whole groups of runs; none where
+// a block holds a row's neighbours itself or a run holds no two rows (1e6 x 1 with the sine
+// 138 us, 144 in runs; 2 x 500000 back 229, 265).
+unsigned run_blocks(const St& s, bool vec) {
+  const int64_t row = vec ? s.W / 4 : s.W, nb = ((int64_t)s.H * row + 255) / 256;
+  return row >= 64 && row <= 128 * kRun ? (unsigned)(nb / (8 * kRun) * (8 * kRun)) : 0u;
+}
+
+// One step by itself.
 void step(const St& s, const float* u, float* un, float* snap, hipStream_t st) {
   if (s.vec) {
     const int64_t nt = s.n / 4;
     hipLaunchKernelGGL(stencil_step_vec, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, st, u,
-                       un, snap, s.H, s.W, s.c, s.rho);
+                       un, snap, s.H, s.W, s.c, s.rho, run_blocks(s, true));
   } else {
     hipLaunchKernelGGL(stencil_step_scalar, dim3((unsigned)((s.n + 255) / 256)), dim3(256), 0, st,
-                       u, un, snap, s.H, s.W, s.c, s.rho);
+                       u, un, snap, s.H, s.W, s.c, s.rho, run_blocks(s, false));
   }
 }
 
@@ -1036,10 +1056,11 @@ void adj(const St& s, int form, const float* g, const float* u, float* out, bool
                        s.rho);
   } else if (s.vec) {
     hipLaunchKernelGGL(stencil_adj_gather_vec, dim3((unsigned)((s.n / 4 + 255) / 256)), dim3(256),
-                       0, st, g, u, out, s.H, s.W, s.c, s.rho, accumulate ? 1 : 0);
+                       0, st, g, u, out, s.H, s.W, s.c, s.rho, accumulate ? 1 : 0,
+                       run_blocks(s, true));
   } else {
     hipLaunchKernelGGL(stencil_adj_gather, dim3(nb), dim3(256), 0, st, g, u, out, s.H, s.W, s.c,
-                       s.rho, accumulate ? 1 : 0);
+                       s.rho, accumulate ? 1 : 0, run_blocks(s, false));
   }
 }
 }  // namespace
@@ -1072,34 +1093,29 @@ dex_status stencil_fwd(const dex_desc& d, int cfg, const float* u0, const float*
   const float* cur = u0;
   ProfRange pr(DEX_PROF_STENCIL_FWD, st);
   TbPlan plan(s);
-  if (cfg == 0 && !plan.one_step(std::min(s.every, s.T), TbPlan::FWD)) {
-    // each stretch between checkpoints ends in the next one's storage (the last
-    // in uT); its inner launches alternate between uT and the workspace field,
-    // the one before uT's writing the workspace. The first launch also copies
-    // u0 to its checkpoint.
-    for (int sg = 0; sg < s.nck; ++sg) {
-      const int len = std::min(s.every, s.T - sg * s.every);
-      const bool last = sg == s.nck - 1;
-      int pieces = tb_pieces(len);
-      for (int left = len; left > 0; --pieces) {
-        const int tb = tb_of(left);
-        left -= tb;
-        TbArgs a{};
-        a.in = cur;
-        a.out = left == 0 ? (last ? uT : ckpt + (int64_t)(sg + 1) * s.n)
-                          : (pieces % 2 == 0 ? other : uT);
-        if (sg == 0 && left + tb == len) a.snap = ckpt;
+  const bool one = cfg != 0 || plan.one_step(std::min(s.every, s.T), TbPlan::FWD);
+  // each stretch between checkpoints ends in the next one's storage (the last
+  // in uT); its inner launches alternate between uT and the workspace field,
+  // the one before uT's writing the workspace. The first launch also copies
+  // u0 to its checkpoint.
+  for (int sg = 0; sg < s.nck; ++sg) {
+    const int len = std::min(s.every, s.T - sg * s.every);
+    const bool last = sg == s.nck - 1;
+    int pieces = one ? len : tb_pieces(len);
+    for (int left = len; left > 0; --pieces) {
+      const int tb = one ? 1 : tb_of(left);
+      left -= tb;
+      TbArgs a{};
+      a.in = cur;
+      a.out = left == 0 ? (last ? uT : ckpt + (int64_t)(sg + 1) * s.n)
+                        : (pieces % 2 == 0 ? other : uT);
+      if (sg == 0 && left + tb == len) a.snap = ckpt;
+      // (one step by itself: 2048^2, a checkpoint every step, 24 steps 193 us, blocked 266)
+      if (one || (tb == 1 && s.vec))
+        step(s, a.in, a.out, a.snap, st);
+      else
         tb_steps<TB_FWD>(plan, tb, a, st);
-        cur = a.out;
-      }
-    }
-  } else {
-    // step t writes into uT when (T-1-t) is even, so the last step lands in uT
-    for (int t = 0; t < s.T; ++t) {
-      float* dst = ((s.T - 1 - t) % 2 == 0) ? uT : other;
-      float* snap = (t % s.every == 0) ? ckpt + (int64_t)(t / s.every) * s.n : nullptr;
-      step(s, cur, dst, snap, st);
-      cur = dst;
+      cur = a.out;
     }
   }
   pr.end(s.T);
@@ -1133,7 +1149,7 @@ dex_status stencil_jvp(const dex_desc& d, const float* u0, const float* target, 
     a.out2 = buf[q][1];
     if (one)
       hipLaunchKernelGGL(stencil_tan_step, dim3((unsigned)((s.n + 255) / 256)), dim3(256), 0, st, u,
-                         du, a.out, a.out2, s.H, s.W, s.c, s.rho);
+                         du, a.out, a.out2, s.H, s.W, s.c, s.rho, run_blocks(s, false));
     else
       tb_steps<TB_TAN>(plan, tb, a, st);
     u = a.out;
@@ -1169,7 +1185,7 @@ dex_status stencil_vjp(const dex_desc& d, int cfg, const float* u0, const float*
       // du0 += dL (u0 - target)
       hipLaunchKernelGGL(stencil_lam_init, dim3(nb), dim3(256), 0, st, uT_in, target, dL, s.n, lamA);
       hipLaunchKernelGGL(stencil_adj_gather, dim3(nb), dim3(256), 0, st, lamA, nullptr, du0, s.H,
-                         s.W, 0.f, 0.f, 1);
+                         s.W, 0.f, 0.f, 1, 0u);
     } else {
       hipLaunchKernelGGL(stencil_lam_init, dim3(nb), dim3(256), 0, st, uT_in, target, dL, s.n, du0);
     }

@@ -242,6 +242,21 @@ def test_forms_round_alike(dev, H, W, steps, every, rho):
     assert abs(run_jvp(u0, tg, t0, t1, steps, rho) - want) <= 1e-5 * max(abs(want), scale)
 
 
+# One step a launch in runs of blocks (whole groups of 512 and a tail; rows of four cells a
+# thread and of one), and the linear adjoint past checkpoints: the bits of the blocked form.
+@pytest.mark.parametrize("rho", [0.0, -0.2])
+@pytest.mark.parametrize("H,W", [(2049, 256), (4100, 300), (301, 511), (600, 513), (70, 8200)])
+def test_runs_of_blocks(dev, H, W, rho):
+    u0, tg = workloads.stencil_inputs(H, W, 19)
+    a = run(u0, tg, 8, 8, rho=rho)
+    assert rel(a[2], ost.loss_and_grad(u0, tg, 8, rho=rho)[2]) <= 1e-5
+    states = run(u0, tg, 8, 1, rho=rho, fcfg=2, vcfg=3)[3]
+    for every, cfgs in ((1, {}), (3, {}), (8, dict(fcfg=2, vcfg=3)), (3, dict(fcfg=2, vcfg=3))):
+        L, uT, du, ck = run(u0, tg, 8, every, rho=rho, **cfgs)
+        assert L == a[0] and np.array_equal(uT, a[1]) and np.array_equal(du, a[2]), (every, cfgs)
+        assert np.array_equal(ck, states[::every]), (every, cfgs)
+
+
 # Reverse: DEX_ACCUMULATE in every form, and du0 over a buffer that the call reads (the
 # linear adjoint's target and final state, the non-linear one's first checkpoint too).
 @pytest.mark.parametrize("rho", [0.0, -0.2])
